@@ -73,8 +73,8 @@ typedef struct sbc_ctx sbc_ctx;
 
 /* Scratch memory for problems of up to max_total_elems entries in up to max_tensors
  * tensors per call, on HIP device `device`.  Device memory taken: about
- * 17 bytes per entry of max_total_elems plus 50 KiB per tensor, and 2.4 MiB whatever
- * the sizes.  The context also owns a few HIP events.  *out receives the
+ * 17 bytes per entry of max_total_elems plus 50 KiB per tensor, and up to 2.3 MiB more (35 KiB for each of
+ * the first 64 tensors).  The context also owns a few HIP events.  *out receives the
  * context.  SBC_EINVAL for non-positive sizes or a bad device, SBC_EHIP if an
  * allocation fails (nothing is leaked). */
 int sbc_create(sbc_ctx** out, int device, int64_t max_total_elems, int max_tensors);
@@ -218,10 +218,10 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream,
  *       of the call before it would have held.  0 estimates the keys from a sample of the new
  *       data in every call.
  *   SBC_OPT_WIDE_MIN_KEPT      (default 0 = 8192)  a tensor that keeps at least this many entries
- *       per side is selected by grid-wide kernels instead of one workgroup, and its stream is
- *       decoded tile by tile by many workgroups instead of one (a 1.5e9-entry tensor at
- *       p = 0.001 keeps 1.5e6); tests lower it to send small tensors that way, or raise it (one
- *       workgroup selects and encodes up to 16384 kept entries by itself).
+ *       per side has its candidate lists narrowed down by many workgroups before one workgroup
+ *       per side selects among the rest, and its stream is decoded tile by tile by many workgroups
+ *       instead of one (a 1.5e9-entry tensor at p = 0.001 keeps 1.5e6); tests lower it to send
+ *       small tensors that way, or raise it.
  *   SBC_OPT_SAMPLED_THRESHOLD  (0/1, default 0)  1 selects the subsampled variant of
  *       "Sparse Binarization" (the threshold is estimated from a random subsample, which makes
  *       the amount of sparsity noisy).  Per tensor t of the call a stratified sample of at most
@@ -259,7 +259,7 @@ int sbc_decode_status(sbc_ctx* ctx, void* hip_stream);
 /* Which routes the most recent successful sbc_compress() took: a bit set of
  * SBC_ROUTE_CARRIED_KEYS (filter keys came from the previous call, no sampling) and
  * SBC_ROUTE_HISTOGRAM (the histogram route ran for at least one tensor), SBC_ROUTE_WIDE (the
- * grid-wide selection kernels completed at least one tensor); SBC_EINVAL (negative) without a
+ * workgroup sweeps for long lists narrowed down at least one tensor's); SBC_EINVAL (negative) without a
  * successful call. */
 enum { SBC_ROUTE_CARRIED_KEYS = 1, SBC_ROUTE_HISTOGRAM = 2, SBC_ROUTE_WIDE = 4,
        SBC_ROUTE_LOOSE_KEYS = 8,    /* some filter key let so many entries pass that the next call samples afresh */

@@ -11,7 +11,7 @@
 // If a side ends up with fewer than k candidates the filter was too tight for that tensor;
 // the histogram path below then finds its candidates exactly from a second read of A:
 //   k_hist_flagged, k_pick_bins, k_extract
-// Either way the select kernel receives, per tensor and side, a list that contains the k most
+// Either way k_threshold receives, per tensor and side, a list that contains the k most
 // extreme entries, and the result is exact.
 #pragma once
 
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
         z.kc[0] = z.kc[1] = 0u;
         z.S[0] = z.S[1] = 0.0;
         z.side = 0; z.mu_signed = 0.f; z.nnz = 0u; z.flags = 0u; z.bit_len = 0ull;
-        z.done = 0u; z.pad = 0u; z.cand_seen[0] = z.cand_seen[1] = 0u; z.expect[0] = z.expect[1] = 0u;
+        z.done = 0u; z.sorted_kept = 0u; z.cand_seen[0] = z.cand_seen[1] = 0u; z.expect[0] = z.expect[1] = 0u;
         st[t] = z;
     }
     if (force_exact) return;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
         if (tid == 0) {
             uint32_t ap = 0u, an = 0u;
             for (int wv = 0; wv < kSampleThreads / 64; ++wv) { ap += wave_above[wv] & 0xFFFFu; an += wave_above[wv] >> 16; }
-            // scaled to the tensor; the limit is the one beyond which k_select calls a list loose
+            // scaled to the tensor; the limit is the one beyond which k_threshold calls a list loose
             const double scale = (double)n / (double)m, many = (double)loose_limit(d.k, n);
             if ((double)ap * scale > many || (double)an * scale > many) atomicOr(&result->err, kErrStaleKeys);
         }
@@ -322,34 +322,37 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
 
 // --------------------------------------------------------------------------
 // Appends flagged entries of one chunk to the two candidate lists of its tensor with a block
-// scan: used by the histogram path and as the second try of a chunk whose LDS queue
-// overflowed.  key[s] is the plain key of the thread's s-th entry (entry s*NT + tid of the
+// scan (histogram path).  key[s] is the plain key of the thread's s-th entry (entry s*NT + tid of the
 // chunk); bit s of mp / mn flags it for the positive / negative list; the negative list stores
 // complemented keys.  Contains barriers; every thread of the workgroup must call it.
 // --------------------------------------------------------------------------
 template <int PER>
 __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], uint32_t mp, uint32_t mn,
                                                   uint32_t e_first, const TensorDesc& d, TensorState* __restrict__ st_t,
-                                                  uint2* __restrict__ cand, ResultBlock* __restrict__ result,
+                                                  uint2* __restrict__ cand, ChunkRun* __restrict__ run,
                                                   uint32_t* scratch, uint32_t* base) {
     const int tid = threadIdx.x;
     const uint32_t packed = __popc(mp) | (__popc(mn) << 16);
     uint32_t total;
     const uint32_t ex = block_excl_sum<uint32_t, kStreamThreads>(packed, &total, scratch);
-    if (total == 0u) return;                          // uniform
+    if (total == 0u) {                                // uniform
+        if (tid == 0) *run = chunk_run(d, 0u, 0u, 0u, 0u);
+        return;
+    }
     if (tid == 0) {
         const uint32_t tp = total & 0xFFFFu, tn = total >> 16;
         const unsigned long long old = atomicAdd(reinterpret_cast<unsigned long long*>(&st_t->cand_cnt[0]),
                                                  (unsigned long long)tp | ((unsigned long long)tn << 32));
         base[0] = (uint32_t)old;
         base[1] = (uint32_t)(old >> 32);
+        *run = chunk_run(d, (uint32_t)old, (uint32_t)(old >> 32), tp, tn);
     }
     __syncthreads();
     uint32_t op = base[0] + (ex & 0xFFFFu);
     uint32_t on = base[1] + (ex >> 16);
     __syncthreads();                                  // base may be rewritten by the next call
     // (beyond a list's capacity nothing is stored: the counters then show that the tensor's lists
-    // are not usable, see k_select; a list of a full context holds every entry)
+    // are not usable, see lists_unusable; a list of a full context holds every entry)
     if (op + __popc(mp) > d.cand_cap || on + __popc(mn) > d.cand_cap) return;
     uint2* __restrict__ cp = cand + d.cand_off;
     uint2* __restrict__ cn = cand + d.cand_off + d.cand_cap;
@@ -366,9 +369,8 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
 // 8 x 16-byte loads of each operand in flight per thread, A stored over R, and the few
 // entries at or beyond a side's filter key queued in LDS, then appended to the tensor's
 // candidate list with one atomic per side.  A chunk with more candidates than the queue
-// holds (tie-heavy or constant data) appends them again from a second read of its entries.
-// Chunks of tensors that are encoded from the bitmap also clear their bitmap words and their
-// share of the tensor's staging words.
+// holds (tie-heavy or constant data) appends them again from a second read of its entries.  Where
+// the chunk's candidates went is recorded (ChunkRun) for k_apply.
 // --------------------------------------------------------------------------
 struct FilterShared {
     uint2 queue[2][kFilterQueue];
@@ -398,8 +400,8 @@ __device__ __forceinline__ void filter_entry(float a, uint32_t idx, uint32_t lo_
 template <bool STREAM>
 __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ sched,
-        TensorState* __restrict__ st, uint2* __restrict__ cand, uint32_t* __restrict__ bitmap,
-        uint32_t* __restrict__ stage, ResultBlock* __restrict__ result) {
+        TensorState* __restrict__ st, uint2* __restrict__ cand, ChunkRun* __restrict__ runs,
+        ResultBlock* __restrict__ result) {
     __shared__ FilterShared sh;
     const int tid = threadIdx.x;
     // sched[workgroup] = (first chunk in the call-wide numbering, tensor | consecutive chunks of it << 24)
@@ -418,13 +420,6 @@ __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
         const uint32_t cc = c - d.chunk0;
         const uint32_t e0 = cc * (uint32_t)kChunk;
         const uint32_t cnt = min((uint32_t)kChunk, d.n - e0);
-        if (!(d.flags & kDescFused)) {
-            bitmap[(uint64_t)c * kChunkWords + tid] = 0u;
-            const uint32_t per = (d.bound_words + d.nchunks - 1u) / d.nchunks;
-            const uint32_t lo = per * cc;
-            const uint32_t hi = (lo + per < d.bound_words) ? lo + per : d.bound_words;
-            for (uint32_t w = lo + tid; w < hi; w += kStreamThreads) stage[d.stage_off + w] = 0u;
-        }
         const gcfloat_ptr dw = as_global(d.dW + e0);
         const gfloat_ptr r = as_global(d.R + e0);
         const bool vec = (cnt == (uint32_t)kChunk) && ((((uintptr_t)(d.dW + e0) | (uintptr_t)(d.R + e0)) & 15u) == 0u);
@@ -482,7 +477,10 @@ __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
     __syncthreads();
     const uint32_t qp = sh.qcnt[0], qn = sh.qcnt[1];
     if (qp <= (uint32_t)kFilterQueue && qn <= (uint32_t)kFilterQueue) {
-        if (qp + qn == 0u) return;
+        if (qp + qn == 0u) {
+            if ((uint32_t)tid < n_sub) runs[sc.x + tid] = chunk_run(d, 0u, 0u, 0u, 0u);
+            return;
+        }
         if (tid == 0) {
             // both sides' counters advance in one 64-bit atomic: workgroups of one tensor queue up
             // on this address, and the wait grows with the number of atomics
@@ -492,6 +490,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
             sh.base[1] = (uint32_t)(old >> 32);
         }
         __syncthreads();
+        if ((uint32_t)tid < n_sub) runs[sc.x + tid] = chunk_run(d, sh.base[0], sh.base[1], qp, qn);
         // (beyond a list's capacity nothing is stored: see append_candidates)
         if ((uint64_t)sh.base[0] + qp > d.cand_cap || (uint64_t)sh.base[1] + qn > d.cand_cap) return;
         uint2* __restrict__ cp = cand + d.cand_off + sh.base[0];
@@ -500,16 +499,28 @@ __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
         for (uint32_t i = tid; i < qn; i += kStreamThreads) cn[i] = sh.queue[1][i];
         return;
     }
-    // queue overflow: append the candidates of this workgroup's chunks from a second read of A,
-    // 4096 entries at a time (the barrier above ordered the workgroup's stores of A before these
-    // loads).  Filter keys that let a flood pass send most workgroups of a call this way, so a step
-    // takes as many entries as the scan's 16-bit counts per side allow.
+    // queue overflow: the candidates of this workgroup's chunks (all of them have been counted) are
+    // appended from a second read of A, 4096 entries at a time, in chunk order, so that each chunk's are
+    // one run (the barrier above ordered the workgroup's stores of A before these loads).  Filter keys
+    // that let a flood pass send most workgroups of a call this way.
     constexpr int kRedo = 16;
     static_assert(kRedo * kStreamThreads <= 65535, "the per-side counts of one step fit their 16-bit fields");
+    if (tid == 0) {
+        const unsigned long long old = atomicAdd(reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]),
+                                                 (unsigned long long)qp | ((unsigned long long)qn << 32));
+        sh.base[0] = (uint32_t)old;
+        sh.base[1] = (uint32_t)(old >> 32);
+    }
+    __syncthreads();
+    uint32_t at_p = sh.base[0], at_n = sh.base[1];
+    if ((uint64_t)at_p + qp > d.cand_cap || (uint64_t)at_n + qn > d.cand_cap) return;
+    uint2* __restrict__ cp = cand + d.cand_off;
+    uint2* __restrict__ cn = cand + d.cand_off + d.cand_cap;
     for (uint32_t sub = 0; sub < n_sub; ++sub) {
         const uint32_t e0 = (sc.x + sub - d.chunk0) * (uint32_t)kChunk;
         const uint32_t cnt = min((uint32_t)kChunk, d.n - e0);
         const gcfloat_ptr r = as_global(d.R + e0);
+        const uint32_t from_p = at_p, from_n = at_n;
         for (uint32_t off = 0; off < cnt; off += kRedo * kStreamThreads) {
             uint32_t key[kRedo];
             uint32_t mp = 0u, mn = 0u;
@@ -526,8 +537,18 @@ __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
                 if (in && key[s] >= lo_p) mp |= 1u << s;
                 if (in && ~key[s] >= lo_n) mn |= 1u << s;
             }
-            append_candidates<kRedo>(key, mp, mn, e0 + off, d, &st[t], cand, result, sh.scratch, sh.base);
+            uint32_t total;
+            const uint32_t ex = block_excl_sum<uint32_t, kStreamThreads>(__popc(mp) | (__popc(mn) << 16), &total, sh.scratch);
+            uint32_t op = at_p + (ex & 0xFFFFu), on = at_n + (ex >> 16);
+#pragma unroll
+            for (int s = 0; s < kRedo; ++s) {
+                const uint32_t idx = e0 + off + s * kStreamThreads + tid;
+                if (mp & (1u << s)) cp[op++] = make_uint2(key[s], idx);
+                if (mn & (1u << s)) cn[on++] = make_uint2(~key[s], idx);
+            }
+            at_p += total & 0xFFFFu; at_n += total >> 16;
         }
+        if (tid == 0) runs[sc.x + sub] = chunk_run(d, from_p, from_n, at_p - from_p, at_n - from_n);
     }
 }
 
@@ -536,12 +557,12 @@ __global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
 // k_hist_flagged: per chunk, first-digit histogram of A (already stored in R).
 // --------------------------------------------------------------------------
 __global__ __launch_bounds__(kStreamThreads) void k_hist_flagged(
-        const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ chunk_tensor,
+        const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor,
         const TensorState* __restrict__ st, uint32_t* __restrict__ hist) {
     __shared__ uint32_t lh[kL1Bins];
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x;
-    const int t = (int)chunk_tensor[c];
+    const int t = (int)chunk_tensor[c].x;
     if (!(st[t].flags & kStFailed)) return;
     const TensorDesc d = desc[t];
     const uint32_t e0 = (c - d.chunk0) * (uint32_t)kChunk;
@@ -597,14 +618,14 @@ __global__ __launch_bounds__(256) void k_pick_bins(const TensorDesc* __restrict_
 // k_extract: per chunk of a tensor in the exact pass, every entry whose first digit lies in or
 // beyond a side's threshold bin becomes a candidate of that side.
 __global__ __launch_bounds__(kStreamThreads) void k_extract(
-        const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ chunk_tensor,
-        TensorState* __restrict__ st, uint2* __restrict__ cand, ResultBlock* __restrict__ result) {
+        const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor,
+        TensorState* __restrict__ st, uint2* __restrict__ cand, ChunkRun* __restrict__ runs) {
     constexpr int PER = kChunk / kStreamThreads;
     __shared__ uint32_t scratch[kStreamThreads / 64];
     __shared__ uint32_t base[2];
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x;
-    const int t = (int)chunk_tensor[c];
+    const int t = (int)chunk_tensor[c].x;
     if (!(st[t].flags & kStExact)) return;
     const TensorDesc d = desc[t];
     const uint32_t e0 = (c - d.chunk0) * (uint32_t)kChunk;
@@ -623,7 +644,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_extract(
         if (in && bin >= bin_p) mp |= 1u << s;
         if (in && bin <= bin_n) mn |= 1u << s;
     }
-    append_candidates<PER>(key, mp, mn, e0, d, &st[t], cand, result, scratch, base);
+    append_candidates<PER>(key, mp, mn, e0, d, &st[t], cand, &runs[c], scratch, base);
 }
 
 }  // namespace sbc

@@ -46,7 +46,6 @@ constexpr int kChunk = 8192;             // entries of one tensor handled by one
 constexpr int kChunkWords = kChunk / 32; // bitmap words per chunk (= threads of a chunk kernel)
 constexpr int kStreamThreads = 256;      // workgroup size of the streaming kernels
 constexpr int kSampleThreads = 512;      // workgroup size of the sample kernel
-constexpr int kSelThreads = 1024;        // workgroup size of the select kernel
 constexpr int kSampleMax = 16384;        // entries sampled per tensor for the prefilter threshold
 constexpr int kSampleWindow = 2048;      // leading-16-bit key values counted below the sample's extreme
 
@@ -55,15 +54,6 @@ constexpr int kL1Bits = 12;
 constexpr int kL1Bins = 1 << kL1Bits;
 constexpr int kL1Shift = 32 - kL1Bits;
 
-constexpr int kBucketBits = 11;          // index sort of the fused encoder: buckets by leading index bits
-constexpr int kBuckets = 1 << kBucketBits;
-constexpr uint32_t kFusedMaxK = 6144;    // a tensor with k up to this, and a stream bound of up to
-constexpr uint32_t kFusedMaxWords = 4096; // this many words, is sorted and encoded inside the select kernel
-// ... and so is one that keeps up to kFusedBigK entries, if that is below the threshold of the
-// grid-wide kernels: beyond kSelLds kept entries the candidate lists cannot be staged in LDS,
-// which leaves their space to the sort.  (One workgroup reads such lists from memory in every
-// sweep; by default the grid-wide kernels take over from 8192 kept entries.)
-constexpr uint32_t kFusedBigK = 16384;
 constexpr int kFilterQueue = 1024;       // candidates per side a workgroup of the streaming kernel can queue in LDS
 constexpr uint32_t kMaxChunksPerWorkgroup = 8;   // consecutive chunks of one very long tensor per such workgroup
 
@@ -73,10 +63,10 @@ constexpr uint32_t kErrInternal = 2u;
 constexpr uint32_t kErrCorrupt = 4u;
 constexpr uint32_t kErrOverflow = 128u;  // a candidate list of a compact context cannot hold what the histogram route extracts
 constexpr uint32_t kErrPrefilter = 8u;   // not an error: some tensor needs the histogram path
-constexpr uint32_t kErrWide = 32u;       // not an error: the grid-wide selection kernels completed some tensor
+constexpr uint32_t kErrWide = 32u;       // not an error: the sweeps for long lists narrowed some tensor down
 constexpr uint32_t kErrLoose = 16u;      // not an error: a carried-over filter key let far too many entries pass
 constexpr uint32_t kErrStaleKeys = 256u; // not an error: the filter keys the previous call left would have let far too many entries pass now
-constexpr uint32_t kErrDeferred = 64u;   // not an error: a tensor the streaming kernel could not finish itself is left to k_select
+constexpr uint32_t kErrDeferred = 64u;   // not an error: a tensor the streaming kernel could not finish itself is left to the kernels after it
 
 // Candidates per side beyond which a list counts as a flood (the next call then estimates its keys
 // afresh): 16 k + 8192, but at most one entry in 16 of the tensor if that is above 8 k + 4096 (a
@@ -91,31 +81,15 @@ __host__ __device__ inline unsigned long long loose_limit(uint32_t k, uint32_t n
 }
 
 // TensorDesc::flags
-constexpr int kWindow = 2048;             // bins of the leading-bits histograms (k_select, grid-wide selection)
-// Grid-wide selection, first histogram: the leading 19 key bits (1024 steps per octave) counted in a window of two octaves
-// above the filter key.  Wider than k_select's half octave on purpose: a filter key carried over
-// from the previous call may lie far below this call's k-th entry while the data still grows, and
-// a tensor whose k-th entry lies beyond the window falls to one workgroup.
-constexpr int kWideShift = 13;
-
-// The window bin of a side key, given the side's filter key.
-__device__ __forceinline__ uint32_t wide_window_bin(uint32_t key, uint32_t lo_key) {
-    const uint32_t v = key >> kWideShift, base = lo_key >> kWideShift;
-    const uint32_t o = v >= base ? v - base : 0u;       // (no candidate lies below its filter key)
-    return o < (uint32_t)(kWindow - 1) ? o : (uint32_t)(kWindow - 1);
-}
-
-constexpr uint32_t kDescFused = 1u;      // sorted and encoded inside the select kernel
-constexpr uint32_t kDescWide = 2u;       // keeps so many entries that the grid-wide selection kernels take it
+constexpr uint32_t kDescWide = 2u;       // keeps so many entries that sweeps by many workgroups narrow its lists down first
 constexpr uint32_t kDescSampled = 4u;    // subsampled variant: the sampled threshold decides what is kept
 constexpr uint32_t kDescInline = 8u;     // finished inside the streaming kernel by the last of its workgroups
 // TensorState::flags
 constexpr uint32_t kStFailed = 1u;       // prefilter kept fewer than k candidates on a side
 constexpr uint32_t kStExact = 2u;        // taken over by the histogram path
-constexpr uint32_t kStWideDone = 4u;     // selected and applied by the grid-wide kernels
 constexpr uint32_t kStInlineDone = 8u;   // selected and encoded inside the streaming kernel
 constexpr uint32_t kStResidualDone = 16u; // ... which also applied the residual update (one-chunk tensors)
-constexpr uint32_t kStDeferred = 32u;    // the streaming kernel left this tensor to k_select
+constexpr uint32_t kStDeferred = 32u;    // the streaming kernel left this tensor to the kernels after it
 
 // One tensor of the call, built on the host.
 struct TensorDesc {
@@ -128,11 +102,13 @@ struct TensorDesc {
     uint64_t cand_off;    // candidate list of the positive side starts here; negative side at +cand_cap
     uint64_t stage_off;   // first word of this tensor's stream in the staging area
     uint32_t bound_words; // worst-case stream length in words
-    uint32_t kept_off;    // first entry of this tensor in the kept-index scratch
+    uint32_t kept_off;    // (tensors finished in the streaming kernel) first entry of this tensor in the kept-index scratch
     uint32_t flags;
     uint32_t kcap;        // most entries a side may keep: k, or min(n, 2k + 64) in the subsampled variant
     uint32_t grp0;        // first of this tensor's chunk groups
+    uint32_t wide;        // (kDescWide) its number among the call's wide tensors
     uint32_t cand_cap;    // entries each side's candidate list holds: n, or fewer in a compact context
+    uint32_t pad;
 };
 
 // Per-tensor results, written on the device.
@@ -150,10 +126,10 @@ struct alignas(8) TensorState {
     uint32_t flags;
     uint64_t bit_len;
     uint32_t done;         // chunks (or groups of chunks) of this tensor that the streaming kernel has completed
-    uint32_t pad;
+    uint32_t sorted_kept;  // 1: the kept positions are in the kept-index scratch (streaming kernel), 0: in the bitmap
     uint32_t cand_seen[2]; // candidates per side the finishing workgroup found (inspection)
-    uint32_t expect[2];    // carried keys: entries per side known to lie at or beyond lo_key before the next update
-                           // is added (0: not known)
+    uint32_t expect[2];    // carried keys: entries per side known to lie at or beyond lo_key before this call's k are
+                           // sent and the next update is added (0: not known)
 };
 
 // Per group of kGroupChunks consecutive chunks of a tensor that the streaming kernel finishes
@@ -165,6 +141,19 @@ struct alignas(16) GroupState {
     uint32_t done;
     uint32_t pad[3];
 };
+
+// Where the candidates of a chunk lie in its tensor's lists: one run per side.  (The chunks of a
+// streaming workgroup that takes several consecutive ones share one run.)
+struct alignas(8) ChunkRun {
+    uint64_t at[2];        // place of the first one in the call's candidate array
+    uint32_t cnt[2];
+};
+__device__ __forceinline__ ChunkRun chunk_run(const TensorDesc& d, uint32_t base_p, uint32_t base_n, uint32_t cnt_p, uint32_t cnt_n) {
+    ChunkRun r;
+    r.at[0] = d.cand_off + base_p; r.at[1] = d.cand_off + d.cand_cap + base_n;
+    r.cnt[0] = cnt_p; r.cnt[1] = cnt_n;
+    return r;
+}
 
 // Per-chunk summary of the kept-position bitmap.
 struct ChunkSummary {
@@ -295,6 +284,25 @@ __device__ __forceinline__ T wave_incl_max(T v) {
     o = dpp_fetch<0x142, 0xa>(v); v = o > v ? o : v;
     o = dpp_fetch<0x143, 0xc>(v); v = o > v ? o : v;
     return v;
+}
+
+// Sum of one fp64 value per lane; lane 63 gets it (the same tree as wave_incl_sum's).
+__device__ __forceinline__ double wave_sum_f64(double v) {
+    auto add = [&](unsigned long long x) { v += __longlong_as_double((long long)x); };
+    add(dpp_fetch<0x111, 0xf>((unsigned long long)__double_as_longlong(v)));
+    add(dpp_fetch<0x112, 0xf>((unsigned long long)__double_as_longlong(v)));
+    add(dpp_fetch<0x114, 0xf>((unsigned long long)__double_as_longlong(v)));
+    add(dpp_fetch<0x118, 0xf>((unsigned long long)__double_as_longlong(v)));
+    add(dpp_fetch<0x142, 0xa>((unsigned long long)__double_as_longlong(v)));
+    add(dpp_fetch<0x143, 0xc>((unsigned long long)__double_as_longlong(v)));
+    return v;
+}
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+__device__ __forceinline__ unsigned long long last_lane(unsigned long long v) {
+    return ((unsigned long long)last_lane((uint32_t)(v >> 32)) << 32) | last_lane((uint32_t)v);
+}
+__device__ __forceinline__ double last_lane(double v) {
+    return __longlong_as_double((long long)last_lane((unsigned long long)__double_as_longlong(v)));
 }
 
 // Exclusive prefix sum over the NT threads of a workgroup; *total receives the sum.

@@ -17,21 +17,20 @@
 #include <vector>
 
 #include "sbc_accumulate_kernels.hpp"
-#include "sbc_select_kernels.hpp"
+#include "sbc_threshold_kernels.hpp"
 #include "sbc_encode_kernels.hpp"
 #include "sbc_decode_kernels.hpp"
-#include "sbc_wide_kernels.hpp"
 #include "sbc_step_kernels.hpp"
 
 using namespace sbc;
 
 namespace {
 // kernels of sbc_compress in launch order (the histogram path repeats some of them)
-enum Stage { kStSample = 0, kStAccumulate, kStWide, kStSelect, kStChunkSummary, kStTensorScan, kStPack,
+enum Stage { kStSample = 0, kStAccumulate, kStWide, kStThreshold, kStApply, kStTensorScan, kStEmit,
              kStGather, kNumStages };
 const char* const kStageNames[kNumStages] = {
-    "k_sample_thresholds", "k_client_step", "k_wide_* (grid-wide selection, all launches)", "k_select",
-    "k_chunk_summary", "k_tensor_scan", "k_pack", "k_finish_message"};
+    "k_sample_thresholds", "k_client_step", "k_wide_* (sweeps over long lists)", "k_threshold",
+    "k_apply", "k_tensor_scan", "k_emit", "k_finish_message"};
 }  // namespace
 
 constexpr int kDescSlots = 4;             // device copies of the tensor table, keyed by the pointer lists
@@ -58,7 +57,7 @@ struct sbc_ctx {
 
     // ---- device scratch of sbc_compress ----
     TensorDesc* d_desc = nullptr;         // kDescSlots tables of max_tensors entries
-    uint32_t* d_chunk_tensor = nullptr;
+    uint2* d_chunk_tensor = nullptr;      // chunk -> (tensor, the tensor's first chunk)
     uint2* d_sched = nullptr;             // workgroup of the streaming kernel -> (chunk, tensor)
     GroupState* d_group = nullptr;        // per group of chunks: candidate and completion counters
     uint64_t max_groups = 0;
@@ -69,22 +68,20 @@ struct sbc_ctx {
     uint32_t* d_hist = nullptr;
     TensorState* d_state = nullptr;
     uint2* d_cand = nullptr;
+    ChunkRun* d_runs = nullptr;           // per chunk: where its candidates lie
     uint32_t* d_bitmap = nullptr;
     uint32_t* d_stage = nullptr;
     uint32_t* d_kept = nullptr;
     ChunkSummary* d_sum = nullptr;
     uint32_t* d_prev_end = nullptr;
     uint64_t* d_bitoff = nullptr;
-    TileSummary* d_tile = nullptr;        // per tile of kScanTile chunks of a tensor encoded from the bitmap
+    TileSummary* d_tile = nullptr;        // per tile of kScanTile chunks of a tensor
     ResultBlock* d_result = nullptr;      // two for compress, two for decode, used in turn; [4] collects the
                                           // errors of decode calls whose status is deferred, [5] is a spare
     // grid-wide selection
     WideState* d_wide_state = nullptr;
     uint32_t* d_wide_hist = nullptr;
-    uint32_t* d_wide_hist2 = nullptr;
-    uint32_t* d_wide_tie_cnt = nullptr;
     long long* d_wide_acc = nullptr;
-    uint32_t* d_wide_tie = nullptr;
 
     // ---- device scratch of sbc_decompress_accumulate ----
     DecDesc* d_dec = nullptr;
@@ -99,10 +96,11 @@ struct sbc_ctx {
 
     // ---- pinned host staging ----
     TensorDesc* h_desc = nullptr;
-    uint32_t* h_chunk_tensor = nullptr;
+    uint2* h_chunk_tensor = nullptr;
     uint2* h_sched = nullptr;
     uint32_t* h_order = nullptr;
-    uint32_t* h_wide_ids = nullptr;
+    WideIds wide_ids = {};
+    int max_wide = 0;
     ResultBlock* h_result_dev = nullptr;  // h_result as the device addresses it
     ResultBlock* h_result = nullptr;      // compress
     uint32_t result_seq = 0;              // number of the latest launch of the message-assembly kernel
@@ -119,15 +117,15 @@ struct sbc_ctx {
     bool cache_valid = false; int cache_T = 0; double cache_p = 0.0;
     std::vector<int64_t> cache_numel;
     uint64_t cache_total = 0, cache_chunks = 0, cache_stage_words = 0, cache_kept_total = 0, cache_max_bound = 0;
-    uint32_t cache_scan_tiles = 1;        // most tiles of the chunk scan among the tensors encoded from the bitmap
-    uint32_t cache_bitmap_chunks_max = 0; // most chunks among those tensors
-    bool cache_any_bitmap = false;
+    uint32_t cache_scan_tiles = 1;        // most tiles of the chunk scan that a tensor has
+    uint32_t cache_chunks_max = 0;        // most chunks that a tensor has
     bool cache_all_inline = false;        // every tensor is finished inside the streaming kernel
     int cache_force_exact = 0;
     std::vector<TensorDesc> plan;         // without the pointers
     std::vector<uint32_t> plan_order;
-    int n_wide = 0;                       // tensors given to the grid-wide selection
+    int n_wide = 0;                       // tensors whose long lists are narrowed down by sweeps
     uint32_t wide_blocks = 0;
+    uint32_t staged_keys = 0;             // keys of a list that k_threshold stages in LDS
     DescSlot slot[kDescSlots];            // which pointer lists the device tables hold
     uint64_t slot_clock = 0;
 
@@ -175,7 +173,7 @@ struct sbc_ctx {
         hipStream_t stream = nullptr;
         int T = 0, b = 0, slot = 0, force_exact = 0, carry = 0;
         double p = 0.0;
-        bool slot_is_new = false, use_history = false, sampled = false, any_bitmap = false, all_inline = false;
+        bool slot_is_new = false, use_history = false, sampled = false, all_inline = false;
         bool wait_on_event = false;   // begin/end form: the wait ends with this step, not with the stream
         bool timed[kNumStages] = {};
         ResultBlock* res_now = nullptr;
@@ -184,7 +182,7 @@ struct sbc_ctx {
         uint8_t* msg8 = nullptr;
         size_t msg_capacity = 0, need = 0;
         uint32_t n_chunks = 0;
-        unsigned gather_y = 1, scan_tiles = 1, bitmap_chunks_max = 0;
+        unsigned gather_y = 1, scan_tiles = 1, chunks_max = 0;
     } pend;
 
     // last compress call, for the inspection entry points
@@ -250,9 +248,7 @@ void free_all(sbc_ctx* c) {
     (void)hipFree(c->d_dec_wide); (void)hipFree(c->d_seg_fn); (void)hipFree(c->d_seg_pack); (void)hipFree(c->d_tile_fn);
     (void)hipFree(c->d_tile_sum); (void)hipFree(c->d_tile_entry);
     if (c->h_dec_wide) (void)hipHostFree(c->h_dec_wide);
-    (void)hipFree(c->d_wide_state); (void)hipFree(c->d_wide_hist);
-    (void)hipFree(c->d_wide_acc); (void)hipFree(c->d_wide_tie); (void)hipFree(c->d_wide_hist2); (void)hipFree(c->d_wide_tie_cnt);
-    if (c->h_wide_ids) (void)hipHostFree(c->h_wide_ids);
+    (void)hipFree(c->d_wide_state); (void)hipFree(c->d_wide_hist); (void)hipFree(c->d_wide_acc); (void)hipFree(c->d_runs);
     if (c->h_desc) (void)hipHostFree(c->h_desc);
     if (c->h_chunk_tensor) (void)hipHostFree(c->h_chunk_tensor);
     if (c->h_sched) (void)hipHostFree(c->h_sched);
@@ -279,97 +275,70 @@ int status_of_err(uint32_t err) {
 // stop event that take the dispatch's own begin and end time stamps (event 2s and 2s+1 for
 // stage s), so the figure is the kernel's duration without the gaps between dispatches.
 // Expects c (context), lvl (profile level), stream and timed[] in scope.
-#define SBC_LAUNCH(stage, on, kernel, grid, block, ...)                                                    \
+#define SBC_LAUNCH(stage, on, kernel, grid, block, ...) SBC_LAUNCH_LDS(stage, on, kernel, grid, block, 0, __VA_ARGS__)
+#define SBC_LAUNCH_LDS(stage, on, kernel, grid, block, lds, ...)                                           \
     do {                                                                                                   \
         if ((on) && (lvl >= 2 || (lvl == 1 && ((stage) == kStAccumulate || (stage) == kStSample)))) {      \
-            hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, c->ev[2 * (stage)], c->ev[2 * (stage) + 1], 0, \
+            hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, c->ev[2 * (stage)], c->ev[2 * (stage) + 1], 0, \
                                   __VA_ARGS__);                                                            \
             timed[stage] = true;                                                                           \
         } else {                                                                                           \
-            hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);                               \
+            hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                             \
         }                                                                                                  \
     } while (0)
 
-// Alg. 3 for the tensors whose positions are in the bitmap, then the message assembly, for the
-// pending client step.
-void launch_encode_and_gather(sbc_ctx* c, bool profile) {
+// From the candidate lists to the message, for the pending client step: thresholds and sums (pass
+// 0: of every tensor the streaming kernel has not finished itself; pass 1: of those handed over),
+// side decision, residual update and bitmap, Alg. 3, message assembly.
+void launch_selection_and_encode(sbc_ctx* c, int pass) {
     sbc_ctx::Pending& P = c->pend;
+    const bool profile = pass == 0;
     const int lvl = c->profile_level;
     hipStream_t stream = P.stream;
     bool* timed = P.timed;
     const int T = P.T, b = P.b;
-    if (P.any_bitmap && P.bitmap_chunks_max <= kSelfScanChunks && P.n_chunks <= 8192u) {
-        // no tensor of many chunks among those encoded from the bitmap: the workgroups that write
-        // the codes scan the few summaries before their chunk themselves, one launch less
-        SBC_LAUNCH(kStChunkSummary, profile, k_chunk_summary<1>, dim3(P.n_chunks), dim3(kChunkWords), P.d_desc,
-                   c->d_chunk_tensor, c->d_bitmap, c->d_sum, b, P.n_chunks);
-        SBC_LAUNCH(kStPack, profile, (k_pack<1, true>), dim3(P.n_chunks), dim3(kChunkWords), P.d_desc, c->d_chunk_tensor,
-                   c->d_bitmap, c->d_sum, c->d_prev_end, c->d_bitoff, c->d_state, b, c->d_stage, P.res_now, P.n_chunks);
-    } else if (P.any_bitmap) {
-        // (with very many chunks a workgroup takes four of them: see the kernels)
-        const bool batch = P.n_chunks > 8192u;
-        const dim3 per_chunk(batch ? (P.n_chunks + 3u) / 4u : P.n_chunks);
-        if (batch) {
-            SBC_LAUNCH(kStChunkSummary, profile, k_chunk_summary<4>, per_chunk, dim3(kChunkWords), P.d_desc,
-                       c->d_chunk_tensor, c->d_bitmap, c->d_sum, b, P.n_chunks);
-        } else {
-            SBC_LAUNCH(kStChunkSummary, profile, k_chunk_summary<1>, per_chunk, dim3(kChunkWords), P.d_desc,
-                       c->d_chunk_tensor, c->d_bitmap, c->d_sum, b, P.n_chunks);
+    if (pass != 0 || !P.all_inline) {
+        if (pass == 0 && c->n_wide > 0) {
+            const dim3 sweep(c->wide_blocks, 2u * (unsigned)c->n_wide);
+            if (lvl >= 2) {
+                hipExtLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, c->ev[2 * kStWide], nullptr, 0,
+                                      P.d_desc, c->wide_ids, c->d_state, c->d_cand, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
+                hipExtLaunchKernelGGL(k_wide_collect, sweep, dim3(kWideThreads), 0, stream, nullptr, c->ev[2 * kStWide + 1], 0,
+                                      P.d_desc, c->wide_ids, c->d_state, c->d_cand, c->d_bitmap, c->d_wide_hist, c->d_wide_acc,
+                                      c->d_wide_state);
+                timed[kStWide] = true;
+            } else {
+                hipLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, P.d_desc, c->wide_ids, c->d_state,
+                                   c->d_cand, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
+                hipLaunchKernelGGL(k_wide_collect, sweep, dim3(kWideThreads), 0, stream, P.d_desc, c->wide_ids, c->d_state,
+                                   c->d_cand, c->d_bitmap, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
+            }
         }
-        if (P.scan_tiles > 1)
-            hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_sum,
-                               c->d_tile, b);
-        SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
-                   c->d_tile, c->d_prev_end, c->d_bitoff, c->d_state, b);
-        if (batch) {
-            SBC_LAUNCH(kStPack, profile, (k_pack<4, false>), per_chunk, dim3(kChunkWords), P.d_desc, c->d_chunk_tensor,
-                       c->d_bitmap, c->d_sum, c->d_prev_end, c->d_bitoff, c->d_state, b, c->d_stage, P.res_now, P.n_chunks);
+        // (largest tensors first if not all workgroups fit the chip at once)
+        SBC_LAUNCH_LDS(kStThreshold, profile, k_threshold, dim3(2u * (unsigned)T), dim3(kThThreads), c->staged_keys * sizeof(uint32_t),
+                       P.d_desc, T > 256 ? c->d_order : nullptr, c->d_state, c->d_cand, c->d_bitmap, c->d_wide_state,
+                       c->d_wide_hist, c->d_wide_acc, pass, P.carry, c->staged_keys, P.res_now);
+        const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
+        SBC_LAUNCH(kStApply, profile, k_apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
+                   c->d_cand, c->cand_entries, c->d_bitmap, c->d_sum, c->d_stage, b, pass, P.n_chunks, P.res_now);
+        if (P.chunks_max <= kSelfScanChunks) {
+            // no tensor of many chunks: the wavefronts that write the codes scan the few summaries before
+            // their chunk themselves, one launch less
+            SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_bitmap, c->d_sum,
+                       c->d_prev_end, c->d_bitoff, c->d_state, c->d_state, b, pass, c->d_stage, P.n_chunks, P.res_now);
         } else {
-            SBC_LAUNCH(kStPack, profile, (k_pack<1, false>), per_chunk, dim3(kChunkWords), P.d_desc, c->d_chunk_tensor,
-                       c->d_bitmap, c->d_sum, c->d_prev_end, c->d_bitoff, c->d_state, b, c->d_stage, P.res_now, P.n_chunks);
+            if (P.scan_tiles > 1)
+                hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_state,
+                                   c->d_sum, c->d_tile, b, pass);
+            SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
+                       c->d_tile, c->d_prev_end, c->d_bitoff, c->d_state, b, pass);
+            SBC_LAUNCH(kStEmit, profile, k_emit<false>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_bitmap, c->d_sum,
+                       c->d_prev_end, c->d_bitoff, c->d_state, c->d_state, b, pass, c->d_stage, P.n_chunks, P.res_now);
         }
     }
     SBC_LAUNCH(kStGather, profile, k_finish_message, dim3(T, P.gather_y), dim3(256), P.d_desc, c->d_state, T, b,
                c->d_stage, c->d_kept, c->d_group, P.msg8, (uint64_t)P.msg_capacity, P.res_now, P.res_next,
                c->h_result_dev, ++c->result_seq);
-}
-
-// Alg. 2 for the pending step's tensors that keep very many entries, as grid-wide sweeps over
-// their candidate lists with one-workgroup steps in between (the tensors k_select then skips).
-void launch_wide_selection(sbc_ctx* c, bool handback) {
-    sbc_ctx::Pending& P = c->pend;
-    const int lvl = c->profile_level;
-    hipStream_t stream = P.stream;
-    bool* timed = P.timed;
-    TensorDesc* const d_desc = P.d_desc;
-    ResultBlock* const res_now = P.res_now;
-    // (the sweeps that carry the second histogram have four times the threads per workgroup)
-    const dim3 sweep(c->wide_blocks, (unsigned)c->n_wide), sweep4(std::max(128u, c->wide_blocks / 4u), (unsigned)c->n_wide);
-    const bool time_wide = lvl >= 2;
-    WideIds ids = {};
-    std::memcpy(ids.id, c->h_wide_ids, sizeof(uint32_t) * (size_t)c->n_wide);
-    if (time_wide) {
-        hipExtLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, c->ev[2 * kStWide], nullptr, 0,
-                              d_desc, ids, c->d_state, c->d_cand, c->d_wide_hist);
-    } else {
-        hipLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, d_desc, ids, c->d_state,
-                           c->d_cand, c->d_wide_hist);
-    }
-    hipLaunchKernelGGL(k_wide_refine, sweep4, dim3(kWideSweepThreads), 0, stream, d_desc, ids, c->d_state,
-                       c->d_cand, c->d_wide_state, c->d_wide_hist, c->d_wide_hist2, c->d_wide_acc, c->d_wide_tie_cnt);
-    hipLaunchKernelGGL(k_wide_sums, sweep4, dim3(kWideSweepThreads), 0, stream, d_desc, ids, c->d_state,
-                       c->d_cand, c->d_wide_state, c->d_wide_hist, c->d_wide_hist2, c->d_wide_acc, c->d_wide_tie,
-                       c->d_wide_tie_cnt);
-    if (time_wide) {
-        hipExtLaunchKernelGGL(k_wide_apply, sweep, dim3(kWideThreads), 0, stream, nullptr, c->ev[2 * kStWide + 1], 0,
-                              d_desc, ids, c->d_state, c->d_cand, c->d_wide_state, c->d_wide_hist2, c->d_wide_acc,
-                              c->d_wide_tie, c->d_wide_tie_cnt, c->d_bitmap, handback ? 1 : 0, res_now);
-        timed[kStWide] = true;
-    } else {
-        hipLaunchKernelGGL(k_wide_apply, sweep, dim3(kWideThreads), 0, stream, d_desc, ids, c->d_state,
-                           c->d_cand, c->d_wide_state, c->d_wide_hist2, c->d_wide_acc, c->d_wide_tie, c->d_wide_tie_cnt,
-                           c->d_bitmap, handback ? 1 : 0, res_now);
-    }
 }
 
 // The pending step's result block on its way to the host / waited for.
@@ -550,8 +519,9 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     // full: both sides' lists of every tensor hold every entry; compact: half an entry per entry in all
     // (plus the lists' fixed part), shared out by the plan of each call
     c->cand_entries = compact ? (uint64_t)max_total_elems / 2 + 2048ull * (uint64_t)max_tensors : 2ull * (uint64_t)max_total_elems;
+    c->cand_entries = std::max<uint64_t>(c->cand_entries, 128u);      // (k_apply reads a run's first 64 ahead)
     c->max_chunks = (uint64_t)max_total_elems / kChunk + (uint64_t)max_tensors;
-    c->kept_cap = std::min<uint64_t>((uint64_t)max_total_elems, (uint64_t)kFusedBigK * (uint64_t)max_tensors);
+    c->kept_cap = std::min<uint64_t>((uint64_t)max_total_elems, (uint64_t)std::max(kInlineMaxK, kSmallMaxN) * (uint64_t)max_tensors);
     // A tensor's stream is at most k(1+b*) + (n-k)/2^b* bits, which stays below 1.3 n for every p
     // (b* shrinks as p grows); n/16 words plus rounding per tensor is ample, and sbc_compress
     // checks the actual need against this capacity.
@@ -571,6 +541,7 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_state, T) == hipSuccess;
     ok = ok && hipMemset(c->d_state, 0, sizeof(TensorState) * T) == hipSuccess;
     ok = ok && dev_alloc(&c->d_cand, (size_t)c->cand_entries) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_runs, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_bitmap, (size_t)c->max_chunks * kChunkWords) == hipSuccess;
     ok = ok && dev_alloc(&c->d_stage, (size_t)c->stage_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_kept, (size_t)c->kept_cap) == hipSuccess;
@@ -592,17 +563,12 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_tile_fn, (size_t)c->dec_tile_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile_sum, (size_t)c->dec_tile_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile_entry, (size_t)c->dec_tile_cap) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_wide_state, (size_t)kMaxWide) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_wide_hist, (size_t)kMaxWide * 2 * kWindow) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_wide_hist2, (size_t)kMaxWide * 2 * kWideRefine) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_wide_tie_cnt, (size_t)kMaxWide * 2) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_wide_acc, (size_t)kMaxWide * 512) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_wide_tie, (size_t)kMaxWide * 2 * kWideTieMax) == hipSuccess;
-    ok = ok && host_alloc(&c->h_wide_ids, (size_t)kMaxWide) == hipSuccess;
-    // the histograms and accumulators start out zero; the kernels that read them leave them zero
-    ok = ok && hipMemset(c->d_wide_hist, 0, sizeof(uint32_t) * kMaxWide * 2 * kWindow) == hipSuccess;
-    ok = ok && hipMemset(c->d_wide_hist2, 0, sizeof(uint32_t) * kMaxWide * 2 * kWideRefine) == hipSuccess;
-    ok = ok && hipMemset(c->d_wide_acc, 0, sizeof(long long) * kMaxWide * 512) == hipSuccess;
+    c->max_wide = std::min(kMaxWide, max_tensors);
+    ok = ok && dev_alloc(&c->d_wide_state, (size_t)c->max_wide * 2) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_wide_hist, (size_t)c->max_wide * 2 * kThBins) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_wide_acc, (size_t)c->max_wide * 2 * 256) == hipSuccess;
+    // the histograms start out zero; the kernel that reads them leaves them zero
+    ok = ok && hipMemset(c->d_wide_hist, 0, sizeof(uint32_t) * c->max_wide * 2 * kThBins) == hipSuccess;
     ok = ok && host_alloc(&c->h_desc, T) == hipSuccess;
     ok = ok && host_alloc(&c->h_chunk_tensor, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && host_alloc(&c->h_order, T) == hipSuccess;
@@ -711,8 +677,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     // pointers) lives in one of kDescSlots device copies keyed by the pointer lists, so a caller
     // that alternates between a few sets of buffers uploads nothing in the steady state.
     uint64_t total = 0, chunks = 0, stage_words = 0, kept_total = 0, max_bound = 0, groups = 0, cand_total = 0;
-    bool any_bitmap = false, all_inline = true;
-    uint32_t scan_tiles = 1, bitmap_chunks_max = 0;
+    bool all_inline = true;
+    uint32_t scan_tiles = 1, chunks_max = 0;
     // in the subsampled variant the keys must come from this call's sample
     const bool sampled = c->sampled != 0;
     const int force_exact = sampled ? 0 : c->force_exact;
@@ -732,8 +698,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     int slot = -1;
     if (sizes_same) {
         total = c->cache_total; chunks = c->cache_chunks; stage_words = c->cache_stage_words;
-        kept_total = c->cache_kept_total; max_bound = c->cache_max_bound; any_bitmap = c->cache_any_bitmap;
-        scan_tiles = c->cache_scan_tiles; bitmap_chunks_max = c->cache_bitmap_chunks_max;
+        kept_total = c->cache_kept_total; max_bound = c->cache_max_bound;
+        scan_tiles = c->cache_scan_tiles; chunks_max = c->cache_chunks_max;
         all_inline = c->cache_all_inline;
         for (int i = 0; i < kDescSlots; ++i) {
             const DescSlot& sl = c->slot[i];
@@ -748,6 +714,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         if (c->plan.size() < (size_t)T) c->plan.resize(T);
         int n_wide = 0;
         uint64_t wide_max_n = 0;
+        uint32_t kmax = 0;
         for (int t = 0; t < T; ++t) {
             const int64_t n = numel[t];
             if (n < 1 || n >= (int64_t)1 << 32) return SBC_EINVAL;
@@ -769,31 +736,32 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
             const uint64_t bw = bound_words_of(n, d.kcap, b);
             if (bw >= (1ull << 32)) return SBC_ECAPACITY;
             d.bound_words = (uint32_t)bw;
-            const bool fused = (d.kcap <= kFusedMaxK && bw <= kFusedMaxWords) ||
-                               (d.kcap <= kFusedBigK && d.kcap < c->wide_min_kept && bw + 1u <= fused_sort_capacity(d.kcap));
             // finished inside the streaming kernel: exact mode, and few enough kept entries and stream
             // words for one workgroup's LDS (a one-chunk tensor: any k, encoded from a bitmap)
             const uint32_t n_groups = (d.nchunks + kGroupChunks - 1u) / kGroupChunks;
-            const bool inl = c->fused_step && !sampled && !force_exact && fused && n_groups <= (uint32_t)kMaxGroups &&
+            const bool inl = c->fused_step && !sampled && !force_exact && n_groups <= (uint32_t)kMaxGroups &&
                              (d.nchunks == 1u && d.n <= kSmallMaxN ? bw <= kSmallMaxWords
                                                                    : (d.kcap <= kInlineMaxK && bw <= kInlineMaxWords));
-            d.flags = (fused ? kDescFused : 0u) | (sampled ? kDescSampled : 0u) | (inl ? kDescInline : 0u);
+            d.flags = (sampled ? kDescSampled : 0u) | (inl ? kDescInline : 0u);
             all_inline = all_inline && inl;
             d.grp0 = (uint32_t)groups;
             if (inl) groups += n_groups;
-            if (!fused && d.kcap >= c->wide_min_kept && n_wide < kMaxWide) {
+            if (!inl && d.kcap >= c->wide_min_kept && n_wide < c->max_wide) {
                 d.flags |= kDescWide;
-                c->h_wide_ids[n_wide++] = (uint32_t)t;
+                d.wide = (uint32_t)n_wide;
+                c->wide_ids.id[n_wide++] = (uint32_t)t;
                 wide_max_n = std::max<uint64_t>(wide_max_n, (uint64_t)n);
+            } else {
+                kmax = std::max(kmax, d.kcap);
             }
             d.kept_off = (uint32_t)kept_total;
-            if (fused) kept_total += d.kcap; else any_bitmap = true;
+            if (inl) kept_total += d.kcap;
             total += (uint64_t)n;
             chunks += d.nchunks;
             stage_words += bw;
             max_bound = std::max<uint64_t>(max_bound, bw);
-            if (!fused) scan_tiles = std::max<uint32_t>(scan_tiles, (d.nchunks + kScanTile - 1u) / kScanTile);
-            if (!fused) bitmap_chunks_max = std::max<uint32_t>(bitmap_chunks_max, d.nchunks);
+            scan_tiles = std::max<uint32_t>(scan_tiles, (d.nchunks + kScanTile - 1u) / kScanTile);
+            chunks_max = std::max<uint32_t>(chunks_max, d.nchunks);
             if (total > (uint64_t)c->max_elems || cand_total > c->cand_entries || chunks > c->max_chunks || kept_total > c->kept_cap ||
                 stage_words > c->stage_cap || groups > c->max_groups)
                 return SBC_ECAPACITY;
@@ -801,6 +769,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         }
         if (chunks >= (1ull << 31)) return SBC_ECAPACITY;
         c->n_wide = n_wide;
+        c->staged_keys = threshold_staged(kmax, n_wide > 0);
         // sweeps over a candidate list: enough workgroups to fill the chip, each with several rounds;
         // at least 128 even for short lists (a compute unit pulls a small share sooner than a large one,
         // and the tensor-wide step every workgroup repeats costs the same in all of them at once)
@@ -825,8 +794,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
                          [&](uint32_t x, uint32_t y) { return c->plan[x].n > c->plan[y].n; });
         for (int t = 0; t < T; ++t) {
             c->h_order[t] = c->plan_order[t];
-            uint32_t* ct = c->h_chunk_tensor + c->plan[t].chunk0;
-            for (uint32_t j = 0; j < c->plan[t].nchunks; ++j) ct[j] = (uint32_t)t;
+            uint2* ct = c->h_chunk_tensor + c->plan[t].chunk0;
+            for (uint32_t j = 0; j < c->plan[t].nchunks; ++j) ct[j] = make_uint2((uint32_t)t, c->plan[t].chunk0);
         }
         // Order of the streaming kernel's workgroups: the one-chunk tensors it finishes on the spot
         // go first (their selection then runs beside the streaming of everything else), the others
@@ -858,15 +827,15 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         }
         if (hipMemcpyAsync(c->d_order, c->h_order, sizeof(uint32_t) * T, hipMemcpyHostToDevice, stream) != hipSuccess ||
             hipMemcpyAsync(c->d_sched, c->h_sched, sizeof(uint2) * c->n_sched, hipMemcpyHostToDevice, stream) != hipSuccess ||
-            hipMemcpyAsync(c->d_chunk_tensor, c->h_chunk_tensor, sizeof(uint32_t) * chunks, hipMemcpyHostToDevice, stream) != hipSuccess) {
+            hipMemcpyAsync(c->d_chunk_tensor, c->h_chunk_tensor, sizeof(uint2) * chunks, hipMemcpyHostToDevice, stream) != hipSuccess) {
             (void)hipGetLastError();
             return SBC_EHIP;
         }
         c->cache_numel.assign(numel, numel + T);
         c->cache_T = T; c->cache_p = p;
         c->cache_total = total; c->cache_chunks = chunks; c->cache_stage_words = stage_words;
-        c->cache_kept_total = kept_total; c->cache_max_bound = max_bound; c->cache_any_bitmap = any_bitmap;
-        c->cache_scan_tiles = scan_tiles; c->cache_bitmap_chunks_max = bitmap_chunks_max;
+        c->cache_kept_total = kept_total; c->cache_max_bound = max_bound;
+        c->cache_scan_tiles = scan_tiles; c->cache_chunks_max = chunks_max;
         c->cache_all_inline = all_inline; c->cache_force_exact = force_exact;
         // (cache_valid is set once this call has completed: the uploads above must have happened)
     }
@@ -904,9 +873,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
                            (uint64_t)(2 * sizeof(ResultBlock) / 4));
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_group),
                            (uint64_t)c->max_groups * (sizeof(GroupState) / 4));
-        // (the grid-wide kernels leave their histograms clean only if all of them have run)
-        hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, c->d_wide_hist, (uint64_t)kMaxWide * 2 * kWindow);
-        hipLaunchKernelGGL(k_zero_words, dim3(256), dim3(256), 0, stream, c->d_wide_hist2, (uint64_t)kMaxWide * 2 * kWideRefine);
+        // (the sweeps' histograms are left clean only if all of the call's kernels have run)
+        hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, c->d_wide_hist, (uint64_t)c->max_wide * 2 * kThBins);
     }
     c->result_dirty = true;                           // until this call has completed normally
     c->hist_valid = false;
@@ -918,19 +886,19 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     // what sbc_compress_end and the launch helpers need
     sbc_ctx::Pending& P = c->pend;
     P.stream = stream; P.T = T; P.b = b; P.p = p; P.slot = slot; P.slot_is_new = slot_is_new;
-    P.force_exact = force_exact; P.use_history = use_history; P.sampled = sampled; P.any_bitmap = any_bitmap;
+    P.force_exact = force_exact; P.use_history = use_history; P.sampled = sampled;
     P.all_inline = all_inline;
     for (int st = 0; st < kNumStages; ++st) P.timed[st] = false;
     P.res_now = res_now; P.res_next = res_next; P.d_desc = d_desc; P.msg8 = msg8;
-    P.msg_capacity = msg_capacity; P.need = need; P.n_chunks = n_chunks; P.gather_y = gather_y; P.scan_tiles = scan_tiles; P.bitmap_chunks_max = bitmap_chunks_max;
+    P.msg_capacity = msg_capacity; P.need = need; P.n_chunks = n_chunks; P.gather_y = gather_y; P.scan_tiles = scan_tiles; P.chunks_max = chunks_max;
     P.wait_on_event = wait_on_event;
     const int lvl = c->profile_level;
     bool* timed = P.timed;
 
     SBC_HOST_TS(1);
-    // ---- fast path: [sample ->] accumulate + filter -> select (+ fused encode) -> gather ----
+    // ---- [sample ->] accumulate + filter [-> sweeps over long lists] -> thresholds -> apply -> emit -> message ----
     // The sampling kernel is skipped when the previous call left filter keys for the same tensor
-    // sizes and sparsity (its select kernel derives them from the exact thresholds it found).
+    // sizes and sparsity (k_threshold derives them from the ranks it counted).
     if (!use_history) {
         SBC_LAUNCH(kStSample, true, k_sample_thresholds, dim3(T), dim3(kSampleThreads), d_desc, c->d_state,
                    res_now, force_exact, sampled ? p : 0.0);
@@ -942,30 +910,19 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     if (!c->fused_step) {
         if (total * 12ull > (512ull << 20)) {
             SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<true>, dim3(c->n_sched), dim3(kStreamThreads), d_desc,
-                       c->d_sched, c->d_state, c->d_cand, c->d_bitmap, c->d_stage, res_now);
+                       c->d_sched, c->d_state, c->d_cand, c->d_runs, res_now);
         } else {
             SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<false>, dim3(c->n_sched), dim3(kStreamThreads), d_desc,
-                       c->d_sched, c->d_state, c->d_cand, c->d_bitmap, c->d_stage, res_now);
+                       c->d_sched, c->d_state, c->d_cand, c->d_runs, res_now);
         }
     } else if (total * 12ull > (512ull << 20)) {
         SBC_LAUNCH(kStAccumulate, true, k_client_step<true>, dim3(n_chunks), dim3(kStepThreads), d_desc, c->d_sched,
-                   c->d_state, c->d_cand, c->d_bitmap, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
+                   c->d_state, c->d_cand, c->d_runs, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
     } else {
         SBC_LAUNCH(kStAccumulate, true, k_client_step<false>, dim3(n_chunks), dim3(kStepThreads), d_desc, c->d_sched,
-                   c->d_state, c->d_cand, c->d_bitmap, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
+                   c->d_state, c->d_cand, c->d_runs, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
     }
-    if (!all_inline) {
-        // the tensors the streaming kernel does not finish itself
-        // (if every tensor goes through the grid-wide kernels, k_select has nothing to do unless one of
-        // them is handed back: the last of those kernels then asks for the second pass below)
-        const bool only_wide = c->n_wide == T;
-        if (c->n_wide > 0) launch_wide_selection(c, only_wide);
-        if (!only_wide) {
-            SBC_LAUNCH(kStSelect, true, k_select, dim3(T), dim3(kSelThreads), d_desc, c->d_order,
-                       c->d_state, c->d_cand, c->d_bitmap, c->d_stage, c->d_kept, b, 0, carry, res_now);
-        }
-    }
-    launch_encode_and_gather(c, true);
+    launch_selection_and_encode(c, 0);
     SBC_HOST_TS(2);
     const int rc = enqueue_result_copy(c);
     if (rc != SBC_OK) return rc;
@@ -985,7 +942,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
     P.active = false;
     DeviceGuard guard(c->device);
     hipStream_t stream = P.stream;
-    const int T = P.T, b = P.b;
+    const int T = P.T;
     TensorDesc* const d_desc = P.d_desc;
     ResultBlock* const res_now = P.res_now;
     int rc = wait_result(c);
@@ -1011,7 +968,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
 
     // ---- histogram path for the tensors whose filter kept fewer than k candidates ----
     // ---- second pass: the histogram route for the tensors whose filter kept fewer than k candidates,
-    // and k_select for the tensors the streaming kernel left to it ----
+    // and the selection for the tensors the streaming kernel left to it ----
     const uint32_t loose = err & (kErrLoose | kErrStaleKeys);
     c->last_deferred = (err & kErrDeferred) != 0u;
     if ((err & (kErrPrefilter | kErrDeferred)) && !(err & (kErrInternal | kErrNonFinite | kErrOverflow))) {
@@ -1026,11 +983,9 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
                                c->d_chunk_tensor, c->d_state, c->d_hist);
             hipLaunchKernelGGL(k_pick_bins, dim3(T), dim3(256), 0, stream, d_desc, c->d_hist, c->d_state, res_now);
             hipLaunchKernelGGL(k_extract, dim3(P.n_chunks), dim3(kStreamThreads), 0, stream, d_desc,
-                               c->d_chunk_tensor, c->d_state, c->d_cand, res_now);
+                               c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs);
         }
-        hipLaunchKernelGGL(k_select, dim3(T), dim3(kSelThreads), 0, stream, d_desc, c->d_order,
-                           c->d_state, c->d_cand, c->d_bitmap, c->d_stage, c->d_kept, b, 1, P.carry, res_now);
-        launch_encode_and_gather(c, false);
+        launch_selection_and_encode(c, 1);
         rc = enqueue_result_copy(c);
         if (rc == SBC_OK) rc = wait_result(c);
         if (rc != SBC_OK) return rc;
@@ -1302,12 +1257,12 @@ int sbc_last_mask(sbc_ctx* c, int tensor, uint32_t* mask_words, size_t n_words) 
     if (n_words != ((size_t)d.n + 31) / 32) return SBC_EINVAL;
     DeviceGuard guard(c->device);
     if (hipStreamSynchronize(c->last_stream) != hipSuccess) { (void)hipGetLastError(); return SBC_EHIP; }
-    if (d.flags & kDescFused) {
-        // the select kernel left the sorted kept indices in scratch
-        if (hipMemcpy(c->h_state, c->d_state + tensor, sizeof(TensorState), hipMemcpyDeviceToHost) != hipSuccess) {
-            (void)hipGetLastError();
-            return SBC_EHIP;
-        }
+    if (hipMemcpy(c->h_state, c->d_state + tensor, sizeof(TensorState), hipMemcpyDeviceToHost) != hipSuccess) {
+        (void)hipGetLastError();
+        return SBC_EHIP;
+    }
+    if (c->h_state[0].sorted_kept) {
+        // the streaming kernel left the sorted kept indices in scratch
         const uint32_t nnz = c->h_state[0].nnz;
         if (nnz > d.kcap) return SBC_EINTERNAL;
         std::vector<uint32_t> idx(nnz);

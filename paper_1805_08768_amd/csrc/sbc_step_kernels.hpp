@@ -31,7 +31,7 @@
 #pragma once
 
 #include "sbc_device.hpp"
-#include "sbc_select_kernels.hpp"
+#include "sbc_encode_kernels.hpp"
 
 namespace sbc {
 
@@ -40,7 +40,7 @@ constexpr int kStepWaves = kStepThreads / 64;
 constexpr int kSlots = kChunk / kStepThreads;            // 32 entries per thread
 constexpr int kWaveQueue = 128;                          // candidates per side a wavefront can queue in LDS
 constexpr uint32_t kInlineMaxK = 4224;                   // kept entries a finishing workgroup can sort and encode
-constexpr uint32_t kInlineMaxWords = kFusedMaxWords;     // (k_select must be able to take the tensor over)
+constexpr uint32_t kInlineMaxWords = 4096;               // ... and stream words
 constexpr int kInlineBuckets = 1024;                     // index sort: buckets by leading index bits
 constexpr uint32_t kSmallMaxWords = 512;                 // stream words of a one-chunk tensor (at most 1.3 bits per entry)
 constexpr uint32_t kInlineMaxCand = 32768;               // longest list a finishing workgroup takes on
@@ -214,7 +214,7 @@ struct Decision {
     int chosen;            // 0: positive side kept, 1: negative side
     float mu_signed;
     bool ok;
-    bool defer;            // not ok because the tensor is better left to k_select (no error)
+    bool defer;            // not ok because the tensor is better left to the kernels that follow (no error)
 };
 
 // --------------------------------------------------------------------------
@@ -223,7 +223,7 @@ struct Decision {
 // integers, the side with the larger mean, the transmitted mean.  Records the results in the
 // tensor's state; with `carry`, also the filter keys for a following call.  cnt[s]: entries of
 // side s; lo_cur[s]: the filter key they passed.  Returns ok = false (after raising an error bit
-// or flagging the tensor for k_select) if it cannot complete.  Contains barriers.
+// or flagging the tensor for the kernels that follow) if it cannot complete.  Contains barriers.
 // --------------------------------------------------------------------------
 template <typename Src, bool CAN_BISECT>
 __device__ __forceinline__ Decision select_tensor(StepShared& sh, int& parity, const Src& src, const TensorDesc& d,
@@ -348,7 +348,7 @@ __device__ __forceinline__ Decision select_tensor(StepShared& sh, int& parity, c
         const uint32_t kk[2] = {k, k};
         bisect_thresholds(sh, parity, src, kk, tau, itau);
     } else {
-        // tie-heavy data in lists too long for LDS: left to k_select
+        // tie-heavy data in lists too long for LDS: left to k_threshold
         dec.defer = true;
         return dec;
     }
@@ -573,7 +573,7 @@ __device__ __forceinline__ void finish_small(StepShared& sh, const LdsChunk& src
 
 // --------------------------------------------------------------------------
 // A tensor of several chunks, finished by the last of its workgroups to arrive, from the
-// candidate lists the others have appended; returns true if the tensor is to be left to k_select.
+// candidate lists the others have appended; returns true if the tensor is to be left to k_threshold.
 // offs (kInlineBuckets words), grp (k + 2 words) and
 // sorted (k words): LDS for the index sort, which may overlay the histogram but not the entries
 // `src` reads.
@@ -651,7 +651,7 @@ __device__ __forceinline__ bool finish_from_lists(StepShared& sh, const Src& src
 template <bool STREAM>
 __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ sched, TensorState* __restrict__ st,
-        uint2* __restrict__ cand, uint32_t* __restrict__ bitmap, uint32_t* __restrict__ stage,
+        uint2* __restrict__ cand, ChunkRun* __restrict__ runs, uint32_t* __restrict__ stage,
         uint32_t* __restrict__ kept_idx, GroupState* __restrict__ groups, int b, int carry,
         ResultBlock* __restrict__ result) {
     __shared__ StepShared sh;
@@ -667,15 +667,6 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
     const uint32_t cnt = min((uint32_t)kChunk, d.n - e0);
     const bool inline_t = (d.flags & kDescInline) != 0u;
     const bool small = inline_t && d.nchunks == 1u && d.n <= kSmallMaxN;
-
-    if (!(d.flags & kDescFused)) {
-        // encoded from the bitmap later: clear this chunk's bitmap words and share of the staging words
-        bitmap[(uint64_t)c * kChunkWords + tid] = 0u;
-        const uint32_t per = (d.bound_words + d.nchunks - 1u) / d.nchunks;
-        const uint32_t lo = per * cc;
-        const uint32_t hi = (lo + per < d.bound_words) ? lo + per : d.bound_words;
-        for (uint32_t w = lo + tid; w < hi; w += kStepThreads) stage[d.stage_off + w] = 0u;
-    }
 
     // ---- A = R + dW in registers: slot s of a thread is entry local(s) of the chunk ----
     const gcfloat_ptr dw = as_global(d.dW + e0);
@@ -823,7 +814,8 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         if (atomicAdd(&groups[d.grp0 + grp].done, 1u) + 1u != g_size) return false;
         return n_groups == 1u || atomicAdd(&st[t].done, 1u) + 1u == n_groups;
     };
-    bool fatal = false, last = false;
+    bool last = false;
+    uint32_t run_p = 0u, run_n = 0u;                      // where this chunk's candidates go
     if (!overflow) {
         if (qp + qn != 0u) {                              // uniform
             if (tid == 0) {
@@ -834,6 +826,7 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
             }
             __syncthreads();
             const uint32_t bp0 = sh.base[0], bn0 = sh.base[1];
+            run_p = bp0; run_n = bn0;
             if ((uint64_t)bp0 + qp > d.cand_cap || (uint64_t)bn0 + qn > d.cand_cap) {
                 // (beyond a list's capacity nothing is stored: the counters then show that the lists are not usable)
             } else {
@@ -841,7 +834,7 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
                 for (uint32_t i = lane; i < wc_n; i += 64u) { const uint2 e = sh.wq(wave, 1)[i]; store_cand(ln + bn0 + before_n + i, e.x, e.y); }
             }
         }
-        if (fatal) atomicOr(&result->err, kErrInternal);
+        if (tid == 0) runs[c] = chunk_run(d, run_p, run_n, qp, qn);
         SBC_STEP_TS(2);
         if (!inline_t) {                                  // finished by the kernels that follow
             store_A();
@@ -854,12 +847,21 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         store_A();                                        // (goes out while the count comes back)
     } else {
         // a queue overflowed (tie-heavy or constant data, or an all-pass key): A is stored now, and
-        // the chunk's candidates are appended from a second read of it, 2048 entries at a time with
-        // a block scan
+        // the chunk's candidates (the wavefronts have counted all of them) are appended as one run
+        // from a second read of it, 2048 entries at a time with a block scan
         store_A();
         wait_all_memory();
+        if (tid == 0) {
+            const unsigned long long old = atomicAdd(counter, (unsigned long long)qp | ((unsigned long long)qn << 32));
+            sh.base[0] = (uint32_t)old;
+            sh.base[1] = (uint32_t)(old >> 32);
+        }
         __syncthreads();
-        for (uint32_t base0 = 0; base0 < cnt; base0 += 8u * kStepThreads) {
+        uint32_t at_p = sh.base[0], at_n = sh.base[1];
+        if (tid == 0) runs[c] = chunk_run(d, at_p, at_n, qp, qn);
+        // (nothing is stored beyond a list's capacity: the counters then show that the lists are not usable)
+        const bool room = (uint64_t)at_p + qp <= d.cand_cap && (uint64_t)at_n + qn <= d.cand_cap;
+        for (uint32_t base0 = 0; room && base0 < cnt; base0 += 8u * kStepThreads) {      // uniform
             uint32_t mp = 0u, mn = 0u, kk8[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
@@ -871,16 +873,8 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
             const uint32_t packed = __popc(mp) | (__popc(mn) << 16);
             uint32_t total;
             const uint32_t ex = block_excl_sum<uint32_t, kStepThreads>(packed, &total, sh.scratch32);
-            if (total == 0u) continue;                    // uniform
-            if (tid == 0) {
-                const unsigned long long old = atomicAdd(counter, (unsigned long long)(total & 0xFFFFu) | ((unsigned long long)(total >> 16) << 32));
-                sh.base[0] = (uint32_t)old;
-                sh.base[1] = (uint32_t)(old >> 32);
-            }
-            __syncthreads();
-            uint32_t op = sh.base[0] + (ex & 0xFFFFu), on = sh.base[1] + (ex >> 16);
-            __syncthreads();                              // base is rewritten in the next round
-            if ((uint64_t)op + __popc(mp) > d.cand_cap || (uint64_t)on + __popc(mn) > d.cand_cap) continue;   // (nothing is stored beyond a list's capacity)
+            uint32_t op = at_p + (ex & 0xFFFFu), on = at_n + (ex >> 16);
+            at_p += total & 0xFFFFu; at_n += total >> 16;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const uint32_t pos = base0 + (uint32_t)j * kStepThreads + tid;
@@ -888,7 +882,6 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
                 if (mn & (1u << j)) store_cand(ln + on++, ~kk8[j], e0 + pos);
             }
         }
-        if (fatal) atomicOr(&result->err, kErrInternal);
         if (!inline_t) return;
         wait_all_memory();
         __syncthreads();
@@ -952,7 +945,7 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
     } else {
         defer = true;
     }
-    if (defer && tid == 0) {                              // left to k_select
+    if (defer && tid == 0) {                              // left to k_threshold
         st[t].flags = kStDeferred;
         atomicOr(&result->err, kErrDeferred);
     }
@@ -1046,6 +1039,7 @@ __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __rest
             *reinterpret_cast<uint64_t*>(e + 8) = bit_len;
             *reinterpret_cast<uint64_t*>(e + 16) = word_off;
             st[t].cand_cnt[0] = 0u; st[t].cand_cnt[1] = 0u; st[t].flags = 0u; st[t].done = 0u;
+            st[t].sorted_kept = (my_flags & kStInlineDone) ? 1u : 0u;
             if (t == 0) {
                 uint32_t* h = reinterpret_cast<uint32_t*>(msg);
                 h[0] = 0x31434253u; h[1] = 1u; h[2] = (uint32_t)T; h[3] = (uint32_t)b;
