@@ -11,7 +11,6 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <numeric>
 #include <vector>
@@ -34,10 +33,9 @@ const char* const kStageNames[kNumStages] = {
 }  // namespace
 
 constexpr int kDescSlots = 4;             // device copies of the tensor table, keyed by the pointer lists
-constexpr int kMaxWideDec = 16;
 constexpr uint32_t kMaxDecExtra = 512;    // additional decode workgroups that share a stream's scatter
-constexpr uint32_t kDecSharePer = 384;    // kept entries per sharing workgroup
-constexpr uint32_t kDecShareMax = 8;           // streams per call that the tile decoder can take
+constexpr uint32_t kDecSharePer = 256;    // kept entries per sharing workgroup
+constexpr uint32_t kDecShareMax = kDecWaves;    // (a wavefront's updates each)
 constexpr uint32_t kWideMinKept = 8192;   // kept entries per side from which a tensor takes those routes
 
 struct DescSlot {
@@ -84,14 +82,10 @@ struct sbc_ctx {
     long long* d_wide_acc = nullptr;
 
     // ---- device scratch of sbc_decompress_accumulate ----
-    DecDesc* d_dec = nullptr;
-    uint2* d_dec_blocks = nullptr;        // workgroup -> (tensor, share | shares << 16) of the decode kernel
-    DecWide* d_dec_wide = nullptr;        // long streams decoded tile by tile
-    unsigned long long* d_seg_fn = nullptr;
+    DecBlock* d_dec_blocks = nullptr;     // what each workgroup of the decode kernel works on
     unsigned long long* d_seg_pack = nullptr;
-    unsigned long long* d_tile_fn = nullptr;
+    uint4* d_tile_fn = nullptr;
     unsigned long long* d_tile_sum = nullptr;
-    uint32_t* d_tile_entry = nullptr;
     uint64_t dec_seg_cap = 0, dec_tile_cap = 0;
 
     // ---- pinned host staging ----
@@ -107,10 +101,9 @@ struct sbc_ctx {
     ResultBlock* h_result_dec = nullptr;  // decode (its own block: a decode call may come between begin and end)
     ResultBlock* h_result_dec_dev = nullptr;
     uint32_t dec_seq = 0;
-    DecDesc* h_dec = nullptr;
-    uint2* h_dec_blocks = nullptr;
+    DecBlock* h_dec_blocks = nullptr;
     uint32_t n_dec_blocks = 0;
-    DecWide* h_dec_wide = nullptr;
+    DecWides dec_wides = {};              // long streams decoded tile by tile
     TensorState* h_state = nullptr;
 
     // ---- plan of the last compress call: everything that depends on sizes and p only ----
@@ -133,8 +126,9 @@ struct sbc_ctx {
     int dev_dec_T = 0;
     bool dev_dec_valid = false;
     double dec_p = 0.0;
-    int n_dec_wide = 0;
     uint32_t dec_tiles = 0;
+    std::vector<float*> dec_out;
+    std::vector<int64_t> dec_numel;
 
     // ---- options ----
     int force_exact = 0;
@@ -243,11 +237,9 @@ void free_all(sbc_ctx* c) {
     (void)hipFree(c->d_desc); (void)hipFree(c->d_chunk_tensor); (void)hipFree(c->d_sched); (void)hipFree(c->d_group); (void)hipFree(c->d_order); (void)hipFree(c->d_hist);
     (void)hipFree(c->d_state); (void)hipFree(c->d_cand); (void)hipFree(c->d_bitmap); (void)hipFree(c->d_stage);
     (void)hipFree(c->d_kept); (void)hipFree(c->d_sum); (void)hipFree(c->d_prev_end); (void)hipFree(c->d_bitoff); (void)hipFree(c->d_tile);
-    (void)hipFree(c->d_result); (void)hipFree(c->d_dec); (void)hipFree(c->d_dec_blocks);
+    (void)hipFree(c->d_result); (void)hipFree(c->d_dec_blocks);
     if (c->h_dec_blocks) (void)hipHostFree(c->h_dec_blocks);
-    (void)hipFree(c->d_dec_wide); (void)hipFree(c->d_seg_fn); (void)hipFree(c->d_seg_pack); (void)hipFree(c->d_tile_fn);
-    (void)hipFree(c->d_tile_sum); (void)hipFree(c->d_tile_entry);
-    if (c->h_dec_wide) (void)hipHostFree(c->h_dec_wide);
+    (void)hipFree(c->d_seg_pack); (void)hipFree(c->d_tile_fn); (void)hipFree(c->d_tile_sum);
     (void)hipFree(c->d_wide_state); (void)hipFree(c->d_wide_hist); (void)hipFree(c->d_wide_acc); (void)hipFree(c->d_runs);
     if (c->h_desc) (void)hipHostFree(c->h_desc);
     if (c->h_chunk_tensor) (void)hipHostFree(c->h_chunk_tensor);
@@ -255,7 +247,6 @@ void free_all(sbc_ctx* c) {
     if (c->h_order) (void)hipHostFree(c->h_order);
     if (c->h_result) (void)hipHostFree(c->h_result);
     if (c->h_result_dec) (void)hipHostFree(c->h_result_dec);
-    if (c->h_dec) (void)hipHostFree(c->h_dec);
     if (c->h_state) (void)hipHostFree(c->h_state);
     if (c->ev_ok) for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     if (c->ev_result) (void)hipEventDestroy(c->ev_result);
@@ -382,75 +373,47 @@ int wait_result(sbc_ctx* c) {
 
 // ---------------------------------------------------------------------------------------------
 // Server step without any allocation, for callers that cannot call hipMalloc (code under HIP graph
-// capture, tight serving loops, harnesses that forbid allocation).  The tables the decode kernel
-// reads (tensor descriptors, workgroup -> stream table, result block) live in a file-scope device
-// array instead of a context; one small kernel fills them from the launch arguments, the decode
-// kernel of sbc_decompress_accumulate runs on them, and a last kernel stores the status where the
-// caller asked for it.  Nothing is copied to or from the host and nothing waits.
+// capture, tight serving loops, harnesses that forbid allocation).  What the decode kernel works on
+// travels in its arguments, and its errors go straight to the caller's status word, which a dispatch
+// of one thread sets to SBC_OK before it.  Nothing is copied to or from the host and nothing waits.
 // ---------------------------------------------------------------------------------------------
 namespace {
 
-struct NoAllocScratch {
-    ResultBlock result[2];
-    DecDesc dec[SBC_NOALLOC_MAX_TENSORS];
-    uint2 blocks[SBC_NOALLOC_MAX_TENSORS + kMaxDecExtra];
-};
-
-// launch arguments of the set-up kernel (kernel arguments may take 4 KiB)
-struct NoAllocArgs {
+// What the decode kernel of the context-free call works on, in its arguments (4 KiB at the most).
+struct ArgBlocks {
     float* out[SBC_NOALLOC_MAX_TENSORS];
     uint32_t n[SBC_NOALLOC_MAX_TENSORS];
-    uint16_t first_block[SBC_NOALLOC_MAX_TENSORS];
-    uint8_t shares[SBC_NOALLOC_MAX_TENSORS];
+    uint16_t block[SBC_NOALLOC_MAX_TENSORS + kMaxDecExtra];   // tensor, share and shares - 1 of a workgroup in 8 + 3 + 3 bits
+    int32_t* status;
+    __device__ __forceinline__ DecBlock at(uint32_t i) const {
+        const uint32_t v = block[i], t = v & 255u;
+        DecBlock b;
+        b.out = out[t]; b.n = n[t]; b.t = t; b.share = (v >> 8) & 7u; b.shares = ((v >> 11) & 7u) + 1u;
+        return b;
+    }
+    __device__ __forceinline__ ResultBlock* errors() const { return nullptr; }
+    __device__ __forceinline__ int32_t* status_word() const { return status; }
+    __device__ __forceinline__ void begin() const {}
 };
-static_assert(sizeof(NoAllocArgs) <= 3584, "must fit the kernel argument segment");
-
+static_assert(SBC_NOALLOC_MAX_TENSORS <= 256 && kDecShareMax <= 8, "a workgroup's word holds its numbers");
+static_assert(sizeof(ArgBlocks) <= 4096 - 256, "must fit the kernel argument segment");
 constexpr int kNoAllocMaxDevices = 64;
 
-}  // namespace
+__global__ void k_status_ok(int32_t* __restrict__ status) { if (threadIdx.x == 0) *status = SBC_OK; }
 
-// Every GPU the library runs on holds its own copy of this array until the process ends.  In
-// host code the name is only a handle for hipGetSymbolAddress: the address the kernels receive
-// is looked up once per device (noalloc_scratch_of) and kept.
-static __device__ __align__(256) unsigned char scratch[(sizeof(NoAllocScratch) + 255) / 256 * 256];
-
-__global__ __launch_bounds__(256) void k_noalloc_setup(NoAllocScratch* __restrict__ s, NoAllocArgs a, int T) {
-    const int tid = threadIdx.x;
-    // the array keeps the previous call's contents: everything the decode kernel reads is rewritten
-    if (tid < 2) { s->result[tid].err = 0u; s->result[tid].pad = 0u; s->result[tid].msg_bytes = 0ull; }
-    for (int t = tid; t < T; t += 256) {
-        DecDesc d;
-        d.out = a.out[t]; d.n = a.n[t]; d.wide = 0u;
-        s->dec[t] = d;
-        const uint32_t shares = a.shares[t];
-        for (uint32_t sh = 0; sh < shares; ++sh) s->blocks[a.first_block[t] + sh] = make_uint2((uint32_t)t, sh | (shares << 16));
-    }
+// The decode kernel for b.
+template <typename Blocks, typename Wides>
+void launch_decode(hipStream_t stream, uint32_t n_blocks, uint32_t n_tiles, const uint8_t* msg, unsigned long long msg_bytes,
+                   const Blocks& blocks, int T, int b, float scale, const Wides& dw, uint4* tile_fn) {
+    const dim3 grid(n_blocks + n_tiles), block(kDecThreads);
+    if (b <= 7) hipLaunchKernelGGL((k_decode<2, Blocks, Wides>), grid, block, 0, stream, msg, msg_bytes, blocks, n_blocks, T, b, scale, dw, tile_fn);
+    else if (b <= 11) hipLaunchKernelGGL((k_decode<3, Blocks, Wides>), grid, block, 0, stream, msg, msg_bytes, blocks, n_blocks, T, b, scale, dw, tile_fn);
+    else if (b <= kPackedMaxB) hipLaunchKernelGGL((k_decode<4, Blocks, Wides>), grid, block, 0, stream, msg, msg_bytes, blocks, n_blocks, T, b, scale, dw, tile_fn);
+    else hipLaunchKernelGGL((k_decode_generic<Blocks>), grid, block, 0, stream, msg, msg_bytes, blocks, T, b, scale);
 }
 
-__global__ void k_noalloc_finish(const NoAllocScratch* __restrict__ s, int32_t* __restrict__ status) {
-    if (threadIdx.x == 0) {
-        const uint32_t err = s->result[0].err;
-        *status = (err & kErrInternal) ? SBC_EINTERNAL : (err & kErrCorrupt) ? SBC_ECORRUPT : SBC_OK;
-    }
-}
-
-namespace {
-
-// Device address of `scratch` on `device` (which must be current), looked up on first use.
-NoAllocScratch* noalloc_scratch_of(int device) {
-    static NoAllocScratch* ptr[kNoAllocMaxDevices] = {};
-    static std::mutex lock;
-    if (device < 0 || device >= kNoAllocMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> g(lock);
-    if (!ptr[device]) {
-        void* p = nullptr;
-        if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        ptr[device] = static_cast<NoAllocScratch*>(p);
-    }
-    return ptr[device];
+uint32_t decode_shares(int64_t kept) {
+    return (uint32_t)std::min<int64_t>(kDecShareMax, std::max<int64_t>(1, kept / kDecSharePer));
 }
 
 }  // namespace
@@ -550,19 +513,14 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_bitoff, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile, (size_t)(c->max_chunks / kScanTile) + T + 1) == hipSuccess;
     ok = ok && dev_alloc(&c->d_result, 6) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_dec, T) == hipSuccess;
     ok = ok && dev_alloc(&c->d_dec_blocks, T + kMaxDecExtra) == hipSuccess;
     ok = ok && host_alloc(&c->h_dec_blocks, T + kMaxDecExtra) == hipSuccess;
     // tile decode: a stream of w words has w/2 segments; every stream is rounded up to whole tiles
     c->dec_seg_cap = c->stage_cap / 2 + (uint64_t)(kMaxWideDec + 1) * kDecThreads;
     c->dec_tile_cap = c->dec_seg_cap / kDecThreads + kMaxWideDec;
-    ok = ok && dev_alloc(&c->d_dec_wide, (size_t)kMaxWideDec) == hipSuccess;
-    ok = ok && host_alloc(&c->h_dec_wide, (size_t)kMaxWideDec) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_seg_fn, (size_t)c->dec_seg_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_seg_pack, (size_t)c->dec_seg_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile_fn, (size_t)c->dec_tile_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile_sum, (size_t)c->dec_tile_cap) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_tile_entry, (size_t)c->dec_tile_cap) == hipSuccess;
     c->max_wide = std::min(kMaxWide, max_tensors);
     ok = ok && dev_alloc(&c->d_wide_state, (size_t)c->max_wide * 2) == hipSuccess;
     ok = ok && dev_alloc(&c->d_wide_hist, (size_t)c->max_wide * 2 * kThBins) == hipSuccess;
@@ -579,7 +537,6 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && host_alloc(&c->h_result_dec, 1) == hipSuccess;
     ok = ok && hipHostGetDevicePointer(reinterpret_cast<void**>(&c->h_result_dec_dev), c->h_result_dec, 0) == hipSuccess;
     if (ok) std::memset(c->h_result_dec, 0, sizeof(ResultBlock));
-    ok = ok && host_alloc(&c->h_dec, T) == hipSuccess;
     ok = ok && host_alloc(&c->h_state, T) == hipSuccess;
     if (ok) {
         int made = 0;
@@ -1057,56 +1014,66 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
     SBC_HOST_TS(8);
     if (msg_bytes < 32 + 24ull * (unsigned)T) return SBC_ECORRUPT;
     bool same = c->dev_dec_valid && c->dev_dec_T == T && c->dec_p == p;
-    for (int t = 0; t < T; ++t) {
-        if (numel[t] < 1 || numel[t] >= (int64_t)1 << 32 || !out[t] || ((uintptr_t)out[t] & 3u)) return SBC_EINVAL;
-        if (same && (c->h_dec[t].out != out[t] || c->h_dec[t].n != (uint32_t)numel[t])) same = false;
-    }
+    if (same)
+        same = std::memcmp(c->dec_numel.data(), numel, sizeof(int64_t) * T) == 0 && std::memcmp(c->dec_out.data(), out, sizeof(float*) * T) == 0;
+    if (!same)
+        for (int t = 0; t < T; ++t)
+            if (numel[t] < 1 || numel[t] >= (int64_t)1 << 32 || !out[t] || ((uintptr_t)out[t] & 3u)) return SBC_EINVAL;
     DeviceGuard guard(c->device);
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     const bool deferred = c->defer_decode != 0;
     if (!same && c->deferred_pending) {
-        // the pinned tables below may still be read by an upload of an earlier deferred call
+        // the pinned table below may still be read by an upload of an earlier deferred call
         if (hipStreamSynchronize(stream) != hipSuccess) { (void)hipGetLastError(); return SBC_EHIP; }
     }
     if (!same) {
         // Streams of tensors that keep very many entries are decoded tile by tile by many
         // workgroups, as far as the scratch arrays reach; all others by one workgroup each.
-        int n_wide = 0;
+        // If there are any, so are the streams of more than one tile, which a single workgroup would take
+        // one after another: the launches are there anyway (ResNet-50 shape at p = 0.01: k_decode 14.8
+        // us with streams of up to three tiles).
+        DecWides& dw = c->dec_wides;
+        dw = DecWides{};
+        bool any_wide = false;
+        for (int t = 0; t < T; ++t)
+            any_wide = any_wide || (uint64_t)cap_of(numel[t], kept_of(numel[t], p), c->sampled != 0) >= (uint64_t)c->wide_min_kept;
         uint64_t segs = 0, tiles = 0;
         uint32_t n_blocks = 0, extra = 0;
         for (int t = 0; t < T; ++t) {
-            c->h_dec[t].out = out[t]; c->h_dec[t].n = (uint32_t)numel[t]; c->h_dec[t].wide = 0u;
             // (a context that expects messages of the subsampled variant reserves for its cap)
             const int64_t k = cap_of(numel[t], kept_of(numel[t], p), c->sampled != 0);
+            if (b <= kPackedMaxB && any_wide && dw.count < kMaxWideDec) {
+                const uint64_t max_seg = (bound_words_of(numel[t], (uint32_t)k, b) + 1) / 2;
+                const uint64_t max_tiles = (max_seg + kDecThreads - 1) / kDecThreads;
+                if (((uint64_t)k >= (uint64_t)c->wide_min_kept || max_tiles > 1) && max_tiles != 0 && max_tiles < (1ull << 29) && segs + max_tiles * kDecThreads <= c->dec_seg_cap &&
+                    tiles + max_tiles <= c->dec_tile_cap) {
+                    DecWide& w = dw.w[dw.count++];
+                    w.out = out[t]; w.n = (uint32_t)numel[t]; w.t = (uint32_t)t;
+                    w.tile0 = (uint32_t)tiles; w.max_tiles = (uint32_t)max_tiles; w.seg0 = segs;
+                    segs += max_tiles * kDecThreads; tiles += max_tiles;
+                    continue;
+                }
+            }
             // One workgroup decodes a stream; the scattered updates of a stream with many codes are
             // shared among several workgroups that each decode it (a compute unit sustains only so
             // many scattered accesses at a time, and decoding again costs no more time than once).
-            uint32_t shares = (uint32_t)std::min<int64_t>(kDecShareMax, std::max<int64_t>(1, k / kDecSharePer));
+            uint32_t shares = decode_shares(k);
             if (extra + shares - 1u > kMaxDecExtra) shares = 1u;
             extra += shares - 1u;
-            for (uint32_t sh = 0; sh < shares; ++sh) c->h_dec_blocks[n_blocks++] = make_uint2((uint32_t)t, sh | (shares << 16));
-            if (b > kPackedMaxB || (uint64_t)k < (uint64_t)c->wide_min_kept || n_wide >= kMaxWideDec) continue;
-            const uint64_t max_seg = (bound_words_of(numel[t], (uint32_t)k, b) + 1) / 2;
-            const uint64_t max_tiles = (max_seg + kDecThreads - 1) / kDecThreads;
-            if (max_tiles == 0 || max_tiles >= (1ull << 31) || segs + max_tiles * kDecThreads > c->dec_seg_cap ||
-                tiles + max_tiles > c->dec_tile_cap)
-                continue;
-            DecWide& w = c->h_dec_wide[n_wide++];
-            w.t = (uint32_t)t; w.tile0 = (uint32_t)tiles; w.max_tiles = (uint32_t)max_tiles; w.pad = 0u; w.seg0 = segs;
-            c->h_dec[t].wide = 1u;
-            n_blocks -= shares - 1u; extra -= shares - 1u;     // its workgroup of this kernel only returns
-            c->h_dec_blocks[n_blocks - 1u] = make_uint2((uint32_t)t, 1u << 16);
-            segs += max_tiles * kDecThreads; tiles += max_tiles;
+            for (uint32_t sh = 0; sh < shares; ++sh) {
+                DecBlock& blk = c->h_dec_blocks[n_blocks++];
+                blk.out = out[t]; blk.n = (uint32_t)numel[t]; blk.t = (uint32_t)t; blk.share = sh; blk.shares = shares;
+            }
         }
-        c->n_dec_wide = n_wide; c->dec_tiles = (uint32_t)tiles; c->dec_p = p;
+        c->dec_tiles = (uint32_t)tiles; c->dec_p = p;
         c->n_dec_blocks = n_blocks;
         c->dev_dec_valid = false;
-        if (hipMemcpyAsync(c->d_dec, c->h_dec, sizeof(DecDesc) * T, hipMemcpyHostToDevice, stream) != hipSuccess ||
-            hipMemcpyAsync(c->d_dec_blocks, c->h_dec_blocks, sizeof(uint2) * n_blocks, hipMemcpyHostToDevice, stream) != hipSuccess ||
-            (n_wide > 0 && hipMemcpyAsync(c->d_dec_wide, c->h_dec_wide, sizeof(DecWide) * n_wide, hipMemcpyHostToDevice, stream) != hipSuccess)) {
+        if (n_blocks > 0 && hipMemcpyAsync(c->d_dec_blocks, c->h_dec_blocks, sizeof(DecBlock) * n_blocks, hipMemcpyHostToDevice, stream) != hipSuccess) {
             (void)hipGetLastError();
             return SBC_EHIP;
         }
+        c->dec_out.assign(out, out + T);
+        c->dec_numel.assign(numel, numel + T);
         c->dev_dec_T = T;
     }
     // the decode kernel leaves the other of its two result blocks clean for the next call; calls
@@ -1132,21 +1099,18 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
         c->dec_result_idx ^= 1;
     }
     SBC_HOST_TS(9);
-    hipLaunchKernelGGL(k_decode_accumulate, dim3(c->n_dec_blocks), dim3(kDecThreads), 0, stream,
-                       static_cast<const uint8_t*>(msg), (unsigned long long)msg_bytes, c->d_dec, c->d_dec_blocks, T, b, scale,
-                       res_dec, res_dec_next);
-    if (c->n_dec_wide > 0) {
-        const uint8_t* m8 = static_cast<const uint8_t*>(msg);
-        const unsigned long long mb = (unsigned long long)msg_bytes;
-        const dim3 tiles(c->dec_tiles);
-        hipLaunchKernelGGL(k_dec_tile_fn, tiles, dim3(kDecThreads), 0, stream, m8, mb, c->d_dec, c->d_dec_wide,
-                           c->n_dec_wide, T, b, c->d_seg_fn, c->d_tile_fn, res_dec);
-        hipLaunchKernelGGL(k_dec_tile_sums, tiles, dim3(kDecThreads), 0, stream, m8, mb, c->d_dec, c->d_dec_wide,
-                           c->n_dec_wide, T, b, c->d_seg_fn, c->d_tile_fn, c->d_tile_entry, c->d_seg_pack,
-                           c->d_tile_sum, res_dec);
-        hipLaunchKernelGGL(k_dec_tile_place, tiles, dim3(kDecThreads), 0, stream, m8, mb, c->d_dec, c->d_dec_wide,
-                           c->n_dec_wide, T, b, scale, c->d_seg_fn, c->d_tile_entry, c->d_seg_pack, c->d_tile_sum,
-                           res_dec);
+    const uint8_t* m8 = static_cast<const uint8_t*>(msg);
+    const unsigned long long mb = (unsigned long long)msg_bytes;
+    MemBlocks blocks;
+    blocks.table = c->d_dec_blocks; blocks.result = res_dec; blocks.next_result = res_dec_next;
+    launch_decode(stream, c->n_dec_blocks, c->dec_tiles, m8, mb, blocks, T, b, scale, c->dec_wides, c->d_tile_fn);
+    if (c->dec_tiles > 0) {
+        const dim3 tiles(c->dec_tiles), block(kDecThreads);
+        if (b <= 7) hipLaunchKernelGGL(k_dec_tile_sums<2>, tiles, block, 0, stream, m8, mb, c->dec_wides, T, b, c->d_tile_fn, c->d_seg_pack, c->d_tile_sum, res_dec);
+        else if (b <= 11) hipLaunchKernelGGL(k_dec_tile_sums<3>, tiles, block, 0, stream, m8, mb, c->dec_wides, T, b, c->d_tile_fn, c->d_seg_pack, c->d_tile_sum, res_dec);
+        else hipLaunchKernelGGL(k_dec_tile_sums<4>, tiles, block, 0, stream, m8, mb, c->dec_wides, T, b, c->d_tile_fn, c->d_seg_pack, c->d_tile_sum, res_dec);
+        hipLaunchKernelGGL(k_dec_tile_place, dim3(c->dec_tiles * kPlacePer), dim3(kPlaceThreads), 0, stream, m8, mb, c->dec_wides, T, b, scale,
+                           c->d_seg_pack, c->d_tile_sum, res_dec);
     }
     SBC_HOST_TS(10);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
@@ -1297,28 +1261,22 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream, const void* 
     const int b = bstar_of(p);
     if (b > kMaxB) return SBC_EINVAL;
     if (msg_bytes < 32 + 24ull * (unsigned)T) return SBC_ECORRUPT;
-    NoAllocArgs a;
-    std::memset(&a, 0, sizeof(a));
+    ArgBlocks a;
+    std::memset(static_cast<void*>(&a), 0, sizeof(a));
     uint32_t n_blocks = 0, extra = 0;
     for (int t = 0; t < T; ++t) {
         if (numel[t] < 1 || numel[t] >= (int64_t)1 << 32 || !out[t] || ((uintptr_t)out[t] & 3u)) return SBC_EINVAL;
-        const int64_t k = kept_of(numel[t], p);
-        uint32_t shares = (uint32_t)std::min<int64_t>(kDecShareMax, std::max<int64_t>(1, k / kDecSharePer));
+        uint32_t shares = decode_shares(kept_of(numel[t], p));
         if (extra + shares - 1u > kMaxDecExtra) shares = 1u;
         extra += shares - 1u;
         a.out[t] = out[t]; a.n[t] = (uint32_t)numel[t];
-        a.first_block[t] = (uint16_t)n_blocks; a.shares[t] = (uint8_t)shares;
-        n_blocks += shares;
+        for (uint32_t sh = 0; sh < shares; ++sh) a.block[n_blocks++] = (uint16_t)((uint32_t)t | (sh << 8) | ((shares - 1u) << 11));
     }
+    a.status = status;
     DeviceGuard guard(device);
-    NoAllocScratch* const s = noalloc_scratch_of(device);
-    if (!s) return SBC_EHIP;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    hipLaunchKernelGGL(k_noalloc_setup, dim3(1), dim3(256), 0, stream, s, a, T);
-    hipLaunchKernelGGL(k_decode_accumulate, dim3(n_blocks), dim3(kDecThreads), 0, stream,
-                       static_cast<const uint8_t*>(msg), (unsigned long long)msg_bytes, s->dec, s->blocks, T, b, scale,
-                       &s->result[0], &s->result[1]);
-    hipLaunchKernelGGL(k_noalloc_finish, dim3(1), dim3(64), 0, stream, s, status);
+    hipLaunchKernelGGL(k_status_ok, dim3(1), dim3(64), 0, stream, status);
+    launch_decode(stream, n_blocks, 0u, static_cast<const uint8_t*>(msg), (unsigned long long)msg_bytes, a, T, b, scale, NoWides{}, nullptr);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
     return SBC_OK;
 }

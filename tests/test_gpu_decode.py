@@ -1,0 +1,52 @@
+"""The server step against the oracle's bit-serial decoder at every width of the state functions
+(b from 0 to 19), with streams just below, at and above whole tiles of 512 segments, one workgroup
+and the tile kernels, and with sub-normal accumulators and addends (the update is an fp32 addition
+that rounds once and flushes nothing)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sbc_oracle as o
+from paper_1805_08768_amd import binding as sbc, synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+TILE_BITS = 64 * 512
+
+
+def _sizes(p):
+    """Tensor sizes whose streams are about 1 and 2 tiles long, on both sides of the boundary, as far
+    as that stays below four million entries; and small ones."""
+    b = sbc.sbc_golomb_bstar(p)
+    out = [1, 70, 8192]
+    for bits in (TILE_BITS - 40, TILE_BITS + 40, 2 * TILE_BITS + 700):
+        n = int(bits / (p * (b + 1.6)))
+        if n <= 4_000_000:
+            out.append(n)
+    return out if len(out) > 3 else out + [3_000_001]
+
+
+@pytest.mark.parametrize("p", [0.45, 0.2, 0.05, 0.02, 0.01, 0.004, 0.001, 2e-4, 6e-5, 1.2e-5, 1e-6])
+def test_every_state_function_width_at_tile_edges(p):
+    sizes = _sizes(p)
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        dW = [torch.from_numpy(x).to(DEV) for x in synth.small_model_update(sizes)]
+        R = [torch.zeros(n, dtype=torch.float32, device=DEV) for n in sizes]
+        msg = torch.zeros(sbc.sbc_msg_bound(sizes, p), dtype=torch.uint8, device=DEV)
+        nbytes = sbc.sbc_compress(ctx, dW, R, p, msg)
+        data = bytes(msg[:nbytes].cpu().numpy().tobytes())
+        g = np.random.default_rng(int(1e7 * p))
+        for scale, unit in ((1.0, 1.0), (1e-37, 1e-39)):
+            base = [(g.standard_normal(n) * unit).astype(np.float32) for n in sizes]
+            want = [x.copy() for x in base]
+            o.decode_accumulate(data, sizes, scale, want)
+            for wide_min in (0, 20):                     # one workgroup a stream / long ones tile by tile
+                sbc.sbc_set_option(ctx, sbc.SBC_OPT_WIDE_MIN_KEPT, wide_min)
+                out = [torch.from_numpy(x).to(DEV) for x in base]
+                sbc.sbc_decompress_accumulate(ctx, msg, nbytes, p, scale, out)
+                for t, (x, w) in enumerate(zip(out, want)):
+                    assert np.array_equal(x.cpu().numpy().view(np.uint32), w.view(np.uint32)), (p, t, scale, wide_min)
+    finally:
+        sbc.sbc_destroy(ctx)
