@@ -365,191 +365,161 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
 }
 
 // --------------------------------------------------------------------------
-// Residual accumulation fused with the prefilter.  One workgroup per chunk of 8192 entries:
-// 8 x 16-byte loads of each operand in flight per thread, A stored over R, and the few
-// entries at or beyond a side's filter key queued in LDS, then appended to the tensor's
-// candidate list with one atomic per side.  A chunk with more candidates than the queue
-// holds (tie-heavy or constant data) appends them again from a second read of its entries.  Where
-// the chunk's candidates went is recorded (ChunkRun) for k_apply.
+// Residual accumulation fused with the prefilter.  One workgroup per chunk of 8192 entries: 8 x 16-byte loads of each operand in flight
+// per thread, A stored over R and kept in LDS.  Every thread gathers two bit masks of its 32 entries, those at
+// or beyond each side's filter key (the keys' order is that of the values, so this is one comparison
+// of floats per side); one scan of the counts and one 64-bit atomic for both sides then give every
+// candidate its place, and each thread copies its few from LDS.  However many there are, the path is
+// the same.  Where a chunk's candidates went is recorded (ChunkRun).  Bound by HBM on large calls (54 us
+// on 25.6e6 entries, a plain R += dW takes 54.5 us there).  Small ones are bound by latency: with a test, an LDS
+// counter and a queue per entry, 18 KB of code, 128 chunks took 11.8 us and 41 took 10.3; now 7.4 and
+// 5.6.  Operands that are only 4-byte aligned take the same loads (24 ragged tensors of 12e6 entries in
+// one buffer: 27.4 us, 35 with scalar ones).
 // --------------------------------------------------------------------------
 struct FilterShared {
-    uint2 queue[2][kFilterQueue];
-    uint32_t qcnt[2];
+    f32x4 a[kChunk / 4];
     uint32_t base[2];
     uint32_t scratch[kStreamThreads / 64];
 };
 
-__device__ __forceinline__ void filter_entry(float a, uint32_t idx, uint32_t lo_p, uint32_t lo_n,
-                                             FilterShared& sh, uint32_t& bad) {
-    const uint32_t u = __float_as_uint(a);
-    if ((u & 0x7F800000u) == 0x7F800000u) bad = 1u;
-    const uint32_t kk = key_of_bits(u);
-    if (kk >= lo_p) {
-        const uint32_t s = atomicAdd(&sh.qcnt[0], 1u);
-        if (s < (uint32_t)kFilterQueue) sh.queue[0][s] = make_uint2(kk, idx);
-    }
-    if (~kk >= lo_n) {
-        const uint32_t s = atomicAdd(&sh.qcnt[1], 1u);
-        if (s < (uint32_t)kFilterQueue) sh.queue[1][s] = make_uint2(~kk, idx);
-    }
+// The value whose comparison stands for that of the side key: an entry a has a side key at or above
+// `key` if and only if a >= value_of_key<0>(key) on the positive side, -a >= value_of_key<1>(key) on the
+// negative side, for every finite a.  (A zero's key is above the middle on the positive side and,
+// complemented, below it on the negative one.)
+template <int S>
+__device__ __forceinline__ float value_of_key(uint32_t key) {
+    if (S && key == 0x80000000u) return __uint_as_float(1u);
+    return key < 0x00800000u ? -__builtin_inff() : __uint_as_float(bits_of_key(key));     // (below -inf's: all; above +inf's: NaN, none)
 }
 
-// STREAM: the update is loaded with the nontemporal hint.  It is read exactly once, and when a
-// call's footprint is well beyond the last-level cache, keeping it out of that cache leaves more
-// of it to the residual, which is read and written.
+// 16 bytes at any 4-byte aligned address (multi-dword accesses to global memory need no more)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
+typedef const SBC_GLOBAL_AS f32x4_any* gcf32x4_any_ptr;
+
+// STREAM: update and residual are loaded, and the residual stored, with the nontemporal hint, for calls
+// that move more than the last-level cache holds: little of the residual could stay there until the
+// next round anyway, and what does has to be written back in the middle of somebody else's traffic.
+// With several clients' states in turn: 25.6e6 entries 54 us instead of 67 at p = 0.001 and 56 instead
+// of 74 at p = 0.01, 66e6 entries 132 us instead of 149, 1.5e9 entries 3.29 ms instead of 3.79 (only the
+// update with the hint: 60, 69, 149, 3.79; update and the residual's loads: 55, 69, 148, 3.51); one
+// client alone, its residual still in the cache from the round before: 52 us instead of 48.5 on 25.6e6.
+// Below the cache's size it loses: 12e6 entries 30 us instead of 27.4.
 template <bool STREAM>
-__global__ __launch_bounds__(kStreamThreads) void k_accumulate_filter(
-        const TensorDesc* __restrict__ desc, const uint2* __restrict__ sched,
+__global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
+        const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor,
         TensorState* __restrict__ st, uint2* __restrict__ cand, ChunkRun* __restrict__ runs,
         ResultBlock* __restrict__ result) {
     __shared__ FilterShared sh;
     const int tid = threadIdx.x;
-    // sched[workgroup] = (first chunk in the call-wide numbering, tensor | consecutive chunks of it << 24)
-    const uint2 sc = sched[blockIdx.x];
-    const int t = (int)(sc.y & 0xFFFFFFu);
-    const uint32_t n_sub = sc.y >> 24;
+    const uint32_t c = blockIdx.x;
+    const uint2 ct = chunk_tensor[c];                     // (tensor, its first chunk)
+    const int t = (int)ct.x;
     const TensorDesc d = desc[t];
-    const uint32_t lo_p = st[t].lo_key[0], lo_n = st[t].lo_key[1];
-    if (tid < 2) sh.qcnt[tid] = 0u;
-    __syncthreads();
-    uint32_t bad = 0u;
-
-#pragma unroll 1
-    for (uint32_t sub = 0; sub < n_sub; ++sub) {
-        const uint32_t c = sc.x + sub;
-        const uint32_t cc = c - d.chunk0;
-        const uint32_t e0 = cc * (uint32_t)kChunk;
-        const uint32_t cnt = min((uint32_t)kChunk, d.n - e0);
-        const gcfloat_ptr dw = as_global(d.dW + e0);
-        const gfloat_ptr r = as_global(d.R + e0);
-        const bool vec = (cnt == (uint32_t)kChunk) && ((((uintptr_t)(d.dW + e0) | (uintptr_t)(d.R + e0)) & 15u) == 0u);
-        if (vec) {
-            const gcf32x4_ptr dw4 = (gcf32x4_ptr)dw;
-            const gf32x4_ptr r4 = (gf32x4_ptr)r;
-            constexpr int IT = kChunk / 4 / kStreamThreads;   // 8
-            f32x4 dv[IT], rv[IT];
+    const float lo_p = value_of_key<0>(st[t].lo_key[0]), lo_n = -value_of_key<1>(st[t].lo_key[1]);
+    constexpr int IT = kChunk / 4 / kStreamThreads;       // 8 vectors of four entries per thread
+    static_assert(IT * 4 == 32, "a bit per entry");
+    const uint32_t e0 = (c - ct.y) * (uint32_t)kChunk;
+    const uint32_t cnt = min((uint32_t)kChunk, d.n - e0);
+    const gcfloat_ptr dw = as_global(d.dW + e0);
+    const gfloat_ptr r = as_global(d.R + e0);
+    const gcf32x4_any_ptr dw4 = (gcf32x4_any_ptr)dw;
+    const gf32x4_any_ptr r4 = (gf32x4_any_ptr)r;
+    const bool whole = cnt == (uint32_t)kChunk;           // uniform
+    f32x4 dv[IT], rv[IT];
+    uint32_t valid = 0xFFFFFFFFu;                         // entry 4 i + j of the thread is bit 31 - (4 i + j)
+    if (whole) {
 #pragma unroll
-            for (int i = 0; i < IT; ++i) {
-                dv[i] = STREAM ? __builtin_nontemporal_load(&dw4[i * kStreamThreads + tid]) : dw4[i * kStreamThreads + tid];
-                rv[i] = r4[i * kStreamThreads + tid];
-            }
+        for (int i = 0; i < IT; ++i) {
+            dv[i] = STREAM ? __builtin_nontemporal_load(&dw4[i * kStreamThreads + tid]) : dw4[i * kStreamThreads + tid];
+            rv[i] = STREAM ? __builtin_nontemporal_load(&r4[i * kStreamThreads + tid]) : r4[i * kStreamThreads + tid];
+        }
+    } else {
+        valid = 0u;
 #pragma unroll
-            for (int i = 0; i < IT; ++i) {
-                f32x4 a;
-                a.x = rv[i].x + dv[i].x;
-                a.y = rv[i].y + dv[i].y;
-                a.z = rv[i].z + dv[i].z;
-                a.w = rv[i].w + dv[i].w;
-                r4[i * kStreamThreads + tid] = a;
-                const uint32_t idx = e0 + (i * kStreamThreads + tid) * 4;
-                filter_entry(a.x, idx + 0, lo_p, lo_n, sh, bad);
-                filter_entry(a.y, idx + 1, lo_p, lo_n, sh, bad);
-                filter_entry(a.z, idx + 2, lo_p, lo_n, sh, bad);
-                filter_entry(a.w, idx + 3, lo_p, lo_n, sh, bad);
-            }
-        } else {
-            // a tensor's last, partial chunk, or operands that are only 4-byte aligned: eight entries per
-            // thread in flight at a time (later loads may not pass earlier stores to the same array,
-            // so a plain loop would pay the memory latency once per entry)
-            constexpr int IT = 8;
-            for (uint32_t base = 0; base < cnt; base += IT * kStreamThreads) {
-                float dv[IT], rv[IT];
-#pragma unroll
-                for (int j = 0; j < IT; ++j) {
-                    const uint32_t i = base + j * kStreamThreads + tid;
-                    const uint32_t ii = i < cnt ? i : 0u;
-                    dv[j] = dw[ii];
-                    rv[j] = r[ii];
-                }
-#pragma unroll
-                for (int j = 0; j < IT; ++j) {
-                    const uint32_t i = base + j * kStreamThreads + tid;
-                    if (i < cnt) {
-                        const float a = rv[j] + dv[j];
-                        r[i] = a;
-                        filter_entry(a, e0 + i, lo_p, lo_n, sh, bad);
-                    }
-                }
+        for (int i = 0; i < IT; ++i) {
+            const uint32_t at = (uint32_t)(i * kStreamThreads + tid) * 4u;
+            dv[i] = 0.f; rv[i] = 0.f;
+            valid <<= 4;
+            if (at + 4u <= cnt) {
+                dv[i] = dw4[i * kStreamThreads + tid]; rv[i] = r4[i * kStreamThreads + tid];
+                valid |= 15u;
+            } else if (at < cnt) {                    // the one vector that the tensor ends in
+                dv[i].x = dw[at]; rv[i].x = r[at];
+                if (at + 1u < cnt) { dv[i].y = dw[at + 1u]; rv[i].y = r[at + 1u]; }
+                if (at + 2u < cnt) { dv[i].z = dw[at + 2u]; rv[i].z = r[at + 2u]; }
+                valid |= at + 2u < cnt ? 14u : at + 1u < cnt ? 12u : 8u;
             }
         }
     }
-    if (bad) atomicOr(&result->err, kErrNonFinite);
-    __syncthreads();
-    const uint32_t qp = sh.qcnt[0], qn = sh.qcnt[1];
-    if (qp <= (uint32_t)kFilterQueue && qn <= (uint32_t)kFilterQueue) {
-        if (qp + qn == 0u) {
-            if ((uint32_t)tid < n_sub) runs[sc.x + tid] = chunk_run(d, 0u, 0u, 0u, 0u);
-            return;
+    uint32_t mp = 0u, mn = 0u;
+    float nonfinite = 0.f;                                // a NaN as soon as some entry is a NaN or an infinity
+    auto test = [&](float x) {
+        // mask = 2 mask + (comparison): two instructions a side (the compiler makes four and holds every
+        // bit in a register of its own)
+        asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mp) : "v"(x), "v"(lo_p) : "vcc");
+        asm("v_cmp_le_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(mn) : "v"(x), "v"(lo_n) : "vcc");
+        nonfinite = __builtin_fmaf(x, 0.f, nonfinite);
+    };
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+        f32x4 a;
+        a.x = rv[i].x + dv[i].x;
+        a.y = rv[i].y + dv[i].y;
+        a.z = rv[i].z + dv[i].z;
+        a.w = rv[i].w + dv[i].w;
+        sh.a[i * kStreamThreads + tid] = a;
+        if (whole) {                                  // uniform
+            if (STREAM) __builtin_nontemporal_store((f32x4_any)a, &r4[i * kStreamThreads + tid]);
+            else r4[i * kStreamThreads + tid] = a;
         }
-        if (tid == 0) {
-            // both sides' counters advance in one 64-bit atomic: workgroups of one tensor queue up
-            // on this address, and the wait grows with the number of atomics
-            const unsigned long long old = atomicAdd(reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]),
-                                                     (unsigned long long)qp | ((unsigned long long)qn << 32));
-            sh.base[0] = (uint32_t)old;
-            sh.base[1] = (uint32_t)(old >> 32);
-        }
-        __syncthreads();
-        if ((uint32_t)tid < n_sub) runs[sc.x + tid] = chunk_run(d, sh.base[0], sh.base[1], qp, qn);
-        // (beyond a list's capacity nothing is stored: see append_candidates)
-        if ((uint64_t)sh.base[0] + qp > d.cand_cap || (uint64_t)sh.base[1] + qn > d.cand_cap) return;
-        uint2* __restrict__ cp = cand + d.cand_off + sh.base[0];
-        uint2* __restrict__ cn = cand + d.cand_off + d.cand_cap + sh.base[1];
-        for (uint32_t i = tid; i < qp; i += kStreamThreads) cp[i] = sh.queue[0][i];
-        for (uint32_t i = tid; i < qn; i += kStreamThreads) cn[i] = sh.queue[1][i];
-        return;
+        test(a.x); test(a.y); test(a.z); test(a.w);
     }
-    // queue overflow: the candidates of this workgroup's chunks (all of them have been counted) are
-    // appended from a second read of A, 4096 entries at a time, in chunk order, so that each chunk's are
-    // one run (the barrier above ordered the workgroup's stores of A before these loads).  Filter keys
-    // that let a flood pass send most workgroups of a call this way.
-    constexpr int kRedo = 16;
-    static_assert(kRedo * kStreamThreads <= 65535, "the per-side counts of one step fit their 16-bit fields");
+    if (!whole) {                                     // uniform: the stores of a tensor's last chunk
+#pragma unroll
+        for (int i = 0; i < IT; ++i) {
+            const uint32_t at = (uint32_t)(i * kStreamThreads + tid) * 4u;
+            if (at + 4u <= cnt) r4[i * kStreamThreads + tid] = sh.a[i * kStreamThreads + tid];
+            else if (at < cnt) {
+                const f32x4 a = sh.a[i * kStreamThreads + tid];
+                r[at] = a.x;
+                if (at + 1u < cnt) r[at + 1u] = a.y;
+                if (at + 2u < cnt) r[at + 2u] = a.z;
+            }
+        }
+        mp &= valid; mn &= valid;
+    }
+    if (nonfinite != 0.f) atomicOr(&result->err, kErrNonFinite);    // (true for a NaN)
+    uint32_t total;
+    const uint32_t ex = block_excl_sum<uint32_t, kStreamThreads>(__popc(mp) | (__popc(mn) << 16), &total, sh.scratch);
+    const uint32_t qp = total & 0xFFFFu, qn = total >> 16;
     if (tid == 0) {
-        const unsigned long long old = atomicAdd(reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]),
-                                                 (unsigned long long)qp | ((unsigned long long)qn << 32));
+        // both sides' counters advance in one 64-bit atomic: workgroups of one tensor queue up on this
+        // address, and the wait grows with the number of atomics
+        unsigned long long old = 0ull;
+        if (total)
+            old = atomicAdd(reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]), (unsigned long long)qp | ((unsigned long long)qn << 32));
         sh.base[0] = (uint32_t)old;
         sh.base[1] = (uint32_t)(old >> 32);
+        runs[c] = chunk_run(d, (uint32_t)old, (uint32_t)(old >> 32), qp, qn);
     }
+    if (total == 0u) return;                              // uniform
     __syncthreads();
-    uint32_t at_p = sh.base[0], at_n = sh.base[1];
-    if ((uint64_t)at_p + qp > d.cand_cap || (uint64_t)at_n + qn > d.cand_cap) return;
-    uint2* __restrict__ cp = cand + d.cand_off;
-    uint2* __restrict__ cn = cand + d.cand_off + d.cand_cap;
-    for (uint32_t sub = 0; sub < n_sub; ++sub) {
-        const uint32_t e0 = (sc.x + sub - d.chunk0) * (uint32_t)kChunk;
-        const uint32_t cnt = min((uint32_t)kChunk, d.n - e0);
-        const gcfloat_ptr r = as_global(d.R + e0);
-        const uint32_t from_p = at_p, from_n = at_n;
-        for (uint32_t off = 0; off < cnt; off += kRedo * kStreamThreads) {
-            uint32_t key[kRedo];
-            uint32_t mp = 0u, mn = 0u;
-#pragma unroll
-            for (int s = 0; s < kRedo; ++s) {
-                const uint32_t i = off + s * kStreamThreads + tid;
-                key[s] = __float_as_uint(r[i < cnt ? i : 0u]);
-            }
-#pragma unroll
-            for (int s = 0; s < kRedo; ++s) {
-                const uint32_t i = off + s * kStreamThreads + tid;
-                const bool in = i < cnt;
-                key[s] = key_of_bits(key[s]);
-                if (in && key[s] >= lo_p) mp |= 1u << s;
-                if (in && ~key[s] >= lo_n) mn |= 1u << s;
-            }
-            uint32_t total;
-            const uint32_t ex = block_excl_sum<uint32_t, kStreamThreads>(__popc(mp) | (__popc(mn) << 16), &total, sh.scratch);
-            uint32_t op = at_p + (ex & 0xFFFFu), on = at_n + (ex >> 16);
-#pragma unroll
-            for (int s = 0; s < kRedo; ++s) {
-                const uint32_t idx = e0 + off + s * kStreamThreads + tid;
-                if (mp & (1u << s)) cp[op++] = make_uint2(key[s], idx);
-                if (mn & (1u << s)) cn[on++] = make_uint2(~key[s], idx);
-            }
-            at_p += total & 0xFFFFu; at_n += total >> 16;
+    const uint32_t base_p = sh.base[0], base_n = sh.base[1];
+    // (beyond a list's capacity nothing is stored: the counters then show that the tensor's lists are not
+    // usable, see lists_unusable; a list of a full context holds every entry)
+    if ((uint64_t)base_p + qp > d.cand_cap || (uint64_t)base_n + qn > d.cand_cap) return;   // uniform
+    const float* const flat = reinterpret_cast<const float*>(sh.a);
+    auto copy_out = [&](uint32_t m, uint2* __restrict__ to, uint32_t flip) {
+        while (m) {
+            const uint32_t s = (uint32_t)__clz((int)m);
+            m &= ~(0x80000000u >> s);
+            const uint32_t at = ((s >> 2) * (uint32_t)kStreamThreads + (uint32_t)tid) * 4u + (s & 3u);
+            *to++ = make_uint2(key_of_bits(__float_as_uint(flat[at])) ^ flip, e0 + at);
         }
-        if (tid == 0) runs[sc.x + sub] = chunk_run(d, from_p, from_n, at_p - from_p, at_n - from_n);
-    }
+    };
+    copy_out(mp, cand + d.cand_off + base_p + (ex & 0xFFFFu), 0u);
+    copy_out(mn, cand + d.cand_off + d.cand_cap + base_n + (ex >> 16), 0xFFFFFFFFu);
 }
 
 // --------------------------------------------------------------------------

@@ -54,8 +54,6 @@ constexpr int kL1Bits = 12;
 constexpr int kL1Bins = 1 << kL1Bits;
 constexpr int kL1Shift = 32 - kL1Bits;
 
-constexpr int kFilterQueue = 1024;       // candidates per side a workgroup of the streaming kernel can queue in LDS
-constexpr uint32_t kMaxChunksPerWorkgroup = 8;   // consecutive chunks of one very long tensor per such workgroup
 
 // error bits raised by kernels (word 0 of the result block)
 constexpr uint32_t kErrNonFinite = 1u;
@@ -69,9 +67,7 @@ constexpr uint32_t kErrStaleKeys = 256u; // not an error: the filter keys the pr
 constexpr uint32_t kErrDeferred = 64u;   // not an error: a tensor the streaming kernel could not finish itself is left to the kernels after it
 
 // Candidates per side beyond which a list counts as a flood (the next call then estimates its keys
-// afresh): 16 k + 8192, but at most one entry in 16 of the tensor if that is above 8 k + 4096 (a
-// workgroup of the streaming kernel queues up to 1024 candidates per side of its 8192 entries in
-// LDS; beyond that it reads its chunk a second time).  Lists of a few times k are the normal
+// afresh): 16 k + 8192, but at most one entry in 16 of the tensor if that is above 8 k + 4096.  Lists of a few times k are the normal
 // state while a residual still builds up and cost a selection a few microseconds; a key that has
 // fallen behind the data lets 30 to 60 times k pass.
 __host__ __device__ inline unsigned long long loose_limit(uint32_t k, uint32_t n) {
@@ -142,8 +138,7 @@ struct alignas(16) GroupState {
     uint32_t pad[3];
 };
 
-// Where the candidates of a chunk lie in its tensor's lists: one run per side.  (The chunks of a
-// streaming workgroup that takes several consecutive ones share one run.)
+// Where the candidates of a chunk lie in its tensor's lists: one run per side.
 struct alignas(8) ChunkRun {
     uint64_t at[2];        // place of the first one in the call's candidate array
     uint32_t cnt[2];

@@ -93,8 +93,7 @@ __device__ __forceinline__ uint32_t last_bit_end(const uint4& w, uint32_t first_
 }
 
 // --------------------------------------------------------------------------
-// Side, mean, residual update and bitmap.  The chunk's run may be shared by the consecutive chunks
-// of one streaming workgroup: entries of other chunks are passed over.
+// Side, mean, residual update and bitmap.
 // --------------------------------------------------------------------------
 __global__ __launch_bounds__(kEncThreads) void k_apply(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor, const ChunkRun* __restrict__ runs,
@@ -143,8 +142,8 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
     wave_lds_fence();
     bool bad = false;
     auto keep = [&](const uint2& e) {
-        if (!cand_kept(e.x, e.y, tau, itau) || e.y / (uint32_t)kChunk != cc) return;
-        if (e.y >= d.n) { bad = true; return; }
+        if (!cand_kept(e.x, e.y, tau, itau)) return;
+        if (e.y >= d.n || e.y / (uint32_t)kChunk != cc) { bad = true; return; }      // (cannot happen)
         const float a = __uint_as_float(bits_of_key(chosen ? ~e.x : e.x));
         R[e.y] = a - mu_signed;                        // Alg. 1: R <- dW - dW*
         atomicOr(&bm[(e.y % (uint32_t)kChunk) >> 5], 1u << (e.y & 31u));

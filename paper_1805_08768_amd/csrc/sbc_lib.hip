@@ -56,12 +56,11 @@ struct sbc_ctx {
     // ---- device scratch of sbc_compress ----
     TensorDesc* d_desc = nullptr;         // kDescSlots tables of max_tensors entries
     uint2* d_chunk_tensor = nullptr;      // chunk -> (tensor, the tensor's first chunk)
-    uint2* d_sched = nullptr;             // workgroup of the streaming kernel -> (chunk, tensor)
+    uint2* d_sched = nullptr;             // workgroup of k_client_step -> (chunk, tensor)
     GroupState* d_group = nullptr;        // per group of chunks: candidate and completion counters
     uint64_t max_groups = 0;
     bool compact = false;                 // candidate lists of a few times k entries instead of n
     uint64_t cand_entries = 0;            // entries d_cand holds
-    uint32_t n_sched = 0;                 // workgroups of the streaming kernel
     uint32_t* d_order = nullptr;
     uint32_t* d_hist = nullptr;
     TensorState* d_state = nullptr;
@@ -767,23 +766,9 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
                     if (first != (pass == 0)) continue;
                     for (uint32_t j = 0; j < d.nchunks; ++j) c->h_sched[w++] = make_uint2(d.chunk0 + j, c->plan_order[i]);
                 }
-            c->n_sched = (uint32_t)w;
-        } else {
-            // k_accumulate_filter: chunks in memory order.  Every workgroup reserves room in its
-            // tensor's candidate lists with one atomic on one address, and those of one tensor queue
-            // up there (about 20 ns each): a tensor of very many chunks gives each workgroup several
-            // consecutive chunks, so that the queue is no longer what bounds the pass.
-            uint64_t w = 0;
-            for (int t = 0; t < T; ++t) {
-                const TensorDesc& d = c->plan[t];
-                const uint32_t m = std::min<uint32_t>(kMaxChunksPerWorkgroup, std::max<uint32_t>(1u, d.nchunks / 4096u));
-                for (uint32_t j = 0; j < d.nchunks; j += m)
-                    c->h_sched[w++] = make_uint2(d.chunk0 + j, (uint32_t)t | (std::min(m, d.nchunks - j) << 24));
-            }
-            c->n_sched = (uint32_t)w;
         }
         if (hipMemcpyAsync(c->d_order, c->h_order, sizeof(uint32_t) * T, hipMemcpyHostToDevice, stream) != hipSuccess ||
-            hipMemcpyAsync(c->d_sched, c->h_sched, sizeof(uint2) * c->n_sched, hipMemcpyHostToDevice, stream) != hipSuccess ||
+            (c->fused_step && hipMemcpyAsync(c->d_sched, c->h_sched, sizeof(uint2) * chunks, hipMemcpyHostToDevice, stream) != hipSuccess) ||
             hipMemcpyAsync(c->d_chunk_tensor, c->h_chunk_tensor, sizeof(uint2) * chunks, hipMemcpyHostToDevice, stream) != hipSuccess) {
             (void)hipGetLastError();
             return SBC_EHIP;
@@ -860,17 +845,16 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         SBC_LAUNCH(kStSample, true, k_sample_thresholds, dim3(T), dim3(kSampleThreads), d_desc, c->d_state,
                    res_now, force_exact, sampled ? p : 0.0);
     }
-    // 12 bytes per entry pass through; beyond about twice the 256 MiB last-level cache the update
-    // is loaded with the nontemporal hint
+    // 12 bytes per entry pass through; beyond the 256 MiB of the last-level cache they are streamed past it
     const int carry = c->carry_keys && !sampled && !force_exact ? 1 : 0;
     P.carry = carry;
     if (!c->fused_step) {
-        if (total * 12ull > (512ull << 20)) {
-            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<true>, dim3(c->n_sched), dim3(kStreamThreads), d_desc,
-                       c->d_sched, c->d_state, c->d_cand, c->d_runs, res_now);
+        if (total * 12ull > (256ull << 20)) {
+            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<true>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+                       c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
         } else {
-            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<false>, dim3(c->n_sched), dim3(kStreamThreads), d_desc,
-                       c->d_sched, c->d_state, c->d_cand, c->d_runs, res_now);
+            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<false>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+                       c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
         }
     } else if (total * 12ull > (512ull << 20)) {
         SBC_LAUNCH(kStAccumulate, true, k_client_step<true>, dim3(n_chunks), dim3(kStepThreads), d_desc, c->d_sched,
