@@ -154,7 +154,7 @@ int sbc_compress(sbc_ctx* ctx, void* hip_stream,
  * caller has enqueued behind it on the stream; see "Completion" above for what may be read
  * when), completes the rare tensors that need a second pass, and returns the status
  * and the message size.  Between the two calls the context accepts
- * sbc_decompress_accumulate and nothing else (SBC_EINVAL), dW, residual and msg must not be
+ * sbc_decompress_accumulate and sbc_decompress_average and nothing else (SBC_EINVAL), dW, residual and msg must not be
  * touched, and the host arrays passed to begin are no longer needed.  sbc_compress_end without
  * a pending step returns SBC_EINVAL.  sbc_compress is begin followed by end. */
 int sbc_compress_begin(sbc_ctx* ctx, void* hip_stream,
@@ -180,6 +180,16 @@ int sbc_decompress_accumulate(sbc_ctx* ctx, void* hip_stream,
                               const void* msg, size_t msg_bytes,
                               const int64_t* numel, int n_tensors, double p,
                               float scale, float* const* out);
+
+/* The server step for all messages of a round (Alg. 1: dW <- 1/|I_t| sum of the clients' updates,
+ * with scale = 1/|I_t|): out_t is overwritten with what clearing it and one call of
+ * sbc_decompress_accumulate per message, in order, would leave there, bit for bit.  The messages are
+ * decoded at the same time and the dense result is written once.
+ * msgs, msg_bytes   host arrays of n_msgs device pointers (8-byte aligned) and sizes
+ * other arguments, errors and completion as for sbc_decompress_accumulate; the status is final when the
+ * call returns, whatever SBC_OPT_DEFER_DECODE_STATUS says.  After SBC_ECORRUPT out may hold anything. */
+int sbc_decompress_average(sbc_ctx* ctx, void* hip_stream, const void* const* msgs, const size_t* msg_bytes, int n_msgs,
+                           const int64_t* numel, int n_tensors, double p, float scale, float* const* out);
 
 /* The server step for callers that cannot allocate: code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc.  Same operation as sbc_decompress_accumulate on the

@@ -40,6 +40,7 @@ EXPORTS = (
     "sbc_compress", "sbc_compress_begin", "sbc_compress_end", "sbc_decompress_accumulate", "sbc_last_tensor_stats", "sbc_last_mask",
     "sbc_profile_enable", "sbc_profile_level", "sbc_profile_read", "sbc_copy_baseline", "sbc_set_option",
     "sbc_last_route", "sbc_strerror", "sbc_decode_status", "sbc_decompress_accumulate_noalloc", "sbc_last_candidates",
+    "sbc_decompress_average",
 )
 
 
@@ -84,6 +85,9 @@ def load() -> ctypes.CDLL:
     lib.sbc_decompress_accumulate.argtypes = [vp, vp, vp, sz, ctypes.POINTER(i64), ctypes.c_int,
                                               ctypes.c_double, ctypes.c_float, ctypes.POINTER(vp)]
     lib.sbc_decompress_accumulate.restype = ctypes.c_int
+    lib.sbc_decompress_average.argtypes = [vp, vp, ctypes.POINTER(vp), ctypes.POINTER(sz), ctypes.c_int, ctypes.POINTER(i64),
+                                           ctypes.c_int, ctypes.c_double, ctypes.c_float, ctypes.POINTER(vp)]
+    lib.sbc_decompress_average.restype = ctypes.c_int
     lib.sbc_last_tensor_stats.argtypes = [vp, ctypes.c_int, ctypes.POINTER(ctypes.c_double),
                                           ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int),
                                           ctypes.POINTER(i64), ctypes.POINTER(i64)]
@@ -278,6 +282,25 @@ def sbc_decompress_accumulate(ctx, msg: torch.Tensor, msg_bytes: int, p: float, 
                                           len(out.tensors), p, scale, out.ptrs)
     if rc != SBC_OK:
         raise SbcError(rc, "sbc_decompress_accumulate")
+
+
+def sbc_decompress_average(ctx, messages, p: float, scale: float, out, stream=None) -> None:
+    """Overwrites `out` with the sum over `messages` ((tensor or MessageBuffer, size) pairs, in order) of
+    scale * (decoded sparse binary update); returns when the status is known."""
+    n = len(messages)
+    ptrs, sizes = (ctypes.c_void_p * n)(), (ctypes.c_size_t * n)()
+    keep = []
+    for i, (msg, nbytes) in enumerate(messages):
+        m = _as_msg(msg)
+        if nbytes > m.capacity:
+            raise ValueError("msg must be a contiguous uint8 tensor holding msg_bytes bytes")
+        keep.append(m)
+        ptrs[i], sizes[i] = m.ptr, nbytes
+    out = _as_list(out)
+    rc = load().sbc_decompress_average(ctx, _stream_handle(stream), ptrs, sizes, n, out.numel_arr, len(out.tensors),
+                                       p, scale, out.ptrs)
+    if rc != SBC_OK:
+        raise SbcError(rc, "sbc_decompress_average")
 
 
 def sbc_decompress_accumulate_noalloc(msg: torch.Tensor, msg_bytes: int, p: float, scale: float, out,

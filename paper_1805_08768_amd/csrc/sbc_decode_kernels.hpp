@@ -230,52 +230,27 @@ __device__ __forceinline__ unsigned long long walk_segment(const Segment& s, int
     return (unsigned long long)ones | ((unsigned long long)codes << 16) | ((unsigned long long)rem << 32);
 }
 
-// The updates out[j] += fl32(scale * mu) of a segment, given the unary ones, codes and remainders of
-// the stream before it.  Positions of a message are distinct, so either way each address sees one
-// rounded fp32 addition.
-//   BATCH = false  an atomic that returns nothing: one access per entry instead of a load and a store,
-//                  and no wait.  For a workgroup that decodes a whole stream, whose compute unit sustains
-//                  only about one scattered access per 3 ns (ResNet-50 shape: k_decode 8.4 us, 11.3
-//                  with loads and stores at p = 0.001, 14.8 and 21.4 us at p = 0.01)
-//   BATCH = true   up to eight loads in flight, then their stores: for updates spread over the chip,
-//                  which are bound by the lines they touch in memory (66e6 entries, 660,000 updates:
-//                  25.9 us, 36.0 with atomics)
-template <bool BATCH>
-__device__ __forceinline__ void place_segment(const Segment& s, int entry, int b, unsigned long long bits_left,
-                                              unsigned long long ones, unsigned long long codes, unsigned long long rem,
-                                              float* __restrict__ out, uint32_t n, uint32_t nnz, float addend, bool& bad) {
-    const unsigned long long w = s.bits();
-    const gfloat_ptr o = as_global(out);
-    int x = entry;
-    // position of the next code (0xFFFFFFFF: none, x is 64 then); a code that runs past the stream's end
-    // has been reported by walk_segment
-    auto next = [&]() -> uint32_t {
-        const int z = first_zero_from(w, x);
+// The codes of a segment one after another, given the unary ones, codes and remainders of the stream
+// before it: next() is the position of the next one (0xFFFFFFFF: none, x is 64 then).
+struct CodeWalk {
+    const Segment& s;
+    unsigned long long ones, codes, rem, bits_left;
+    int x, b;
+    uint32_t n, nnz;
+    bool& bad;
+    __device__ __forceinline__ uint32_t next() {
+        const int z = first_zero_from(s.bits(), x);
         ones += (unsigned)(z - x);
         x = z == 64 ? 64 : z + b + 1;
+        // (a code that runs past the stream's end has been reported by walk_segment)
         if (z == 64 || (unsigned long long)x > bits_left) { x = 64; return 0xFFFFFFFFu; }
         rem += s.field(z + 1, b);
         const unsigned long long pos = (ones << b) + rem + codes;
         if (pos >= n || codes >= nnz) { bad = true; x = 64; return 0xFFFFFFFFu; }
         ++codes;
         return (uint32_t)pos;                          // (below n, so below 0xFFFFFFFF)
-    };
-    while (x < 64) {
-        if constexpr (BATCH) {
-            uint32_t at[8];
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) at[j] = x < 64 ? next() : 0xFFFFFFFFu;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) v[j] = at[j] != 0xFFFFFFFFu ? o[at[j]] : 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) if (at[j] != 0xFFFFFFFFu) o[at[j]] = v[j] + addend;
-        } else {
-            const uint32_t at = next();
-            if (at != 0xFFFFFFFFu) add_to(out + at, addend);
-        }
     }
-}
+};
 
 struct StreamInfo {
     bool ok;
@@ -320,12 +295,98 @@ __device__ __forceinline__ void report_corrupt(ResultBlock* result, int32_t* sta
 }
 
 // --------------------------------------------------------------------------
-// One stream, by the whole workgroup, tile after tile.
+// One validated stream, tile after tile, by NW wavefronts: a whole workgroup, or one wavefront by
+// itself (NW = 1; it then meets no barrier), up to segment seg_end.  f(walk, active, count) is called by
+// every lane of a wavefront for which mine(tile) is true and that has a segment of the stream: walk gives the codes of the lane's segment
+// (only if `active`), the codes of a wavefront's lanes follow one another, and there are `count` of them;
+// bad: the stream is corrupt.  sh.fn must have been built (with NW > 1 a barrier follows before it is read).
+// Returns the smallest position that a further code would have.
 // --------------------------------------------------------------------------
+template <int D, int NW, typename Mine, typename F>
+__device__ __forceinline__ unsigned long long decode_codes(DecShared<D>& sh, const StreamInfo& si, uint32_t n, int b,
+                                                                 unsigned long long seg_end, Mine mine, bool& bad, F f) {
+    const int lane = threadIdx.x & 63, wave = NW > 1 ? (int)(threadIdx.x >> 6) : 0;
+    uint32_t carry_state = 0u;
+    unsigned long long carry_ones = 0ull, carry_codes = 0ull, carry_rem = 0ull;      // of the tiles so far
+    int parity = 0;
+    Segment ahead;                                     // of the next tile, on its way during this one
+    ahead.hi = ahead.lo = ahead.next = 0xFFFFFFFFu;
+    if ((unsigned)(wave * 64) < si.n_seg) ahead = stream_segment(si.words, (unsigned)(wave * 64 + lane), si.n_words, si.bit_len);
+    uint32_t tile_no = 0u;
+    for (unsigned long long seg0 = 0; seg0 < seg_end; seg0 += 64 * NW, ++tile_no) {
+        const unsigned long long seg = seg0 + (unsigned)(wave * 64 + lane);
+        const bool busy = seg0 + (unsigned)(wave * 64) < si.n_seg;     // the same for the whole wavefront
+        const Segment s = ahead;
+        if (seg0 + (unsigned)(64 * NW + wave * 64) < si.n_seg) ahead = stream_segment(si.words, seg + 64 * NW, si.n_words, si.bit_len);
+        if (NW > 1) __syncthreads();                   // the table; the tile before this one is done with LDS
+        SBC_TS(2, 2);
+        StateFn<D> fn = identity_fn<D>();
+        if (busy) {
+            fn = segment_fn<D>(sh.fn, s.hi, s.lo);
+            scan_fns<D, 4>(fn);
+        }
+        // state in which this wavefront is entered, from the functions of those before it
+        uint32_t entry_wave = carry_state;
+        if constexpr (NW > 1) {
+            if (lane == 63) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) sh.wave_fn[wave][i] = fn.v[i];
+            }
+            __syncthreads();
+            SBC_TS(2, 3);
+            StateFn<D> g = identity_fn<D>();
+            if (lane < NW) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) g.v[i] = sh.wave_fn[lane][i];
+            }
+            scan_fns<D, 1>(g);
+            const uint32_t through = apply_uniform<D>(g, carry_state);     // lane w: after wavefronts 0..w
+            if (wave) entry_wave = (uint32_t)__builtin_amdgcn_readlane((int)through, wave - 1);
+            carry_state = (uint32_t)__builtin_amdgcn_readlane((int)through, NW - 1);
+        }
+        const uint32_t up_to = apply_uniform<D>(fn, entry_wave);           // after this lane's segment
+        if constexpr (NW == 1) carry_state = last_lane(up_to);
+        const uint32_t before = __shfl_up(up_to, 1, 64);
+        const int entry = lane ? (int)before : (int)entry_wave;
+        const unsigned long long bits_left = si.bit_len > 64ull * seg ? si.bit_len - 64ull * seg : 0ull;
+        uint32_t last_end = 0u;
+        unsigned long long own = 0ull;
+        if (seg < si.n_seg) own = walk_segment(s, entry, b, bits_left, last_end, bad);
+        const unsigned long long inc = wave_incl_sum(own);
+        unsigned long long tile = last_lane(inc), ex = inc - own;
+        if constexpr (NW > 1) {
+            if (lane == 63) sh.sums[parity][wave] = inc;
+            __syncthreads();
+            SBC_TS(2, 4);
+            const unsigned long long ws = wave_incl_sum(lane < NW ? sh.sums[parity][lane] : 0ull);
+            tile = last_lane(ws);
+            if (wave) ex += ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ws >> 32), wave - 1) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ws, wave - 1);
+            parity ^= 1;
+        }
+        const unsigned long long codes = carry_codes + ((ex >> 16) & 0xFFFFull);
+        const uint32_t n_own = (uint32_t)(own >> 16) & 0xFFFFu;
+        // the stream's last code ends the stream exactly
+        if (n_own && codes + n_own == si.nnz && (unsigned long long)last_end != bits_left) bad = true;
+        if (busy && mine(tile_no)) {
+            CodeWalk w = {s, carry_ones + (ex & 0xFFFFull), codes, carry_rem + (ex >> 32), bits_left, entry, b, n, si.nnz, bad};
+            f(w, seg < si.n_seg && !bad, (uint32_t)(last_lane(inc) >> 16) & 0xFFFFu);
+        }
+        carry_ones += tile & 0xFFFFull; carry_codes += (tile >> 16) & 0xFFFFull; carry_rem += tile >> 32;
+        SBC_TS(2, 5);
+    }
+    if (seg_end >= si.n_seg && carry_codes != si.nnz) bad = true;      // identical in every thread
+    return (carry_ones << b) + carry_rem + carry_codes;
+}
+
+// A stream's updates.  An update out[j] += fl32(scale * mu) is an atomic that returns nothing: one access
+// per entry instead of a load and a store, and no wait, for a compute unit sustains only about one
+// scattered access per 3 ns (ResNet-50 shape: k_decode 8.4 us, 11.3 with loads and stores at p = 0.001).
+// Positions of a message are distinct, so each address sees one rounded fp32 addition either way.
 template <int D>
 __device__ __forceinline__ void decode_stream(DecShared<D>& sh, const uint8_t* __restrict__ msg, unsigned long long msg_bytes,
                                               const DecBlock& blk, int T, int b, float scale, ResultBlock* result, int32_t* status) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = tid >> 6;
     const StreamInfo si = stream_info(msg, msg_bytes, blk.n, T, b, (int)blk.t);
     if (tid < 256) build_table<D>(sh.fn, (uint32_t)tid, b);            // (while the header is on its way)
     SBC_TS(2, 1);
@@ -335,71 +396,16 @@ __device__ __forceinline__ void decode_stream(DecShared<D>& sh, const uint8_t* _
     }
     if (si.nnz == 0u) return;
     const float addend = scale * si.mu;
-    const bool mine = (uint32_t)wave % blk.shares == blk.share;
-    uint32_t carry_state = 0u;
-    unsigned long long carry_ones = 0ull, carry_codes = 0ull, carry_rem = 0ull;      // of the tiles so far
+    float* const out = blk.out;
     bool bad = false;
-    int parity = 0;
-    for (unsigned long long seg0 = 0; seg0 < si.n_seg; seg0 += kDecThreads) {
-        const unsigned long long seg = seg0 + (unsigned)tid;
-        const bool busy = seg0 + (unsigned)(wave * 64) < si.n_seg;     // the same for the whole wavefront
-        Segment s;
-        s.hi = s.lo = s.next = 0xFFFFFFFFu;
-        if (busy) s = stream_segment(si.words, seg, si.n_words, si.bit_len);
-        __syncthreads();                               // the table; the tile before this one is done with LDS
-        SBC_TS(2, 2);
-        StateFn<D> f = identity_fn<D>();
-        if (busy) {
-            f = segment_fn<D>(sh.fn, s.hi, s.lo);
-            scan_fns<D, 4>(f);
-        }
-        if (lane == 63) {
-#pragma unroll
-            for (int i = 0; i < D; ++i) sh.wave_fn[wave][i] = f.v[i];
-        }
-        __syncthreads();
-        SBC_TS(2, 3);
-        // state in which this wavefront is entered, from the functions of those before it
-        StateFn<D> g = identity_fn<D>();
-        if (lane < kDecWaves) {
-#pragma unroll
-            for (int i = 0; i < D; ++i) g.v[i] = sh.wave_fn[lane][i];
-        }
-        scan_fns<D, 1>(g);
-        const uint32_t through = apply_uniform<D>(g, carry_state);     // lane w: after wavefronts 0..w
-        const uint32_t entry_wave = wave ? (uint32_t)__builtin_amdgcn_readlane((int)through, wave - 1) : carry_state;
-        carry_state = (uint32_t)__builtin_amdgcn_readlane((int)through, kDecWaves - 1);
-        const uint32_t up_to = apply_uniform<D>(f, entry_wave);        // after this lane's segment
-        const uint32_t before = __shfl_up(up_to, 1, 64);
-        const int entry = lane ? (int)before : (int)entry_wave;
-        const unsigned long long bits_left = si.bit_len > 64ull * seg ? si.bit_len - 64ull * seg : 0ull;
-        uint32_t last_end = 0u;
-        unsigned long long own = 0ull;
-        if (seg < si.n_seg) own = walk_segment(s, entry, b, bits_left, last_end, bad);
-        const unsigned long long inc = wave_incl_sum(own);
-        if (lane == 63) sh.sums[parity][wave] = inc;
-        __syncthreads();
-        SBC_TS(2, 4);
-        unsigned long long ws = wave_incl_sum(lane < kDecWaves ? sh.sums[parity][lane] : 0ull);
-        const unsigned long long tile = last_lane(ws);
-        ws = wave ? ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ws >> 32), wave - 1) << 32) |
-                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ws, wave - 1)
-                  : 0ull;
-        parity ^= 1;
-        const unsigned long long ex = ws + inc - own;
-        if (seg < si.n_seg) {
-            const unsigned long long codes = carry_codes + ((ex >> 16) & 0xFFFFull);
-            const uint32_t n_own = (uint32_t)(own >> 16) & 0xFFFFu;
-            // the stream's last code ends the stream exactly
-            if (n_own && codes + n_own == si.nnz && (unsigned long long)last_end != bits_left) bad = true;
-            if (mine && !bad)
-                place_segment<false>(s, entry, b, bits_left, carry_ones + (ex & 0xFFFFull), codes, carry_rem + (ex >> 32), blk.out, blk.n,
-                              si.nnz, addend, bad);
-        }
-        carry_ones += tile & 0xFFFFull; carry_codes += (tile >> 16) & 0xFFFFull; carry_rem += tile >> 32;
-        SBC_TS(2, 5);
-    }
-    if (carry_codes != si.nnz) bad = true;             // identical in every thread
+    const bool mine = (uint32_t)wave % blk.shares == blk.share;
+    decode_codes<D, kDecWaves>(sh, si, blk.n, b, si.n_seg, [&](uint32_t) { return mine; }, bad, [&](CodeWalk& w, bool active, uint32_t) {
+        if (active)
+            while (w.x < 64) {
+                const uint32_t at = w.next();
+                if (at != 0xFFFFFFFFu) add_to(out + at, addend);
+            }
+    });
     if (bad) report_corrupt(result, status);
     SBC_TS(2, 6);
 }
@@ -616,7 +622,21 @@ __global__ __launch_bounds__(kPlaceThreads) void k_dec_tile_place(
             const uint32_t n_own = (uint32_t)(own >> 16) & 0xFFFFu;
             if (n_own && codes + n_own == si.nnz && (unsigned long long)last_end != bits_left) bad = true;
         }
-        place_segment<true>(s, entry, b, bits_left, ones, codes, rem, w.out, w.n, si.nnz, scale * si.mu, bad);
+        // Up to eight loads in flight, then their stores: updates spread over the chip are bound by the lines they
+        // touch in memory (66e6 entries, 660,000 updates: 25.9 us, 36.0 with atomics).
+        CodeWalk cw = {s, ones, codes, rem, bits_left, entry, b, w.n, si.nnz, bad};
+        const gfloat_ptr o = as_global(w.out);
+        const float addend = scale * si.mu;
+        while (cw.x < 64) {
+            uint32_t at[8];
+            float v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) at[j] = cw.x < 64 ? cw.next() : 0xFFFFFFFFu;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = at[j] != 0xFFFFFFFFu ? o[at[j]] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) if (at[j] != 0xFFFFFFFFu) o[at[j]] = v[j] + addend;
+        }
     }
     if (bad) report_corrupt(result, nullptr);
 }

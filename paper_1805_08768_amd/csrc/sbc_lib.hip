@@ -20,6 +20,7 @@
 #include "sbc_encode_kernels.hpp"
 #include "sbc_decode_kernels.hpp"
 #include "sbc_step_kernels.hpp"
+#include "sbc_average_kernels.hpp"
 
 using namespace sbc;
 
@@ -33,6 +34,7 @@ const char* const kStageNames[kNumStages] = {
 }  // namespace
 
 constexpr int kDescSlots = 4;             // device copies of the tensor table, keyed by the pointer lists
+constexpr uint32_t kAvgAloneChunks = 1024;  // (8.4e6 entries) beyond these, one message alone is added to the cleared result
 constexpr uint32_t kMaxDecExtra = 512;    // additional decode workgroups that share a stream's scatter
 constexpr uint32_t kDecSharePer = 256;    // kept entries per sharing workgroup
 constexpr uint32_t kDecShareMax = kDecWaves;    // (a wavefront's updates each)
@@ -86,6 +88,20 @@ struct sbc_ctx {
     uint4* d_tile_fn = nullptr;
     unsigned long long* d_tile_sum = nullptr;
     uint64_t dec_seg_cap = 0, dec_tile_cap = 0;
+
+    // ---- ... and of sbc_decompress_average (positions and marks go to the candidate lists' space) ----
+    AvgTensor* d_avg_tensor = nullptr;    // followed by the streams of each decoding workgroup
+    AvgTensor* h_avg_tensor = nullptr;
+    uint2* d_avg_chunk = nullptr;         // chunk -> (tensor, its first chunk)
+    uint2* h_avg_chunk = nullptr;
+    bool avg_valid = false;
+    double avg_p = 0.0;
+    std::vector<float*> avg_out;
+    std::vector<int64_t> avg_numel;
+    uint32_t avg_blocks = 0, avg_chunks = 0, avg_pos = 0;
+    uint64_t avg_marks = 0;
+    bool avg_clears = false;              // the chunk table holds the call's tensors
+    bool avg_fits = false;                // and no stream is too long for one workgroup
 
     // ---- pinned host staging ----
     TensorDesc* h_desc = nullptr;
@@ -243,6 +259,9 @@ void free_all(sbc_ctx* c) {
     if (c->h_desc) (void)hipHostFree(c->h_desc);
     if (c->h_chunk_tensor) (void)hipHostFree(c->h_chunk_tensor);
     if (c->h_sched) (void)hipHostFree(c->h_sched);
+    (void)hipFree(c->d_avg_tensor); (void)hipFree(c->d_avg_chunk);
+    if (c->h_avg_tensor) (void)hipHostFree(c->h_avg_tensor);
+    if (c->h_avg_chunk) (void)hipHostFree(c->h_avg_chunk);
     if (c->h_order) (void)hipHostFree(c->h_order);
     if (c->h_result) (void)hipHostFree(c->h_result);
     if (c->h_result_dec) (void)hipHostFree(c->h_result_dec);
@@ -513,6 +532,11 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_tile, (size_t)(c->max_chunks / kScanTile) + T + 1) == hipSuccess;
     ok = ok && dev_alloc(&c->d_result, 6) == hipSuccess;
     ok = ok && dev_alloc(&c->d_dec_blocks, T + kMaxDecExtra) == hipSuccess;
+    const size_t avg_room = T + (sizeof(uint32_t) * kDecWaves * (T + kMaxDecExtra) + sizeof(AvgTensor) - 1) / sizeof(AvgTensor);
+    ok = ok && dev_alloc(&c->d_avg_tensor, avg_room) == hipSuccess;
+    ok = ok && host_alloc(&c->h_avg_tensor, avg_room) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_avg_chunk, (size_t)c->max_chunks) == hipSuccess;
+    ok = ok && host_alloc(&c->h_avg_chunk, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && host_alloc(&c->h_dec_blocks, T + kMaxDecExtra) == hipSuccess;
     // tile decode: a stream of w words has w/2 segments; every stream is rounded up to whole tiles
     c->dec_seg_cap = c->stage_cap / 2 + (uint64_t)(kMaxWideDec + 1) * kDecThreads;
@@ -1119,6 +1143,146 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
     return status_of_err(c->h_result_dec->err);
 }
 
+// out <- the sum of the messages, one after another: the general way of sbc_decompress_average.
+static int average_in_turn(sbc_ctx* c, hipStream_t stream, const void* const* msgs, const size_t* msg_bytes, int n_msgs,
+                           const int64_t* numel, int T, double p, float scale, float* const* out) {
+    if (c->avg_clears) {
+        hipLaunchKernelGGL(k_average_clear, dim3(c->avg_chunks), dim3(256), 0, stream, c->d_avg_chunk, c->d_avg_tensor,
+                           c->deferred_dirty && !c->deferred_pending ? c->d_result + 4 : nullptr);
+        if (!c->deferred_pending) c->deferred_dirty = false;
+    } else {
+        for (int t = 0; t < T; ++t)
+            hipLaunchKernelGGL(k_zero_words, dim3((unsigned)std::min<uint64_t>(4096, ((uint64_t)numel[t] + 2047) / 2048)), dim3(256), 0,
+                               stream, reinterpret_cast<uint32_t*>(out[t]), (uint64_t)numel[t]);
+    }
+    // one status check at the end, unless the caller still has the status of deferred calls to ask for
+    const int before = c->defer_decode;
+    c->defer_decode = c->deferred_pending ? 0 : 1;
+    int rc = SBC_OK;
+    for (int m = 0; m < n_msgs && rc == SBC_OK; ++m)
+        rc = sbc_decompress_accumulate(c, stream, msgs[m], msg_bytes[m], numel, T, p, scale, out);
+    const int status = c->defer_decode ? sbc_decode_status(c, stream) : SBC_OK;
+    c->defer_decode = before;
+    return rc != SBC_OK ? rc : status;
+}
+
+int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs, const size_t* msg_bytes, int n_msgs,
+                           const int64_t* numel, int n_tensors, double p, float scale, float* const* out) {
+    if (!c || !msgs || !msg_bytes || n_msgs <= 0 || !numel || !out || n_tensors <= 0 || !valid_p(p)) return SBC_EINVAL;
+    for (int m = 0; m < n_msgs; ++m)
+        if (!msgs[m] || ((uintptr_t)msgs[m] & 7u) != 0) return SBC_EINVAL;
+    if (n_tensors > c->max_tensors) return SBC_ECAPACITY;
+    const int T = n_tensors;
+    const int b = bstar_of(p);
+    if (b > kMaxB) return SBC_EINVAL;
+    for (int m = 0; m < n_msgs; ++m)
+        if (msg_bytes[m] < 32 + 24ull * (unsigned)T) return SBC_ECORRUPT;
+    const bool same = c->avg_valid && c->avg_p == p && c->avg_numel.size() == (size_t)T &&
+                      std::memcmp(c->avg_numel.data(), numel, sizeof(int64_t) * T) == 0 &&
+                      std::memcmp(c->avg_out.data(), out, sizeof(float*) * T) == 0;
+    DeviceGuard guard(c->device);
+    hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
+    if (!same) {
+        for (int t = 0; t < T; ++t)
+            if (numel[t] < 1 || numel[t] >= (int64_t)1 << 32 || !out[t] || ((uintptr_t)out[t] & 3u)) return SBC_EINVAL;
+        // (every earlier call has waited for its uploads from the pinned tables)
+        c->avg_valid = false;
+        uint64_t pos = 0, marks = 0, chunks = 0;
+        for (int t = 0; t < T; ++t) chunks += ((uint64_t)numel[t] + kChunk - 1) / kChunk;
+        c->avg_clears = chunks <= c->max_chunks && chunks < (1ull << 31);
+        c->avg_fits = c->avg_clears && b >= kAvgMinB && b <= kPackedMaxB;
+        c->avg_chunks = (uint32_t)chunks;
+        uint32_t* const ids = reinterpret_cast<uint32_t*>(c->h_avg_tensor + T);
+        uint32_t n_ids = 0, chunk0 = 0, n_small = 0, extra = 0;
+        const auto most_segs = [&](int t) { return (bound_words_of(numel[t], cap_of(numel[t], kept_of(numel[t], p), true), b) + 1) / 2; };
+        for (int t = 0; t < T && c->avg_clears; ++t) {
+            // (room for the cap of the subsampled variant, whichever of the two the senders use)
+            const int64_t n = numel[t], k = cap_of(n, kept_of(n, p), true);
+            const uint64_t segs = most_segs(t);
+            AvgTensor& a = c->h_avg_tensor[t];
+            a.out = out[t]; a.n = (uint32_t)n; a.kcap = (uint32_t)k; a.pos_off = (uint32_t)pos; a.mark_off = (uint32_t)marks;
+            const uint32_t nchunks = (uint32_t)(((uint64_t)n + kChunk - 1) / kChunk);
+            for (uint32_t j = 0; j < nchunks; ++j) c->h_avg_chunk[chunk0 + j] = make_uint2((uint32_t)t, chunk0);
+            chunk0 += nchunks;
+            pos += (uint64_t)k;
+            marks += ((uint64_t)n + kAvgBlock - 1) / kAvgBlock + 1;
+            c->avg_fits = c->avg_fits && segs <= (uint64_t)kAvgMaxTiles * kDecThreads && pos < (1ull << 31) && marks < (1ull << 31);
+            if (!c->avg_fits || segs <= kAvgWaveSegs) continue;
+            const uint32_t tiles = (uint32_t)((segs + kDecThreads - 1) / kDecThreads);
+            const uint32_t shares = extra + tiles - 1u <= kMaxDecExtra ? tiles : 1u;
+            extra += shares - 1u;
+            for (uint32_t share = 0; share < shares; ++share) {
+                uint32_t* const w = ids + (size_t)kDecWaves * n_ids++;
+                std::fill_n(w, (size_t)kDecWaves, kAvgNone);
+                w[0] = (uint32_t)t; w[1] = kAvgWhole; w[2] = share; w[3] = shares;
+            }
+        }
+        for (int t = 0; t < T && c->avg_fits; ++t) {
+            if (most_segs(t) > kAvgWaveSegs) continue;
+            if (n_small % kDecWaves == 0) { std::fill_n(ids + (size_t)kDecWaves * n_ids, (size_t)kDecWaves, kAvgNone); ++n_ids; }
+            ids[(size_t)kDecWaves * (n_ids - 1) + n_small++ % kDecWaves] = (uint32_t)t;
+        }
+        if (c->avg_clears &&
+            (hipMemcpyAsync(c->d_avg_tensor, c->h_avg_tensor, sizeof(AvgTensor) * T + sizeof(uint32_t) * kDecWaves * n_ids,
+                            hipMemcpyHostToDevice, stream) != hipSuccess ||
+             hipMemcpyAsync(c->d_avg_chunk, c->h_avg_chunk, sizeof(uint2) * chunks, hipMemcpyHostToDevice, stream) != hipSuccess)) {
+            (void)hipGetLastError();
+            return SBC_EHIP;
+        }
+        c->avg_blocks = n_ids; c->avg_pos = (uint32_t)pos; c->avg_marks = marks; c->avg_p = p;
+        c->avg_out.assign(out, out + T);
+        c->avg_numel.assign(numel, numel + T);
+        c->avg_valid = true;
+    }
+    // Messages per pass: a lane each, and what the scratch memory holds.  A single message for a large model
+    // is added to the cleared result instead: that stores no positions first (ResNet-50 shape at p = 0.001
+    // 35 us, 41 the other way; 66e6 entries 68 and 79 us).  Two messages take 45 us in turn and 42 together, at
+    // 66e6 entries 93 and 80 us; one message of a small model 30 and 25 us, of 2^20 entries at p = 0.01 39 and
+    // 32 us.
+    const uint64_t per_msg = (uint64_t)c->avg_pos + c->avg_marks + (uint64_t)T;
+    const uint64_t room = c->cand_entries * (sizeof(uint2) / sizeof(uint32_t));
+    const int most = c->avg_fits && !c->pend.active ? (int)std::min<uint64_t>(kAvgMaxMsgs, room / per_msg) : 0;
+    if (most < 1 || (n_msgs == 1 && c->avg_chunks > kAvgAloneChunks)) return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);
+    // (the last client step may still be draining on another stream)
+    if (c->last_T > 0 && c->last_stream != stream && hipStreamSynchronize(c->last_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return SBC_EHIP;
+    }
+    if (c->dec_result_dirty)                              // after an error, or on the first call
+        hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(c->d_result + 2),
+                           (uint64_t)(2 * sizeof(ResultBlock) / 4));
+    c->dec_result_dirty = true;                           // until this call has completed normally
+    ResultBlock* const res = c->d_result + 2 + c->dec_result_idx;
+    ResultBlock* const res_next = c->d_result + 2 + (c->dec_result_idx ^ 1);
+    c->dec_result_idx ^= 1;
+    uint32_t* const positions = reinterpret_cast<uint32_t*>(c->d_cand);
+    const uint32_t* const ids = reinterpret_cast<const uint32_t*>(c->d_avg_tensor + T);
+    for (int m0 = 0; m0 < n_msgs; m0 += most) {
+        const int M = std::min(most, n_msgs - m0);
+        AvgMsgs list = {};
+        for (int m = 0; m < M; ++m) { list.msg[m] = static_cast<const uint8_t*>(msgs[m0 + m]); list.bytes[m] = msg_bytes[m0 + m]; }
+        uint32_t* const marks = positions + (size_t)M * c->avg_pos;
+        float* const addends = reinterpret_cast<float*>(marks + (size_t)M * c->avg_marks);
+        const dim3 grid(c->avg_blocks, (unsigned)M), block(kDecThreads);
+        if (b <= 7) hipLaunchKernelGGL(k_average_decode<2>, grid, block, 0, stream, list, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        else if (b <= 11) hipLaunchKernelGGL(k_average_decode<3>, grid, block, 0, stream, list, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        if (m0 == 0) hipLaunchKernelGGL(k_average_apply<false>, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
+        else hipLaunchKernelGGL(k_average_apply<true>, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
+    }
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
+    if (hipGetLastError() != hipSuccess) return SBC_EHIP;
+    if (!result_arrived(c->h_result_dec, c->dec_seq) && hipStreamSynchronize(stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return SBC_EHIP;
+    }
+    const uint32_t err = c->h_result_dec->err;
+    if (err == 0u) c->dec_result_dirty = false;
+    if ((err & kErrDeferred) && !(err & kErrCorrupt))     // a stream of more positions than there is room for
+        return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);
+    return status_of_err(err & ~kErrDeferred);
+}
+
 int sbc_decode_status(sbc_ctx* c, void* hip_stream) {
     if (!c) return SBC_EINVAL;
     if (!c->deferred_pending) return SBC_OK;
@@ -1126,8 +1290,9 @@ int sbc_decode_status(sbc_ctx* c, void* hip_stream) {
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     c->deferred_pending = false;
     c->deferred_dirty = true;
-    if (hipMemcpyAsync(c->h_result_dec, c->d_result + 4, sizeof(ResultBlock), hipMemcpyDeviceToHost, stream) != hipSuccess ||
-        hipStreamSynchronize(stream) != hipSuccess) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, c->d_result + 4, ++c->dec_seq);
+    if (hipGetLastError() != hipSuccess) return SBC_EHIP;
+    if (!result_arrived(c->h_result_dec, c->dec_seq) && hipStreamSynchronize(stream) != hipSuccess) {
         (void)hipGetLastError();
         return SBC_EHIP;
     }

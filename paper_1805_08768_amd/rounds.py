@@ -6,7 +6,7 @@ the messages of the participating clients I_t, average the sparse binary updates
 Here every client is an object holding its residual R_i and an sbc context; "training" is a
 callback that returns the client's dense weight update, so no model, data set or optimizer is
 involved.  All of the method's arithmetic runs in the HIP library through the C ABI binding:
-sbc_compress on the client side, sbc_decompress_accumulate on the server side; this module
+sbc_compress on the client side, sbc_decompress_average on the server side; this module
 only moves buffers and calls the callback.
 
 Two ways of running the loop: with the weights and the callback's updates in host memory
@@ -106,18 +106,14 @@ class Server:
         self.p = float(p)
         index = torch.device(device).index or 0
         self.ctx = sbc.sbc_create(index, sum(self.sizes), len(self.sizes))
-        # the messages of a round are decoded back to back; one status check at the end
+        # (for callers that decode messages of a round one by one with this context)
         sbc.sbc_set_option(self.ctx, sbc.SBC_OPT_DEFER_DECODE_STATUS, 1)
         self.acc_flat, self.acc = flat_buffer(self.sizes, device)
         self._acc_list = sbc.TensorList(self.acc)
 
     def average(self, messages) -> List[torch.Tensor]:
         """dW <- 1/|I_t| * sum of the clients' sparse binary updates (messages in client order)."""
-        self.acc_flat.zero_()
-        scale = 1.0 / len(messages)
-        for msg, nbytes in messages:
-            sbc.sbc_decompress_accumulate(self.ctx, msg, nbytes, self.p, scale, self._acc_list)
-        sbc.sbc_decode_status(self.ctx)
+        sbc.sbc_decompress_average(self.ctx, messages, self.p, 1.0 / len(messages), self._acc_list)
         return self.acc
 
     def close(self):
