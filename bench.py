@@ -480,7 +480,7 @@ def main() -> int:
         per_round = sorted(b_ - a_ for a_, b_ in zip(stamps[3:-1], stamps[4:]))      # (the first rounds: warm-up)
         round_loop = {"clients": n_cl, "ms_per_round_median": per_round[len(per_round) // 2] * 1e3,
                       "ms_per_round_min": per_round[0] * 1e3, "rounds": len(per_round),
-                      "what": "update copied into each client's buffer, 4 x sbc_compress, 4 x sbc_decompress_accumulate, W += average; all in device memory"}
+                      "what": "update copied into each client's buffer, 4 x sbc_compress, sbc_decompress_average, W += average; all in device memory"}
         del ups
     torch.cuda.synchronize()
 

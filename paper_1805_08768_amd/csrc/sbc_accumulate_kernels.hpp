@@ -403,7 +403,9 @@ typedef const SBC_GLOBAL_AS f32x4_any* gcf32x4_any_ptr;
 // With several clients' states in turn: 25.6e6 entries 54 us instead of 67 at p = 0.001 and 56 instead
 // of 74 at p = 0.01, 66e6 entries 132 us instead of 149, 1.5e9 entries 3.29 ms instead of 3.79 (only the
 // update with the hint: 60, 69, 149, 3.79; update and the residual's loads: 55, 69, 148, 3.51); one
-// client alone, its residual still in the cache from the round before: 52 us instead of 48.5 on 25.6e6.
+// client alone, its residual still in the cache from the round before: 53 us instead of 48.5 on 25.6e6, 132
+// instead of 117 on 66e6.  (A quarter or half of the chunks kept in the cache: 50 and 119 us alone, but 55 and
+// 160 us with three states in turn.)
 // Below the cache's size it loses: 12e6 entries 30 us instead of 27.4.
 template <bool STREAM>
 __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(

@@ -188,7 +188,7 @@ __device__ __forceinline__ uint32_t carried_key(uint32_t tau_side_key, uint32_t 
     return lo > tau_side_key ? tau_side_key : lo;
 }
 
-// Rank of the entry whose key a following call starts from (see k_select): the k entries kept now
+// Rank of the entry whose key a following call starts from (see k_threshold): the k entries kept now
 // are gone from above that key in the next call (on the side that is sent), and k more must
 // remain even if the next update moves nothing across the key.
 __device__ __forceinline__ uint32_t carried_rank(uint32_t k) {
