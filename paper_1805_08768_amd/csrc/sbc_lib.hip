@@ -1036,36 +1036,51 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
     }
     if (!same) {
         // Streams of tensors that keep very many entries are decoded tile by tile by many
-        // workgroups, as far as the scratch arrays reach; all others by one workgroup each.
+        // workgroups, as far as the places and the scratch arrays reach; all others by one workgroup each.
         // If there are any, so are the streams of more than one tile, which a single workgroup would take
         // one after another: the launches are there anyway (ResNet-50 shape at p = 0.01: k_decode 14.8
-        // us with streams of up to three tiles).
+        // us with streams of up to three tiles).  The longest come first, wherever they stand in the list: one
+        // workgroup takes a stream's tiles one after another (the 19-tile stream of a 51e6-entry tensor behind
+        // 48 two-tile ones at p = 0.001: 149 us a call where it is left without a place, 65 with one; 79
+        // ragged tensors of 6e7 entries at p = 0.02 in tensor order 119 us, the longest first 94).
         DecWides& dw = c->dec_wides;
         dw = DecWides{};
+        struct Long { uint32_t t, tiles; };
+        Long longs[kMaxWideDec];                          // the longest so far, by decreasing length
+        int n_longs = 0;
         bool any_wide = false;
-        for (int t = 0; t < T; ++t)
-            any_wide = any_wide || (uint64_t)cap_of(numel[t], kept_of(numel[t], p), c->sampled != 0) >= (uint64_t)c->wide_min_kept;
-        uint64_t segs = 0, tiles = 0;
-        uint32_t n_blocks = 0, extra = 0;
-        for (int t = 0; t < T; ++t) {
+        for (int t = 0; t < T && b <= kPackedMaxB; ++t) {
             // (a context that expects messages of the subsampled variant reserves for its cap)
             const int64_t k = cap_of(numel[t], kept_of(numel[t], p), c->sampled != 0);
-            if (b <= kPackedMaxB && any_wide && dw.count < kMaxWideDec) {
-                const uint64_t max_seg = (bound_words_of(numel[t], (uint32_t)k, b) + 1) / 2;
-                const uint64_t max_tiles = (max_seg + kDecThreads - 1) / kDecThreads;
-                if (((uint64_t)k >= (uint64_t)c->wide_min_kept || max_tiles > 1) && max_tiles != 0 && max_tiles < (1ull << 29) && segs + max_tiles * kDecThreads <= c->dec_seg_cap &&
-                    tiles + max_tiles <= c->dec_tile_cap) {
-                    DecWide& w = dw.w[dw.count++];
-                    w.out = out[t]; w.n = (uint32_t)numel[t]; w.t = (uint32_t)t;
-                    w.tile0 = (uint32_t)tiles; w.max_tiles = (uint32_t)max_tiles; w.seg0 = segs;
-                    segs += max_tiles * kDecThreads; tiles += max_tiles;
-                    continue;
-                }
-            }
+            const bool wide = (uint64_t)k >= (uint64_t)c->wide_min_kept;
+            any_wide = any_wide || wide;
+            const uint64_t max_seg = (bound_words_of(numel[t], k, b) + 1) / 2, max_tiles = (max_seg + kDecThreads - 1) / kDecThreads;
+            if (!(wide || max_tiles > 1) || max_tiles == 0 || max_tiles >= (1ull << 29)) continue;
+            int at = n_longs;
+            while (at > 0 && longs[at - 1].tiles < max_tiles) --at;
+            if (at == kMaxWideDec) continue;
+            n_longs = std::min(n_longs + 1, kMaxWideDec);
+            std::copy_backward(longs + at, longs + n_longs - 1, longs + n_longs);
+            longs[at] = {(uint32_t)t, (uint32_t)max_tiles};
+        }
+        if (!any_wide) n_longs = 0;
+        std::sort(longs, longs + n_longs, [](const Long& x, const Long& y) { return x.t < y.t; });
+        uint64_t segs = 0, tiles = 0;
+        for (int i = 0; i < n_longs; ++i) {
+            const Long& l = longs[i];
+            if (segs + (uint64_t)l.tiles * kDecThreads > c->dec_seg_cap || tiles + l.tiles > c->dec_tile_cap) continue;
+            DecWide& w = dw.w[dw.count++];
+            w.out = out[l.t]; w.n = (uint32_t)numel[l.t]; w.t = l.t;
+            w.tile0 = (uint32_t)tiles; w.max_tiles = l.tiles; w.seg0 = segs;
+            segs += (uint64_t)l.tiles * kDecThreads; tiles += l.tiles;
+        }
+        uint32_t n_blocks = 0, extra = 0;
+        for (int t = 0, i = 0; t < T; ++t) {
+            if (i < dw.count && dw.w[i].t == (uint32_t)t) { ++i; continue; }
             // One workgroup decodes a stream; the scattered updates of a stream with many codes are
             // shared among several workgroups that each decode it (a compute unit sustains only so
             // many scattered accesses at a time, and decoding again costs no more time than once).
-            uint32_t shares = decode_shares(k);
+            uint32_t shares = decode_shares(cap_of(numel[t], kept_of(numel[t], p), c->sampled != 0));
             if (extra + shares - 1u > kMaxDecExtra) shares = 1u;
             extra += shares - 1u;
             for (uint32_t sh = 0; sh < shares; ++sh) {

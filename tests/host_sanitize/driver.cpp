@@ -12,6 +12,7 @@
 #include <vector>
 
 extern "C" long stub_launches();
+extern "C" unsigned stub_grid(long launch);
 extern "C" long stub_live_blocks();
 extern "C" void stub_fail_allocation(long nth);
 
@@ -211,6 +212,20 @@ int main(int argc, char** argv) {
             sbc_destroy(c); c = nullptr;
             CHECK(stub_live_blocks() == 0);
         }
+    }
+
+    // ---- more streams of two tiles than the tiled decoder has places, and one of 19 tiles: that one has a
+    // place wherever it stands (31 of the others have one, too) ----
+    for (int at : {0, 20, 48}) {
+        std::vector<int64_t> sizes(48, (int64_t)1 << 22);
+        sizes.insert(sizes.begin() + at, 51463000);
+        const Buffers s = fake_buffers(sizes);
+        CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+        const long first = stub_launches() + 1;        // (behind the clearing of the result blocks)
+        CHECK(sbc_decompress_accumulate(c, nullptr, kMsg, 1 << 24, s.numel.data(), s.T(), 0.001, 1.f, s.out.data()) == SBC_OK);
+        const unsigned tiles = 19 + 31 * 2;
+        CHECK(stub_grid(first + 1) == tiles && stub_grid(first + 2) == 4 * tiles);     // k_dec_tile_sums, k_dec_tile_place
+        sbc_destroy(c); c = nullptr;
     }
 
     // ---- a context with short candidate lists: the plan shares them out, large p does not fit ----

@@ -50,3 +50,26 @@ def test_every_state_function_width_at_tile_edges(p):
                     assert np.array_equal(x.cpu().numpy().view(np.uint32), w.view(np.uint32)), (p, t, scale, wide_min)
     finally:
         sbc.sbc_destroy(ctx)
+
+
+@pytest.mark.parametrize("at", [0, 17, 34])
+def test_more_long_streams_than_the_tile_kernels_take(at):
+    """34 streams of two or three tiles and one of 13, the longest anywhere in the list: the same bits as from
+    the context-free call, which gives every stream one workgroup."""
+    sizes, p = [70_001] * 20 + [110_003] * 14, 0.2
+    sizes.insert(at, 640_001)
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        dW = [torch.from_numpy(x).to(DEV) for x in synth.small_model_update(sizes)]
+        R = [torch.zeros(n, dtype=torch.float32, device=DEV) for n in sizes]
+        msg = torch.zeros(sbc.sbc_msg_bound(sizes, p), dtype=torch.uint8, device=DEV)
+        nbytes = sbc.sbc_compress(ctx, dW, R, p, msg)
+        want = [torch.full((n,), 0.5, dtype=torch.float32, device=DEV) for n in sizes]
+        out = [x.clone() for x in want]
+        status = torch.full((1,), -9, dtype=torch.int32, device=DEV)
+        sbc.sbc_decompress_accumulate_noalloc(msg, nbytes, p, 0.25, want, status)
+        sbc.sbc_decompress_accumulate(ctx, msg, nbytes, p, 0.25, out)
+        assert int(status[0]) == sbc.SBC_OK
+        assert all(torch.equal(x, w) for x, w in zip(out, want))
+    finally:
+        sbc.sbc_destroy(ctx)
