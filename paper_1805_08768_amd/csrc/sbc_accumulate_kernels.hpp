@@ -397,17 +397,9 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
 typedef const SBC_GLOBAL_AS f32x4_any* gcf32x4_any_ptr;
 
-// STREAM: update and residual are loaded, and the residual stored, with the nontemporal hint, for calls
-// that move more than the last-level cache holds: little of the residual could stay there until the
-// next round anyway, and what does has to be written back in the middle of somebody else's traffic.
-// With several clients' states in turn: 25.6e6 entries 54 us instead of 67 at p = 0.001 and 56 instead
-// of 74 at p = 0.01, 66e6 entries 132 us instead of 149, 1.5e9 entries 3.29 ms instead of 3.79 (only the
-// update with the hint: 60, 69, 149, 3.79; update and the residual's loads: 55, 69, 148, 3.51); one
-// client alone, its residual still in the cache from the round before: 53 us instead of 48.5 on 25.6e6, 132
-// instead of 117 on 66e6.  (A quarter or half of the chunks kept in the cache: 50 and 119 us alone, but 55 and
-// 160 us with three states in turn.)
-// Below the cache's size it loses: 12e6 entries 30 us instead of 27.4.
-template <bool STREAM>
+// What goes past the last-level cache, with the nontemporal hint (the rule is in accumulate_past_cache):
+constexpr int kPastNothing = 0, kPastUpdate = 1, kPastAll = 2;     // (kPastAll: update loaded, residual loaded and stored)
+template <int PAST>
 __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor,
         TensorState* __restrict__ st, uint2* __restrict__ cand, ChunkRun* __restrict__ runs,
@@ -433,8 +425,8 @@ __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
     if (whole) {
 #pragma unroll
         for (int i = 0; i < IT; ++i) {
-            dv[i] = STREAM ? __builtin_nontemporal_load(&dw4[i * kStreamThreads + tid]) : dw4[i * kStreamThreads + tid];
-            rv[i] = STREAM ? __builtin_nontemporal_load(&r4[i * kStreamThreads + tid]) : r4[i * kStreamThreads + tid];
+            dv[i] = PAST >= kPastUpdate ? __builtin_nontemporal_load(&dw4[i * kStreamThreads + tid]) : dw4[i * kStreamThreads + tid];
+            rv[i] = PAST == kPastAll ? __builtin_nontemporal_load(&r4[i * kStreamThreads + tid]) : r4[i * kStreamThreads + tid];
         }
     } else {
         valid = 0u;
@@ -472,7 +464,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
         a.w = rv[i].w + dv[i].w;
         sh.a[i * kStreamThreads + tid] = a;
         if (whole) {                                  // uniform
-            if (STREAM) __builtin_nontemporal_store((f32x4_any)a, &r4[i * kStreamThreads + tid]);
+            if (PAST == kPastAll) __builtin_nontemporal_store((f32x4_any)a, &r4[i * kStreamThreads + tid]);
             else r4[i * kStreamThreads + tid] = a;
         }
         test(a.x); test(a.y); test(a.z); test(a.w);

@@ -202,6 +202,7 @@ struct sbc_ctx {
     bool last_used_wide = false;
     bool last_loose = false;
     bool last_deferred = false;
+    std::chrono::steady_clock::time_point last_begin;     // when it was enqueued
     hipStream_t last_stream = nullptr;    // stream of the last client step (its last kernel may still be draining)
 };
 
@@ -637,6 +638,32 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
     }
 }
 
+// What a step's streaming pass sends past the last-level cache (no result depends on it).  Up to the
+// cache's size (12 bytes per entry pass through): nothing; 24 ragged tensors of 12e6 entries 27.4 us, 30
+// past it.  Beyond it: update and residual, for whatever ran in between, another client's step or a training
+// step, has displaced the residual by the time of the next step, and where that has written, the cache's
+// dirty lines leave it in the middle of this pass.  Only where the residual is read again before that can
+// happen is it kept: by the histogram route of this very call, or by the next step if that follows
+// at once, that is, if since the step before this one no more than this step's bytes and one and a half
+// times the cache's can have moved at 6 TB/s (ResNet-50 shape: 118 us, of which such a step itself
+// takes 88 to 100).  A residual larger than the cache always goes past it, and so does the update, which
+// nobody reads again (66e6 entries, one client back to back: 170 us with it in the cache, 128 without).
+// Kernel times in us, residual kept / sent past:
+//     entries   one client, back to back   three clients in turn   after 0.6 GiB read   ... read and written
+//     25.6e6           56 / 58                   60 / 59               60 / 59               65 / 61
+//     45e6             90 / 98                  110 / 98               98 / 98              111 / 100
+//     66e6            128 / 139                 168 / 139             136 / 141             163 / 142
+//     100e6           249 / 213                 266 / 211             201 / 214             249 / 220
+constexpr uint64_t kCacheBytes = 256ull << 20;
+static int accumulate_past_cache(sbc_ctx* c, uint64_t total, bool force_exact) {
+    const auto now = std::chrono::steady_clock::now();
+    const std::chrono::duration<double> since = now - c->last_begin;
+    c->last_begin = now;
+    if (total * 12ull <= kCacheBytes) return kPastNothing;
+    const bool at_once = c->last_T > 0 && since.count() * 6e12 <= (double)(total * 12ull + kCacheBytes + kCacheBytes / 2);
+    return total * 4ull <= kCacheBytes && (force_exact || at_once) ? kPastUpdate : kPastAll;
+}
+
 static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, float* const* residual,
                           const int64_t* numel, int n_tensors, double p, void* msg, size_t msg_capacity,
                           bool wait_on_event) {
@@ -869,15 +896,18 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         SBC_LAUNCH(kStSample, true, k_sample_thresholds, dim3(T), dim3(kSampleThreads), d_desc, c->d_state,
                    res_now, force_exact, sampled ? p : 0.0);
     }
-    // 12 bytes per entry pass through; beyond the 256 MiB of the last-level cache they are streamed past it
     const int carry = c->carry_keys && !sampled && !force_exact ? 1 : 0;
     P.carry = carry;
     if (!c->fused_step) {
-        if (total * 12ull > (256ull << 20)) {
-            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<true>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+        const int past = accumulate_past_cache(c, total, force_exact != 0);
+        if (past == kPastAll) {
+            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+                       c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
+        } else if (past == kPastUpdate) {
+            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastUpdate>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
                        c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
         } else {
-            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<false>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastNothing>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
                        c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
         }
     } else if (total * 12ull > (512ull << 20)) {

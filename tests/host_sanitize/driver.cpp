@@ -11,8 +11,11 @@
 #include <cstdlib>
 #include <vector>
 
+#include <unistd.h>
+
 extern "C" long stub_launches();
 extern "C" unsigned stub_grid(long launch);
+extern "C" const void* stub_kernel(long launch);
 extern "C" long stub_live_blocks();
 extern "C" void stub_fail_allocation(long nth);
 
@@ -212,6 +215,35 @@ int main(int argc, char** argv) {
             sbc_destroy(c); c = nullptr;
             CHECK(stub_live_blocks() == 0);
         }
+    }
+
+    // ---- the streaming pass of a step that follows its context's last one at once keeps the residual in the
+    // cache, after a pause it does not; calls below the cache's size and residuals beyond it know no difference ----
+    for (int64_t n : {12000000, 60000000, 100000000}) {
+        const Buffers s = fake_buffers({n, 1000});
+        const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), p);
+        CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+        CHECK(sbc_profile_enable(c, 1) == SBC_OK);     // (no looking for a result that no kernel writes)
+        auto kernels = [&]() {
+            const long from = stub_launches();
+            CHECK(compress(c, s, p, nb, &nbytes) == SBC_OK);
+            std::vector<const void*> k;
+            for (long i = from; i < stub_launches(); ++i) k.push_back(stub_kernel(i));
+            return k;
+        };
+        kernels();                                     // (the first call samples)
+        usleep(50000);
+        const std::vector<const void*> paused = kernels();
+        int most = 0;
+        for (int call = 0; call < 100; ++call) {       // (a busy machine may come late for some of them)
+            const std::vector<const void*> k = kernels();
+            CHECK(k.size() == paused.size());
+            int differ = 0;
+            for (size_t i = 0; i < k.size(); ++i) differ += k[i] != paused[i];
+            most = differ > most ? differ : most;
+        }
+        CHECK(most == (n == 60000000 ? 1 : 0));
+        sbc_destroy(c); c = nullptr;
     }
 
     // ---- more streams of two tiles than the tiled decoder has places, and one of 19 tiles: that one has a

@@ -11,11 +11,13 @@
 
 static long g_launches = 0;
 static unsigned g_grids[64];           // workgroups (x) of the latest launches
+static const void* g_kernels[64];      // and their kernels
 static long g_live_blocks = 0;
 static long g_fail_alloc_at = -1;      // the n-th allocation from now fails (tests the clean-up path)
 
 extern "C" long stub_launches() { return g_launches; }
 extern "C" unsigned stub_grid(long launch) { return g_grids[launch % 64]; }
+extern "C" const void* stub_kernel(long launch) { return g_kernels[launch % 64]; }
 extern "C" long stub_live_blocks() { return g_live_blocks; }
 extern "C" void stub_fail_allocation(long nth) { g_fail_alloc_at = nth; }
 
@@ -60,9 +62,10 @@ hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 
-hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t, hipStream_t) {
     if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x == 0 || block.x * block.y * block.z > 1024) return hipErrorInvalidConfiguration;
-    g_grids[g_launches++ % 64] = grid.x;
+    g_grids[g_launches % 64] = grid.x;
+    g_kernels[g_launches++ % 64] = f;
     return hipSuccess;
 }
 hipError_t hipExtLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shmem, hipStream_t s, hipEvent_t,
