@@ -1,5 +1,5 @@
 // Drives the library's host side (argument validation, planning of a client step, message
-// bounds, sizing of the decode plan, the clean-up paths) in a build where the HIP runtime is
+// bounds, sizing of the decode plan and of the server average's tables, the clean-up paths) in a build where the HIP runtime is
 // replaced by hip_stub.cpp and everything is compiled with AddressSanitizer and
 // UndefinedBehaviorSanitizer.  No GPU.  Usage: driver <file with one model's tensor sizes>.
 // Pointers that stand for device buffers are never dereferenced here (launches do nothing), so
@@ -274,6 +274,76 @@ int main(int argc, char** argv) {
         CHECK(stub_launches() == launched);
         sbc_destroy(c); c = nullptr;
         CHECK(stub_live_blocks() == 0);
+    }
+
+    // ---- the average over a round's messages: argument errors, and its two tables at their limits ----
+    {
+        std::vector<const void*> msgs(130, kMsg);
+        std::vector<size_t> sizes(130, bound);
+        CHECK(sbc_create(&c, 0, m.total(), m.T()) == SBC_OK);
+        const long launched = stub_launches();
+        auto average = [&](const Buffers& b, int n_msgs, double q) {
+            return sbc_decompress_average(c, nullptr, msgs.data(), sizes.data(), n_msgs, b.numel.data(), b.T(), q, 0.5f, b.out.data());
+        };
+        CHECK(sbc_decompress_average(nullptr, nullptr, msgs.data(), sizes.data(), 2, m.numel.data(), m.T(), p, 1.f, m.out.data()) == SBC_EINVAL);
+        CHECK(sbc_decompress_average(c, nullptr, nullptr, sizes.data(), 2, m.numel.data(), m.T(), p, 1.f, m.out.data()) == SBC_EINVAL);
+        CHECK(sbc_decompress_average(c, nullptr, msgs.data(), nullptr, 2, m.numel.data(), m.T(), p, 1.f, m.out.data()) == SBC_EINVAL);
+        CHECK(sbc_decompress_average(c, nullptr, msgs.data(), sizes.data(), 2, nullptr, m.T(), p, 1.f, m.out.data()) == SBC_EINVAL);
+        CHECK(sbc_decompress_average(c, nullptr, msgs.data(), sizes.data(), 2, m.numel.data(), m.T(), p, 1.f, nullptr) == SBC_EINVAL);
+        CHECK(average(m, 0, p) == SBC_EINVAL && average(m, -3, p) == SBC_EINVAL && average(m, 2, 0.0) == SBC_EINVAL);
+        CHECK(sbc_decompress_average(c, nullptr, msgs.data(), sizes.data(), 2, m.numel.data(), m.T() + 1, p, 1.f, m.out.data()) == SBC_ECAPACITY);
+        msgs[1] = nullptr;
+        CHECK(average(m, 2, p) == SBC_EINVAL);
+        msgs[1] = (const char*)kMsg + 4;                  // misaligned
+        CHECK(average(m, 2, p) == SBC_EINVAL);
+        msgs[1] = kMsg;
+        sizes[1] = 31 + 24 * (size_t)m.T();
+        CHECK(average(m, 2, p) == SBC_ECORRUPT);
+        sizes[1] = bound;
+        {
+            Buffers x = m;
+            x.out[4] = nullptr;
+            CHECK(average(x, 2, p) == SBC_EINVAL);
+            x = m; x.out[4] = reinterpret_cast<float*>((uintptr_t)x.out[4] + 2);
+            CHECK(average(x, 2, p) == SBC_EINVAL);
+            x = m; x.numel[4] = 0;
+            CHECK(average(x, 2, p) == SBC_EINVAL);
+        }
+        CHECK(stub_launches() == launched);
+        sbc_destroy(c); c = nullptr;
+
+        // the model; one-chunk tensors up to the context's count; 40 streams of 16 tiles (their shares run
+        // out); one stream beyond 16 tiles; ragged ones on both sides of a block and a chunk
+        const std::vector<std::vector<int64_t>> shapes = {
+            model, std::vector<int64_t>(2000, 64), std::vector<int64_t>(40, 650000), {9000000, 300}, {1}, {2047, 2048, 2049, 8191, 8192, 8193, 70001}};
+        for (const auto& shape : shapes) {
+            const Buffers s = fake_buffers(shape), other = fake_buffers(shape, (uintptr_t)1 << 36);
+            for (int kind = 0; kind < 3; ++kind) {        // full, compact, and created for a sixteenth of the entries
+                const int64_t total = kind == 2 ? s.total() / 16 + 1 : s.total();
+                CHECK((kind == 1 ? sbc_create_compact(&c, 0, total, s.T()) : sbc_create(&c, 0, total, s.T())) == SBC_OK);
+                size_t nb = 0;
+                for (double q : {0.5, 0.2, 0.04, 0.001, 1e-6}) {           // (remainders of 0 to 19 bits)
+                    nb = sbc_msg_bound(s.numel.data(), s.T(), q);
+                    sizes.assign(130, nb);
+                    for (int n_msgs : {1, 2, 64, 130}) CHECK(average(s, n_msgs, q) == SBC_OK);
+                    CHECK(average(other, 3, q) == SBC_OK && average(s, 3, q) == SBC_OK);
+                }
+                // while deferred decodes are outstanding, and while a client step is pending
+                CHECK(sbc_set_option(c, SBC_OPT_DEFER_DECODE_STATUS, 1) == SBC_OK);
+                CHECK(sbc_decompress_accumulate(c, nullptr, kMsg, nb, s.numel.data(), s.T(), 1e-6, 1.f, s.out.data()) == SBC_OK);
+                CHECK(average(s, 2, 1e-6) == SBC_OK && average(s, 2, 0.04) == SBC_OK);
+                CHECK(sbc_set_option(c, SBC_OPT_DEFER_DECODE_STATUS, 0) == SBC_EINVAL);
+                CHECK(sbc_decode_status(c, nullptr) == SBC_OK);
+                if (kind == 0) {
+                    const size_t need = sbc_msg_bound(s.numel.data(), s.T(), p);
+                    CHECK(sbc_compress_begin(c, nullptr, s.dW.data(), s.R.data(), s.numel.data(), s.T(), p, kMsg, need) == SBC_OK);
+                    CHECK(average(s, 2, 0.04) == SBC_OK);
+                    CHECK(sbc_compress_end(c, &nbytes) == SBC_OK);
+                }
+                sbc_destroy(c); c = nullptr;
+                CHECK(stub_live_blocks() == 0);
+            }
+        }
     }
 
     // ---- the server step that allocates nothing ----

@@ -1,5 +1,5 @@
 """The library's host side (argument validation, the plan of a client step, message bounds, the
-sizing of the decode plan, clean-up) built for the CPU alone with AddressSanitizer and
+sizing of the decode plan and of the average's tables, clean-up) built for the CPU alone with AddressSanitizer and
 UndefinedBehaviorSanitizer, the HIP runtime replaced by a stand-in whose "device" memory is heap
 blocks of the requested sizes, and driven through the C ABI by a small program.  No GPU."""
 import os
