@@ -2,6 +2,8 @@
 (b from 0 to 19), with streams just below, at and above whole tiles of 512 segments, one workgroup
 and the tile kernels, and with sub-normal accumulators and addends (the update is an fp32 addition
 that rounds once and flushes nothing)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -52,10 +54,39 @@ def test_every_state_function_width_at_tile_edges(p):
         sbc.sbc_destroy(ctx)
 
 
+def test_into_pinned_host_memory():
+    """The accumulator may be any memory the device can read and write."""
+    sizes, p = [20000, 64, 8193, 300000], 0.01
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        dW = [torch.from_numpy(x).to(DEV) for x in synth.small_model_update(sizes)]
+        R = [torch.zeros(n, dtype=torch.float32, device=DEV) for n in sizes]
+        msg = torch.zeros(sbc.sbc_msg_bound(sizes, p), dtype=torch.uint8, device=DEV)
+        nbytes = sbc.sbc_compress(ctx, dW, R, p, msg)
+        want = [torch.full((n,), 0.5, dtype=torch.float32, device=DEV) for n in sizes]
+        sbc.sbc_decompress_accumulate(ctx, msg, nbytes, p, 0.25, want)
+        status = torch.full((1,), -9, dtype=torch.int32, device=DEV)
+        lib, vp = sbc.load(), ctypes.c_void_p
+        for call in ("context", "no allocation"):
+            host = [torch.full((n,), 0.5, dtype=torch.float32, pin_memory=True) for n in sizes]
+            numel = (ctypes.c_int64 * len(sizes))(*sizes)
+            out = (vp * len(sizes))(*[h.data_ptr() for h in host])
+            if call == "context":
+                rc = lib.sbc_decompress_accumulate(ctx, None, vp(msg.data_ptr()), nbytes, numel, len(sizes), p, 0.25, out)
+            else:
+                rc = lib.sbc_decompress_accumulate_noalloc(0, None, vp(msg.data_ptr()), nbytes, numel, len(sizes), p, 0.25,
+                                                           out, vp(status.data_ptr()))
+            torch.cuda.synchronize()
+            assert rc == sbc.SBC_OK and all(torch.equal(h, w.cpu()) for h, w in zip(host, want)), call
+        assert int(status[0]) == sbc.SBC_OK
+    finally:
+        sbc.sbc_destroy(ctx)
+
+
 @pytest.mark.parametrize("at", [0, 17, 34])
 def test_more_long_streams_than_the_tile_kernels_take(at):
-    """34 streams of two or three tiles and one of 13, the longest anywhere in the list: the same bits as from
-    the context-free call, which gives every stream one workgroup."""
+    """34 streams of two or three tiles and one several times as long anywhere in the list: the same bits as
+    from the context-free call, which gives every stream one workgroup."""
     sizes, p = [70_001] * 20 + [110_003] * 14, 0.2
     sizes.insert(at, 640_001)
     ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
