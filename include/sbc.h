@@ -128,7 +128,7 @@ size_t sbc_msg_bound_sampled(const int64_t* numel, int n_tensors, double p);
  *                                                    variant with a noisy count)
  *     residual_t <- A_t - dW*_t                     (in place)
  *     msg   <- container of { mu_signed_t, Golomb(kept positions of t) }
- * dW[t]        device, read only, numel[t] floats, 4-byte aligned (16 is faster)
+ * dW[t]        device, read only, numel[t] floats, 4-byte aligned (with SBC_OPT_FUSED_STEP 16 is faster)
  * residual[t]  device, read/write, numel[t] floats, must not overlap dW[t]
  * numel        host array
  * msg          device, 8-byte aligned, msg_capacity >= sbc_msg_bound(...) bytes; bytes past
@@ -228,8 +228,9 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream,
  *   SBC_OPT_WIDE_MIN_KEPT      (default 0 = 8192)  a tensor that keeps at least this many entries
  *       per side has its candidate lists narrowed down by many workgroups before one workgroup
  *       per side selects among the rest, and its stream is decoded tile by tile by many workgroups
- *       instead of one (a 1.5e9-entry tensor at p = 0.001 keeps 1.5e6); tests lower it to send
- *       small tensors that way, or raise it.
+ *       instead of one (a 1.5e9-entry tensor at p = 0.001 keeps 1.5e6), and with it those of the
+ *       call's other tensors that are longer than a tile; the 32 longest of a call.  Tests lower it
+ *       to send small tensors that way, or raise it.
  *   SBC_OPT_SAMPLED_THRESHOLD  (0/1, default 0)  1 selects the subsampled variant of
  *       "Sparse Binarization" (the threshold is estimated from a random subsample, which makes
  *       the amount of sparsity noisy).  Per tensor t of the call a stratified sample of at most
@@ -247,7 +248,7 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream,
  *   SBC_OPT_FUSED_STEP         (0/1, default 0)  1 lets the streaming kernel finish, by itself, every
  *       tensor that keeps few enough entries for one workgroup (Alg. 2 and Alg. 3 run in the last
  *       workgroup of the tensor to finish streaming, beside the streaming of the other tensors)
- *       instead of leaving all of them to the selection kernel that follows.  Same results.
+ *       instead of leaving all of them to the kernels that follow.  Same results.
  *   SBC_OPT_DEFER_DECODE_STATUS (0/1, default 0)  1 makes sbc_decompress_accumulate return as
  *       soon as its kernels are enqueued (SBC_OK unless an argument is bad), so that a server can
  *       decode the messages of all clients back to back without waiting for each; validation
@@ -258,8 +259,9 @@ enum { SBC_OPT_FORCE_EXACT_PATH = 1, SBC_OPT_CARRY_FILTER_KEYS = 2, SBC_OPT_WIDE
        SBC_OPT_SAMPLED_THRESHOLD = 4, SBC_OPT_DEFER_DECODE_STATUS = 5, SBC_OPT_FUSED_STEP = 6 };
 int sbc_set_option(sbc_ctx* ctx, int option, int value);
 
-/* With SBC_OPT_DEFER_DECODE_STATUS: waits for hip_stream (the stream the deferred
- * sbc_decompress_accumulate calls were enqueued on) and returns SBC_OK if every such call since
+/* With SBC_OPT_DEFER_DECODE_STATUS: waits until hip_stream (the stream the deferred
+ * sbc_decompress_accumulate calls were enqueued on) has passed those calls and their status is known
+ * (completion as for sbc_compress), and returns SBC_OK if every such call since
  * the previous sbc_decode_status passed validation, else the error (SBC_ECORRUPT, SBC_EHIP); the
  * collected status starts afresh.  SBC_OK at once if nothing is outstanding. */
 int sbc_decode_status(sbc_ctx* ctx, void* hip_stream);
@@ -272,7 +274,7 @@ int sbc_decode_status(sbc_ctx* ctx, void* hip_stream);
 enum { SBC_ROUTE_CARRIED_KEYS = 1, SBC_ROUTE_HISTOGRAM = 2, SBC_ROUTE_WIDE = 4,
        SBC_ROUTE_LOOSE_KEYS = 8,    /* some filter key let so many entries pass that the next call samples afresh */
        SBC_ROUTE_TAKEN_OVER = 16 }; /* a tensor the streaming kernel could not finish was completed by the
-                                       one-workgroup selection kernel in a second pass */
+                                       kernels that follow it in a second pass */
 int sbc_last_route(sbc_ctx* ctx);
 
 /* Inspection of the most recent sbc_compress() on this context, for tests and reports

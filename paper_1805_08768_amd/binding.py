@@ -322,7 +322,7 @@ def sbc_decompress_accumulate_noalloc(msg: torch.Tensor, msg_bytes: int, p: floa
 
 
 def sbc_decode_status(ctx, stream=None) -> None:
-    """With SBC_OPT_DEFER_DECODE_STATUS: waits for the stream and raises if any deferred
+    """With SBC_OPT_DEFER_DECODE_STATUS: waits for the status of, and raises if any, deferred
     sbc_decompress_accumulate call since the previous check failed validation."""
     rc = load().sbc_decode_status(ctx, _stream_handle(stream))
     if rc != SBC_OK:

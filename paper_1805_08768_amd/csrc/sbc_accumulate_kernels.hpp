@@ -392,11 +392,6 @@ __device__ __forceinline__ float value_of_key(uint32_t key) {
     return key < 0x00800000u ? -__builtin_inff() : __uint_as_float(bits_of_key(key));     // (below -inf's: all; above +inf's: NaN, none)
 }
 
-// 16 bytes at any 4-byte aligned address (multi-dword accesses to global memory need no more)
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
-typedef const SBC_GLOBAL_AS f32x4_any* gcf32x4_any_ptr;
-
 // What goes past the last-level cache, with the nontemporal hint (the rule is in accumulate_past_cache):
 constexpr int kPastNothing = 0, kPastUpdate = 1, kPastAll = 2;     // (kPastAll: update loaded, residual loaded and stored)
 template <int PAST>

@@ -134,8 +134,6 @@ __global__ __launch_bounds__(kDecThreads) void k_average_decode(
 __global__ __launch_bounds__(256) void k_average_clear(const uint2* __restrict__ chunk_tensor, const AvgTensor* __restrict__ tensors,
                                                        ResultBlock* __restrict__ block) {
     if (block && blockIdx.x == 0 && threadIdx.x == 0) { block->err = 0u; block->pad = 0u; block->msg_bytes = 0ull; }
-    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-    typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
     const uint2 ct = chunk_tensor[blockIdx.x];             // (tensor, its first chunk)
     const AvgTensor a = tensors[ct.x];
     const uint32_t e0 = (blockIdx.x - ct.y) * (uint32_t)kChunk, cnt = min((uint32_t)kChunk, a.n - e0);
@@ -172,8 +170,6 @@ __global__ __launch_bounds__(kEncThreads) void k_average_apply(
     float* const acc = acc_sh[wave];
     uint32_t* const tag = tag_sh[wave];
     const gfloat_ptr out = as_global(a.out + e0);
-    typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-    typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
     // lane m: the entries of message m, s, s + 1, ... of its list
     uint32_t s = 0u, k = 0u;
     float addend = 0.f;

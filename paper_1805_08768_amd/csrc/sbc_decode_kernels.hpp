@@ -53,7 +53,7 @@ constexpr int kMaxWideDec = 32;               // streams per call that the tile 
 struct DecWides { DecWide w[kMaxWideDec]; int count; };      // (a kernel argument)
 struct NoWides {};                            // (of a call that has none)
 
-__device__ __forceinline__ void add_to(float* p, float v) {
+__device__ __forceinline__ void add_to(gfloat_ptr p, float v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -396,7 +396,7 @@ __device__ __forceinline__ void decode_stream(DecShared<D>& sh, const uint8_t* _
     }
     if (si.nnz == 0u) return;
     const float addend = scale * si.mu;
-    float* const out = blk.out;
+    const gfloat_ptr out = as_global(blk.out);
     bool bad = false;
     const bool mine = (uint32_t)wave % blk.shares == blk.share;
     decode_codes<D, kDecWaves>(sh, si, blk.n, b, si.n_seg, [&](uint32_t) { return mine; }, bad, [&](CodeWalk& w, bool active, uint32_t) {
@@ -752,7 +752,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_generic(const uint8_t* _
                 R += read_bits(tile, (uint32_t)(tid * 64 + z + 1), b);
                 const unsigned long long pos = (U << b) + R + Tn;
                 if (pos >= blk.n || Tn >= si.nnz) { bad = true; break; }
-                add_to(blk.out + pos, addend);
+                add_to(as_global(blk.out) + pos, addend);
                 ++Tn;
                 x = z + b + 1;
             }

@@ -39,6 +39,10 @@ typedef SBC_GLOBAL_AS f32x4* gf32x4_ptr;
 typedef const SBC_GLOBAL_AS f32x4* gcf32x4_ptr;
 __device__ __forceinline__ gfloat_ptr as_global(float* p) { return (gfloat_ptr)p; }
 __device__ __forceinline__ gcfloat_ptr as_global(const float* p) { return (gcfloat_ptr)p; }
+// 16 bytes at any 4-byte aligned address (multi-dword accesses to global memory need no more)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
+typedef const SBC_GLOBAL_AS f32x4_any* gcf32x4_any_ptr;
 
 // ---------------------------------------------------------------- layout ----
 
@@ -174,18 +178,6 @@ __device__ __forceinline__ uint32_t key_of_bits(uint32_t u) {
 }
 __device__ __forceinline__ uint32_t bits_of_key(uint32_t key) {
     return (key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key;
-}
-
-// Filter keys a following call may start from instead of sampling: this call's exact threshold,
-// lowered by a margin that shrinks with k (the k-th order statistic of similar data moves by
-// about 1/sqrt(k) of the tail's scale from round to round).  Only a filter: a tensor it
-// misleads is noticed and redone through the histogram route.
-__device__ __forceinline__ uint32_t carried_key(uint32_t tau_side_key, uint32_t k) {
-    const float margin = fminf(0.25f, fmaxf(0.04f, 3.0f * rsqrtf((float)k)));
-    const float x = __uint_as_float(bits_of_key(tau_side_key));       // how extreme the k-th entry is
-    const float lo_x = x - margin * fabsf(x) - 1.17549435e-38f;
-    const uint32_t lo = key_of_bits(__float_as_uint(lo_x));
-    return lo > tau_side_key ? tau_side_key : lo;
 }
 
 // Rank of the entry whose key a following call starts from (see k_threshold): the k entries kept now
@@ -376,27 +368,9 @@ __device__ __forceinline__ void find_from_top(const uint32_t* hist, uint32_t nee
     __syncthreads();
 }
 
-// Histogram update that first adds up runs of equal bins in a register: the leading bytes of
-// floating-point keys take very few distinct values, and same-address LDS atomics serialize.
-struct RunCounter {
-    uint32_t bin = 0xFFFFFFFFu;
-    uint32_t cnt = 0u;
-    __device__ __forceinline__ void add(uint32_t* hist, uint32_t b) {
-        if (b != bin) {
-            if (cnt) atomicAdd(&hist[bin], cnt);
-            bin = b; cnt = 0u;
-        }
-        ++cnt;
-    }
-    __device__ __forceinline__ void flush(uint32_t* hist) {
-        if (cnt) atomicAdd(&hist[bin], cnt);
-        cnt = 0u; bin = 0xFFFFFFFFu;
-    }
-};
-
 // ------------------------------------------- byte-wise select, two at once ----
 //
-// The select and sample kernels look for the need-th largest 32-bit value of two independent
+// The sample kernel looks for the need-th largest 32-bit value of two independent
 // collections (one per sign side) by fixing one byte per pass, most significant first.  For
 // each pass the caller has filled hist[s][0..255] (LDS) with the counts of byte values among
 // the entries of collection s that match the bytes fixed so far.  pick_byte_both finds, for

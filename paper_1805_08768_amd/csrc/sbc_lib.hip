@@ -77,7 +77,7 @@ struct sbc_ctx {
     TileSummary* d_tile = nullptr;        // per tile of kScanTile chunks of a tensor
     ResultBlock* d_result = nullptr;      // two for compress, two for decode, used in turn; [4] collects the
                                           // errors of decode calls whose status is deferred, [5] is a spare
-    // grid-wide selection
+    // sweeps over long lists
     WideState* d_wide_state = nullptr;
     uint32_t* d_wide_hist = nullptr;
     long long* d_wide_acc = nullptr;
@@ -961,7 +961,6 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
     c->last_used_exact_path = false;
     c->last_used_wide = (err & kErrWide) != 0u;
 
-    // ---- histogram path for the tensors whose filter kept fewer than k candidates ----
     // ---- second pass: the histogram route for the tensors whose filter kept fewer than k candidates,
     // and the selection for the tensors the streaming kernel left to it ----
     const uint32_t loose = err & (kErrLoose | kErrStaleKeys);

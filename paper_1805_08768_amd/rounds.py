@@ -37,8 +37,7 @@ class TensorViews(list):
 
 def flat_buffer(sizes: Sequence[int], device: str):
     """One zeroed fp32 allocation holding a tensor of every size, each at a 256-byte aligned
-    offset (the streaming kernel takes 16-byte loads only from 16-byte aligned chunks), and
-    the per-tensor views (a TensorViews list)."""
+    offset (no two tensors share a cache line), and the per-tensor views (a TensorViews list)."""
     offsets, total = [], 0
     for n in sizes:
         offsets.append(total)

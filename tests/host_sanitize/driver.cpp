@@ -196,7 +196,7 @@ int main(int argc, char** argv) {
     CHECK(stub_live_blocks() == 0);
 
     // ---- shapes at the edges: one entry; a tensor of thousands of chunks; more tensors that keep
-    // very many entries than the grid-wide kernels and the tiled decoder take; many tiny tensors ----
+    // very many entries than the sweeps and the tiled decoder take; many tiny tensors ----
     {
         const std::vector<std::vector<int64_t>> shapes = {
             {1}, {8192}, {8193}, {64000000, 5}, std::vector<int64_t>(70, 70000), std::vector<int64_t>(3000, 7)};

@@ -402,7 +402,7 @@ def test_error_paths(tiled_decode):
     sizes = [5000, 64]
     dWs = synth.small_model_update(sizes)
     with DeviceRun(sizes) as run:
-        if tiled_decode:       # tensor 0 goes through the grid-wide selection and the tile decoder
+        if tiled_decode:       # tensor 0 goes through the sweeps over long lists and the tile decoder
             sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WIDE_MIN_KEPT, 10)
         d_dW = [torch.from_numpy(x).cuda() for x in dWs]
         bound = sbc.sbc_msg_bound(sizes, 0.01)
@@ -512,9 +512,9 @@ def _planted_threshold_ties(n, k, seed_tensor):
 
 
 def test_grid_wide_selection():
-    """Tensors that keep many entries take the grid-wide selection kernels (threshold lowered by
-    option so that the oracle finishes in seconds): plain data, thresholds inside groups of
-    equal values, and tie-heavy data that those kernels hand back to the one-workgroup kernel."""
+    """The lists of tensors that keep many entries are narrowed down by sweeps of many workgroups
+    (threshold lowered by option so that the oracle finishes in seconds): plain data, thresholds inside
+    groups of equal values, and tie-heavy data, which the sweeps leave to k_threshold."""
     sizes = [100000, 300, 65536, 9000]
     p = 0.1
     for carry in (0, 1):
@@ -526,7 +526,7 @@ def test_grid_wide_selection():
                 dWs = [synth.gaussian_update(n, round_=r, tensor=i) for i, n in enumerate(sizes)]
                 res = check_round(run, dWs, R, p)
                 # (with keys carried over from a round whose thresholds were much lower, the k-th entry
-                # may lie beyond the window those kernels count in: they then hand the tensor back)
+                # may lie beyond the window the sweeps count in: k_threshold then takes the whole list)
                 assert carry and r > 0 or sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_WIDE
                 R = [x.R_new for x in res]
     sizes = [200000, 80000]
@@ -542,9 +542,8 @@ def test_grid_wide_selection():
 
 
 def test_grid_wide_selection_four_rounds_at_the_default_threshold():
-    """The 2^20-entry Gaussian tensor of configuration 1 (10485 kept entries: grid-wide kernels at
-    the default threshold) over four rounds with the residual carried, alone (no other selection
-    kernel runs in the call) and with a small tensor beside it."""
+    """The 2^20-entry Gaussian tensor of configuration 1 (10485 kept entries: sweeps at the default
+    threshold) over four rounds with the residual carried, alone and with a small tensor beside it."""
     p = 0.01
     for sizes in ([1 << 20], [1 << 20, 5000]):
         with DeviceRun(sizes) as run:
@@ -558,9 +557,9 @@ def test_grid_wide_selection_four_rounds_at_the_default_threshold():
 
 
 def test_calls_of_grid_wide_tensors_only_that_need_the_second_pass():
-    """A call whose tensors all take the grid-wide kernels runs no other selection kernel unless one
-    of them cannot be finished there: a misleading sample (too few candidates: histogram route),
-    and tie-heavy data (more equal entries at the threshold than those kernels rank: one workgroup)."""
+    """Calls all of whose tensors have sweeps over their lists, and data those cannot narrow down: a
+    misleading sample (too few candidates: histogram route in a second pass), and tie-heavy data (more
+    equal entries at the threshold than there is room to copy: k_threshold on the whole list)."""
     n = 400000
     x = (np.abs(synth.small_model_update([n], round_=4)[0]) * 1e-3).astype(np.float32)
     pos = sampled_positions(n, 0)
@@ -582,10 +581,9 @@ def test_calls_of_grid_wide_tensors_only_that_need_the_second_pass():
 
 def test_histogram_fallback_bitmap_and_grid_wide_tensors_in_one_call():
     """One call whose tensors take every route at once: tensor 0 keeps enough entries for the
-    grid-wide kernels; tensor 1 keeps too many for the fused encoder and too few for those (one
-    workgroup selects, positions go through the bitmap); tensor 2 has its large entries exactly
-    where the sampler looks, so its filter keeps too few and the histogram route redoes it; tensor
-    3 keeps more than the lists staged in LDS hold and is sorted and encoded by one workgroup."""
+    sweeps; tensors 1 and 3 keep fewer, with lists beyond and around what k_threshold stages in LDS;
+    tensor 2 has its large entries exactly where the sampler looks, so its filter keeps too few and the
+    histogram route redoes it; tensor 4 has one chunk."""
     sizes = [250000, 170000, 50000, 100000, 300]
     p = 0.1
     with DeviceRun(sizes) as run:
@@ -606,9 +604,9 @@ def test_histogram_fallback_bitmap_and_grid_wide_tensors_in_one_call():
 
 
 def test_more_wide_tensors_than_the_grid_wide_kernels_take():
-    """70 tensors that each qualify for the grid-wide selection and for the tiled decoder: the
-    selection takes 64 and hands the rest to the one-workgroup kernel, the decoder tiles 16 streams
-    and leaves the rest to the one-workgroup decoder."""
+    """70 tensors that each qualify for the sweeps and for the tiled decoder: 64 have sweeps, the rest
+    goes to k_threshold as it is; the decoder tiles the 32 longest streams and leaves the rest to one
+    workgroup each."""
     sizes = [70000 + 8 * i for i in range(70)]
     p = 0.1
     with DeviceRun(sizes) as run:

@@ -1,8 +1,8 @@
 """Randomly drawn parity cases: tensor sizes, sparsity, data family, route thresholds and context
 kind are drawn from a seeded generator; every round is compared with the oracle to the bar of
 tests/test_gpu_parity.py (message bytes, mask and bitstream bit-exact).  The draw favours the
-grid-wide selection kernels and the bitmap encoder, whose hand-backs and second passes depend on
-where thresholds and ties happen to fall."""
+sweeps over long lists and tie-heavy data, whose second passes depend on where thresholds and ties
+happen to fall."""
 import numpy as np
 import pytest
 

@@ -75,9 +75,9 @@ def test_sampled_bitmap_and_grid_wide_routes():
     gen = lambda r: [synth.gaussian_update(n, round_=r, tensor=i) for i, n in enumerate(sizes)]
     _, routes = run_rounds(sizes, gen, 0.1, rounds=2, wide_min_kept=1 << 30)     # one workgroup per tensor
     assert not any(rt & sbc.SBC_ROUTE_WIDE for rt in routes)
-    _, routes = run_rounds(sizes, gen, 0.1, rounds=2, wide_min_kept=6500)        # grid-wide kernels
+    _, routes = run_rounds(sizes, gen, 0.1, rounds=2, wide_min_kept=6500)        # sweeps first
     assert all(rt & sbc.SBC_ROUTE_WIDE for rt in routes)
-    # ties beyond the cap on a tensor of the grid-wide route
+    # ties beyond the cap on a tensor with sweeps
     sizes = [200000, 70000]
     dWs = [synth.palette_update(200000), synth.palette_update(70000, tensor=1)]
     run_rounds(sizes, lambda r: dWs, 0.1, rounds=2, wide_min_kept=6500)
