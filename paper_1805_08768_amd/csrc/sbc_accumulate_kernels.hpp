@@ -42,17 +42,10 @@ __global__ __launch_bounds__(256) void k_zero_words(uint32_t* __restrict__ p, ui
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
 }
 
-// The result block of a server call, copied to pinned host memory by a dispatch of its own behind
-// the decode kernels (the runtime's own device-to-host copy of 16 bytes and its wait for the
-// stream take longer); the sequence number goes out last, so that a host that looks for it finds
-// the status in place.
-__global__ void k_publish(ResultBlock* __restrict__ host_dst, const ResultBlock* __restrict__ src, uint32_t seq) {
-    if (threadIdx.x == 0) {
-        host_dst->msg_bytes = src->msg_bytes;
-        host_dst->err = src->err;
-        __threadfence_system();
-        __hip_atomic_store(&host_dst->pad, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+// The status of a server call, sent to pinned host memory by a dispatch of its own behind the decode
+// kernels (the runtime's own device-to-host copy and its wait for the stream take longer).
+__global__ void k_publish(unsigned long long* __restrict__ host_word, const ResultBlock* __restrict__ src, uint32_t seq) {
+    if (threadIdx.x == 0) publish(host_word, seq, src->err, 0ull);
 }
 
 __device__ __forceinline__ uint32_t mix32(uint32_t x) {
@@ -108,7 +101,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
         z.tau[0] = z.tau[1] = 0u;
         z.itau[0] = z.itau[1] = 0u;
         z.kc[0] = z.kc[1] = 0u;
-        z.S[0] = z.S[1] = 0.0;
+        z.S[0] = z.S[1] = 0.0; z.mean[0] = z.mean[1] = 0.0;
         z.side = 0; z.mu_signed = 0.f; z.nnz = 0u; z.flags = 0u; z.bit_len = 0ull;
         z.done = 0u; z.sorted_kept = 0u; z.cand_seen[0] = z.cand_seen[1] = 0u; z.expect[0] = z.expect[1] = 0u;
         st[t] = z;

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <numeric>
 #include <vector>
@@ -72,7 +73,8 @@ struct sbc_ctx {
     uint32_t* d_stage = nullptr;
     uint32_t* d_kept = nullptr;
     ChunkSummary* d_sum = nullptr;
-    uint32_t* d_prev_end = nullptr;
+    uint32_t* d_head = nullptr;           // per chunk whose codes do not fit its words: the first word of them
+    uint32_t* d_gap = nullptr;            // per chunk: gap before its first kept entry (calls of very many chunks)
     uint64_t* d_bitoff = nullptr;
     TileSummary* d_tile = nullptr;        // per tile of kScanTile chunks of a tensor
     ResultBlock* d_result = nullptr;      // two for compress, two for decode, used in turn; [4] collects the
@@ -110,11 +112,11 @@ struct sbc_ctx {
     uint32_t* h_order = nullptr;
     WideIds wide_ids = {};
     int max_wide = 0;
-    ResultBlock* h_result_dev = nullptr;  // h_result as the device addresses it
-    ResultBlock* h_result = nullptr;      // compress
-    uint32_t result_seq = 0;              // number of the latest launch of the message-assembly kernel
-    ResultBlock* h_result_dec = nullptr;  // decode (its own block: a decode call may come between begin and end)
-    ResultBlock* h_result_dec_dev = nullptr;
+    unsigned long long* h_result = nullptr;       // compress: see publish
+    unsigned long long* h_result_dev = nullptr;   // ... as the device addresses it
+    uint32_t result_seq = 0;              // number of the latest launch of the kernel that completes the message
+    unsigned long long* h_result_dec = nullptr;   // decode (its own: a decode call may come between begin and end)
+    unsigned long long* h_result_dec_dev = nullptr;
     uint32_t dec_seq = 0;
     DecBlock* h_dec_blocks = nullptr;
     uint32_t n_dec_blocks = 0;
@@ -195,7 +197,7 @@ struct sbc_ctx {
     } pend;
 
     // last compress call, for the inspection entry points
-    int last_T = 0;
+    int last_T = 0, last_b = 0;
     bool last_ok = false;
     bool last_used_exact_path = false;
     bool last_used_history = false;
@@ -252,7 +254,7 @@ hipError_t host_alloc(T** p, size_t count) { return hipHostMalloc(reinterpret_ca
 void free_all(sbc_ctx* c) {
     (void)hipFree(c->d_desc); (void)hipFree(c->d_chunk_tensor); (void)hipFree(c->d_sched); (void)hipFree(c->d_group); (void)hipFree(c->d_order); (void)hipFree(c->d_hist);
     (void)hipFree(c->d_state); (void)hipFree(c->d_cand); (void)hipFree(c->d_bitmap); (void)hipFree(c->d_stage);
-    (void)hipFree(c->d_kept); (void)hipFree(c->d_sum); (void)hipFree(c->d_prev_end); (void)hipFree(c->d_bitoff); (void)hipFree(c->d_tile);
+    (void)hipFree(c->d_kept); (void)hipFree(c->d_sum); (void)hipFree(c->d_head); (void)hipFree(c->d_gap); (void)hipFree(c->d_bitoff); (void)hipFree(c->d_tile);
     (void)hipFree(c->d_result); (void)hipFree(c->d_dec_blocks);
     if (c->h_dec_blocks) (void)hipHostFree(c->h_dec_blocks);
     (void)hipFree(c->d_seg_pack); (void)hipFree(c->d_tile_fn); (void)hipFree(c->d_tile_sum);
@@ -331,21 +333,35 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
                        c->d_wide_hist, c->d_wide_acc, pass, P.carry, c->staged_keys, P.res_now);
         const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
         SBC_LAUNCH(kStApply, profile, k_apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
-                   c->d_cand, c->cand_entries, c->d_bitmap, c->d_sum, c->d_stage, b, pass, P.n_chunks, P.res_now);
-        if (P.chunks_max <= kSelfScanChunks) {
-            // no tensor of many chunks: the wavefronts that write the codes scan the few summaries before
-            // their chunk themselves, one launch less
-            SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_bitmap, c->d_sum,
-                       c->d_prev_end, c->d_bitoff, c->d_state, c->d_state, b, pass, c->d_stage, P.n_chunks, P.res_now);
-        } else {
-            if (P.scan_tiles > 1)
-                hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_state,
-                                   c->d_sum, c->d_tile, b, pass);
-            SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
-                       c->d_tile, c->d_prev_end, c->d_bitoff, c->d_state, b, pass);
-            SBC_LAUNCH(kStEmit, profile, k_emit<false>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_bitmap, c->d_sum,
-                       c->d_prev_end, c->d_bitoff, c->d_state, c->d_state, b, pass, c->d_stage, P.n_chunks, P.res_now);
+                   c->d_cand, c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, pass, P.n_chunks, P.res_now);
+        if (!c->fused_step && P.n_chunks <= kEmitAllChunks) {
+            // the workgroups that write the codes scan the summaries of all chunks themselves, one launch less.  (Two
+            // sizes: few chunks want many small workgroups, the scan over many wants large ones.)
+            const size_t lds = 2u * sizeof(uint32_t) * P.n_chunks;
+            if (P.n_chunks <= kEmitFew)
+                SBC_LAUNCH_LDS(kStEmit, profile, k_emit_all<256>, dim3((P.n_chunks + 3u) / 4u), dim3(256), lds, c->d_chunk_tensor,
+                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                               P.res_next, c->h_result_dev, ++c->result_seq);
+            else
+                SBC_LAUNCH_LDS(kStEmit, profile, k_emit_all<1024>, dim3((P.n_chunks + 15u) / 16u), dim3(1024), lds, c->d_chunk_tensor,
+                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                               P.res_next, c->h_result_dev, ++c->result_seq);
+            return;
         }
+        if (P.scan_tiles > 1)
+            hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_state,
+                               c->d_sum, c->d_tile, b, pass);
+        SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
+                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, pass);
+        if (!c->fused_step) {
+            SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
+                       c->d_gap, c->d_bitoff, c->d_state, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                       P.res_next, c->h_result_dev, ++c->result_seq);
+            return;
+        }
+        SBC_LAUNCH(kStEmit, profile, k_emit<false>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
+                   c->d_gap, c->d_bitoff, c->d_state, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                   P.res_next, c->h_result_dev, 0u);
     }
     SBC_LAUNCH(kStGather, profile, k_finish_message, dim3(T, P.gather_y), dim3(256), P.d_desc, c->d_state, T, b,
                c->d_stage, c->d_kept, c->d_group, P.msg8, (uint64_t)P.msg_capacity, P.res_now, P.res_next,
@@ -357,7 +373,7 @@ int enqueue_result_copy(sbc_ctx* c) {
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
     // In the begin/end form an event lets the wait end when this step is done, whatever the caller
     // has enqueued behind it; the one-call form waits for the stream, which is cheaper.
-    // (k_finish_message has written the result block to pinned host memory)
+    // (the step's last kernel sends the result to pinned host memory itself)
     if (hipGetLastError() != hipSuccess ||
         (c->pend.wait_on_event && hipEventRecord(c->ev_result, c->pend.stream) != hipSuccess)) {
         (void)hipGetLastError();
@@ -366,18 +382,22 @@ int enqueue_result_copy(sbc_ctx* c) {
     return SBC_OK;
 }
 
-// Looks for sequence number `want` in a result block in pinned host memory for up to 0.3 ms.
-bool result_arrived(const ResultBlock* block, uint32_t want) {
+// The call's result in pinned host memory (see publish).
+uint32_t result_seq_of(unsigned long long w) { return (uint32_t)(w >> 50); }
+uint32_t result_err_of(unsigned long long w) { return (uint32_t)(w >> 40) & 0x3FFu; }
+uint64_t result_bytes_of(unsigned long long w) { return w & ((1ull << 40) - 1ull); }
+
+// Looks for sequence number `want` there for up to 0.3 ms.
+bool result_arrived(const unsigned long long* word, uint32_t want) {
     const auto t0 = std::chrono::steady_clock::now();
     for (int spin = 0;; ++spin) {
-        if (__atomic_load_n(&block->pad, __ATOMIC_ACQUIRE) == want) return true;
+        if (result_seq_of(__atomic_load_n(word, __ATOMIC_ACQUIRE)) == (want & kSeqMask)) return true;
         if ((spin & 63) == 63 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(300)) return false;
     }
 }
 
 int wait_result(sbc_ctx* c) {
-    // The message-assembly kernel writes the result block to pinned host memory and its sequence
-    // number last.  Looking for the number takes a microsecond or two once it is there, where the
+    // The kernel that completes the message sends the result to pinned host memory.  Looking for the number takes a microsecond or two once it is there, where the
     // runtime's wait returns several microseconds after the stream has drained; calls that run
     // longer than a fraction of a millisecond fall through to the runtime's wait.  (Not while
     // kernels carry timing events: those are read right after this, and must be complete.)
@@ -529,7 +549,8 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_stage, (size_t)c->stage_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_kept, (size_t)c->kept_cap) == hipSuccess;
     ok = ok && dev_alloc(&c->d_sum, (size_t)c->max_chunks) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_prev_end, (size_t)c->max_chunks) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_head, (size_t)c->max_chunks) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_gap, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_bitoff, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile, (size_t)(c->max_chunks / kScanTile) + T + 1) == hipSuccess;
     ok = ok && dev_alloc(&c->d_result, 6) == hipSuccess;
@@ -557,11 +578,11 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && host_alloc(&c->h_order, T) == hipSuccess;
     ok = ok && host_alloc(&c->h_result, 1) == hipSuccess;
     ok = ok && hipHostGetDevicePointer(reinterpret_cast<void**>(&c->h_result_dev), c->h_result, 0) == hipSuccess;
-    // (a pinned block may come back from an earlier context with that context's sequence number in it)
-    if (ok) std::memset(c->h_result, 0, sizeof(ResultBlock));
+    // (pinned memory may come back from an earlier context with that context's sequence number in it)
+    if (ok) *c->h_result = 0ull;
     ok = ok && host_alloc(&c->h_result_dec, 1) == hipSuccess;
     ok = ok && hipHostGetDevicePointer(reinterpret_cast<void**>(&c->h_result_dec_dev), c->h_result_dec, 0) == hipSuccess;
-    if (ok) std::memset(c->h_result_dec, 0, sizeof(ResultBlock));
+    if (ok) *c->h_result_dec = 0ull;
     ok = ok && host_alloc(&c->h_state, T) == hipSuccess;
     if (ok) {
         int made = 0;
@@ -947,6 +968,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
     c->cache_valid = true;
     if (P.slot_is_new) c->slot[P.slot].valid = true;
     c->last_T = T;
+    c->last_b = P.b;
     c->last_stream = stream;
     for (int st = 0; st < kNumStages; ++st) {
         if (!P.timed[st]) continue;
@@ -958,7 +980,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
             (void)hipGetLastError();
         }
     }
-    uint32_t err = c->h_result->err;
+    uint32_t err = result_err_of(*c->h_result);
     c->last_used_exact_path = false;
     c->last_used_wide = (err & kErrWide) != 0u;
 
@@ -984,13 +1006,14 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
         rc = enqueue_result_copy(c);
         if (rc == SBC_OK) rc = wait_result(c);
         if (rc != SBC_OK) return rc;
-        err = c->h_result->err | loose;
+        err = result_err_of(*c->h_result) | loose;
         if (err & (kErrPrefilter | kErrDeferred)) return SBC_EINTERNAL;
     }
     const int status = status_of_err(err);
     if (status != SBC_OK) return status;
-    if (c->h_result->msg_bytes > P.need) return SBC_EINTERNAL;
-    *msg_bytes = (size_t)c->h_result->msg_bytes;
+    const uint64_t bytes = result_bytes_of(*c->h_result);
+    if (bytes > P.need) return SBC_EINTERNAL;
+    *msg_bytes = (size_t)bytes;
     c->last_ok = true;
     c->last_used_history = P.use_history;
     c->last_loose = (err & kErrLoose) != 0u;
@@ -1184,8 +1207,9 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
     }
     SBC_HOST_TS(11);
     c->dev_dec_valid = true;
-    if (c->h_result_dec->err == 0u) c->dec_result_dirty = false;
-    return status_of_err(c->h_result_dec->err);
+    const uint32_t err = result_err_of(*c->h_result_dec);
+    if (err == 0u) c->dec_result_dirty = false;
+    return status_of_err(err);
 }
 
 // out <- the sum of the messages, one after another: the general way of sbc_decompress_average.
@@ -1321,7 +1345,7 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         (void)hipGetLastError();
         return SBC_EHIP;
     }
-    const uint32_t err = c->h_result_dec->err;
+    const uint32_t err = result_err_of(*c->h_result_dec);
     if (err == 0u) c->dec_result_dirty = false;
     if ((err & kErrDeferred) && !(err & kErrCorrupt))     // a stream of more positions than there is room for
         return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);
@@ -1341,7 +1365,7 @@ int sbc_decode_status(sbc_ctx* c, void* hip_stream) {
         (void)hipGetLastError();
         return SBC_EHIP;
     }
-    return status_of_err(c->h_result_dec->err);
+    return status_of_err(result_err_of(*c->h_result_dec));
 }
 
 int sbc_copy_baseline(void* hip_stream, void* dst, const void* src, size_t bytes) {
@@ -1435,9 +1459,43 @@ int sbc_last_mask(sbc_ctx* c, int tensor, uint32_t* mask_words, size_t n_words) 
         }
         return SBC_OK;
     }
-    if (hipMemcpy(mask_words, c->d_bitmap + (size_t)d.chunk0 * kChunkWords, n_words * 4, hipMemcpyDeviceToHost) != hipSuccess) {
-        (void)hipGetLastError();
-        return SBC_EHIP;
+    // from the chunks' codes, which stay where they are until the next step
+    std::memset(mask_words, 0, n_words * 4);
+    constexpr uint32_t kBatch = 1024;
+    struct Batch { ChunkSummary sum[kBatch]; uint32_t words[kBatch * kChunkWords]; };
+    std::unique_ptr<Batch> host(new (std::nothrow) Batch);
+    if (!host) return SBC_EHIP;
+    const int b = c->last_b;
+    for (uint32_t f0 = 0; f0 < d.nchunks; f0 += kBatch) {
+        const uint32_t count = std::min(kBatch, d.nchunks - f0);
+        const size_t at = (size_t)d.chunk0 + f0;
+        if (hipMemcpy(host->sum, c->d_sum + at, count * sizeof(ChunkSummary), hipMemcpyDeviceToHost) != hipSuccess ||
+            hipMemcpy(host->words, c->d_bitmap + at * kChunkWords, (size_t)count * kChunkWords * 4, hipMemcpyDeviceToHost) != hipSuccess) {
+            (void)hipGetLastError();
+            return SBC_EHIP;
+        }
+        for (uint32_t f = 0; f < count; ++f) {
+            const ChunkSummary& sm = host->sum[f];
+            if (!sum_any(sm)) continue;
+            const uint32_t* const w = host->words + (size_t)f * kChunkWords;
+            const uint64_t e0 = (uint64_t)(f0 + f) * kChunk;
+            if (sum_raw(sm)) {
+                const size_t to = (size_t)(f0 + f) * kChunkWords;
+                std::memcpy(mask_words + to, w, std::min<size_t>(kChunkWords, n_words - to) * 4);
+                continue;
+            }
+            const auto bit = [&](uint32_t i) { return (w[i >> 5] >> (31u - (i & 31u))) & 1u; };
+            uint64_t pos = sum_first(sm);
+            for (uint32_t i = 0, end = sum_inner(sm); ; ) {
+                if (pos >= (uint64_t)kChunk || e0 + pos >= d.n) return SBC_EINTERNAL;
+                mask_words[(e0 + pos) >> 5] |= 1u << (pos & 31u);
+                if (i >= end) break;
+                uint64_t gap = 0;
+                while (i < end && bit(i++)) ++gap;
+                for (int j = 0; j < b; ++j) gap = (gap << 1) | (i < end ? bit(i++) : 0u);
+                pos += 1 + gap;
+            }
+        }
     }
     return SBC_OK;
 }

@@ -35,6 +35,29 @@
 
 namespace sbc {
 
+// val (< 2^nb, 1 <= nb <= 32) written MSB-first at bit `pos` of a zero-initialised word array.
+__device__ __forceinline__ void put_bits(uint32_t* words, unsigned long long pos, uint32_t val, int nb) {
+    const unsigned long long w = pos >> 5;
+    const int off = (int)(pos & 31ull);
+    const unsigned long long v = (unsigned long long)val << (64 - off - nb);
+    const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
+    if (hi) atomicOr(&words[w], hi);
+    if (lo) atomicOr(&words[w + 1], lo);
+}
+
+// q one-bits starting at bit `pos`.
+__device__ __forceinline__ void put_ones(uint32_t* words, unsigned long long pos, unsigned long long q) {
+    while (q) {
+        const unsigned long long w = pos >> 5;
+        const uint32_t room = 32u - (uint32_t)(pos & 31ull);
+        const uint32_t take = q < room ? (uint32_t)q : room;
+        if (take == 32u) words[w] = 0xFFFFFFFFu;        // the whole word belongs to this run
+        else atomicOr(&words[w], ((1u << take) - 1u) << (room - take));
+        pos += take;
+        q -= take;
+    }
+}
+
 constexpr int kStepThreads = 256;
 constexpr int kStepWaves = kStepThreads / 64;
 constexpr int kSlots = kChunk / kStepThreads;            // 32 entries per thread
@@ -967,13 +990,6 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
 // memory.  If some tensor still has to be redone by the kernels of the other routes, nothing but
 // the result block is written: the host launches those kernels and this one again.
 // --------------------------------------------------------------------------
-// The call's result block in pinned host memory is complete: its sequence number goes out last, so
-// that a host that polls for the number finds size and error word in place.
-__device__ __forceinline__ void publish_result(ResultBlock* host_result, uint32_t seq) {
-    __threadfence_system();
-    __hip_atomic_store(&host_result->pad, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
 __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __restrict__ desc,
                                                         TensorState* __restrict__ st, int T, int b,
                                                         const uint32_t* __restrict__ stage,
@@ -982,13 +998,13 @@ __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __rest
                                                         uint8_t* __restrict__ msg, uint64_t msg_capacity,
                                                         ResultBlock* __restrict__ result,
                                                         ResultBlock* __restrict__ next_result,
-                                                        ResultBlock* __restrict__ host_result, uint32_t seq) {
+                                                        unsigned long long* __restrict__ host_word, uint32_t seq) {
     __shared__ unsigned long long part[2][4];
     const int t = blockIdx.x, tid = threadIdx.x;
     const bool lead = (blockIdx.y == 0);
     const uint32_t err_in = result->err;
-    if (err_in & (kErrPrefilter | kErrDeferred | kErrInternal | kErrNonFinite | kErrOverflow)) {
-        if (t == 0 && lead && tid == 0) { host_result->msg_bytes = 0ull; host_result->err = err_in; publish_result(host_result, seq); }
+    if (err_in & kErrStops) {
+        if (t == 0 && lead && tid == 0) publish(host_word, seq, err_in, 0ull);
         return;
     }
     const TensorDesc d = desc[t];
@@ -1013,7 +1029,10 @@ __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __rest
     const unsigned long long n_words = (bit_len + 31ull) >> 5;
     const unsigned long long table_end = 32ull + 24ull * (unsigned)T;
     if (n_words > d.bound_words || table_end + 4ull * (word_off + n_words) > msg_capacity || nnz > d.kcap) {
-        if (tid == 0) { atomicOr(&result->err, kErrInternal); if (lead) atomicOr(&host_result->err, kErrInternal); }
+        if (tid == 0) {
+            atomicOr(&result->err, kErrInternal);
+            if (t == 0 && lead) publish(host_word, seq, err_in | kErrInternal, 0ull);
+        }
         return;
     }
     if (lead) {
@@ -1046,16 +1065,7 @@ __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __rest
             st[t].cand_cnt[0] = 0u; st[t].cand_cnt[1] = 0u; st[t].flags = 0u; st[t].done = 0u;
             st[t].sorted_kept = (my_flags & kStInlineDone) ? 1u : 0u;
             if (t == 0) {
-                uint32_t* h = reinterpret_cast<uint32_t*>(msg);
-                h[0] = 0x31434253u; h[1] = 1u; h[2] = (uint32_t)T; h[3] = (uint32_t)b;
-                *reinterpret_cast<uint64_t*>(msg + 16) = tot_all;
-                *reinterpret_cast<uint64_t*>(msg + 24) = 0ull;
-                const unsigned long long bytes = table_end + 4ull * tot_all;
-                result->msg_bytes = bytes;
-                host_result->msg_bytes = bytes; host_result->err = err_in;
-                publish_result(host_result, seq);
-                // the result block of the next call starts out clean
-                next_result->err = 0u; next_result->pad = 0u; next_result->msg_bytes = 0ull;
+                finish_call(msg, T, b, tot_all, err_in, next_result, host_word, seq);
             }
         }
     }

@@ -428,6 +428,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     st[t].itau[s] = itau;
     st[t].kc[s] = kc;
     st[t].S[s] = S;
+    st[t].mean[s] = S / (double)kc;
     uint32_t raise = 0u;
     if (carry && pick) {
         const bool ranked = next_bin != 0xFFFFFFFFu;
