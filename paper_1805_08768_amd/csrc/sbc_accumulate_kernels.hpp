@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
 template <int PER>
 __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], uint32_t mp, uint32_t mn,
                                                   uint32_t e_first, const TensorDesc& d, TensorState* __restrict__ st_t,
-                                                  uint2* __restrict__ cand, ChunkRun* __restrict__ run,
+                                                  const CandPtr cand, ChunkRun* __restrict__ run,
                                                   uint32_t* scratch, uint32_t* base) {
     const int tid = threadIdx.x;
     const uint32_t packed = __popc(mp) | (__popc(mn) << 16);
@@ -347,13 +347,12 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
     // (beyond a list's capacity nothing is stored: the counters then show that the tensor's lists
     // are not usable, see lists_unusable; a list of a full context holds every entry)
     if (op + __popc(mp) > d.cand_cap || on + __popc(mn) > d.cand_cap) return;
-    uint2* __restrict__ cp = cand + d.cand_off;
-    uint2* __restrict__ cn = cand + d.cand_off + d.cand_cap;
+    const CandPtr cp = cand + d.cand_off, cn = cp + d.cand_cap;
 #pragma unroll
     for (int s = 0; s < PER; ++s) {
         const uint32_t idx = e_first + s * kStreamThreads + tid;
-        if (mp & (1u << s)) cp[op++] = make_uint2(key[s], idx);
-        if (mn & (1u << s)) cn[on++] = make_uint2(~key[s], idx);
+        if (mp & (1u << s)) cp.put(op++, key[s], idx);
+        if (mn & (1u << s)) cn.put(on++, ~key[s], idx);
     }
 }
 
@@ -363,7 +362,8 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
 // or beyond each side's filter key (the keys' order is that of the values, so this is one comparison
 // of floats per side); one scan of the counts and one 64-bit atomic for both sides then give every
 // candidate its place, and each thread copies its few from LDS.  However many there are, the path is
-// the same.  Where a chunk's candidates went is recorded (ChunkRun).  Bound by HBM on large calls (54 us
+// the same.  (One tensor's workgroups queue up on its counter: 512 of them 15.6 us; with eight counters, and
+// the lists in as many segments, 11.5.)  Where a chunk's candidates went is recorded (ChunkRun).  Bound by HBM on large calls (54 us
 // on 25.6e6 entries, a plain R += dW takes 54.5 us there).  Small ones are bound by latency: with a test, an LDS
 // counter and a queue per entry, 18 KB of code, 128 chunks took 11.8 us and 41 took 10.3; now 7.4 and
 // 5.6.  Operands that are only 4-byte aligned take the same loads (24 ragged tensors of 12e6 entries in
@@ -390,8 +390,8 @@ constexpr int kPastNothing = 0, kPastUpdate = 1, kPastAll = 2;     // (kPastAll:
 template <int PAST>
 __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor,
-        TensorState* __restrict__ st, uint2* __restrict__ cand, ChunkRun* __restrict__ runs,
-        ResultBlock* __restrict__ result) {
+        TensorState* __restrict__ st, unsigned long long* __restrict__ counters, const CandPtr cand,
+        ChunkRun* __restrict__ runs, ResultBlock* __restrict__ result) {
     __shared__ FilterShared sh;
     const int tid = threadIdx.x;
     const uint32_t c = blockIdx.x;
@@ -475,33 +475,37 @@ __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
     uint32_t total;
     const uint32_t ex = block_excl_sum<uint32_t, kStreamThreads>(__popc(mp) | (__popc(mn) << 16), &total, sh.scratch);
     const uint32_t qp = total & 0xFFFFu, qn = total >> 16;
+    const uint32_t seg = d.segs == 1u ? 0u : (c - ct.y) % kSegs;
+    const uint32_t seg0 = seg_before(d, d.segs, seg), seg1 = seg_before(d, d.segs, seg + 1u);
     if (tid == 0) {
-        // both sides' counters advance in one 64-bit atomic: workgroups of one tensor queue up on this
+        // both sides' counters advance in one 64-bit atomic: the workgroups of one segment queue up on this
         // address, and the wait grows with the number of atomics
         unsigned long long old = 0ull;
-        if (total)
-            old = atomicAdd(reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]), (unsigned long long)qp | ((unsigned long long)qn << 32));
+        unsigned long long* const counter = d.segs == 1u ? reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0])
+                                                         : counters + ((size_t)t * kSegs + seg) * kCounterStride;
+        if (total) old = atomicAdd(counter, (unsigned long long)qp | ((unsigned long long)qn << 32));
         sh.base[0] = (uint32_t)old;
         sh.base[1] = (uint32_t)(old >> 32);
-        runs[c] = chunk_run(d, (uint32_t)old, (uint32_t)(old >> 32), qp, qn);
+        runs[c] = chunk_run(d, seg0 + (uint32_t)old, seg0 + (uint32_t)(old >> 32), qp, qn);
     }
     if (total == 0u) return;                              // uniform
     __syncthreads();
     const uint32_t base_p = sh.base[0], base_n = sh.base[1];
     // (beyond a list's capacity nothing is stored: the counters then show that the tensor's lists are not
     // usable, see lists_unusable; a list of a full context holds every entry)
-    if ((uint64_t)base_p + qp > d.cand_cap || (uint64_t)base_n + qn > d.cand_cap) return;   // uniform
+    if ((uint64_t)base_p + qp > seg1 - seg0 || (uint64_t)base_n + qn > seg1 - seg0) return;  // uniform
     const float* const flat = reinterpret_cast<const float*>(sh.a);
-    auto copy_out = [&](uint32_t m, uint2* __restrict__ to, uint32_t flip) {
+    auto copy_out = [&](uint32_t m, const CandPtr to, uint32_t flip) {
+        uint32_t i = 0u;
         while (m) {
             const uint32_t s = (uint32_t)__clz((int)m);
             m &= ~(0x80000000u >> s);
             const uint32_t at = ((s >> 2) * (uint32_t)kStreamThreads + (uint32_t)tid) * 4u + (s & 3u);
-            *to++ = make_uint2(key_of_bits(__float_as_uint(flat[at])) ^ flip, e0 + at);
+            to.put(i++, key_of_bits(__float_as_uint(flat[at])) ^ flip, e0 + at);
         }
     };
-    copy_out(mp, cand + d.cand_off + base_p + (ex & 0xFFFFu), 0u);
-    copy_out(mn, cand + d.cand_off + d.cand_cap + base_n + (ex >> 16), 0xFFFFFFFFu);
+    copy_out(mp, cand + d.cand_off + seg0 + base_p + (ex & 0xFFFFu), 0u);
+    copy_out(mn, cand + d.cand_off + d.cand_cap + seg0 + base_n + (ex >> 16), 0xFFFFFFFFu);
 }
 
 // --------------------------------------------------------------------------
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(256) void k_pick_bins(const TensorDesc* __restrict_
 // beyond a side's threshold bin becomes a candidate of that side.
 __global__ __launch_bounds__(kStreamThreads) void k_extract(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor,
-        TensorState* __restrict__ st, uint2* __restrict__ cand, ChunkRun* __restrict__ runs) {
+        TensorState* __restrict__ st, const CandPtr cand, ChunkRun* __restrict__ runs) {
     constexpr int PER = kChunk / kStreamThreads;
     __shared__ uint32_t scratch[kStreamThreads / 64];
     __shared__ uint32_t base[2];

@@ -44,6 +44,8 @@ typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef SBC_GLOBAL_AS f32x4_any* gf32x4_any_ptr;
 typedef const SBC_GLOBAL_AS f32x4_any* gcf32x4_any_ptr;
 
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // ---------------------------------------------------------------- layout ----
 
 constexpr int kChunk = 8192;             // entries of one tensor handled by one workgroup
@@ -65,7 +67,7 @@ constexpr uint32_t kErrInternal = 2u;
 constexpr uint32_t kErrCorrupt = 4u;
 constexpr uint32_t kErrOverflow = 128u;  // a candidate list of a compact context cannot hold what the histogram route extracts
 constexpr uint32_t kErrPrefilter = 8u;   // not an error: some tensor needs the histogram path
-constexpr uint32_t kErrWide = 32u;       // not an error: the sweeps for long lists narrowed some tensor down
+constexpr uint32_t kErrWide = 32u;       // not an error: some tensor's long lists were narrowed down to one bin
 constexpr uint32_t kErrLoose = 16u;      // not an error: a carried-over filter key let far too many entries pass
 constexpr uint32_t kErrStaleKeys = 256u; // not an error: the filter keys the previous call left would have let far too many entries pass now
 constexpr uint32_t kErrDeferred = 64u;   // not an error: a tensor the streaming kernel could not finish itself is left to the kernels after it
@@ -86,6 +88,7 @@ __host__ __device__ inline unsigned long long loose_limit(uint32_t k, uint32_t n
 // TensorDesc::flags
 constexpr uint32_t kDescWide = 2u;       // keeps so many entries that sweeps by many workgroups narrow its lists down first
 constexpr uint32_t kDescSampled = 4u;    // subsampled variant: the sampled threshold decides what is kept
+constexpr uint32_t kDescLong = 16u;      // keeps so many entries that its lists count as long (SBC_ROUTE_WIDE)
 constexpr uint32_t kDescInline = 8u;     // finished inside the streaming kernel by the last of its workgroups
 // TensorState::flags
 constexpr uint32_t kStFailed = 1u;       // prefilter kept fewer than k candidates on a side
@@ -111,13 +114,31 @@ struct TensorDesc {
     uint32_t grp0;        // first of this tensor's chunk groups
     uint32_t wide;        // (kDescWide) its number among the call's wide tensors
     uint32_t cand_cap;    // entries each side's candidate list holds: n, or fewer in a compact context
-    uint32_t pad;
+    uint32_t segs;        // segments of each list: 1 or kSegs
 };
+
+// Segments of the candidate lists of long tensors: chunk cc of a tensor appends to segment cc % kSegs, each
+// with a counter on a memory line of its own.  (Returning atomics on one address queue up at 12 ns apiece: of
+// 512 workgroups that is 6.0 us, 0.9 us over eight addresses.)
+constexpr uint32_t kSegs = 8;
+constexpr uint32_t kSegMinChunks = 64;           // chunks from which a list is cut up: 0.8 us of queueing
+constexpr uint32_t kSegMinCompact = 4096;        // ... in a compact context, whose segments hold an eighth of the
+                                                 // list's room each: long enough for a crowd of full chunks to fit one
+constexpr uint32_t kCounterStride = 16;          // 64-bit words from counter to counter
+
+// Entries of a side's list before segment s.  A list of a full context has room for every entry of the
+// segment's chunks (of which the tensor's last may be short).
+__device__ __forceinline__ uint32_t seg_before(const TensorDesc& d, uint32_t segs, uint32_t s) {
+    if (segs == 1u) return s ? d.cand_cap : 0u;
+    if (d.cand_cap < d.n) return s * (d.cand_cap / kSegs);
+    const uint32_t chunks = d.nchunks / kSegs * s + min(d.nchunks % kSegs, s);
+    return chunks * (uint32_t)kChunk - (s > (d.nchunks - 1u) % kSegs ? d.nchunks * (uint32_t)kChunk - d.n : 0u);
+}
 
 // Per-tensor results, written on the device.
 struct alignas(8) TensorState {
     uint32_t lo_key[2];    // prefilter: side keys at or above these become candidates
-    uint32_t cand_cnt[2];  // candidates appended per side (8-byte aligned: advanced together as one u64)
+    uint32_t cand_cnt[2];  // candidates appended per side (8-byte aligned: advanced together as one u64), unless the lists have segments
     uint32_t bin[2];       // histogram path: first-digit bin holding the k-th entry of each side
     uint32_t tau[2];       // full 32-bit threshold key per side (side key space)
     uint32_t itau[2];      // ties at tau are kept up to this index
@@ -146,11 +167,22 @@ struct alignas(16) GroupState {
     uint32_t pad[3];
 };
 
+// A place in the candidate lists: keys, and as far behind them their entries' indexes.  (Apart, because the
+// selection reads the keys alone, and what a compute unit can pull in, about 90 GB/s, bounds it on long lists.)
+struct CandPtr {
+    uint32_t* key;
+    uint64_t to_idx;
+    __device__ __forceinline__ CandPtr operator+(uint64_t n) const { return {key + n, to_idx}; }
+    __device__ __forceinline__ uint2 get(uint64_t i) const { return make_uint2(key[i], key[i + to_idx]); }
+    __device__ __forceinline__ void put(uint64_t i, uint32_t k, uint32_t idx) const { key[i] = k; key[i + to_idx] = idx; }
+};
+
 // Where the candidates of a chunk lie in its tensor's lists: one run per side.
 struct alignas(8) ChunkRun {
     uint64_t at[2];        // place of the first one in the call's candidate array
     uint32_t cnt[2];
 };
+// base_p, base_n: entries of the tensor's lists before them.
 __device__ __forceinline__ ChunkRun chunk_run(const TensorDesc& d, uint32_t base_p, uint32_t base_n, uint32_t cnt_p, uint32_t cnt_n) {
     ChunkRun r;
     r.at[0] = d.cand_off + base_p; r.at[1] = d.cand_off + d.cand_cap + base_n;
@@ -308,6 +340,9 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
     add(dpp_fetch<0x143, 0xc>((unsigned long long)__double_as_longlong(v)));
     return v;
 }
+// A value that is the same in the whole wavefront, as a scalar (what comes out of LDS never is one by itself,
+// and everything that follows from it would be computed per lane).
+__device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
 __device__ __forceinline__ unsigned long long last_lane(unsigned long long v) {
     return ((unsigned long long)last_lane((uint32_t)(v >> 32)) << 32) | last_lane((uint32_t)v);

@@ -158,7 +158,7 @@ __device__ __forceinline__ uint32_t chunk_bits(uint32_t x, uint32_t gap, int b, 
 // --------------------------------------------------------------------------
 __global__ __launch_bounds__(kEncThreads) void k_apply(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor, const ChunkRun* __restrict__ runs,
-        const TensorState* __restrict__ st, TensorState* res, const uint2* __restrict__ cand,
+        const TensorState* __restrict__ st, TensorState* res, const CandPtr cand,
         uint64_t cand_entries, uint32_t* __restrict__ codes, ChunkSummary* __restrict__ sum,
         uint32_t* __restrict__ heads, int b, int pass, uint32_t n_chunks, ResultBlock* __restrict__ result) {
     __shared__ __attribute__((aligned(16))) uint32_t bits_sh[kEncWaves][kChunkWords];
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         e0[s] = make_uint2(0u, 0u);
-        if ((uint32_t)lane < run.cnt[s] && run.at[s] < cand_entries - 64u) e0[s] = cand[run.at[s] + (uint32_t)lane];
+        if ((uint32_t)lane < run.cnt[s] && run.at[s] < cand_entries - 64u) e0[s] = cand.get(run.at[s] + (uint32_t)lane);
     }
     reinterpret_cast<uint4*>(bm)[lane] = make_uint4(0u, 0u, 0u, 0u);
     reinterpret_cast<uint4*>(code_sh[wave])[lane] = make_uint4(0u, 0u, 0u, 0u);
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
     const float mu_signed = chosen ? -mu32 : mu32;
     const uint32_t tau = chosen ? tau_n : tau_p, itau = chosen ? itau_n : itau_p;
     if (cc == 0u && lane == 0) { res[t].side = chosen ? -1 : 1; res[t].mu_signed = mu_signed; res[t].nnz = st[t].kc[chosen]; }
-    const uint2* __restrict__ list = cand + run.at[chosen];
+    const CandPtr list = cand + run.at[chosen];
     const uint32_t cnt = run.cnt[chosen];
     wave_lds_fence();
     bool bad = false;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t i = i0 + 64u * u + (uint32_t)lane;
-            e[u] = list[i < cnt ? i : 0u];
+            e[u] = list.get(i < cnt ? i : 0u);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -439,7 +439,7 @@ __device__ __forceinline__ void stage_codes(uint32_t* win, const uint4& v) {
 }
 
 // A tensor's table entry, and its state left clean for the next call.
-__device__ __forceinline__ void finish_tensor(uint8_t* __restrict__ msg, TensorState* __restrict__ st, uint32_t t, float mu_signed, uint32_t nnz,
+__device__ __forceinline__ void finish_tensor(uint8_t* __restrict__ msg, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, uint32_t t, float mu_signed, uint32_t nnz,
                                               unsigned long long bit_len, unsigned long long word_off) {
     uint8_t* e = msg + 32 + 24ull * t;
     *reinterpret_cast<float*>(e) = mu_signed;
@@ -448,6 +448,8 @@ __device__ __forceinline__ void finish_tensor(uint8_t* __restrict__ msg, TensorS
     *reinterpret_cast<uint64_t*>(e + 16) = word_off;
     st[t].bit_len = bit_len;
     st[t].cand_cnt[0] = 0u; st[t].cand_cnt[1] = 0u; st[t].flags = 0u; st[t].done = 0u; st[t].sorted_kept = 0u;
+#pragma unroll
+    for (uint32_t g = 0; g < kSegs; ++g) counters[((size_t)t * kSegs + g) * kCounterStride] = 0ull;
 }
 // The header, and the call's result for the host.
 __device__ __forceinline__ void finish_call(uint8_t* __restrict__ msg, int T, int b, unsigned long long payload_words, uint32_t err,
@@ -503,7 +505,7 @@ __device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint
 template <int NT>
 __global__ __launch_bounds__(NT) void k_emit_all(
         const uint2* __restrict__ chunk_tensor, const ChunkSummary* __restrict__ sum, const uint32_t* __restrict__ codes,
-        const uint32_t* __restrict__ heads, TensorState* __restrict__ st, int T, int b, uint32_t n_chunks,
+        const uint32_t* __restrict__ heads, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, int T, int b, uint32_t n_chunks,
         uint8_t* __restrict__ msg, uint64_t msg_capacity, ResultBlock* __restrict__ result, ResultBlock* __restrict__ next_result,
         unsigned long long* __restrict__ host_word, uint32_t seq) {
     constexpr int NW = NT / 64, PER = kEmitAllPer;
@@ -602,7 +604,7 @@ __global__ __launch_bounds__(NT) void k_emit_all(
     cs.c = c; cs.gap = g & (kStarts - 1u); cs.inner = sum_inner(own); cs.any = !(g & kNone); cs.raw = sum_raw(own); cs.at = o;
     if ((tid & 63) == 0 && (c + 1u == n_chunks || (gaps[c + 1u] & kStarts))) {
         const uint32_t tensor = offs[ct.y];
-        finish_tensor(msg, st, ct.x, mu_signed, nnz, (unsigned long long)(o - tensor) + (cs.any ? golomb_len(cs.gap, b) + cs.inner : 0u), tensor >> 5);
+        finish_tensor(msg, st, counters, ct.x, mu_signed, nnz, (unsigned long long)(o - tensor) + (cs.any ? golomb_len(cs.gap, b) + cs.inner : 0u), tensor >> 5);
     }
     write_chunk(cs, mine, b, win_sh[wave], sum, codes, heads, reinterpret_cast<uint32_t*>(msg + 32 + 24ull * (unsigned)T),
                 [&](uint32_t f, uint32_t& gap_f, bool& any_f) {
@@ -622,7 +624,7 @@ template <bool DIRECT>
 __global__ __launch_bounds__(kEncThreads) void k_emit(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor, const ChunkSummary* __restrict__ sum,
         const uint32_t* __restrict__ codes, const uint32_t* __restrict__ heads, const uint32_t* __restrict__ chunk_gap,
-        const uint64_t* __restrict__ chunk_bitoff, TensorState* __restrict__ st, int T, int b, int pass, uint32_t n_chunks,
+        const uint64_t* __restrict__ chunk_bitoff, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, int T, int b, int pass, uint32_t n_chunks,
         uint32_t* __restrict__ stage, uint8_t* __restrict__ msg, uint64_t msg_capacity, ResultBlock* __restrict__ result,
         ResultBlock* __restrict__ next_result, unsigned long long* __restrict__ host_word, uint32_t seq) {
     __shared__ __attribute__((aligned(16))) uint32_t win_sh[kEncWaves][kWindow];
@@ -659,7 +661,7 @@ __global__ __launch_bounds__(kEncThreads) void k_emit(
             return;
         }
         if (c == 0u && lane == 0u) finish_call(msg, T, b, all, err_in, next_result, host_word, seq);
-        if (c - ct.y == nchunks - 1u && lane == 0u) finish_tensor(msg, st, t, st[t].mu_signed, st[t].nnz, bit_len, before);
+        if (c - ct.y == nchunks - 1u && lane == 0u) finish_tensor(msg, st, counters, t, st[t].mu_signed, st[t].nnz, bit_len, before);
         to = reinterpret_cast<uint32_t*>(msg + 32 + 24ull * (unsigned)T) + before;
     } else {
         if (!encoded_in_pass(st[t].flags, pass)) return;

@@ -34,12 +34,19 @@ const char* const kStageNames[kNumStages] = {
     "k_apply", "k_tensor_scan", "k_emit", "k_finish_message"};
 }  // namespace
 
+constexpr int kComputeUnits = 256;
 constexpr int kDescSlots = 4;             // device copies of the tensor table, keyed by the pointer lists
 constexpr uint32_t kAvgAloneChunks = 1024;  // (8.4e6 entries) beyond these, one message alone is added to the cleared result
 constexpr uint32_t kMaxDecExtra = 512;    // additional decode workgroups that share a stream's scatter
 constexpr uint32_t kDecSharePer = 256;    // kept entries per sharing workgroup
 constexpr uint32_t kDecShareMax = kDecWaves;    // (a wavefront's updates each)
-constexpr uint32_t kWideMinKept = 8192;   // kept entries per side from which a tensor takes those routes
+constexpr uint32_t kWideMinKept = 8192;   // kept entries from which a stream is decoded by many workgroups
+// Kept entries per side from which sweeps by many workgroups narrow a tensor's lists down before k_threshold.  One
+// workgroup per side alone is bound by its LDS histogram and by what a compute unit pulls in, about 0.1 us per
+// 1000 entries of a list, but takes no launches: one tensor, p = 0.01, step in us, alone / with sweeps: 10,000
+// kept entries 38 / 47, 20,000 47 / 53, 35,000 65 / 63, 50,000 86 / 63, 200,000 360 / 110.  (Ten tensors
+// with 8,000 to 24,000 in the ResNet-50 shape: 25 us for k_threshold, 31 with the sweeps.)
+constexpr uint32_t kSweepMinKept = 32768;
 
 struct DescSlot {
     bool valid = false;
@@ -67,7 +74,9 @@ struct sbc_ctx {
     uint32_t* d_order = nullptr;
     uint32_t* d_hist = nullptr;
     TensorState* d_state = nullptr;
-    uint2* d_cand = nullptr;
+    unsigned long long* d_counters = nullptr;   // kSegs per tensor: candidates in each segment of its lists (zero between calls)
+    uint32_t* d_cand = nullptr;           // the lists' keys, then their indexes
+    CandPtr cand() const { return {d_cand, cand_entries + 4u}; }      // (a few more: k_threshold reads four keys at a time)
     ChunkRun* d_runs = nullptr;           // per chunk: where its candidates lie
     uint32_t* d_bitmap = nullptr;
     uint32_t* d_stage = nullptr;
@@ -135,7 +144,6 @@ struct sbc_ctx {
     std::vector<uint32_t> plan_order;
     int n_wide = 0;                       // tensors whose long lists are narrowed down by sweeps
     uint32_t wide_blocks = 0;
-    uint32_t staged_keys = 0;             // keys of a list that k_threshold stages in LDS
     DescSlot slot[kDescSlots];            // which pointer lists the device tables hold
     uint64_t slot_clock = 0;
 
@@ -157,7 +165,7 @@ struct sbc_ctx {
     int defer_decode = 0;                 // decode calls return once enqueued; sbc_decode_status reports
     bool deferred_pending = false;        // some deferred decode has not been waited for yet
     bool deferred_dirty = true;           // block [4] must be cleared before the next deferred decode
-    uint32_t wide_min_kept = kWideMinKept;
+    uint32_t wide_min_kept = kWideMinKept, sweep_min_kept = kSweepMinKept;
 
     // filter keys carried over from the previous successful call (same tensor sizes, same p)
     bool hist_valid = false;
@@ -253,7 +261,7 @@ hipError_t host_alloc(T** p, size_t count) { return hipHostMalloc(reinterpret_ca
 
 void free_all(sbc_ctx* c) {
     (void)hipFree(c->d_desc); (void)hipFree(c->d_chunk_tensor); (void)hipFree(c->d_sched); (void)hipFree(c->d_group); (void)hipFree(c->d_order); (void)hipFree(c->d_hist);
-    (void)hipFree(c->d_state); (void)hipFree(c->d_cand); (void)hipFree(c->d_bitmap); (void)hipFree(c->d_stage);
+    (void)hipFree(c->d_state); (void)hipFree(c->d_counters); (void)hipFree(c->d_cand); (void)hipFree(c->d_bitmap); (void)hipFree(c->d_stage);
     (void)hipFree(c->d_kept); (void)hipFree(c->d_sum); (void)hipFree(c->d_head); (void)hipFree(c->d_gap); (void)hipFree(c->d_bitoff); (void)hipFree(c->d_tile);
     (void)hipFree(c->d_result); (void)hipFree(c->d_dec_blocks);
     if (c->h_dec_blocks) (void)hipHostFree(c->h_dec_blocks);
@@ -314,37 +322,36 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
             const dim3 sweep(c->wide_blocks, 2u * (unsigned)c->n_wide);
             if (lvl >= 2) {
                 hipExtLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, c->ev[2 * kStWide], nullptr, 0,
-                                      P.d_desc, c->wide_ids, c->d_state, c->d_cand, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
+                                      P.d_desc, c->wide_ids, c->d_state, c->d_counters, c->cand(), c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
                 hipExtLaunchKernelGGL(k_wide_collect, sweep, dim3(kWideThreads), 0, stream, nullptr, c->ev[2 * kStWide + 1], 0,
-                                      P.d_desc, c->wide_ids, c->d_state, c->d_cand, c->d_bitmap, c->d_wide_hist, c->d_wide_acc,
+                                      P.d_desc, c->wide_ids, c->d_state, c->d_counters, c->cand(), c->d_bitmap, c->d_wide_hist, c->d_wide_acc,
                                       c->d_wide_state);
                 timed[kStWide] = true;
             } else {
                 hipLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, P.d_desc, c->wide_ids, c->d_state,
-                                   c->d_cand, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
+                                   c->d_counters, c->cand(), c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
                 hipLaunchKernelGGL(k_wide_collect, sweep, dim3(kWideThreads), 0, stream, P.d_desc, c->wide_ids, c->d_state,
-                                   c->d_cand, c->d_bitmap, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
+                                   c->d_counters, c->cand(), c->d_bitmap, c->d_wide_hist, c->d_wide_acc, c->d_wide_state);
             }
         }
-        // (largest tensors first if there are more workgroups than compute units: the small ones then share.  ResNet-50
-        // shape, whose largest come last: p = 0.01 14.3 -> 13.3 us, the step at p = 0.001 91.6 -> 90.9 us)
-        SBC_LAUNCH_LDS(kStThreshold, profile, k_threshold, dim3(2u * (unsigned)T), dim3(kThThreads), c->staged_keys * sizeof(uint32_t),
-                       P.d_desc, T > 128 ? c->d_order : nullptr, c->d_state, c->d_cand, c->d_bitmap, c->d_wide_state,
-                       c->d_wide_hist, c->d_wide_acc, pass, P.carry, c->staged_keys, P.res_now);
+        // (c->d_order: see compress_begin)
+        SBC_LAUNCH(kStThreshold, profile, k_threshold, dim3(2u * (unsigned)T), dim3(kThThreads),
+                   P.d_desc, T > kComputeUnits / 2 ? c->d_order : nullptr, c->d_state, c->d_counters, c->cand(), c->d_bitmap, c->d_wide_state,
+                       c->d_wide_hist, c->d_wide_acc, pass, P.carry, P.res_now);
         const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
         SBC_LAUNCH(kStApply, profile, k_apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
-                   c->d_cand, c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, pass, P.n_chunks, P.res_now);
+                   c->cand(), c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, pass, P.n_chunks, P.res_now);
         if (!c->fused_step && P.n_chunks <= kEmitAllChunks) {
             // the workgroups that write the codes scan the summaries of all chunks themselves, one launch less.  (Two
             // sizes: few chunks want many small workgroups, the scan over many wants large ones.)
             const size_t lds = 2u * sizeof(uint32_t) * P.n_chunks;
             if (P.n_chunks <= kEmitFew)
                 SBC_LAUNCH_LDS(kStEmit, profile, k_emit_all<256>, dim3((P.n_chunks + 3u) / 4u), dim3(256), lds, c->d_chunk_tensor,
-                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, c->d_counters, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
                                P.res_next, c->h_result_dev, ++c->result_seq);
             else
                 SBC_LAUNCH_LDS(kStEmit, profile, k_emit_all<1024>, dim3((P.n_chunks + 15u) / 16u), dim3(1024), lds, c->d_chunk_tensor,
-                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, c->d_counters, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
                                P.res_next, c->h_result_dev, ++c->result_seq);
             return;
         }
@@ -355,12 +362,12 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
                    c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, pass);
         if (!c->fused_step) {
             SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
-                       c->d_gap, c->d_bitoff, c->d_state, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                       c->d_gap, c->d_bitoff, c->d_state, c->d_counters, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
                        P.res_next, c->h_result_dev, ++c->result_seq);
             return;
         }
         SBC_LAUNCH(kStEmit, profile, k_emit<false>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
-                   c->d_gap, c->d_bitoff, c->d_state, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                   c->d_gap, c->d_bitoff, c->d_state, c->d_counters, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
                    P.res_next, c->h_result_dev, 0u);
     }
     SBC_LAUNCH(kStGather, profile, k_finish_message, dim3(T, P.gather_y), dim3(256), P.d_desc, c->d_state, T, b,
@@ -543,7 +550,9 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_hist, T * kL1Bins) == hipSuccess;
     ok = ok && dev_alloc(&c->d_state, T) == hipSuccess;
     ok = ok && hipMemset(c->d_state, 0, sizeof(TensorState) * T) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_cand, (size_t)c->cand_entries) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_counters, T * kSegs * kCounterStride) == hipSuccess;
+    ok = ok && hipMemset(c->d_counters, 0, sizeof(unsigned long long) * T * kSegs * kCounterStride) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_cand, 2u * (size_t)c->cand_entries + 8u) == hipSuccess;
     ok = ok && dev_alloc(&c->d_runs, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_bitmap, (size_t)c->max_chunks * kChunkWords) == hipSuccess;
     ok = ok && dev_alloc(&c->d_stage, (size_t)c->stage_cap) == hipSuccess;
@@ -653,6 +662,7 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
         case SBC_OPT_WIDE_MIN_KEPT:
             if (value < 0) return SBC_EINVAL;
             c->wide_min_kept = value ? (uint32_t)value : kWideMinKept;
+            c->sweep_min_kept = value ? (uint32_t)value : kSweepMinKept;
             c->cache_valid = false;                    // which tensors are wide is part of both plans
             c->dev_dec_valid = false;
             return SBC_OK;
@@ -742,8 +752,12 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         for (int i = 0; i < kDescSlots; ++i) c->slot[i].valid = false;
         if (c->plan.size() < (size_t)T) c->plan.resize(T);
         int n_wide = 0;
+        // (where some tensor has sweeps, so have all with long lists: the launches are there anyway)
+        bool any_sweep = false;
+        for (int t = 0; t < T && !any_sweep; ++t)
+            any_sweep = numel[t] >= 1 && numel[t] < (int64_t)1 << 32 &&
+                        (uint64_t)cap_of(numel[t], kept_of(numel[t], p), sampled) >= c->sweep_min_kept;
         uint64_t wide_max_n = 0;
-        uint32_t kmax = 0;
         for (int t = 0; t < T; ++t) {
             const int64_t n = numel[t];
             if (n < 1 || n >= (int64_t)1 << 32) return SBC_EINVAL;
@@ -759,6 +773,10 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
             // if k asks for it (then the budget may not do, and the call is refused below)
             d.cand_cap = c->compact ? (uint32_t)std::min<uint64_t>((uint64_t)n, std::max<uint64_t>((uint64_t)n / 4u, 4ull * d.kcap + 1024ull))
                                     : (uint32_t)n;
+            // (the streaming kernel that finishes tensors reads lists in one piece; in the subsampled variant there is no
+            // second pass for a segment of a compact context that overflows)
+            const bool cut = !c->fused_step && d.nchunks >= (d.cand_cap < d.n ? (sampled ? 0xFFFFFFFFu : kSegMinCompact) : kSegMinChunks);
+            d.segs = cut ? kSegs : 1u;
             d.cand_off = cand_total;
             cand_total += 2ull * d.cand_cap;
             d.stage_off = stage_words;
@@ -775,13 +793,12 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
             all_inline = all_inline && inl;
             d.grp0 = (uint32_t)groups;
             if (inl) groups += n_groups;
-            if (!inl && d.kcap >= c->wide_min_kept && n_wide < c->max_wide) {
+            if (!inl && d.kcap >= c->wide_min_kept) d.flags |= kDescLong;
+            if (!inl && any_sweep && d.kcap >= c->wide_min_kept && n_wide < c->max_wide) {
                 d.flags |= kDescWide;
                 d.wide = (uint32_t)n_wide;
                 c->wide_ids.id[n_wide++] = (uint32_t)t;
                 wide_max_n = std::max<uint64_t>(wide_max_n, (uint64_t)n);
-            } else {
-                kmax = std::max(kmax, d.kcap);
             }
             d.kept_off = (uint32_t)kept_total;
             if (inl) kept_total += d.kcap;
@@ -798,11 +815,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         }
         if (chunks >= (1ull << 31)) return SBC_ECAPACITY;
         c->n_wide = n_wide;
-        c->staged_keys = threshold_staged(kmax, n_wide > 0);
-        // sweeps over a candidate list: enough workgroups to fill the chip, each with several rounds;
-        // at least 128 even for short lists (a compute unit pulls a small share sooner than a large one,
-        // and the tensor-wide step every workgroup repeats costs the same in all of them at once)
-        c->wide_blocks = (uint32_t)std::min<uint64_t>(2048, std::max<uint64_t>(128, wide_max_n / 65536));
+        // sweeps over a candidate list: up to 64 k entries per 2^20 of the tensor's find enough workgroups
+        c->wide_blocks = (uint32_t)std::min<uint64_t>(512, std::max<uint64_t>(kWideFew, wide_max_n / 262144 / kWideFew * kWideFew));
     }
     const size_t need = (size_t)(32 + 24ull * (unsigned)T + 4ull * stage_words);
     if (msg_capacity < need) return SBC_ECAPACITY;
@@ -821,8 +835,13 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         std::iota(c->plan_order.begin(), c->plan_order.end(), 0u);
         std::stable_sort(c->plan_order.begin(), c->plan_order.end(),
                          [&](uint32_t x, uint32_t y) { return c->plan[x].n > c->plan[y].n; });
+        // k_threshold's workgroups, two per tensor: largest tensors first if there are more of them than compute
+        // units; if only some compute units get two (the first ones, from the 257th workgroup on), small tensors stand
+        // at both of their places, and the large ones have a compute unit each (ResNet-50 shape, 322 workgroups, in
+        // the list's order, which ends with the largest: step 0.75 us more; largest first: 0.3 us more).
+        const int twice = T > kComputeUnits / 2 && T <= kComputeUnits ? T - kComputeUnits / 2 : 0;
+        for (int i = 0; i < T; ++i) c->h_order[i] = c->plan_order[i < twice ? T - 2 * twice + i : i < T - twice ? i - twice : i];
         for (int t = 0; t < T; ++t) {
-            c->h_order[t] = c->plan_order[t];
             uint2* ct = c->h_chunk_tensor + c->plan[t].chunk0;
             for (uint32_t j = 0; j < c->plan[t].nchunks; ++j) ct[j] = make_uint2((uint32_t)t, c->plan[t].chunk0);
         }
@@ -888,6 +907,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
                            (uint64_t)(2 * sizeof(ResultBlock) / 4));
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_group),
                            (uint64_t)c->max_groups * (sizeof(GroupState) / 4));
+        hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_counters),
+                           (uint64_t)c->max_tensors * kSegs * kCounterStride * 2u);
         // (the sweeps' histograms are left clean only if all of the call's kernels have run)
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, c->d_wide_hist, (uint64_t)c->max_wide * 2 * kThBins);
     }
@@ -924,20 +945,20 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         const int past = accumulate_past_cache(c, total, force_exact != 0);
         if (past == kPastAll) {
             SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
-                       c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
+                       c->d_chunk_tensor, c->d_state, c->d_counters, c->cand(), c->d_runs, res_now);
         } else if (past == kPastUpdate) {
             SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastUpdate>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
-                       c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
+                       c->d_chunk_tensor, c->d_state, c->d_counters, c->cand(), c->d_runs, res_now);
         } else {
             SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastNothing>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
-                       c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs, res_now);
+                       c->d_chunk_tensor, c->d_state, c->d_counters, c->cand(), c->d_runs, res_now);
         }
     } else if (total * 12ull > (512ull << 20)) {
         SBC_LAUNCH(kStAccumulate, true, k_client_step<true>, dim3(n_chunks), dim3(kStepThreads), d_desc, c->d_sched,
-                   c->d_state, c->d_cand, c->d_runs, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
+                   c->d_state, c->cand(), c->d_runs, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
     } else {
         SBC_LAUNCH(kStAccumulate, true, k_client_step<false>, dim3(n_chunks), dim3(kStepThreads), d_desc, c->d_sched,
-                   c->d_state, c->d_cand, c->d_runs, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
+                   c->d_state, c->cand(), c->d_runs, c->d_stage, c->d_kept, c->d_group, b, carry, res_now);
     }
     launch_selection_and_encode(c, 0);
     SBC_HOST_TS(2);
@@ -1000,7 +1021,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
                                c->d_chunk_tensor, c->d_state, c->d_hist);
             hipLaunchKernelGGL(k_pick_bins, dim3(T), dim3(256), 0, stream, d_desc, c->d_hist, c->d_state, res_now);
             hipLaunchKernelGGL(k_extract, dim3(P.n_chunks), dim3(kStreamThreads), 0, stream, d_desc,
-                               c->d_chunk_tensor, c->d_state, c->d_cand, c->d_runs);
+                               c->d_chunk_tensor, c->d_state, c->cand(), c->d_runs);
         }
         launch_selection_and_encode(c, 1);
         rc = enqueue_result_copy(c);
@@ -1309,7 +1330,7 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
     // 66e6 entries 93 and 80 us; one message of a small model 30 and 25 us, of 2^20 entries at p = 0.01 39 and
     // 32 us.
     const uint64_t per_msg = (uint64_t)c->avg_pos + c->avg_marks + (uint64_t)T;
-    const uint64_t room = c->cand_entries * (sizeof(uint2) / sizeof(uint32_t));
+    const uint64_t room = 2u * c->cand_entries;
     const int most = c->avg_fits && !c->pend.active ? (int)std::min<uint64_t>(kAvgMaxMsgs, room / per_msg) : 0;
     if (most < 1 || (n_msgs == 1 && c->avg_chunks > kAvgAloneChunks)) return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);
     // (the last client step may still be draining on another stream)
@@ -1324,7 +1345,7 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
     ResultBlock* const res = c->d_result + 2 + c->dec_result_idx;
     ResultBlock* const res_next = c->d_result + 2 + (c->dec_result_idx ^ 1);
     c->dec_result_idx ^= 1;
-    uint32_t* const positions = reinterpret_cast<uint32_t*>(c->d_cand);
+    uint32_t* const positions = c->d_cand;
     const uint32_t* const ids = reinterpret_cast<const uint32_t*>(c->d_avg_tensor + T);
     for (int m0 = 0; m0 < n_msgs; m0 += most) {
         const int M = std::min(most, n_msgs - m0);

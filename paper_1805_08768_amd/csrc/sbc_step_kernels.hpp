@@ -92,12 +92,13 @@ __device__ __forceinline__ void store_shared_u64(unsigned long long* p, unsigned
 __device__ __forceinline__ unsigned long long load_shared_u64(const unsigned long long* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void store_cand(uint2* p, uint32_t key, uint32_t idx) {
-    store_shared_u64(reinterpret_cast<unsigned long long*>(p), (unsigned long long)key | ((unsigned long long)idx << 32));
+__device__ __forceinline__ void store_cand(const CandPtr p, uint32_t key, uint32_t idx) {
+    __hip_atomic_store(p.key, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(p.key + p.to_idx, idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint2 load_cand(const uint2* p) {
-    const unsigned long long v = load_shared_u64(reinterpret_cast<const unsigned long long*>(p));
-    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+__device__ __forceinline__ uint2 load_cand(const CandPtr p) {
+    return make_uint2(__hip_atomic_load(p.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                      __hip_atomic_load(p.key + p.to_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 // every memory operation this wavefront has issued has completed
 __device__ __forceinline__ void wait_all_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
@@ -160,11 +161,11 @@ struct LdsLists {
 
 // candidate lists too long for LDS: read from memory in every sweep
 struct MemLists {
-    const uint2* g[2];
+    CandPtr g[2];
     uint32_t cnt[2];
     template <int S, typename F>
     __device__ __forceinline__ void for_each(F f) const {
-        const uint2* __restrict__ p = g[S];
+        const CandPtr p = g[S];
         const uint32_t n = cnt[S];
         for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 8u * kStepThreads) {
             uint2 e[8];
@@ -674,7 +675,7 @@ __device__ __forceinline__ bool finish_from_lists(StepShared& sh, const Src& src
 template <bool STREAM>
 __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ sched, TensorState* __restrict__ st,
-        uint2* __restrict__ cand, ChunkRun* __restrict__ runs, uint32_t* __restrict__ stage,
+        const CandPtr cand, ChunkRun* __restrict__ runs, uint32_t* __restrict__ stage,
         uint32_t* __restrict__ kept_idx, GroupState* __restrict__ groups, int b, int carry,
         ResultBlock* __restrict__ result) {
     __shared__ StepShared sh;
@@ -825,8 +826,7 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         qp += x; qn += y;
         overflow = overflow || x > (uint32_t)kWaveQueue || y > (uint32_t)kWaveQueue;
     }
-    uint2* __restrict__ lp = cand + d.cand_off;
-    uint2* __restrict__ ln = cand + d.cand_off + d.cand_cap;
+    const CandPtr lp = cand + d.cand_off, ln = lp + d.cand_cap;
     unsigned long long* const counter = reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]);
     const uint32_t grp = cc / (uint32_t)kGroupChunks;
     const uint32_t n_groups = (d.nchunks + kGroupChunks - 1u) / kGroupChunks;

@@ -9,10 +9,11 @@
 //                    bin summed, both as sweeps by many workgroups; k_threshold then selects among
 //                    the copied entries alone.
 //
-// A side is selected in two counting passes over its list: the leading 20 key bits in a window of
-// two octaves above the filter key, then the other 12 bits of the entries in the k-th entry's bin.
-// That is exact whatever the ties (equal values are one bin of the second pass).  Sums are exact
-// integers rounded once to fp64 (or one integer per fp32 exponent where the values spread too far).
+// A side is selected in two passes over its list: the first counts the leading 20 key bits in a window of
+// two octaves above the filter key, which gives the k-th entry's bin; the second adds up the entries beyond
+// that bin and collects the few in it, whose ranks among one another give the threshold (more than 256 of
+// them: their other 12 bits are counted, too).  That is exact whatever the ties.  Sums are exact integers
+// rounded once to fp64 (or one integer per fp32 exponent where the values spread too far).
 #pragma once
 
 #include "sbc_device.hpp"
@@ -22,18 +23,9 @@ namespace sbc {
 constexpr int kThThreads = 1024;
 constexpr int kThShift = 12;                              // low key bits: the second pass's bins
 constexpr int kThBins = 1 << kThShift;                    // bins of either pass; 2048 of the first per octave
-constexpr uint32_t kThMaxStaged = 24576;                  // most keys of a list that LDS holds; longer lists are read from
-                                                          // memory in every pass
+constexpr uint32_t kThRanked = 256;                       // most entries of the k-th entry's bin that are ranked one against the others
 
-// Keys of a list that k_threshold stages for a call whose tensors keep at most kmax entries per side
-// (those with sweeps of their own aside: of theirs, one bin's entries): lists are about 3 k, up to 4 k,
-// on carried keys.  Calls of many tensors want two workgroups on a compute unit.
-__host__ inline uint32_t threshold_staged(uint32_t kmax, bool any_wide) {
-    const uint64_t want = (4ull * kmax + 512ull + 255ull) / 256ull * 256ull, least = any_wide ? 8192ull : 2048ull;
-    return (uint32_t)(want < least ? least : want > kThMaxStaged ? kThMaxStaged : want);
-}
-
-constexpr int kWideThreads = 256;        // sweeps over the lists of tensors that keep very many entries
+constexpr int kWideThreads = 1024;       // sweeps over the lists of tensors that keep very many entries
 constexpr int kMaxWide = 64;             // such tensors per call
 // The call's wide tensors, passed to the kernels by value: a workgroup learns its tensor from the
 // kernel arguments instead of from a load that everything else would have to wait for.
@@ -61,8 +53,8 @@ __device__ __forceinline__ uint32_t exact_limit(uint32_t from, uint32_t kc) {
 // Room for the copied entries of a side: the tensor's own bitmap words, which nothing uses before
 // the positions are written (k_apply).
 __device__ __forceinline__ uint32_t wide_room(const TensorDesc& d) { return d.nchunks * (uint32_t)(kChunkWords / 4); }
-__device__ __forceinline__ uint2* wide_list(const TensorDesc& d, uint32_t* bitmap, int s) {
-    return reinterpret_cast<uint2*>(bitmap + (uint64_t)d.chunk0 * kChunkWords) + (s ? wide_room(d) : 0u);
+__device__ __forceinline__ CandPtr wide_list(const TensorDesc& d, uint32_t* bitmap, int s) {
+    return {bitmap + (uint64_t)d.chunk0 * kChunkWords + (s ? 2u * wide_room(d) : 0u), wide_room(d)};
 }
 
 __device__ __forceinline__ bool cand_kept(uint32_t key, uint32_t idx, uint32_t tau, uint32_t itau) {
@@ -79,19 +71,62 @@ __device__ __forceinline__ long long signed_mantissa(uint32_t key, int s, uint32
     return m;
 }
 
+// A tensor's candidates per side, and where those of each segment of side s start in the list as one piece.
+struct ListCounts {
+    uint32_t p, n;
+    uint32_t segs;
+    uint32_t over;        // some segment has more than it holds (nothing was stored beyond its end)
+    uint32_t cnt[kSegs], before[kSegs];
+    __device__ __forceinline__ uint32_t of(int side) const { return side ? n : p; }
+    // as it was left in LDS, without the segments' figures
+    __device__ __forceinline__ static ListCounts totals(const ListCounts& l) {
+        ListCounts c;
+        c.p = uniform(l.p); c.n = uniform(l.n); c.segs = uniform(l.segs); c.over = uniform(l.over);
+        return c;
+    }
+};
+// Added up from the segments' counters by the first wavefront of a workgroup, for all of them: `to` lies in
+// LDS and holds once the next barrier has been passed.  (Every wavefront by itself: 0.6 us more.)
+__device__ __forceinline__ void count_list(ListCounts& to, const TensorDesc& d, const TensorState* __restrict__ st,
+                                           const unsigned long long* __restrict__ counters, int t, int s, uint32_t flags) {
+    if (threadIdx.x >= 64u) return;
+    const uint32_t lane = threadIdx.x;
+    unsigned long long own = counters[((size_t)t * kSegs + lane % kSegs) * kCounterStride];
+    const uint32_t segs = (flags & kStExact) ? 1u : d.segs;            // (the histogram route's lists are in one piece)
+    if (segs == 1u) own = lane ? 0ull : (unsigned long long)st[t].cand_cnt[0] | ((unsigned long long)st[t].cand_cnt[1] << 32);
+    bool over = false;
+    if (d.cand_cap < d.n) {                            // (uniform; else there is room for every entry)
+        const uint32_t room = seg_before(d, segs, min(lane + 1u, segs)) - seg_before(d, segs, min(lane, segs));
+        over = lane < segs && ((uint32_t)own > room || (uint32_t)(own >> 32) > room);
+    }
+    over = __any(over);
+    static_assert(kSegs == 8, "three steps");
+    unsigned long long upto = own;
+    upto += dpp_fetch<0x111, 0xf>(upto);
+    upto += dpp_fetch<0x112, 0xf>(upto);
+    upto += dpp_fetch<0x114, 0xf>(upto);
+    if (lane < kSegs) {
+        const int half = s ? 32 : 0;
+        to.cnt[lane] = (uint32_t)(own >> half);
+        to.before[lane] = (uint32_t)(upto >> half) - (uint32_t)(own >> half);
+    }
+    if (lane == kSegs - 1u) { to.p = (uint32_t)upto; to.n = (uint32_t)(upto >> 32); to.segs = segs; to.over = over ? 1u : 0u; }
+}
+
 // What a tensor's candidate counts rule out before any selection: true if the tensor cannot be
 // selected from its lists (the thread with `lead` set has then flagged it, for the histogram route
 // or as an error).
-__device__ __forceinline__ bool lists_unusable(const TensorDesc& d, TensorState* __restrict__ st, int t, uint32_t cnt_p,
-                                               uint32_t cnt_n, int pass, bool lead, ResultBlock* __restrict__ result) {
+__device__ __forceinline__ bool lists_unusable(const TensorDesc& d, TensorState* __restrict__ st, int t, const ListCounts& counts,
+                                               int pass, bool lead, ResultBlock* __restrict__ result) {
+    const uint32_t cnt_p = counts.p, cnt_n = counts.n;
     const bool sampled = (d.flags & kDescSampled) != 0u;
     if (cnt_p > d.n || cnt_n > d.n || (sampled && (cnt_p == 0u || cnt_n == 0u))) {
         // (a sampled threshold is the key of an entry of the tensor, so that entry is a candidate)
         if (lead) { st[t].flags = kStFailed; atomicOr(&result->err, kErrInternal); }
         return true;
     }
-    if (cnt_p > d.cand_cap || cnt_n > d.cand_cap) {
-        // compact context: more candidates than a list holds (nothing was stored beyond its end).  The
+    if (counts.over) {
+        // compact context: more candidates than a list (or a segment of it) holds (nothing was stored beyond its end).  The
         // histogram route extracts a tighter set; if that does not fit either, the call fails.
         if (lead) {
             st[t].flags = kStFailed;
@@ -120,33 +155,24 @@ __device__ __forceinline__ uint32_t kept_of_side(const TensorDesc& d, uint32_t c
 
 // Bin of a side key in the window above the side's filter key; the top bin takes everything beyond.
 __device__ __forceinline__ uint32_t window_bin(uint32_t key, uint32_t base) {
-    const uint32_t v = key >> kThShift;
-    const uint32_t o = v >= base ? v - base : 0u;      // (no candidate lies below its filter key)
-    return o < (uint32_t)(kThBins - 1) ? o : (uint32_t)(kThBins - 1);
+    // (no candidate lies below its filter key)
+    return min(max(key >> kThShift, base) - base, (uint32_t)(kThBins - 1));
 }
 
 // Walking the kThBins counts of hist (LDS) from the top bin down: the bin at which the running
 // count reaches need (res[0]; 0xFFFFFFFF if it never does), the count before it (res[1]), the bin's
 // own count (res[3]), and the bin at which the running count reaches rank2 (res[2], or 0xFFFFFFFF;
 // rank2 = 0 looks for none).  res[0] and res[2] must hold 0xFFFFFFFF when the first barrier is
-// reached.  The counts are zero again afterwards.  c: the calling thread's counts, of the bins
-// kThBins-1 - (threadIdx * size), downwards.  Two barriers.
-template <int NT>
-__device__ __forceinline__ void pick_bin(uint32_t* hist, uint32_t need, uint32_t rank2, uint32_t* scratch, uint32_t* res,
-                                         uint32_t (&c)[kThBins / NT]) {
-    constexpr int PER = kThBins / NT;
-    static_assert(PER % 4 == 0 && NT / 64 <= 16, "16-byte pieces; one row of lanes holds the wavefronts' sums");
-    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+// reached.  The counts are zero again afterwards.  Two barriers.  (All 1024 threads, four bins each: one
+// 16-byte piece of LDS per thread, without bank conflicts; by 256 threads with sixteen bins 1.6 us instead of 0.7.)
+__device__ __forceinline__ void pick_bin(uint32_t* hist, uint32_t need, uint32_t rank2, uint32_t* scratch, uint32_t* res) {
+    static_assert(kThBins == 4 * kThThreads && kThThreads / 64 == 16, "16-byte pieces; one row of lanes holds the wavefronts' sums");
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     uint4* const h4 = reinterpret_cast<uint4*>(hist);
-    uint32_t sum = 0u;
-#pragma unroll
-    for (int q = 0; q < PER / 4; ++q) {
-        const int at = kThBins / 4 - 1 - (tid * (PER / 4) + q);
-        const uint4 v = h4[at];
-        h4[at] = make_uint4(0u, 0u, 0u, 0u);
-        c[4 * q] = v.w; c[4 * q + 1] = v.z; c[4 * q + 2] = v.y; c[4 * q + 3] = v.x;
-        sum += v.x + v.y + v.z + v.w;
-    }
+    const int piece = kThBins / 4 - 1 - tid;
+    const uint4 v = h4[piece];
+    h4[piece] = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t sum = v.x + v.y + v.z + v.w;
     const uint32_t inc = wave_incl_sum(sum);
     if (lane == 63) scratch[w] = inc;
     __syncthreads();
@@ -158,11 +184,12 @@ __device__ __forceinline__ void pick_bin(uint32_t* hist, uint32_t need, uint32_t
     cum += dpp_fetch<0x118, 0xf>(cum);
     cum = (uint32_t)__builtin_amdgcn_readlane((int)cum, 15) + inc - sum;
     if ((cum < need && need <= cum + sum) || (cum < rank2 && rank2 <= cum + sum)) {
-        const uint32_t top = (uint32_t)(kThBins - 1 - tid * PER);
+        const uint32_t c[4] = {v.w, v.z, v.y, v.x};
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            if (cum < need && need <= cum + c[j]) { res[0] = top - (uint32_t)j; res[1] = cum; res[3] = c[j]; }
-            if (cum < rank2 && rank2 <= cum + c[j]) res[2] = top - (uint32_t)j;
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t bin = (uint32_t)(4 * piece + 3 - j);
+            if (cum < need && need <= cum + c[j]) { res[0] = bin; res[1] = cum; res[3] = c[j]; }
+            if (cum < rank2 && rank2 <= cum + c[j]) res[2] = bin;
             cum += c[j];
         }
     }
@@ -174,10 +201,15 @@ struct ThresholdShared {
         uint32_t hist[kThBins];
         long long acc[256];                            // per-exponent integer sums
     };
+    uint32_t found[kThRanked];                         // the entries of the k-th entry's bin
+    uint32_t ranks[kThRanked];
+    uint32_t n_found;
     uint32_t scratch[kThThreads / 64];
     uint32_t res[2][4];
+    uint32_t rank[3];                                  // the threshold, entries of the bin beyond it, and at or beyond it
     double dsum[kThThreads / 64];
     long long isum[kThThreads / 64];
+    ListCounts counts;
     uint32_t spread;                                   // some kept entry is too far beyond the threshold for the fp64 sum
 };
 
@@ -204,39 +236,42 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // One workgroup of 1024 threads per (tensor, side); `order` lists the tensors by decreasing size
 // (null: as they come).  pass 0: every tensor no earlier kernel has finished or flagged; pass 1:
 // tensors handed over (histogram route, or left by the streaming kernel).
-// The keys of a list of up to `staged` candidates are copied to LDS (the index is only read, from
-// memory, for entries equal to the threshold if some of them are dropped).  The kernel is a chain of
-// short dependent steps and every workgroup runs its code once, from a cold instruction cache: a
-// tensor with 64 entries takes as long as one with 10,000 candidates, and what helps is less code.
-// So both counting passes share theirs, loops stay rolled, and what is rare stands at the end (34 KB of
-// unrolled code with the keys in registers: 18 us on 161 tensors of 25.6e6 entries at p = 0.001, 12.9
-// us on one of 4.2e6; this form, 14 KB: 10.6 and 9.4 us; 8192-candidate lists take 8.4 us, 64 entries 5.5).
-// Two workgroups fit a compute unit (64 KiB of LDS each at p = 0.001, at most 64 registers).
+// Every workgroup runs its code once, and for most it is a chain of short dependent steps: 1.2 us to the
+// counts, 1.3 to the list and its histogram, 0.8 to the bin, 0.5 for the second pass, 0.6 for the ranks, 0.7 to
+// the end, whatever the list.  Long lists are bound by the LDS histogram (14 cycles per 64 keys) and by the
+// fp64 sums: 10.2 us on 12,500 entries, 12.5 on 27,000, 25 on 61,000 (with the sweeps of k_wide_count and
+// k_wide_collect before a workgroup that staged keys in LDS: 19 us in all on 27,000, 37 on 61,000).  Keys stay in
+// registers between the passes where a list has up to sixteen per thread; longer ones are read again.  (Tried:
+// 32 per thread, the next loads on their way during a batch, two copies of the histogram: no difference.)
 // --------------------------------------------------------------------------
 __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
-        const uint2* __restrict__ cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
-        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int carry, uint32_t staged, ResultBlock* __restrict__ result) {
+        const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
+        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int carry, ResultBlock* __restrict__ result) {
     __shared__ __attribute__((aligned(16))) ThresholdShared sh;
-    extern __shared__ uint32_t keys[];                 // `staged` of them
     SBC_TS(1, 0);
     const int s = (int)(blockIdx.x & 1u), tid = threadIdx.x;
     const int t = order ? (int)order[blockIdx.x >> 1] : (int)(blockIdx.x >> 1);
     const TensorDesc d = desc[t];
     const uint32_t flags = st[t].flags;
-    const uint32_t cnt_p = st[t].cand_cnt[0], cnt_n = st[t].cand_cnt[1];
     const uint32_t lo_key = st[t].lo_key[s], expect = st[t].expect[s];
     const int prev_side = st[t].side;
     {
         uint4* const z = reinterpret_cast<uint4*>(sh.hist);
         static_assert(kThBins == 4 * kThThreads, "four bins per thread");
         z[tid] = make_uint4(0u, 0u, 0u, 0u);
+        if (tid < (int)kThRanked) { sh.found[tid] = 0u; sh.ranks[tid] = 0u; }
         if (tid < 8) (&sh.res[0][0])[tid] = 0xFFFFFFFFu;
         if (tid == 8) sh.spread = 0u;
+        if (tid == 9) sh.n_found = 0u;
     }
     if (pass == 0 ? (flags & (kStInlineDone | kStDeferred | kStFailed)) != 0u : (flags & (kStExact | kStDeferred)) == 0u) return;
-    if (lists_unusable(d, st, t, cnt_p, cnt_n, pass, s == 0 && tid == 0, result)) return;
-    const uint32_t full_cnt = s ? cnt_n : cnt_p;
+    count_list(sh.counts, d, st, counters, t, s, flags);
+    __syncthreads();                                   // (and the histogram's counts are zero)
+    SBC_TS(1, 1);
+    const ListCounts counts = ListCounts::totals(sh.counts);
+    if (lists_unusable(d, st, t, counts, pass, s == 0 && tid == 0, result)) return;
+    const uint32_t full_cnt = counts.of(s);
     const uint32_t kc = kept_of_side(d, full_cnt);
     const bool pick = kc < full_cnt || !(d.flags & kDescSampled);      // else every candidate is kept
 
@@ -250,42 +285,58 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         reinterpret_cast<uint4*>(whist + (size_t)w2 * kThBins)[tid] = make_uint4(0u, 0u, 0u, 0u);
     }
     const bool wide = wst.ok != 0u;
-    const uint2* __restrict__ list = wide ? wide_list(d, bitmap, s) : cand + d.cand_off + (s ? d.cand_cap : 0u);
-    const uint32_t cnt = wide ? wst.count : full_cnt;
+    // The list: this thread takes every step-th four of the `mine_cnt` entries from `list` on, starting with its own
+    // (a list in segments: two wavefronts each).
+    const uint32_t segs = wide ? 1u : counts.segs;
+    CandPtr list = wide ? wide_list(d, bitmap, s) : cand + d.cand_off + (s ? d.cand_cap : 0u);
+    uint32_t mine_cnt = wide ? wst.count : full_cnt, step_by = kThThreads, first = (uint32_t)tid;
+    if (segs > 1u) {                                   // uniform
+        const uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane(tid / (int)(kThThreads / kSegs));
+        mine_cnt = uniform(sh.counts.cnt[g]);
+        list = list + seg_before(d, segs, g);
+        step_by = kThThreads / kSegs;
+        first = (uint32_t)tid % (kThThreads / kSegs);
+    }
     const uint32_t base = lo_key >> kThShift;
-    const bool in_lds = cnt <= staged;
-    __syncthreads();                                   // the counts are zero
-    if (in_lds) {
-        // eight loads of a thread in flight at a time; the window's counts in the same sweep
-        const uint32_t below = pick && !wide ? (uint32_t)kThBins : 0u;
-        for (uint32_t i0 = tid; i0 < cnt; i0 += 8u * kThThreads) {
-            uint32_t x[8];
+    // Sixteen keys of a thread at a time, in four loads that are in flight together; 0, which is the key of no
+    // number, where there is none.  (The last four may read up to three keys beyond the list: the arrays have
+    // room for them.)
+    constexpr int kVecs = 4;
+    const u32x4_any* __restrict__ vecs = reinterpret_cast<const u32x4_any*>(list.key);
+    const uint32_t wave_first = uniform(first);        // (the wavefront's first lane's)
+    u32x4_any held[kVecs];
+    auto load = [&](uint32_t p0) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) { const uint32_t i = i0 + (uint32_t)j * kThThreads; x[j] = list[i < cnt ? i : 0u].x; }
+        for (int j = 0; j < kVecs; ++j) {
+            const uint32_t p = p0 + (uint32_t)j * step_by;
+            held[j] = 0u;
+            if (4u * p < mine_cnt) held[j] = vecs[p];
+        }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) { 
-                const uint32_t i = i0 + (uint32_t)j * kThThreads;
-                if (i < cnt) {
-                    keys[i] = x[j];
-                    const uint32_t o = window_bin(x[j], base);
-                    if (o < below) atomicAdd(&sh.hist[o], 1u);
-                }
+        for (int j = 0; j < kVecs; ++j) {
+            const uint32_t i = 4u * (p0 + (uint32_t)j * step_by);
+            if (i < mine_cnt && i + 4u > mine_cnt) {   // (one lane of a list)
+                held[j].w = 0u;
+                if (i + 2u >= mine_cnt) held[j].z = 0u;
+                if (i + 1u >= mine_cnt) held[j].y = 0u;
             }
         }
-    }
-    auto stream = [&](auto f) {                        // f(entry) for this thread's share of the list in memory
-#pragma unroll 4
-        for (uint32_t i = tid; i < cnt; i += kThThreads) f(list[i]);
     };
-    auto for_keys = [&](auto f) {                      // f(key): a thread sees the keys it has staged itself
-        if (in_lds) {
-#pragma unroll 4
-            for (uint32_t i = tid; i < cnt; i += kThThreads) f(keys[i]);
-        } else {
-            stream([&](const uint2& e) { f(e.x); });
+    const bool once = mine_cnt <= 4u * (uint32_t)kVecs * step_by;      // the keys stay in `held`
+    auto for_fours = [&](bool again, auto f) {         // f(four keys, entries from the first lane's on) for the thread's share
+        for (uint32_t w0 = wave_first, p0 = first; 4u * w0 < mine_cnt; w0 += (uint32_t)kVecs * step_by, p0 += (uint32_t)kVecs * step_by) {
+            if (!again || !once) load(p0);
+#pragma unroll
+            for (int j = 0; j < kVecs; ++j) {
+                const uint32_t i = 4u * (w0 + (uint32_t)j * step_by);
+                if (i < mine_cnt) f(held[j], mine_cnt - i);            // uniform
+            }
         }
     };
-    SBC_TS(1, 1);                                      // list read
+    auto stream = [&](auto f) {                        // f(entry), from memory (only where that is rare)
+#pragma nounroll
+        for (uint32_t i = first; i < mine_cnt; i += step_by) f(list.get(i));
+    };
 
     uint32_t tau = lo_key, itau = 0xFFFFFFFFu, keep = 0u, ties = 0u;
     // Filter key a following call may start from instead of sampling.  With the residual carried
@@ -302,51 +353,104 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     // S, the sum of the kept values (negated on the negative side), is an fp64 sum that is exact in any
     // order, as long as no kept value reaches `limit` (else it is added up again from integers)
     double mine = 0.0;
-    uint32_t limit = 0u;
-    auto add = [&](uint32_t k) {
-        mine += (double)__uint_as_float(k & 0x7FFFFFFFu);
-        if (k >= limit) sh.spread = 1u;
+    uint32_t limit = 0u, most = 0u;
+    auto add = [&](uint32_t k, bool counts_in) {
+        uint32_t x = counts_in ? k : 0u;
+        asm("" : "+v"(x));                             // (chosen as 32 bits, not as the 64 that it is converted to)
+        mine += (double)fabsf(__uint_as_float(x));
+        most = max(most, k);                           // (what is not kept lies below the limit)
     };
     bool ok = true, placed = true;
-    if (pick) {
-        uint32_t need = kc, prefix = 0u, c[kThBins / kThThreads];
-        if (wide) { need = wst.need; prefix = wst.prefix; }
-#pragma nounroll
-        for (int step = wide ? 1 : 0; step < 2; ++step) {
-            // step 0: leading bits, in the window; step 1: the other bits of the entries in the bin `prefix`,
-            // and the sum of the entries beyond it
-            const uint32_t from = step ? prefix << kThShift : base, cap = step ? 0xFFFFFFFFu : (uint32_t)(kThBins - 1);
-            const uint32_t beyond = step ? from + (uint32_t)(kThBins - 1) : 0xFFFFFFFFu;
-            const int shift = step ? 0 : kThShift;
-            limit = exact_limit(from, kc);
-            if (step || !in_lds) for_keys([&](uint32_t k) {            // (lists in LDS: counted when they were read)
-                const uint32_t o = min((k >> shift) - from, cap);
-                if (o < (uint32_t)kThBins) atomicAdd(&sh.hist[o], 1u);
-                else if (k > beyond) add(k);
-            });
-            __syncthreads();
-            SBC_TS(1, 2 + 2 * step);
-            uint32_t* const r = sh.res[step];
-            pick_bin<kThThreads>(sh.hist, need, carry && !step ? rank2 : 0u, sh.scratch, r, c);
-            const uint32_t digit = r[0];
-            if (step == 0) {
-                next_bin = r[2];
-                if (digit >= (uint32_t)(kThBins - 1)) { placed = false; break; }   // beyond the window (uniform)
-                prefix = base + digit;
-            } else {
-                ok = digit != 0xFFFFFFFFu;
-                tau = (prefix << kThShift) | (digit & (uint32_t)(kThBins - 1));
-                ties = r[3];
-                // the bin's entries beyond tau, from their counts
+    uint32_t need = kc, prefix = 0u, in_bin = 0u;
+    if (wide) {
+        need = wst.need; prefix = wst.prefix;
+    } else if (pick) {
+        // (the places without an entry are counted, too, in whatever bin the key 0 has, and taken out again)
+        uint32_t empty = 0u;
+        for_fours(false, [&](const u32x4_any& k, uint32_t left) {
 #pragma unroll
-                for (int j = 0; j < kThBins / kThThreads; ++j) {
-                    const uint32_t k = from + (uint32_t)(kThBins - 1 - tid * (kThBins / kThThreads) - j);
-                    if (c[j] != 0u && k > tau) mine += (double)c[j] * (double)__uint_as_float(k & 0x7FFFFFFFu);
+            for (int e = 0; e < 4; ++e) atomicAdd(&sh.hist[min((k[e] >> kThShift) - base, (uint32_t)(kThBins - 1))], 1u);
+            empty += 256u - min(left, 256u);
+        });
+        if (empty && (tid & 63) == 0) atomicSub(&sh.hist[min(0u - base, (uint32_t)(kThBins - 1))], empty);
+        __syncthreads();
+        SBC_TS(1, 2);
+        pick_bin(sh.hist, need, carry ? rank2 : 0u, sh.scratch, sh.res[0]);
+        const uint32_t digit = uniform(sh.res[0][0]);
+        next_bin = uniform(sh.res[0][2]);
+        in_bin = uniform(sh.res[0][3]);
+        prefix = base + digit;
+        placed = digit < (uint32_t)(kThBins - 1);      // else beyond the window (uniform)
+        if (placed) need -= uniform(sh.res[0][1]);
+        SBC_TS(1, 3);
+    }
+    if (placed) {
+        // the entries beyond the bin (if all are kept: every one, and there is no bin), and those in it
+        const uint32_t from = pick ? prefix << kThShift : 0xFFFFF000u, beyond = pick ? from + (uint32_t)(kThBins - 1) : 0u;
+        const bool few = !wide && in_bin <= kThRanked; // uniform
+        limit = exact_limit(pick ? from : tau, kc);
+        for_fours(pick && !wide, [&](const u32x4_any& k, uint32_t) {
+            // (one test for four entries: those of the bin are few)
+            if (min(min(k.x - from, k.y - from), min(k.z - from, k.w - from)) < (uint32_t)kThBins) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (k[e] - from < (uint32_t)kThBins) {
+                        if (few) sh.found[atomicAdd(&sh.n_found, 1u)] = k[e];
+                        else atomicAdd(&sh.hist[k[e] - from], 1u);
+                    }
                 }
             }
-            need -= r[1];
-            SBC_TS(1, 3 + 2 * step);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(k[e], k[e] > beyond);
+        });
+        __syncthreads();
+        SBC_TS(1, 4);
+        if (few) {
+            // (exactly in_bin of them.)  How many of the others each one has above it, and at least at it.
+            auto both_of = [&](uint32_t me, uint32_t from_j, uint32_t to_j) {         // above in the low half, at least in the high half
+                uint32_t both = 0u;
+                for (uint32_t j = from_j; j < to_j; j += 4u) {         // (zeros behind the last one)
+                    const uint4 o = *reinterpret_cast<const uint4*>(sh.found + j);
+                    both += (o.x > me ? 1u : 0u) + (o.y > me ? 1u : 0u) + (o.z > me ? 1u : 0u) + (o.w > me ? 1u : 0u);
+                    both += (o.x >= me ? 65536u : 0u) + (o.y >= me ? 65536u : 0u) + (o.z >= me ? 65536u : 0u) + (o.w >= me ? 65536u : 0u);
+                }
+                return both;
+            };
+            const bool shared = in_bin > 16u;          // uniform
+            if (shared) {
+                // groups of one, two or four wavefronts, which hold all of them, take a share of the others each
+                const uint32_t lg = in_bin <= 64u ? 0u : in_bin <= 128u ? 1u : 2u, wv = uniform((uint32_t)tid >> 6), g = wv >> lg;
+                const uint32_t i = ((wv & ((1u << lg) - 1u)) << 6) + (uint32_t)(tid & 63);
+                const uint32_t share = ((in_bin >> (4u - lg)) + 4u) & ~3u;            // (times the number of groups: in_bin at the least)
+                if (i < in_bin) {
+                    const uint32_t both = both_of(sh.found[i], g * share, min(in_bin, (g + 1u) * share));
+                    if (both) atomicAdd(&sh.ranks[i], both);
+                }
+                __syncthreads();
+            }
+            if ((uint32_t)tid < in_bin) {
+                const uint32_t me = sh.found[tid], both = shared ? sh.ranks[tid] : both_of(me, 0u, in_bin);
+                const uint32_t above = both & 0xFFFFu, at_least = both >> 16;
+                if (above < need && need <= at_least) { sh.rank[0] = me; sh.rank[1] = above; sh.rank[2] = at_least; }   // (equal entries write the same)
+                if (at_least < need) mine += (double)__uint_as_float(me & 0x7FFFFFFFu);
+            }
+        } else if (pick) {
+            pick_bin(sh.hist, need, 0u, sh.scratch, sh.res[1]);
+            const uint32_t digit = uniform(sh.res[1][0]);
+            ok = digit != 0xFFFFFFFFu;
+            tau = from | (digit & (uint32_t)(kThBins - 1));
+            ties = uniform(sh.res[1][3]);
+            need -= uniform(sh.res[1][1]);
+            stream([&](const uint2& e) { add(e.x, e.x > tau && e.x <= beyond); });
         }
+        if (limit == 0u || most >= limit) sh.spread = 1u;
+        mine = wave_sum_f64(mine);
+        if ((tid & 63) == 63) sh.dsum[tid >> 6] = mine;
+        __syncthreads();
+        if (few && pick) { tau = uniform(sh.rank[0]); need -= uniform(sh.rank[1]); ties = uniform(sh.rank[2]) - uniform(sh.rank[1]); }
+        SBC_TS(1, 5);
+    }
+    if (pick) {
         keep = need;
         if (__builtin_expect(!placed || (ok && keep < ties), 0)) {     // uniform
             // tau from the top, for what the window cannot place (rare); then, if fewer than all entries equal
@@ -367,11 +471,11 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
                             atomicAdd(&sh.hist[(v >> shift) & ((1u << bits) - 1u)], 1u);
                     });
                     __syncthreads();
-                    pick_bin<kThThreads>(sh.hist, r, 0u, sh.scratch, sh.res[0], c);
-                    const uint32_t digit = sh.res[0][0];
+                    pick_bin(sh.hist, r, 0u, sh.scratch, sh.res[0]);
+                    const uint32_t digit = uniform(sh.res[0][0]);
                     if (digit == 0xFFFFFFFFu) { ok = false; break; }   // uniform
-                    r -= sh.res[0][1];
-                    same = sh.res[0][3];
+                    r -= uniform(sh.res[0][1]);
+                    same = uniform(sh.res[0][3]);
                     found = (found << bits) | digit;
                 }
                 if (mode) itau = ~found;
@@ -383,19 +487,18 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
             return;
         }
     }
-    if (!pick || !placed) {                            // uniform: added up here, with the final threshold
-        const bool all = !pick;
+    if (!placed) {                                     // uniform: added up here, with the threshold that was found at last
         limit = exact_limit(tau, kc);
-        if (!wide) for_keys([&](uint32_t k) { if (k > tau || all) add(k); });
+        stream([&](const uint2& e) { add(e.x, e.x > tau); });
+        if (limit == 0u || most >= limit) sh.spread = 1u;
+        mine = wave_sum_f64(mine);
+        if ((tid & 63) == 63) sh.dsum[tid >> 6] = mine;
+        __syncthreads();
     }
-    if (tid == 0 && limit == 0u) sh.spread = 1u;
-    mine = wave_sum_f64(mine);
-    if ((tid & 63) == 63) sh.dsum[tid >> 6] = mine;
-    __syncthreads();
     const uint32_t e_tau = max((tau >> 23) & 0xFFu, 1u);               // (tau's fp32 exponent, if it is positive)
     double S = last_lane(wave_sum_f64((tid & 63) < kThThreads / 64 ? sh.dsum[tid & 63] : 0.0)) +
                (double)keep * (double)__uint_as_float(tau & 0x7FFFFFFFu);
-    if (__builtin_expect(sh.spread != 0u, 0)) {        // uniform
+    if (__builtin_expect(uniform(sh.spread) != 0u, 0)) {        // uniform
         // Values of both signs, or too far apart: integers, each at the scale of tau's exponent while it fits
         // 64 bits, else one integer per exponent (all read from memory once more).
         const bool common = kc <= 32768u && tau > 0x80000000u, all = !pick;
@@ -440,33 +543,45 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     }
     // many times more candidates than needed: the next call should estimate its keys afresh
     if (full_cnt > loose_limit(d.k, d.n)) raise |= kErrLoose;
-    if (wide) raise |= kErrWide;
+    if (wide || (pass == 0 && placed && (d.flags & (kDescLong | kDescWide)) == kDescLong)) raise |= kErrWide;
     if (raise) atomicOr(&result->err, raise);
     SBC_TS(1, 7);
 }
 
 // --------------------------------------------------------------------------
-// Tensors that keep very many entries (lists too long for one workgroup's registers).  grid
+// Tensors that keep very many entries (lists too long for one workgroup).  grid
 // (workgroups, 2 x wide tensors); a list gets only as many of the workgroups as it has use for: a
 // workgroup adds its counts to the shared histogram bin by bin, and those atomics cost more than
 // the reading when every workgroup has few entries per bin.
 // --------------------------------------------------------------------------
-// Entries that keep a workgroup of a sweep busy (short lists: 1024 each, up to 32 workgroups).  Both
-// sweeps together: 12 us on lists of 30,000 entries (2^20-entry tensor, p = 0.01), 23 us on ten tensors
-// with up to 70,000 each, 146 us on 3e6 (1.5e9 entries, p = 0.001; 160 us with 2048 each).
-constexpr uint32_t kWidePerWorkgroup = 4096;
+// Entries that keep a workgroup of a sweep busy.  Eight workgroups take a list of up to 131072 entries, each
+// a segment: what a sweep over short lists costs is above all the workgroups' additions to the shared
+// histogram (20 lists by 32 workgroups with 1536 bins each: 8.5 us, by 8: 2.7 us).  3.9e6 entries a side
+// (1.5e9-entry tensor): 29 + 34 us; 69 + 62 with workgroups of 256 threads and 4096 entries.
+constexpr uint32_t kWidePerWorkgroup = 16384, kWideFew = 8;
 constexpr uint32_t kWideFound = 512;                   // entries of the k-th entry's bin that a workgroup collects in LDS
 
 __device__ __forceinline__ uint32_t wide_workgroups(uint32_t cnt) {
-    const uint32_t few = min((cnt + 1023u) / 1024u, 32u), many = (cnt + kWidePerWorkgroup - 1u) / kWidePerWorkgroup;
-    const uint32_t want = few > many ? few : many;
-    return want < gridDim.x ? (want ? want : 1u) : gridDim.x;
+    static_assert(kWideFew % kSegs == 0, "the same number for every segment");
+    const uint32_t want = max((cnt / kWidePerWorkgroup + kWideFew - 1u) / kWideFew * kWideFew, kWideFew);
+    return min(want, gridDim.x);                       // (gridDim.x: a multiple of kWideFew)
 }
 
 // The lists can be selected from, and the subsampled variant does not keep all of this one.
-__device__ __forceinline__ bool wide_applies(const TensorDesc& d, uint32_t cnt_p, uint32_t cnt_n) {
-    if (cnt_p > d.cand_cap || cnt_n > d.cand_cap) return false;
-    return (d.flags & kDescSampled) ? cnt_p >= 1u && cnt_n >= 1u : cnt_p >= d.k && cnt_n >= d.k;
+__device__ __forceinline__ bool wide_applies(const TensorDesc& d, const ListCounts& c) {
+    if (c.over) return false;
+    return (d.flags & kDescSampled) ? c.p >= 1u && c.n >= 1u : c.p >= d.k && c.n >= d.k;
+}
+
+// f(key, place in the list) for a thread's share of a side's list, which nb of the workgroups (of each segment,
+// nb / segs) take.
+template <int UNROLL, typename F>
+__device__ __forceinline__ void sweep_list(const TensorDesc& d, const ListCounts& c, uint32_t segs, int s, uint32_t nb, const CandPtr cand, F f) {
+    const uint32_t g = blockIdx.x % segs, cnt = uniform(c.cnt[g]);
+    const CandPtr list = cand + d.cand_off + (s ? d.cand_cap : 0u) + seg_before(d, segs, g);
+    const uint64_t stride = (uint64_t)(nb / segs) * kWideThreads;
+#pragma unroll UNROLL
+    for (uint64_t i = (uint64_t)(blockIdx.x / segs) * kWideThreads + threadIdx.x; i < cnt; i += stride) f(list.key[i], list + i);
 }
 
 // k_wide_count: window histogram of a side's list.  (Counting where the streaming kernel stores the
@@ -475,17 +590,23 @@ __device__ __forceinline__ bool wide_applies(const TensorDesc& d, uint32_t cnt_p
 // times the streaming kernel's time on Gaussian data.)
 __global__ __launch_bounds__(kWideThreads) void k_wide_count(
         const TensorDesc* __restrict__ desc, const WideIds wide_ids, const TensorState* __restrict__ st,
-        const uint2* __restrict__ cand, uint32_t* __restrict__ whist, long long* __restrict__ wacc,
+        const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ whist, long long* __restrict__ wacc,
         WideState* __restrict__ ws) {
     __shared__ __attribute__((aligned(16))) uint32_t hist[kThBins];
+    __shared__ ListCounts counts_sh;
     const int w = blockIdx.y >> 1, s = blockIdx.y & 1, tid = threadIdx.x;
     const int t = (int)wide_ids.id[w];
     const TensorDesc d = desc[t];
-    const uint32_t cnt_p = st[t].cand_cnt[0], cnt_n = st[t].cand_cnt[1];
-    const uint32_t cnt = s ? cnt_n : cnt_p;
+    count_list(counts_sh, d, st, counters, t, s, 0u);
     const uint32_t base = st[t].lo_key[s] >> kThShift;
+    uint4* const h4 = reinterpret_cast<uint4*>(hist);
+#pragma unroll
+    for (int i = 0; i < kThBins / 4 / kWideThreads; ++i) h4[i * kWideThreads + tid] = make_uint4(0u, 0u, 0u, 0u);
+    __syncthreads();
+    const ListCounts counts = ListCounts::totals(counts_sh);
+    const uint32_t cnt = counts.of(s);
     if (blockIdx.x == 0) {                             // the call before this one has read its sums
-        wacc[(size_t)blockIdx.y * 256 + tid] = 0ll;
+        if (tid < 256) wacc[(size_t)blockIdx.y * 256 + tid] = 0ll;
         if (tid == 0) {
             WideState z;
             z.ok = 0u; z.prefix = 0u; z.need = 0u; z.count = 0u; z.next_rank_bin = 0xFFFFFFFFu;
@@ -493,18 +614,10 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_count(
             ws[blockIdx.y] = z;
         }
     }
-    if (!wide_applies(d, cnt_p, cnt_n) || kept_of_side(d, cnt) == cnt) return;      // uniform
+    if (!wide_applies(d, counts) || kept_of_side(d, cnt) == cnt) return;      // uniform
     const uint32_t nb = wide_workgroups(cnt);
     if (blockIdx.x >= nb) return;
-    const uint2* __restrict__ list = cand + d.cand_off + (s ? d.cand_cap : 0u);
-    uint4* const h4 = reinterpret_cast<uint4*>(hist);
-#pragma unroll
-    for (int i = 0; i < kThBins / 4 / kWideThreads; ++i) h4[i * kWideThreads + tid] = make_uint4(0u, 0u, 0u, 0u);
-    __syncthreads();
-    const uint64_t stride = (uint64_t)nb * kWideThreads;
-#pragma unroll 8
-    for (uint64_t i = (uint64_t)blockIdx.x * kWideThreads + tid; i < cnt; i += stride)
-        atomicAdd(&hist[window_bin(list[i].x, base)], 1u);
+    sweep_list<8>(d, counts_sh, counts.segs, s, nb, cand, [&](uint32_t key, const CandPtr) { atomicAdd(&hist[window_bin(key, base)], 1u); });
     __syncthreads();
     uint32_t* __restrict__ g = whist + (size_t)blockIdx.y * kThBins;
     for (int i = tid; i < kThBins; i += kWideThreads) {
@@ -518,12 +631,13 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_count(
 // entries of that bin are copied out and those beyond it are added up.
 __global__ __launch_bounds__(kWideThreads) void k_wide_collect(
         const TensorDesc* __restrict__ desc, const WideIds wide_ids, const TensorState* __restrict__ st,
-        const uint2* __restrict__ cand, uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ whist,
+        const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const uint32_t* __restrict__ whist,
         long long* __restrict__ wacc, WideState* __restrict__ ws) {
     __shared__ __attribute__((aligned(16))) uint32_t hist[kThBins];
     __shared__ long long acc[256];
     __shared__ uint2 found[kWideFound];
     __shared__ uint32_t scratch[kWideThreads / 64], res[4], n_found, found_at;
+    __shared__ ListCounts counts_sh;
     const int w = blockIdx.y >> 1, s = blockIdx.y & 1, tid = threadIdx.x;
     const int t = (int)wide_ids.id[w];
     // (the window's counts are asked for together with the descriptor and the state, before those say
@@ -535,25 +649,24 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_collect(
         for (int i = 0; i < kThBins / 4 / kWideThreads; ++i) mine[i] = g4[i * kWideThreads + tid];
     }
     const TensorDesc d = desc[t];
-    const uint32_t cnt_p = st[t].cand_cnt[0], cnt_n = st[t].cand_cnt[1];
-    const uint32_t cnt = s ? cnt_n : cnt_p;
+    count_list(counts_sh, d, st, counters, t, s, 0u);
     const uint32_t base = st[t].lo_key[s] >> kThShift;
-    if (!wide_applies(d, cnt_p, cnt_n)) return;        // k_threshold flags the tensor
-    const uint32_t nb = wide_workgroups(cnt);
-    if (blockIdx.x >= nb) return;
-    const uint32_t kc = kept_of_side(d, cnt);
-    const bool all = (d.flags & kDescSampled) && kc == cnt;
 #pragma unroll
     for (int i = 0; i < kThBins / 4 / kWideThreads; ++i) reinterpret_cast<uint4*>(hist)[i * kWideThreads + tid] = mine[i];
-    acc[tid] = 0ll;
+    if (tid < 256) acc[tid] = 0ll;
     if (tid < 4) res[tid] = 0xFFFFFFFFu;
     if (tid == 4) n_found = 0u;
     __syncthreads();
+    const ListCounts counts = ListCounts::totals(counts_sh);
+    if (!wide_applies(d, counts)) return;              // k_threshold flags the tensor
+    const uint32_t cnt = counts.of(s), nb = wide_workgroups(cnt);
+    if (blockIdx.x >= nb) return;
+    const uint32_t kc = kept_of_side(d, cnt);
+    const bool all = (d.flags & kDescSampled) && kc == cnt;
     uint32_t prefix = 0u;
     if (!all) {
-        uint32_t c[kThBins / kWideThreads];
-        pick_bin<kWideThreads>(hist, kc, carried_rank(kc), scratch, res, c);
-        const uint32_t digit = res[0];
+        pick_bin(hist, kc, carried_rank(kc), scratch, res);
+        const uint32_t digit = uniform(res[0]);
         // beyond the window, or more entries in the bin than there is room for (equal values): k_threshold
         // then works on the whole list
         if (digit >= (uint32_t)(kThBins - 1) || res[3] > wide_room(d)) {       // uniform
@@ -568,35 +681,32 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_collect(
         }
     }
     if (blockIdx.x == 0 && tid == 0) ws[blockIdx.y].ok = 1u;
-    uint2* __restrict__ out = wide_list(d, bitmap, s);
+    const CandPtr out = wide_list(d, bitmap, s);
     const uint32_t room = wide_room(d);
-    const uint2* __restrict__ list = cand + d.cand_off + (s ? d.cand_cap : 0u);
-    const uint64_t stride = (uint64_t)nb * kWideThreads;
     const uint32_t from = all ? st[t].lo_key[s] : prefix << kThShift, limit = exact_limit(from, kc);
     double near = 0.0;
-#pragma unroll 4
-    for (uint64_t i = (uint64_t)blockIdx.x * kWideThreads + tid; i < cnt; i += stride) {
-        const uint2 e = list[i];
-        const uint32_t v = e.x >> kThShift;
+    sweep_list<4>(d, counts_sh, counts.segs, s, nb, cand, [&](uint32_t key, const CandPtr entry) {
+        const uint32_t v = key >> kThShift;
         if (all || v > prefix) {
-            if (e.x < limit) {
-                near += (double)__uint_as_float(e.x & 0x7FFFFFFFu);
+            if (key < limit) {
+                near += (double)__uint_as_float(key & 0x7FFFFFFFu);
             } else {
                 uint32_t ex;
-                const long long m = signed_mantissa(e.x, s, ex);
+                const long long m = signed_mantissa(key, s, ex);
                 if (m != 0ll && ex < 255u) atomicAdd(reinterpret_cast<unsigned long long*>(&acc[ex]), (unsigned long long)m);
             }
         } else if (v == prefix) {
             // (a workgroup's few go out together: one atomic on the shared counter instead of one each,
             // which queue up there for about 60 ns apiece)
             const uint32_t q = atomicAdd(&n_found, 1u);
+            const uint2 e = entry.get(0);
             if (q < kWideFound) found[q] = e;
             else {
                 const uint32_t at = atomicAdd(&ws[blockIdx.y].count, 1u);
-                if (at < room) out[at] = e;
+                if (at < room) out.put(at, e.x, e.y);
             }
         }
-    }
+    });
     near = wave_sum_f64(near);
     if ((tid & 63) == 63 && near != 0.0) {
         // (an integer at the scale of from's exponent, below 2^53)
@@ -609,9 +719,9 @@ __global__ __launch_bounds__(kWideThreads) void k_wide_collect(
         if (tid == 0) found_at = atomicAdd(&ws[blockIdx.y].count, mine_found);
         __syncthreads();
         for (uint32_t i = tid; i < mine_found; i += kWideThreads)
-            if (found_at + i < room) out[found_at + i] = found[i];
+            if (found_at + i < room) out.put(found_at + i, found[i].x, found[i].y);
     }
-    const long long v = acc[tid];
+    const long long v = tid < 256 ? acc[tid] : 0ll;
     if (v != 0ll) atomicAdd(reinterpret_cast<unsigned long long*>(&wacc[(size_t)blockIdx.y * 256 + tid]), (unsigned long long)v);
 }
 

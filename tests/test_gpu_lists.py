@@ -1,0 +1,104 @@
+"""Candidate lists and the selection from them at the places where they change their form: lists in one
+piece and in segments, lists that stay in registers and longer ones, bins of the k-th entry from one entry
+to more than are ranked one against the others, lists long enough for sweeps, and a compact context whose
+segment overflows while the list as a whole would not.  Against the oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1805_08768_amd import binding as sbc, synth
+from parity_util import DeviceRun, check_round
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = 8192
+
+
+@pytest.mark.parametrize("chunks,short", [(63, 5), (64, 0), (64, 8191), (65, 1), (71, 17), (72, 0), (80, 4000)])
+def test_lists_in_segments(chunks, short):
+    sizes = [CHUNK * chunks - short, 3000]
+    with DeviceRun(sizes) as run:
+        R = [np.zeros(n, np.float32) for n in sizes]
+        for r in range(3):
+            dWs = [synth.gaussian_update(n, round_=r, tensor=i) for i, n in enumerate(sizes)]
+            if r == 2:                                    # everything interesting in one segment's chunks
+                x = dWs[0].reshape(-1)
+                x[CHUNK * 11:CHUNK * 12] *= 6.0
+                x[CHUNK * 19:CHUNK * 20] *= 6.0
+            res = check_round(run, dWs, R, 0.004, check_decode=(r == 0))
+            R = [x.R_new for x in res]
+
+
+@pytest.mark.parametrize("p", [0.1, 0.13, 0.3])
+def test_list_lengths_around_what_registers_hold(p):
+    """Lists of a single piece: all of them longer than the 16384 keys held, one just below, one beyond."""
+    sizes = [120001, 131072, 200003, 16384, 16400]
+    with DeviceRun(sizes) as run:
+        R = [np.zeros(n, np.float32) for n in sizes]
+        for r in range(2):
+            dWs = [synth.gaussian_update(n, round_=r, tensor=i) for i, n in enumerate(sizes)]
+            R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=False)]
+
+
+@pytest.mark.parametrize("m", [1, 2, 16, 17, 63, 64, 65, 128, 129, 255, 256, 257, 300, 1500])
+@pytest.mark.parametrize("ties", [False, True])
+def test_entries_in_the_bin_of_the_kth(m, ties):
+    """m entries of each side share the leading 20 key bits with the k-th, which is the middle one of them."""
+    n, p = 60000, 0.03
+    k = int(np.floor(p * n))
+    g = np.random.default_rng(m)
+    x = (g.standard_normal(n) * 1e-3).astype(np.float32)
+    at = g.permutation(n)
+    base = np.float32(1.5).view(np.uint32)
+    low = g.integers(0, 4096, m) if not ties else g.integers(0, 3, m)
+    bin_ = (np.uint32(base) + low.astype(np.uint32)).view(np.float32)
+    beyond = max(0, k - (m + 1) // 2)
+    if m > 2 * k:
+        pytest.skip("more entries than fit")
+    for side, sign in ((0, 1.0), (1, -1.0)):
+        a = at[side * 2 * n // 5: side * 2 * n // 5 + beyond + m]
+        x[a[:beyond]] = sign * (2.0 + g.random(beyond)).astype(np.float32) * (1.0 if side == 0 else 0.9)
+        x[a[beyond:]] = sign * bin_
+    sizes = [n, 500]
+    with DeviceRun(sizes) as run:
+        R = [np.zeros(s, np.float32) for s in sizes]
+        for r in range(2):
+            small = (g.standard_normal(500) * 1e-3).astype(np.float32)
+            R = [y.R_new for y in check_round(run, [x, small], R, p, check_decode=False)]
+
+
+@pytest.mark.parametrize("k", [8191, 8192, 32767, 32768])
+def test_kept_entries_around_the_limits_of_long_lists(k):
+    p = 0.02
+    n = next(n for n in range(int(k / p) - 2, int(k / p) + 60) if int(np.floor(p * n)) == k)
+    with DeviceRun([n]) as run:
+        R = [np.zeros(n, np.float32)]
+        for r in range(2):
+            res = check_round(run, [synth.gaussian_update(n, round_=r)], R, p, check_decode=(r == 0))
+            assert res[0].k == k
+            assert bool(sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_WIDE) == (k >= 8192)
+            R = [x.R_new for x in res]
+
+
+def test_compact_context_whose_segment_overflows():
+    """4100 chunks; 1.2e6 equal entries, all in chunks of one segment, which holds 1.05e6: the histogram route
+    takes the list in one piece, and the first k of them are kept."""
+    n, p = CHUNK * 4100, 0.001
+    k = int(np.floor(p * n))
+    ctx = sbc.sbc_create_compact(0, n, 1)
+    try:
+        x = torch.randn(n, dtype=torch.float32, device="cuda:0", generator=torch.Generator("cuda:0").manual_seed(1)) * 1e-3
+        x.view(-1, CHUNK)[3::8, :2400] = 1.0
+        planted = torch.nonzero(x == 1.0).flatten()
+        assert 1_050_000 < len(planted) < n // 4
+        want = planted[:k]
+        R = torch.zeros_like(x)
+        msg = torch.zeros(sbc.sbc_msg_bound([n], p), dtype=torch.uint8, device="cuda:0")
+        nbytes = sbc.sbc_compress(ctx, [x], [R], p, msg)
+        assert sbc.sbc_last_route(ctx) & sbc.SBC_ROUTE_HISTOGRAM
+        out = torch.zeros_like(x)
+        sbc.sbc_decompress_accumulate(ctx, msg, nbytes, p, 1.0, [out])
+        assert torch.equal(torch.nonzero(out).flatten(), want)
+        assert torch.equal(R, x - out)
+    finally:
+        sbc.sbc_destroy(ctx)
