@@ -165,9 +165,16 @@ def _as_list(x) -> "TensorList":
     return x if isinstance(x, TensorList) else TensorList(x)
 
 
+# torch's current stream as the raw handle, without the Stream object that torch.cuda.current_stream() makes
+# for every call (2.9 us; the handle alone: 0.2)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream) -> Optional[int]:
     """stream: None (torch's current stream), a torch stream, or a raw hipStream_t as an int."""
     if stream is None:
+        if _raw_stream is not None:
+            return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
