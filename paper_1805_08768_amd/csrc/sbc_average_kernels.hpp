@@ -19,6 +19,7 @@ namespace sbc {
 constexpr int kAvgMaxMsgs = 64;               // messages per pass (a lane each)
 constexpr uint32_t kAvgBlock = 2048;          // entries per wavefront of k_average_apply
 constexpr uint32_t kAvgPerChunk = kChunk / kAvgBlock;
+constexpr uint32_t kAvgHalf = kAvgBlock / 2u; // ... of which it holds half at a time
 constexpr uint32_t kAvgTags = 256;            // places of k_average_apply where entries of equal positions meet
 constexpr uint32_t kAvgNone = 0xFFFFFFFFu;    // no stream
 constexpr uint32_t kAvgWhole = 0xFFFFFFFEu;   // in a workgroup's second place: all wavefronts take the first stream
@@ -45,27 +46,29 @@ template <int D>
 constexpr uint32_t kAvgStage = D == 2 ? 1408u : 512u;
 
 // Bound by the latency of a tile's steps (about 8 us: header, words, functions, sums, positions) times
-// the tiles in turn and the workgroups' turns on a compute unit: 26 us for 32 messages at p = 0.001 of the
+// the tiles in turn and the workgroups' turns on a compute unit: 24 us for 32 messages at p = 0.001 of the
 // ResNet-50 shape (28.5 with a limit of 64 segments for one wavefront instead of 128, 28.0 with 256).
 // Positions go through LDS, for a compute unit sustains one scattered store per 3 ns (65 us for four
 // messages at p = 0.01 with a store per lane and code, 46 with whole lines, 35 with the tiles of a
 // stream shared).
-// grid (workgroups, messages).  ids: eight places per workgroup: a stream for each wavefront, or one
+// The streams that take whole workgroups come first, for all messages, the workgroups of short streams last: they are
+// done soonest, and a few of them begin a second turn (message after message: 26 us).
+// Workgroup by workgroup of the table, for all M messages.  ids: eight places per workgroup: a stream for each wavefront, or one
 // for all of them, kAvgWhole, and which share of its tiles out of how many.
 template <int D>
 __global__ __launch_bounds__(kDecThreads) void k_average_decode(
-        const AvgMsgs msgs, const uint32_t* __restrict__ ids, const AvgTensor* __restrict__ tensors, int T, int b, float scale,
+        const AvgMsgs msgs, uint32_t M, const uint32_t* __restrict__ ids, const AvgTensor* __restrict__ tensors, int T, int b, float scale,
         uint32_t pos_stride, uint32_t* __restrict__ positions, uint32_t* __restrict__ marks, float* __restrict__ addends,
         ResultBlock* __restrict__ result, ResultBlock* __restrict__ next_result) {
     __shared__ __attribute__((aligned(16))) DecShared<D> sh;
     __shared__ uint32_t stage_sh[kDecWaves][kAvgStage<D>];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t m = blockIdx.y, M = gridDim.y;
+    const uint32_t which = blockIdx.x / M, m = blockIdx.x - which * M;
     SBC_TS(2, 0);
-    if (blockIdx.x == 0 && m == 0u && tid == 0) { next_result->err = 0u; next_result->pad = 0u; next_result->msg_bytes = 0ull; }
-    const uint32_t second = ids[blockIdx.x * kDecWaves + 1];
+    if (which == 0u && m == 0u && tid == 0) { next_result->err = 0u; next_result->pad = 0u; next_result->msg_bytes = 0ull; }
+    const uint32_t second = ids[which * kDecWaves + 1];
     const bool whole = second == kAvgWhole;
-    const uint32_t t = ids[blockIdx.x * kDecWaves + (whole ? 0 : wave)];
+    const uint32_t t = ids[which * kDecWaves + (whole ? 0 : wave)];
     if (tid < 256) build_table<D>(sh.fn, (uint32_t)tid, b);
     __syncthreads();
     if (t == kAvgNone) return;                             // (a wavefront of a workgroup that meets no barrier below)
@@ -79,8 +82,8 @@ __global__ __launch_bounds__(kDecThreads) void k_average_decode(
     }
     // The tiles of a long stream are shared among workgroups: each decodes those before its own, too, but
     // puts down only its own, and the last one what there is behind its tile.
-    const uint32_t share = whole ? ids[blockIdx.x * kDecWaves + 2] : 0u;
-    const bool last = !whole || share + 1u == ids[blockIdx.x * kDecWaves + 3];
+    const uint32_t share = whole ? ids[which * kDecWaves + 2] : 0u;
+    const bool last = !whole || share + 1u == ids[which * kDecWaves + 3];
     const unsigned long long seg_end = last ? si.n_seg : min(si.n_seg, (unsigned long long)(share + 1u) * kDecThreads);
     if (share && si.n_seg <= (unsigned long long)share * kDecThreads) return;
     if ((whole ? tid : lane) == 0 && share == 0u) addends[(size_t)t * M + m] = scale * si.mu;
@@ -149,8 +152,10 @@ __global__ __launch_bounds__(256) void k_average_clear(const uint2* __restrict__
 
 // A workgroup per chunk of 8192 entries, a wavefront per block of 2048: enough entries of all messages
 // together (about 64 for 32 messages at p = 0.001) to give each lane one.  Bound by the store of the
-// result: 102 MB in 23.6 us, 4.3 TB/s (55.9 us with the messages one after another in each wavefront, two
-// lanes busy at a time; issue bound).  ADD: out already
+// result, which starts four round trips after the kernel: 102 MB in 22.4 us (a plain fill: 16 us); 23.3 with a
+// whole block per wavefront in LDS instead of half of it, which leaves room for four workgroups on a compute
+// unit instead of seven; 55.9 us with the messages one after another in each wavefront, two
+// lanes busy at a time (issue bound).  ADD: out already
 // holds the sum of the messages before these.
 template <bool ADD>
 __global__ __launch_bounds__(kEncThreads) void k_average_apply(
@@ -158,7 +163,7 @@ __global__ __launch_bounds__(kEncThreads) void k_average_apply(
         const uint32_t* __restrict__ positions, const uint32_t* __restrict__ marks, const float* __restrict__ addends,
         const ResultBlock* __restrict__ result) {
     static_assert(kAvgPerChunk == (uint32_t)kEncWaves, "a wavefront per block");
-    __shared__ __attribute__((aligned(16))) float acc_sh[kEncWaves][kAvgBlock];
+    __shared__ __attribute__((aligned(16))) float acc_sh[kEncWaves][kAvgHalf];
     __shared__ __attribute__((aligned(16))) uint32_t tag_sh[kEncWaves][kAvgTags];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -192,54 +197,61 @@ __global__ __launch_bounds__(kEncThreads) void k_average_apply(
         if (e < total) r.at = positions[(size_t)m * pos_stride + a.pos_off + i] - e0;
         return r;
     };
-    Entry next = entry(lane);
+    const Entry first = entry(lane);                   // (of most blocks, all there are)
+    uint32_t turn = 0u;
 #pragma unroll
     for (uint32_t i = 0; i < kAvgTags / 256u; ++i) reinterpret_cast<uint4*>(tag)[i * 64u + lane] = make_uint4(0u, 0u, 0u, 0u);
+#pragma nounroll
+    for (uint32_t h0 = 0u; h0 < cnt; h0 += kAvgHalf) {
 #pragma unroll
-    for (uint32_t i = 0; i < kAvgBlock / 256u; ++i) {
-        const uint32_t at = (i * 64u + lane) * 4u;
-        f32x4 v = 0.f;
-        if (ADD) {
-            if (at + 4u <= cnt) v = *(const gf32x4_any_ptr)(out + at);
-            else for (uint32_t j = 0; j < 4u; ++j) if (at + j < cnt) v[j] = out[at + j];
-        }
-        reinterpret_cast<f32x4*>(acc)[i * 64u + lane] = v;
-    }
-    wave_lds_fence();
-    // A lane per entry, in message order.  Entries of one position are added in that order: where lanes meet at a
-    // tag (a hash of the position), the first of them goes first, the others take another turn.  A message's
-    // positions are distinct, so a batch of one message has nothing to sort out.
-    uint32_t turn = 0u;
-    for (uint32_t base = 0u; base < total; base += 64u) {
-        const Entry now = next;
-        if (base + 64u < total) next = entry(base + 64u + lane);
-        bool todo = now.at < kAvgBlock;
-        const bool single = (uint32_t)__builtin_amdgcn_readfirstlane((int)now.m) ==
-                            (uint32_t)__builtin_amdgcn_readlane((int)now.m, (int)min(63u, total - base - 1u));
-        if (single) {
-            if (todo) acc[now.at] += now.x;
-        } else {
-            while (__any(todo)) {
-                turn += 64u;                           // (tags only grow: none is ever cleared)
-                const uint32_t mine = turn + 63u - lane;
-                uint32_t* const place = tag + (now.at & (kAvgTags - 1u));
-                if (todo) __hip_atomic_fetch_max(place, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                wave_lds_fence();
-                if (todo && *place == mine) {
-                    acc[now.at] += now.x;
-                    todo = false;
-                }
-                wave_lds_fence();
+        for (uint32_t i = 0; i < kAvgHalf / 256u; ++i) {
+            const uint32_t at = h0 + (i * 64u + lane) * 4u;
+            f32x4 v = 0.f;
+            if (ADD) {
+                if (at + 4u <= cnt) v = *(const gf32x4_any_ptr)(out + at);
+                else for (uint32_t j = 0; j < 4u; ++j) if (at + j < cnt) v[j] = out[at + j];
             }
+            reinterpret_cast<f32x4*>(acc)[i * 64u + lane] = v;
         }
         wave_lds_fence();
-    }
+        // A lane per entry, in message order.  Entries of one position are added in that order: where lanes meet at a
+        // tag (a hash of the position), the first of them goes first, the others take another turn.  A message's
+        // positions are distinct, so a batch of one message has nothing to sort out.
+        Entry next = first;
+        if (h0 && total > 64u) next = entry(lane);
+        for (uint32_t base = 0u; base < total; base += 64u) {
+            const Entry now = next;
+            if (base + 64u < total) next = entry(base + 64u + lane);
+            const uint32_t at = now.at - h0;
+            bool todo = at < kAvgHalf;                 // (kAvgNone, or of the other half: not)
+            const bool single = (uint32_t)__builtin_amdgcn_readfirstlane((int)now.m) ==
+                                (uint32_t)__builtin_amdgcn_readlane((int)now.m, (int)min(63u, total - base - 1u));
+            if (single) {
+                if (todo) acc[at] += now.x;
+            } else {
+                while (__any(todo)) {
+                    turn += 64u;                       // (tags only grow: none is ever cleared)
+                    const uint32_t mine = turn + 63u - lane;
+                    uint32_t* const place = tag + (at & (kAvgTags - 1u));
+                    if (todo) __hip_atomic_fetch_max(place, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    wave_lds_fence();
+                    if (todo && *place == mine) {
+                        acc[at] += now.x;
+                        todo = false;
+                    }
+                    wave_lds_fence();
+                }
+            }
+            wave_lds_fence();
+        }
 #pragma unroll
-    for (uint32_t i = 0; i < kAvgBlock / 256u; ++i) {
-        const uint32_t at = (i * 64u + lane) * 4u;
-        const f32x4 v = reinterpret_cast<const f32x4*>(acc)[i * 64u + lane];
-        if (at + 4u <= cnt) *(gf32x4_any_ptr)(out + at) = v;
-        else for (uint32_t j = 0; j < 4u; ++j) if (at + j < cnt) out[at + j] = v[j];
+        for (uint32_t i = 0; i < kAvgHalf / 256u; ++i) {
+            const uint32_t at = h0 + (i * 64u + lane) * 4u;
+            const f32x4 v = reinterpret_cast<const f32x4*>(acc)[i * 64u + lane];
+            if (at + 4u <= cnt) *(gf32x4_any_ptr)(out + at) = v;
+            else for (uint32_t j = 0; j < 4u; ++j) if (at + j < cnt) out[at + j] = v[j];
+        }
+        wave_lds_fence();
     }
 }
 

@@ -1353,10 +1353,10 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         for (int m = 0; m < M; ++m) { list.msg[m] = static_cast<const uint8_t*>(msgs[m0 + m]); list.bytes[m] = msg_bytes[m0 + m]; }
         uint32_t* const marks = positions + (size_t)M * c->avg_pos;
         float* const addends = reinterpret_cast<float*>(marks + (size_t)M * c->avg_marks);
-        const dim3 grid(c->avg_blocks, (unsigned)M), block(kDecThreads);
-        if (b <= 7) hipLaunchKernelGGL(k_average_decode<2>, grid, block, 0, stream, list, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
-        else if (b <= 11) hipLaunchKernelGGL(k_average_decode<3>, grid, block, 0, stream, list, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
-        else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        const dim3 grid((unsigned)M * c->avg_blocks), block(kDecThreads);
+        if (b <= 7) hipLaunchKernelGGL(k_average_decode<2>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        else if (b <= 11) hipLaunchKernelGGL(k_average_decode<3>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         if (m0 == 0) hipLaunchKernelGGL(k_average_apply<false>, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
         else hipLaunchKernelGGL(k_average_apply<true>, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
     }
