@@ -27,7 +27,7 @@
 // stores to one line from two L2s inside one kernel have no order.
 //
 // k_finish_message assembles the message, applies the residual update of the tensors finished
-// here, resets the per-tensor counters and writes the call's result block to pinned host memory.
+// here, resets the per-tensor counters and sends the call's result to pinned host memory.
 #pragma once
 
 #include "sbc_device.hpp"
@@ -986,9 +986,9 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
 // starting on a word boundary); the lead workgroup of a tensor writes its table entry, applies
 // the residual update R[j] = A[j] - mu at the kept entries of a tensor finished inside
 // k_client_step (Alg. 1: R <- dW - dW*), and leaves the tensor's counters clean for the next
-// call; workgroup (0, 0) writes the header and the call's result block, also to pinned host
+// call; workgroup (0, 0) writes the header and sends the call's result to pinned host
 // memory.  If some tensor still has to be redone by the kernels of the other routes, nothing but
-// the result block is written: the host launches those kernels and this one again.
+// the result is sent: the host launches those kernels and this one again.
 // --------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __restrict__ desc,
                                                         TensorState* __restrict__ st, int T, int b,
