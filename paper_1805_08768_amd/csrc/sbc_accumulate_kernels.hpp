@@ -54,7 +54,7 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 }
 
 // --------------------------------------------------------------------------
-// Prefilter thresholds from a sample.  One workgroup (512 threads) per tensor.  Tensors of up to
+// Prefilter thresholds from a sample.  One workgroup (1024 threads) per tensor.  Tensors of up to
 // kSampleMax entries are read completely (the threshold is then the exact k-th key to 16
 // bits); larger ones contribute 256 runs of 64 consecutive entries, one run at a pseudo-random
 // place in each of 256 equal strata.  With m sampled entries out of n, lambda = k*m/n of them
@@ -69,19 +69,23 @@ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
 // For tensors flagged kDescSampled ("Sparse Binarization": the threshold is estimated from a
 // random subsample, which makes the amount of sparsity noisy) the key is instead the full 32-bit
 // key of the sample's r-th most extreme entry, r = max(1, floor(p*m)): the threshold itself.
+// Bound by its chain of dependent steps, of which the counting passes over a thread's share of the sample grow
+// with that share: 13.6 us on 9 tensors with 1024 threads (15.8 with 512, and the counts cleared before the
+// loads went out).  No more than 512 keys are ranked: beyond that the byte passes are the shorter way.
 // --------------------------------------------------------------------------
 __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
         const TensorDesc* __restrict__ desc, TensorState* __restrict__ st,
         ResultBlock* __restrict__ result, int force_exact, double sampled_p) {
     constexpr int RUNS = kSampleMax / 64;             // 256
     constexpr int COPIES = 16;
+    constexpr uint32_t RANKED = 512u;                 // most keys of a bucket that are ranked one against the others
     __shared__ uint32_t skey[kSampleMax];             // the sample, as keys (loops stay rolled: small code)
     __shared__ uint32_t hist0[2][256][COPIES];        // first byte: lane-private copies, one bank each
     __shared__ uint32_t hist[4][2][256];
     __shared__ uint32_t whist[2][kSampleWindow];      // leading 16 key bits, counted down from the extreme
     __shared__ uint32_t wave_ext[2][kSampleThreads / 64];
     __shared__ uint32_t wave_above[kSampleThreads / 64];
-    __shared__ uint32_t blist[2][kSampleThreads];     // subsampled variant: the sampled keys of the threshold's bucket
+    __shared__ uint32_t blist[2][RANKED];     // subsampled variant: the sampled keys of the threshold's bucket
     __shared__ uint32_t bcnt[2], btau[2];
     __shared__ uint32_t res[4][8];
     __shared__ unsigned long long scratch[kSampleThreads / 64];
@@ -126,10 +130,6 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
     if (rs >= m) return;                              // keep the all-pass keys (0, 0)
     const int passes = sampled ? 4 : 2;               // all 32 key bits, or the leading 16
 
-    for (int i = tid; i < 3 * 2 * 256; i += kSampleThreads) (&hist[1][0][0])[i] = 0u;
-    for (int i = tid; i < 2 * 256 * COPIES; i += kSampleThreads) (&hist0[0][0][0])[i] = 0u;
-    for (int i = tid; i < 2 * kSampleWindow; i += kSampleThreads) (&whist[0][0])[i] = 0u;
-    __syncthreads();
     uint32_t need[2] = {rs, rs};
     const bool active[2] = {true, true};
     uint32_t prefix[2] = {0u, 0u};
@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
     const gcfloat_ptr R = as_global(d.R);
     const gcfloat_ptr dW = as_global(d.dW);
     {
-        constexpr int PER = kSampleMax / kSampleThreads;      // 32
+        constexpr int PER = kSampleMax / kSampleThreads;      // 16
         float a[PER], w[PER];
         if (n <= (uint32_t)kSampleMax) {
 #pragma unroll
@@ -160,6 +160,9 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
                 a[s] = R[i]; w[s] = dW[i];
             }
         }
+        // (the counts are cleared while the loads are on their way; the barrier below precedes their first use)
+        for (int i = tid; i < 3 * 2 * 256; i += kSampleThreads) (&hist[1][0][0])[i] = 0u;
+        for (int i = tid; i < 2 * kSampleWindow; i += kSampleThreads) (&whist[0][0])[i] = 0u;
         // Keys, and the most extreme key of each side (this thread's, then the workgroup's).
         uint32_t key[PER], ext_p = 0u, ext_n = 0u, above = 0u;       // above: sampled entries at or beyond the old keys, 16 bits per side
 #pragma unroll
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
             const uint32_t op = __shfl_xor(ext_p, off, 64), on = __shfl_xor(ext_n, off, 64);
             ext_p = op > ext_p ? op : ext_p;
             ext_n = on > ext_n ? on : ext_n;
-            above += __shfl_xor(above, off, 64);      // (at most 2048 per side and wavefront)
+            above += __shfl_xor(above, off, 64);      // (at most 1024 per side and wavefront)
         }
         if ((tid & 63) == 0) { wave_ext[0][tid >> 6] = ext_p; wave_ext[1][tid >> 6] = ext_n; wave_above[tid >> 6] = above; }
         __syncthreads();
@@ -231,17 +234,17 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
                 if ((uint32_t)(s * kSampleThreads + tid) < m) {
                     if ((key[s] >> 16) == prefix[0]) {
                         const uint32_t q = atomicAdd(&bcnt[0], 1u);
-                        if (q < (uint32_t)kSampleThreads) blist[0][q] = key[s];
+                        if (q < RANKED) blist[0][q] = key[s];
                     }
                     if ((~key[s] >> 16) == prefix[1]) {
                         const uint32_t q = atomicAdd(&bcnt[1], 1u);
-                        if (q < (uint32_t)kSampleThreads) blist[1][q] = ~key[s];
+                        if (q < RANKED) blist[1][q] = ~key[s];
                     }
                 }
             }
             __syncthreads();
             const uint32_t c0 = bcnt[0], c1 = bcnt[1];
-            if (c0 <= (uint32_t)kSampleThreads && c1 <= (uint32_t)kSampleThreads) {      // uniform
+            if (c0 <= RANKED && c1 <= RANKED) {      // uniform
 #pragma unroll
                 for (int sd = 0; sd < 2; ++sd) {
                     const uint32_t cn = sd ? c1 : c0;
@@ -267,6 +270,8 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
         // The r-th entry lies below the window (mostly-zero tensors): byte by byte from the top.
         // First byte: floating-point keys take only a handful of values here, so every lane group
         // counts into its own copy and the copies are added up afterwards.
+        for (int i = tid; i < 2 * 256 * COPIES; i += kSampleThreads) (&hist0[0][0][0])[i] = 0u;
+        __syncthreads();
         const int copy = ((tid >> 6) & 1) * 8 + (tid & 7);
 #pragma unroll 8
         for (uint32_t i = tid; i < m; i += kSampleThreads) {

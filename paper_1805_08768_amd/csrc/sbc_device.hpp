@@ -51,7 +51,7 @@ typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 constexpr int kChunk = 8192;             // entries of one tensor handled by one workgroup
 constexpr int kChunkWords = kChunk / 32; // bitmap words per chunk (= threads of a chunk kernel)
 constexpr int kStreamThreads = 256;      // workgroup size of the streaming kernels
-constexpr int kSampleThreads = 512;      // workgroup size of the sample kernel
+constexpr int kSampleThreads = 1024;     // workgroup size of the sample kernel
 constexpr int kSampleMax = 16384;        // entries sampled per tensor for the prefilter threshold
 constexpr int kSampleWindow = 2048;      // leading-16-bit key values counted below the sample's extreme
 
