@@ -193,7 +193,11 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
     const float mu32 = (float)(chosen ? mean_n : mean_p);
     const float mu_signed = chosen ? -mu32 : mu32;
     const uint32_t tau = chosen ? tau_n : tau_p, itau = chosen ? itau_n : itau_p;
-    if (cc == 0u && lane == 0) { res[t].side = chosen ? -1 : 1; res[t].mu_signed = mu_signed; res[t].nnz = st[t].kc[chosen]; }
+    if (cc == 0u && lane == 0) {
+        const uint32_t nnz = st[t].kc[chosen];
+        res[t].side = chosen ? -1 : 1; res[t].mu_signed = mu_signed; res[t].nnz = nnz;
+        if (nnz > desc[t].kcap) atomicOr(&result->err, kErrInternal);          // (cannot happen)
+    }
     const CandPtr list = cand + run.at[chosen];
     const uint32_t cnt = run.cnt[chosen];
     wave_lds_fence();
@@ -335,7 +339,8 @@ __global__ __launch_bounds__(kScanThreads) void k_tensor_scan(const TensorDesc* 
                                                               const TileSummary* __restrict__ tiles,
                                                               uint32_t* __restrict__ chunk_gap,
                                                               uint64_t* __restrict__ chunk_bitoff,
-                                                              TensorState* __restrict__ st, int b, int pass) {
+                                                              TensorState* __restrict__ st, int b, int pass,
+                                                              ResultBlock* __restrict__ result) {
     __shared__ uint32_t scratch32[kScanThreads / 64];
     __shared__ unsigned long long scratch64[kScanThreads / 64];
     const int t = blockIdx.x, tid = threadIdx.x;
@@ -358,7 +363,12 @@ __global__ __launch_bounds__(kScanThreads) void k_tensor_scan(const TensorDesc* 
     bool has_first;
     scan_tile<true>(d, blockIdx.y, sum, carry_end, carry_bits, b, chunk_gap, chunk_bitoff, scratch32, scratch64,
                     tile_end, tile_bits, first_pos, has_first);
-    if (tid == 0 && blockIdx.y == n_tiles - 1u) st[t].bit_len = carry_bits + tile_bits;
+    if (tid == 0 && blockIdx.y == n_tiles - 1u) {
+        const unsigned long long bit_len = carry_bits + tile_bits;
+        st[t].bit_len = bit_len;
+        // (cannot happen; said here, for k_emit sends the call's result before the streams are written)
+        if (((bit_len + 31ull) >> 5) > d.bound_words) atomicOr(&result->err, kErrInternal);
+    }
 }
 
 // ------------------------------------------------------------ the payload ----
@@ -638,7 +648,7 @@ __global__ __launch_bounds__(kEncThreads) void k_emit(
     const unsigned long long at = chunk_bitoff[c];
     const uint4 mine = load_codes(codes, c, own);
     const uint32_t err_in = DIRECT ? result->err : 0u;
-    const uint32_t nchunks = desc[t].nchunks, bound_words = desc[t].bound_words;
+    const uint32_t nchunks = desc[t].nchunks;
     const unsigned long long bit_len = st[t].bit_len, n_words = (bit_len + 31ull) >> 5;
     uint32_t* to;
     if constexpr (DIRECT) {
@@ -655,20 +665,20 @@ __global__ __launch_bounds__(kEncThreads) void k_emit(
         }
         before = last_lane(wave_incl_sum(before));
         all = last_lane(wave_incl_sum(all));
+        // (a stream beyond its bound cannot happen, k_tensor_scan has looked; nor can all of them together be too
+        // long for the message then: the first chunk says so, the others write nothing)
         const unsigned long long most = (msg_capacity - 32ull - 24ull * (unsigned)T) >> 2;
-        if (before + n_words > most || n_words > bound_words) {        // (cannot happen)
-            if (lane == 0u) atomicOr(&result->err, kErrInternal);
-            return;
+        const bool fits = (c == 0u ? all : before + n_words) <= most;
+        if (c == 0u && lane == 0u) {
+            if (fits) finish_call(msg, T, b, all, err_in, next_result, host_word, seq);
+            else publish(host_word, seq, err_in | kErrInternal, 0ull);
         }
-        if (c == 0u && lane == 0u) finish_call(msg, T, b, all, err_in, next_result, host_word, seq);
+        if (!fits) return;
         if (c - ct.y == nchunks - 1u && lane == 0u) finish_tensor(msg, st, counters, t, st[t].mu_signed, st[t].nnz, bit_len, before);
         to = reinterpret_cast<uint32_t*>(msg + 32 + 24ull * (unsigned)T) + before;
     } else {
         if (!encoded_in_pass(st[t].flags, pass)) return;
-        if (n_words > bound_words) {                   // would leave the tensor's staging words (cannot happen)
-            if (lane == 0u) atomicOr(&result->err, kErrInternal);
-            return;
-        }
+        if (n_words > desc[t].bound_words) return;     // would leave the tensor's staging words (cannot happen: k_tensor_scan)
         to = stage + desc[t].stage_off;
     }
     stage_codes(win_sh[wave], mine);

@@ -359,7 +359,7 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
             hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_state,
                                c->d_sum, c->d_tile, b, pass);
         SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
-                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, pass);
+                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, pass, P.res_now);
         if (!c->fused_step) {
             SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
                        c->d_gap, c->d_bitoff, c->d_state, c->d_counters, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
@@ -403,17 +403,24 @@ bool result_arrived(const unsigned long long* word, uint32_t want) {
     }
 }
 
-int wait_result(sbc_ctx* c) {
-    // The kernel that completes the message sends the result to pinned host memory.  Looking for the number takes a microsecond or two once it is there, where the
-    // runtime's wait returns several microseconds after the stream has drained; calls that run
-    // longer than a fraction of a millisecond fall through to the runtime's wait.  (Not while
-    // kernels carry timing events: those are read right after this, and must be complete.)
-    if (c->profile_level == 0 && result_arrived(c->h_result, c->result_seq)) return SBC_OK;
-    if ((c->pend.wait_on_event ? hipEventSynchronize(c->ev_result) : hipStreamSynchronize(c->pend.stream)) != hipSuccess) {
+// Until the result numbered `seq` is there.  Looking for the number takes a microsecond or two once it is,
+// where the runtime's wait (for the event, or without one for the stream) returns several microseconds after
+// the stream has drained; calls that run longer than a fraction of a millisecond fall through to that wait.
+// A kernel that has ended without sending its result has found an invariant violated: the word then still
+// holds the call before's.
+int wait_result(const unsigned long long* word, uint32_t seq, bool look, hipStream_t stream, hipEvent_t event = nullptr) {
+    if (look && result_arrived(word, seq)) return SBC_OK;
+    if ((event ? hipEventSynchronize(event) : hipStreamSynchronize(stream)) != hipSuccess) {
         (void)hipGetLastError();
         return SBC_EHIP;
     }
-    return SBC_OK;
+    return result_seq_of(__atomic_load_n(word, __ATOMIC_ACQUIRE)) == (seq & kSeqMask) ? SBC_OK : SBC_EINTERNAL;
+}
+
+// The pending step's result.  (Not looked for while kernels carry timing events: those are read right after
+// this, and must be complete.)
+int wait_result(sbc_ctx* c) {
+    return wait_result(c->h_result, c->result_seq, c->profile_level == 0, c->pend.stream, c->pend.wait_on_event ? c->ev_result : nullptr);
 }
 
 }  // namespace
@@ -1222,10 +1229,7 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
     // enqueued on the stream afterwards
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res_dec, ++c->dec_seq);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
-    if (!result_arrived(c->h_result_dec, c->dec_seq) && hipStreamSynchronize(stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return SBC_EHIP;
-    }
+    if (const int rc = wait_result(c->h_result_dec, c->dec_seq, true, stream)) return rc;
     SBC_HOST_TS(11);
     c->dev_dec_valid = true;
     const uint32_t err = result_err_of(*c->h_result_dec);
@@ -1362,10 +1366,7 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
     }
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
-    if (!result_arrived(c->h_result_dec, c->dec_seq) && hipStreamSynchronize(stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return SBC_EHIP;
-    }
+    if (const int rc = wait_result(c->h_result_dec, c->dec_seq, true, stream)) return rc;
     const uint32_t err = result_err_of(*c->h_result_dec);
     if (err == 0u) c->dec_result_dirty = false;
     if ((err & kErrDeferred) && !(err & kErrCorrupt))     // a stream of more positions than there is room for
@@ -1382,10 +1383,7 @@ int sbc_decode_status(sbc_ctx* c, void* hip_stream) {
     c->deferred_dirty = true;
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, c->d_result + 4, ++c->dec_seq);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
-    if (!result_arrived(c->h_result_dec, c->dec_seq) && hipStreamSynchronize(stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return SBC_EHIP;
-    }
+    if (const int rc = wait_result(c->h_result_dec, c->dec_seq, true, stream)) return rc;
     return status_of_err(result_err_of(*c->h_result_dec));
 }
 

@@ -1014,25 +1014,26 @@ __global__ __launch_bounds__(256) void k_finish_message(const TensorDesc* __rest
     const float mu_signed = st[t].mu_signed;
     // word offset of this tensor's stream: streams are packed in tensor order
     unsigned long long mine = 0ull, all = 0ull;
-    const int upto = (t == 0 && lead) ? T : t;          // workgroup (0, 0) also needs the grand total
+    const bool first = t == 0 && lead;                  // workgroup (0, 0) also needs the grand total,
+    const int upto = first ? T : t;
+    bool bad = false;                                   // and whether some tensor has more than it may (cannot happen)
     for (int i = tid; i < upto; i += 256) {
         const unsigned long long words = (st[i].bit_len + 31ull) >> 5;
         all += words;
         if (i < t) mine += words;
+        if (first) bad = bad || words > desc[i].bound_words || st[i].nnz > desc[i].kcap;
     }
     mine = wave_incl_sum(mine);                         // (the scan's last lane holds the wavefront's total)
     all = wave_incl_sum(all);
     if ((tid & 63) == 63) { part[0][tid >> 6] = mine; part[1][tid >> 6] = all; }
-    __syncthreads();
+    bad = __syncthreads_or(bad) != 0;
     const unsigned long long word_off = part[0][0] + part[0][1] + part[0][2] + part[0][3];
     const unsigned long long tot_all = part[1][0] + part[1][1] + part[1][2] + part[1][3];
     const unsigned long long n_words = (bit_len + 31ull) >> 5;
     const unsigned long long table_end = 32ull + 24ull * (unsigned)T;
-    if (n_words > d.bound_words || table_end + 4ull * (word_off + n_words) > msg_capacity || nnz > d.kcap) {
-        if (tid == 0) {
-            atomicOr(&result->err, kErrInternal);
-            if (t == 0 && lead) publish(host_word, seq, err_in | kErrInternal, 0ull);
-        }
+    bad = bad || n_words > d.bound_words || table_end + 4ull * (first ? tot_all : word_off + n_words) > msg_capacity || nnz > d.kcap;
+    if (bad) {                                          // uniform; the call's result says so if any workgroup finds one
+        if (first && tid == 0) publish(host_word, seq, err_in | kErrInternal, 0ull);
         return;
     }
     if (lead) {

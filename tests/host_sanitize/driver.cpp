@@ -18,6 +18,8 @@ extern "C" unsigned stub_grid(long launch);
 extern "C" const void* stub_kernel(long launch);
 extern "C" long stub_live_blocks();
 extern "C" void stub_fail_allocation(long nth);
+extern "C" void stub_withhold_results(int on);
+extern "C" int stub_known_senders();
 
 #define CHECK(cond)                                                                     \
     do {                                                                                \
@@ -64,6 +66,7 @@ int main(int argc, char** argv) {
         std::fclose(f);
     }
     CHECK(model.size() >= 100);
+    CHECK(stub_known_senders() == 5);                  // k_emit_all for few and for many chunks, k_emit, k_finish_message, k_publish
 
     // ---- scalar helpers ----
     const double bad_p[] = {0.0, 1.0, -1.0, 2.0, 0.0 / 1.0 - 0.0, 1e-12};
@@ -275,6 +278,33 @@ int main(int argc, char** argv) {
         sbc_destroy(c); c = nullptr;
         CHECK(stub_live_blocks() == 0);
     }
+
+    // ---- a kernel that ends without sending the call's result: the call fails (the word in pinned memory then
+    // still holds the call before's), and the next one works again ----
+    for (const std::vector<int64_t>& shape : {model, std::vector<int64_t>{40000000, 5}})          // k_emit_all; k_emit
+        for (int fused = 0; fused < 2; ++fused) {
+            const Buffers s = fake_buffers(shape);
+            const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), p);
+            const void* const msgs[2] = {kMsg, kMsg};
+            const size_t lens[2] = {nb, nb};
+            CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            CHECK(sbc_set_option(c, SBC_OPT_FUSED_STEP, fused) == SBC_OK);
+            for (int withheld : {0, 1, 1, 0}) {
+                stub_withhold_results(withheld);
+                const int want = withheld ? SBC_EINTERNAL : SBC_OK;
+                CHECK(compress(c, s, p, nb, &nbytes) == want);
+                CHECK(sbc_compress_begin(c, nullptr, s.dW.data(), s.R.data(), s.numel.data(), s.T(), p, kMsg, nb) == SBC_OK);
+                CHECK(sbc_compress_end(c, &nbytes) == want);
+                CHECK(sbc_decompress_accumulate(c, nullptr, kMsg, nb, s.numel.data(), s.T(), p, 1.f, s.out.data()) == want);
+                CHECK(sbc_decompress_average(c, nullptr, msgs, lens, 2, s.numel.data(), s.T(), p, 0.5f, s.out.data()) == want);
+                CHECK(sbc_set_option(c, SBC_OPT_DEFER_DECODE_STATUS, 1) == SBC_OK);
+                CHECK(sbc_decompress_accumulate(c, nullptr, kMsg, nb, s.numel.data(), s.T(), p, 1.f, s.out.data()) == SBC_OK);
+                CHECK(sbc_decode_status(c, nullptr) == want);
+                CHECK(sbc_set_option(c, SBC_OPT_DEFER_DECODE_STATUS, 0) == SBC_OK);
+            }
+            sbc_destroy(c); c = nullptr;
+            CHECK(stub_live_blocks() == 0);
+        }
 
     // ---- the average over a round's messages: argument errors, and its two tables at their limits ----
     {

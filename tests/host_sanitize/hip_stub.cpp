@@ -2,10 +2,12 @@
 // UndefinedBehaviorSanitizer (CPU only).  "Device" and pinned memory are ordinary heap blocks of
 // exactly the requested size, so that every table the planner fills and every copy it enqueues is
 // checked against the size it allocated; copies and fills happen at once; kernel launches do
-// nothing (the result block a launch would have written stays zero: "no error, empty message");
-// events and streams are inert.  One device.
+// nothing, but that those which send a call's result to pinned host memory send "no error, empty
+// message" with the call's number (or, if the test says so, end without it, as a kernel does that
+// finds an invariant violated); events and streams are inert.  One device.
 #include <hip/hip_runtime_api.h>
 
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 
@@ -14,12 +16,24 @@ static unsigned g_grids[64];           // workgroups (x) of the latest launches
 static const void* g_kernels[64];      // and their kernels
 static long g_live_blocks = 0;
 static long g_fail_alloc_at = -1;      // the n-th allocation from now fails (tests the clean-up path)
+static bool g_withhold = false;        // no results are sent
+// The kernels that send results, by a part of their mangled name, and which of their arguments are the word
+// in pinned memory and the call's number.
+struct Sender { const char* name; int word, seq; const void* host[2]; };
+static Sender g_senders[] = {
+    {"10k_emit_all", 13, 14, {}}, {"6k_emitILb1E", 18, 19, {}}, {"16k_finish_message", 11, 12, {}}, {"9k_publish", 0, 2, {}}};
 
 extern "C" long stub_launches() { return g_launches; }
 extern "C" unsigned stub_grid(long launch) { return g_grids[launch % 64]; }
 extern "C" const void* stub_kernel(long launch) { return g_kernels[launch % 64]; }
 extern "C" long stub_live_blocks() { return g_live_blocks; }
 extern "C" void stub_fail_allocation(long nth) { g_fail_alloc_at = nth; }
+extern "C" void stub_withhold_results(int on) { g_withhold = on != 0; }
+extern "C" int stub_known_senders() {
+    int n = 0;
+    for (const Sender& s : g_senders) n += (s.host[0] != nullptr) + (s.host[1] != nullptr);
+    return n;
+}
 
 static hipError_t stub_alloc(void** p, size_t bytes) {
     if (!p) return hipErrorInvalidValue;
@@ -62,8 +76,11 @@ hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
     if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x == 0 || block.x * block.y * block.z > 1024) return hipErrorInvalidConfiguration;
+    for (const Sender& s : g_senders)
+        if ((f == s.host[0] || f == s.host[1]) && !g_withhold)       // (the number: bits 50 to 63 of the word)
+            **static_cast<uint64_t**>(args[s.word]) = (uint64_t)(*static_cast<uint32_t*>(args[s.seq]) & 0x3FFFu) << 50;
     g_grids[g_launches % 64] = grid.x;
     g_kernels[g_launches++ % 64] = f;
     return hipSuccess;
@@ -78,7 +95,10 @@ hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<v
 // what the compiler-generated registration code calls
 void** __hipRegisterFatBinary(const void*) { static void* handle = nullptr; return &handle; }
 void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*, void*, int*) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+    for (Sender& s : g_senders)
+        if (std::strstr(name, s.name)) s.host[s.host[0] ? 1 : 0] = host;
+}
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 static dim3 g_grid, g_block;
 static size_t g_shmem;
