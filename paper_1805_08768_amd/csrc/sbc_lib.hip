@@ -1328,14 +1328,16 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         c->avg_numel.assign(numel, numel + T);
         c->avg_valid = true;
     }
-    // Messages per pass: a lane each, and what the scratch memory holds.  A single message for a large model
+    // Messages per pass: a lane each, what the scratch memory holds, and what one launch can have (2^32 - 1 work
+    // items: from a million streams of one wavefront each on, fewer than 64).  A single message for a large model
     // is added to the cleared result instead: that stores no positions first (ResNet-50 shape at p = 0.001
     // 35 us, 41 the other way; 66e6 entries 68 and 79 us).  Two messages take 45 us in turn and 42 together, at
     // 66e6 entries 93 and 80 us; one message of a small model 30 and 25 us, of 2^20 entries at p = 0.01 39 and
     // 32 us.
     const uint64_t per_msg = (uint64_t)c->avg_pos + c->avg_marks + (uint64_t)T;
     const uint64_t room = 2u * c->cand_entries;
-    const int most = c->avg_fits && !c->pend.active ? (int)std::min<uint64_t>(kAvgMaxMsgs, room / per_msg) : 0;
+    const uint64_t launchable = 0xFFFFFFFFull / ((uint64_t)kDecThreads * std::max<uint32_t>(c->avg_blocks, 1u));
+    const int most = c->avg_fits && !c->pend.active ? (int)std::min<uint64_t>({kAvgMaxMsgs, room / per_msg, launchable}) : 0;
     if (most < 1 || (n_msgs == 1 && c->avg_chunks > kAvgAloneChunks)) return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);
     // (the last client step may still be draining on another stream)
     if (c->last_T > 0 && c->last_stream != stream && hipStreamSynchronize(c->last_stream) != hipSuccess) {

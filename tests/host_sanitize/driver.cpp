@@ -376,6 +376,25 @@ int main(int argc, char** argv) {
         }
     }
 
+    // ---- the average over 64 messages of more tensors than one launch can decode for all of them: fewer
+    // messages at a time, whatever the tensors ----
+    {
+        const Buffers s = fake_buffers(std::vector<int64_t>(1100000, 1));
+        const std::vector<const void*> msgs(64, kMsg);
+        const std::vector<size_t> lens(64, sbc_msg_bound(s.numel.data(), s.T(), p));
+        CHECK(sbc_create(&c, 0, 64 * s.total(), s.T()) == SBC_OK);
+        const long from = stub_launches();
+        CHECK(sbc_decompress_average(c, nullptr, msgs.data(), lens.data(), 64, s.numel.data(), s.T(), p, 1.f, s.out.data()) == SBC_OK);
+        CHECK(stub_launches() - from == 1 + 2 * 2 + 1);   // cleared result blocks, two passes of two kernels, the status
+        unsigned rows = 0;
+        for (long i : {1, 3}) {
+            CHECK((uint64_t)stub_grid(from + i) * 512u < (uint64_t)1 << 32);
+            rows += stub_grid(from + i);
+        }
+        CHECK(rows == 64u * 137500u);
+        sbc_destroy(c); c = nullptr;
+    }
+
     // ---- the server step that allocates nothing ----
     {
         int32_t* const status = reinterpret_cast<int32_t*>(0x500000000000ull);

@@ -17,6 +17,7 @@ static const void* g_kernels[64];      // and their kernels
 static long g_live_blocks = 0;
 static long g_fail_alloc_at = -1;      // the n-th allocation from now fails (tests the clean-up path)
 static bool g_withhold = false;        // no results are sent
+static hipError_t g_launch_error = hipSuccess;
 // The kernels that send results, by a part of their mangled name, and which of their arguments are the word
 // in pinned memory and the call's number.
 struct Sender { const char* name; int word, seq; const void* host[2]; };
@@ -53,7 +54,7 @@ extern "C" {
 hipError_t hipGetDeviceCount(int* n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int d) { return d == 0 ? hipSuccess : hipErrorInvalidDevice; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) { const hipError_t e = g_launch_error; g_launch_error = hipSuccess; return e; }
 
 hipError_t hipMalloc(void** p, size_t bytes) { return stub_alloc(p, bytes); }
 hipError_t hipFree(void* p) { return stub_free(p); }
@@ -77,7 +78,10 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
-    if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x == 0 || block.x * block.y * block.z > 1024) return hipErrorInvalidConfiguration;
+    // (as the runtime does: at most 2^32 - 1 work items in a dimension)
+    if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x == 0 || block.x * block.y * block.z > 1024 ||
+        (uint64_t)grid.x * block.x > 0xFFFFFFFFull || grid.y > 65535u || grid.z > 65535u)
+        return g_launch_error = hipErrorInvalidConfiguration;
     for (const Sender& s : g_senders)
         if ((f == s.host[0] || f == s.host[1]) && !g_withhold)       // (the number: bits 50 to 63 of the word)
             **static_cast<uint64_t**>(args[s.word]) = (uint64_t)(*static_cast<uint32_t*>(args[s.seq]) & 0x3FFFu) << 50;
