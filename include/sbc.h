@@ -225,13 +225,13 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream,
  *       saw many times k candidates (the data grew), until a call's sample says that the keys
  *       of the call before it would have held.  0 estimates the keys from a sample of the new
  *       data in every call.
- *   SBC_OPT_WIDE_MIN_KEPT      (default 0 = 8192 and 32768)  the candidate lists of a tensor that keeps at least
- *       this many entries per side count as long, its stream is decoded tile by tile by many
- *       workgroups instead of one, and with it those of the call's other tensors that are longer
- *       than a tile (the 32 longest of a call), by default from 8192 entries on; and its lists are
- *       narrowed down by many workgroups before one workgroup per side selects among the rest, by
- *       default if some tensor of the call keeps 32768 or more (a 1.5e9-entry tensor at p = 0.001
- *       keeps 1.5e6).  Tests lower it to send small tensors that way, or raise it.
+ *   SBC_OPT_WIDE_MIN_KEPT      (default 0 = 8192 and 32768)  the stream of a tensor that keeps at least this
+ *       many entries per side (8192 by default) is decoded tile by tile by many workgroups instead
+ *       of one, and with it those of the call's other tensors that are longer than a tile (the 32
+ *       longest of a call); and its candidate lists are narrowed down by many workgroups before one
+ *       workgroup per side selects among the rest, by default if some tensor of the call keeps 32768
+ *       or more (a 1.5e9-entry tensor at p = 0.001 keeps 1.5e6).  Tests lower it to send small
+ *       tensors that way, or raise it.
  *   SBC_OPT_SAMPLED_THRESHOLD  (0/1, default 0)  1 selects the subsampled variant of
  *       "Sparse Binarization" (the threshold is estimated from a random subsample, which makes
  *       the amount of sparsity noisy).  Per tensor t of the call a stratified sample of at most
@@ -269,9 +269,9 @@ int sbc_decode_status(sbc_ctx* ctx, void* hip_stream);
 
 /* Which routes the most recent successful sbc_compress() took: a bit set of
  * SBC_ROUTE_CARRIED_KEYS (filter keys came from the previous call, no sampling) and
- * SBC_ROUTE_HISTOGRAM (the histogram route ran for at least one tensor), SBC_ROUTE_WIDE (at
- * least one tensor's long lists were narrowed down to a bin of their window); SBC_EINVAL (negative) without a
- * successful call. */
+ * SBC_ROUTE_HISTOGRAM (the histogram route ran for at least one tensor), SBC_ROUTE_WIDE (the
+ * sweeps of many workgroups over long lists narrowed down at least one tensor's); SBC_EINVAL (negative)
+ * without a successful call. */
 enum { SBC_ROUTE_CARRIED_KEYS = 1, SBC_ROUTE_HISTOGRAM = 2, SBC_ROUTE_WIDE = 4,
        SBC_ROUTE_LOOSE_KEYS = 8,    /* some filter key let so many entries pass that the next call samples afresh */
        SBC_ROUTE_TAKEN_OVER = 16 }; /* a tensor the streaming kernel could not finish was completed by the

@@ -67,7 +67,7 @@ constexpr uint32_t kErrInternal = 2u;
 constexpr uint32_t kErrCorrupt = 4u;
 constexpr uint32_t kErrOverflow = 128u;  // a candidate list of a compact context cannot hold what the histogram route extracts
 constexpr uint32_t kErrPrefilter = 8u;   // not an error: some tensor needs the histogram path
-constexpr uint32_t kErrWide = 32u;       // not an error: some tensor's long lists were narrowed down to one bin
+constexpr uint32_t kErrWide = 32u;       // not an error: the sweeps for long lists narrowed some tensor down
 constexpr uint32_t kErrLoose = 16u;      // not an error: a carried-over filter key let far too many entries pass
 constexpr uint32_t kErrStaleKeys = 256u; // not an error: the filter keys the previous call left would have let far too many entries pass now
 constexpr uint32_t kErrDeferred = 64u;   // not an error: a tensor the streaming kernel could not finish itself is left to the kernels after it
@@ -88,7 +88,6 @@ __host__ __device__ inline unsigned long long loose_limit(uint32_t k, uint32_t n
 // TensorDesc::flags
 constexpr uint32_t kDescWide = 2u;       // keeps so many entries that sweeps by many workgroups narrow its lists down first
 constexpr uint32_t kDescSampled = 4u;    // subsampled variant: the sampled threshold decides what is kept
-constexpr uint32_t kDescLong = 16u;      // keeps so many entries that its lists count as long (SBC_ROUTE_WIDE)
 constexpr uint32_t kDescInline = 8u;     // finished inside the streaming kernel by the last of its workgroups
 // TensorState::flags
 constexpr uint32_t kStFailed = 1u;       // prefilter kept fewer than k candidates on a side

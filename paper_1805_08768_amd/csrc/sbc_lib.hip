@@ -800,7 +800,6 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
             all_inline = all_inline && inl;
             d.grp0 = (uint32_t)groups;
             if (inl) groups += n_groups;
-            if (!inl && d.kcap >= c->wide_min_kept) d.flags |= kDescLong;
             if (!inl && any_sweep && d.kcap >= c->wide_min_kept && n_wide < c->max_wide) {
                 d.flags |= kDescWide;
                 d.wide = (uint32_t)n_wide;

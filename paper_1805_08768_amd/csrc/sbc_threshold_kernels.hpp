@@ -543,7 +543,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     }
     // many times more candidates than needed: the next call should estimate its keys afresh
     if (full_cnt > loose_limit(d.k, d.n)) raise |= kErrLoose;
-    if (wide || (pass == 0 && placed && (d.flags & (kDescLong | kDescWide)) == kDescLong)) raise |= kErrWide;
+    if (wide) raise |= kErrWide;
     if (raise) atomicOr(&result->err, raise);
     SBC_TS(1, 7);
 }

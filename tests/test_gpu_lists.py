@@ -76,7 +76,7 @@ def test_kept_entries_around_the_limits_of_long_lists(k):
         for r in range(2):
             res = check_round(run, [synth.gaussian_update(n, round_=r)], R, p, check_decode=(r == 0))
             assert res[0].k == k
-            assert bool(sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_WIDE) == (k >= 8192)
+            assert bool(sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_WIDE) == (k >= 32768)
             R = [x.R_new for x in res]
 
 

@@ -541,18 +541,20 @@ def test_grid_wide_selection():
         check_round(run, dWs, [np.zeros(n, np.float32) for n in sizes], p)
 
 
-def test_grid_wide_selection_four_rounds_at_the_default_threshold():
-    """The 2^20-entry Gaussian tensor of configuration 1 (10485 kept entries: sweeps at the default
-    threshold) over four rounds with the residual carried, alone and with a small tensor beside it."""
+@pytest.mark.parametrize("n,k,sweeps", [(1 << 20, 10485, False), (3300000, 33000, True)])
+def test_grid_wide_selection_four_rounds_at_the_default_threshold(n, k, sweeps):
+    """The 2^20-entry Gaussian tensor of configuration 1 (10485 kept entries: one workgroup per side) and
+    one with sweeps at the default threshold, over four rounds with the residual carried, alone and with a
+    small tensor beside it."""
     p = 0.01
-    for sizes in ([1 << 20], [1 << 20, 5000]):
+    for sizes in ([n], [n, 5000]):
         with DeviceRun(sizes) as run:
             R = [np.zeros(n, np.float32) for n in sizes]
             for r in range(4):
                 dWs = [synth.gaussian_update(n, round_=r, tensor=i) for i, n in enumerate(sizes)]
                 res = check_round(run, dWs, R, p, check_decode=(r in (0, 3)))
-                assert res[0].k == 10485
-                assert sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_WIDE
+                assert res[0].k == k
+                assert bool(sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_WIDE) == sweeps
                 R = [x.R_new for x in res]
 
 
