@@ -229,9 +229,10 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream,
  *       many entries per side (8192 by default) is decoded tile by tile by many workgroups instead
  *       of one, and with it those of the call's other tensors that are longer than a tile (the 32
  *       longest of a call); and its candidate lists are narrowed down by many workgroups before one
- *       workgroup per side selects among the rest, by default if some tensor of the call keeps 32768
- *       or more (a 1.5e9-entry tensor at p = 0.001 keeps 1.5e6).  Tests lower it to send small
- *       tensors that way, or raise it.
+ *       workgroup per side selects among the rest: in every call if the option is set, by default in
+ *       calls whose longest list is expected to hold 98304 entries or more (some tensor keeps 32768,
+ *       or the call before saw such a list).  Tests lower it to send small tensors that way, or raise
+ *       it.
  *   SBC_OPT_SAMPLED_THRESHOLD  (0/1, default 0)  1 selects the subsampled variant of
  *       "Sparse Binarization" (the threshold is estimated from a random subsample, which makes
  *       the amount of sparsity noisy).  Per tensor t of the call a stratified sample of at most

@@ -124,8 +124,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_thresholds(
         const double r = floor(sampled_p * (double)m);
         rs = r < 1.0 ? 1u : (uint32_t)r;
     } else if (n > (uint32_t)kSampleMax) {
-        const double lambda = (double)d.k * (double)m / (double)n;
-        rs = (uint32_t)ceil(lambda + 4.0 * sqrt(lambda) + 3.0);
+        rs = sample_rank(d.k, m, n);
     }
     if (rs >= m) return;                              // keep the all-pass keys (0, 0)
     const int passes = sampled ? 4 : 2;               // all 32 key bits, or the leading 16

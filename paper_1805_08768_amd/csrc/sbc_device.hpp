@@ -70,6 +70,7 @@ constexpr uint32_t kErrPrefilter = 8u;   // not an error: some tensor needs the 
 constexpr uint32_t kErrWide = 32u;       // not an error: the sweeps for long lists narrowed some tensor down
 constexpr uint32_t kErrLoose = 16u;      // not an error: a carried-over filter key let far too many entries pass
 constexpr uint32_t kErrStaleKeys = 256u; // not an error: the filter keys the previous call left would have let far too many entries pass now
+constexpr uint32_t kErrLong = 512u;      // not an error: a list of a tensor that the sweeps can take was longer than long_list()
 constexpr uint32_t kErrDeferred = 64u;   // not an error: a tensor the streaming kernel could not finish itself is left to the kernels after it
 
 // ... that stop a client step before its message: tensors to be redone, or failures
@@ -85,8 +86,25 @@ __host__ __device__ inline unsigned long long loose_limit(uint32_t k, uint32_t n
     return hi < cap ? hi : cap;
 }
 
+// Candidates per side beyond which sweeps by many workgroups are worth their two launches.  One workgroup per
+// side alone (k_threshold) is bound by its LDS histogram and by what a compute unit pulls in, 0.35 us per 1000
+// candidates, but takes no launches: one Gaussian tensor, p = 0.01, residual carried, step in us, alone / with
+// sweeps: 1e6 entries (26,000 candidates alone, 33,000 with sweeps, for those do not look at what the update
+// moved, see net_known in k_threshold) 44.5 / 50.0, 2e6 50.7 / 53.0, 3e6 58.2 / 58.1 (77,000, 100,000), 4e6 75.7 /
+// 64.9, 7e6 105 / 72, 20e6 229 / 99.  (A tensor of k kept entries whose lists are no longer than 5 k is left
+// alone: they get that long with sweeps, and half as long without.)
+constexpr uint32_t kLongList = 98304;
+__host__ __device__ inline unsigned long long long_list(uint32_t k) {
+    return 5ull * k > kLongList ? 5ull * k : kLongList;
+}
+// Entries of a sample of m out of n that the filter key of a side lets pass (k_sample_thresholds).
+__host__ __device__ inline uint32_t sample_rank(uint32_t k, uint32_t m, uint32_t n) {
+    const double lambda = (double)k * (double)m / (double)n;
+    return (uint32_t)ceil(lambda + 4.0 * sqrt(lambda) + 3.0);
+}
+
 // TensorDesc::flags
-constexpr uint32_t kDescWide = 2u;       // keeps so many entries that sweeps by many workgroups narrow its lists down first
+constexpr uint32_t kDescWide = 2u;       // keeps so many entries that sweeps can narrow its lists down first
 constexpr uint32_t kDescSampled = 4u;    // subsampled variant: the sampled threshold decides what is kept
 constexpr uint32_t kDescInline = 8u;     // finished inside the streaming kernel by the last of its workgroups
 // TensorState::flags

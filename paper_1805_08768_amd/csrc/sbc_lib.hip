@@ -41,11 +41,12 @@ constexpr uint32_t kMaxDecExtra = 512;    // additional decode workgroups that s
 constexpr uint32_t kDecSharePer = 256;    // kept entries per sharing workgroup
 constexpr uint32_t kDecShareMax = kDecWaves;    // (a wavefront's updates each)
 constexpr uint32_t kWideMinKept = 8192;   // kept entries from which a stream is decoded by many workgroups
-// Kept entries per side from which sweeps by many workgroups narrow a tensor's lists down before k_threshold.  One
-// workgroup per side alone is bound by its LDS histogram and by what a compute unit pulls in, about 0.1 us per
-// 1000 entries of a list, but takes no launches: one tensor, p = 0.01, step in us, alone / with sweeps: 10,000
-// kept entries 38 / 47, 20,000 47 / 53, 35,000 65 / 63, 50,000 86 / 63, 200,000 360 / 110.  (Ten tensors
-// with 8,000 to 24,000 in the ResNet-50 shape: 25 us for k_threshold, 31 with the sweeps.)
+// Sweeps by many workgroups narrow the lists of tensors of kWideMinKept kept entries or more down before
+// k_threshold in calls whose longest list is expected beyond kLongList: a tensor of kSweepMinKept kept entries
+// has lists of three times that in most calls; a sampled call's lists follow from its sample's rank; otherwise
+// the call before has seen a long one (kErrLong).  (Ten tensors with 8,000 to 24,000 in the ResNet-50 shape: 25
+// us for k_threshold, 31 with the sweeps.  Expecting lists of six times the kept entries in the second call of
+// a run, where a residual that starts from nothing lets them grow to five to eight times: no difference.)
 constexpr uint32_t kSweepMinKept = 32768;
 
 struct DescSlot {
@@ -142,7 +143,8 @@ struct sbc_ctx {
     int cache_force_exact = 0;
     std::vector<TensorDesc> plan;         // without the pointers
     std::vector<uint32_t> plan_order;
-    int n_wide = 0;                       // tensors whose long lists are narrowed down by sweeps
+    int n_wide = 0;                       // tensors whose lists the sweeps can take, and which calls have sweeps:
+    bool sweep_always = false, sweep_sampled = false;      // all; those that sample
     uint32_t wide_blocks = 0;
     DescSlot slot[kDescSlots];            // which pointer lists the device tables hold
     uint64_t slot_clock = 0;
@@ -165,10 +167,12 @@ struct sbc_ctx {
     int defer_decode = 0;                 // decode calls return once enqueued; sbc_decode_status reports
     bool deferred_pending = false;        // some deferred decode has not been waited for yet
     bool deferred_dirty = true;           // block [4] must be cleared before the next deferred decode
-    uint32_t wide_min_kept = kWideMinKept, sweep_min_kept = kSweepMinKept;
+    uint32_t wide_min_kept = kWideMinKept;
+    bool sweep_all = false;               // tensors that keep that many have sweeps in every call
 
     // filter keys carried over from the previous successful call (same tensor sizes, same p)
     bool hist_valid = false;
+    bool hist_long = false;               // that call had a long list
     double hist_p = 0.0;
     std::vector<uint32_t> hist_n;
 
@@ -192,7 +196,7 @@ struct sbc_ctx {
         hipStream_t stream = nullptr;
         int T = 0, b = 0, slot = 0, force_exact = 0, carry = 0;
         double p = 0.0;
-        bool slot_is_new = false, use_history = false, sampled = false, all_inline = false;
+        bool slot_is_new = false, use_history = false, sampled = false, all_inline = false, sweeps = false;
         bool wait_on_event = false;   // begin/end form: the wait ends with this step, not with the stream
         bool timed[kNumStages] = {};
         ResultBlock* res_now = nullptr;
@@ -318,7 +322,8 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
     bool* timed = P.timed;
     const int T = P.T, b = P.b;
     if (pass != 0 || !P.all_inline) {
-        if (pass == 0 && c->n_wide > 0) {
+        const bool sweeps = pass == 0 && P.sweeps;
+        if (sweeps) {
             const dim3 sweep(c->wide_blocks, 2u * (unsigned)c->n_wide);
             if (lvl >= 2) {
                 hipExtLaunchKernelGGL(k_wide_count, sweep, dim3(kWideThreads), 0, stream, c->ev[2 * kStWide], nullptr, 0,
@@ -337,7 +342,7 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
         // (c->d_order: see compress_begin)
         SBC_LAUNCH(kStThreshold, profile, k_threshold, dim3(2u * (unsigned)T), dim3(kThThreads),
                    P.d_desc, T > kComputeUnits / 2 ? c->d_order : nullptr, c->d_state, c->d_counters, c->cand(), c->d_bitmap, c->d_wide_state,
-                       c->d_wide_hist, c->d_wide_acc, pass, P.carry, P.res_now);
+                       c->d_wide_hist, c->d_wide_acc, pass, sweeps ? 1 : 0, P.carry, P.res_now);
         const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
         SBC_LAUNCH(kStApply, profile, k_apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
                    c->cand(), c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, pass, P.n_chunks, P.res_now);
@@ -669,7 +674,7 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
         case SBC_OPT_WIDE_MIN_KEPT:
             if (value < 0) return SBC_EINVAL;
             c->wide_min_kept = value ? (uint32_t)value : kWideMinKept;
-            c->sweep_min_kept = value ? (uint32_t)value : kSweepMinKept;
+            c->sweep_all = value != 0;
             c->cache_valid = false;                    // which tensors are wide is part of both plans
             c->dev_dec_valid = false;
             return SBC_OK;
@@ -759,11 +764,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         for (int i = 0; i < kDescSlots; ++i) c->slot[i].valid = false;
         if (c->plan.size() < (size_t)T) c->plan.resize(T);
         int n_wide = 0;
-        // (where some tensor has sweeps, so have all with long lists: the launches are there anyway)
-        bool any_sweep = false;
-        for (int t = 0; t < T && !any_sweep; ++t)
-            any_sweep = numel[t] >= 1 && numel[t] < (int64_t)1 << 32 &&
-                        (uint64_t)cap_of(numel[t], kept_of(numel[t], p), sampled) >= c->sweep_min_kept;
+        // (where some tensor has sweeps, so have all that can: the launches are there anyway)
+        c->sweep_always = c->sweep_sampled = false;
         uint64_t wide_max_n = 0;
         for (int t = 0; t < T; ++t) {
             const int64_t n = numel[t];
@@ -800,8 +802,12 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
             all_inline = all_inline && inl;
             d.grp0 = (uint32_t)groups;
             if (inl) groups += n_groups;
-            if (!inl && any_sweep && d.kcap >= c->wide_min_kept && n_wide < c->max_wide) {
+            if (!inl && d.kcap >= c->wide_min_kept && n_wide < c->max_wide) {
                 d.flags |= kDescWide;
+                const uint32_t rank = sampled || n <= kSampleMax ? 0u : sample_rank(d.k, kSampleMax, d.n);
+                const uint64_t by_sample = rank >= (uint32_t)kSampleMax ? (uint64_t)n : rank ? (uint64_t)rank * (uint64_t)n / kSampleMax : d.k;
+                c->sweep_always = c->sweep_always || c->sweep_all || (!sampled && d.k >= kSweepMinKept);
+                c->sweep_sampled = c->sweep_sampled || by_sample > kLongList;
                 d.wide = (uint32_t)n_wide;
                 c->wide_ids.id[n_wide++] = (uint32_t)t;
                 wide_max_n = std::max<uint64_t>(wide_max_n, (uint64_t)n);
@@ -930,6 +936,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     P.stream = stream; P.T = T; P.b = b; P.p = p; P.slot = slot; P.slot_is_new = slot_is_new;
     P.force_exact = force_exact; P.use_history = use_history; P.sampled = sampled;
     P.all_inline = all_inline;
+    P.sweeps = c->n_wide > 0 && (c->sweep_always || (use_history ? c->hist_long : c->sweep_sampled));
     for (int st = 0; st < kNumStages; ++st) P.timed[st] = false;
     P.res_now = res_now; P.res_next = res_next; P.d_desc = d_desc; P.msg8 = msg8;
     P.msg_capacity = msg_capacity; P.need = need; P.n_chunks = n_chunks; P.gather_y = gather_y; P.scan_tiles = scan_tiles; P.chunks_max = chunks_max;
@@ -1074,6 +1081,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
         }
     }
     if (c->hist_valid) {
+        c->hist_long = (err & kErrLong) != 0u;
         c->hist_p = P.p;
         c->hist_n.resize(T);
         for (int t = 0; t < T; ++t) c->hist_n[t] = c->plan[t].n;

@@ -235,7 +235,8 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // --------------------------------------------------------------------------
 // One workgroup of 1024 threads per (tensor, side); `order` lists the tensors by decreasing size
 // (null: as they come).  pass 0: every tensor no earlier kernel has finished or flagged; pass 1:
-// tensors handed over (histogram route, or left by the streaming kernel).
+// tensors handed over (histogram route, or left by the streaming kernel).  sweeps: k_wide_count and
+// k_wide_collect have run in this pass.
 // Every workgroup runs its code once, and for most it is a chain of short dependent steps: 1.2 us to the
 // counts, 1.3 to the list and its histogram, 0.8 to the bin, 0.5 for the second pass, 0.6 for the ranks, 0.7 to
 // the end, whatever the list.  Long lists are bound by the LDS histogram (14 cycles per 64 keys) and by the
@@ -247,7 +248,7 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
         const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
-        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int carry, ResultBlock* __restrict__ result) {
+        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int sweeps, int carry, ResultBlock* __restrict__ result) {
     __shared__ __attribute__((aligned(16))) ThresholdShared sh;
     SBC_TS(1, 0);
     const int s = (int)(blockIdx.x & 1u), tid = threadIdx.x;
@@ -279,7 +280,8 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     const uint32_t w2 = 2u * d.wide + (uint32_t)s;
     WideState wst;
     wst.ok = 0u;
-    if (pass == 0 && (d.flags & kDescWide)) {
+    const bool swept = sweeps && (d.flags & kDescWide);
+    if (swept) {
         wst = ws[w2];
         // (every workgroup of k_wide_collect has read the window's counts: they end the call clean)
         reinterpret_cast<uint4*>(whist + (size_t)w2 * kThBins)[tid] = make_uint4(0u, 0u, 0u, 0u);
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     // entry (carried_rank).  A call that started from a carried key sees how many entries its update
     // moved across it: `expect` were known to lie beyond it, less those the call before then sent.
     uint32_t next_bin = wide ? wst.next_rank_bin : 0xFFFFFFFFu;
-    const bool net_known = pass == 0 && carry && expect != 0u && !(d.flags & kDescWide);
+    const bool net_known = pass == 0 && carry && expect != 0u && !swept;
     const uint32_t sent_before = prev_side == (s ? -1 : 1) ? d.k : 0u;
     const uint32_t rank2 = net_known ? carried_rank(d.k, (long long)full_cnt - ((long long)expect - (long long)sent_before))
                                      : carried_rank(d.k);
@@ -537,13 +539,14 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         const bool ranked = next_bin != 0xFFFFFFFFu;
         uint32_t next = (base + next_bin) << kThShift;
         if (__builtin_expect(!ranked, 0))
-            next = (d.flags & kDescWide) ? lowered_key(lo_key, 0.1f) : extrapolated_key(tau, lo_key, d.k, rank2, d.n, full_cnt);
+            next = swept ? lowered_key(lo_key, 0.1f) : extrapolated_key(tau, lo_key, d.k, rank2, d.n, full_cnt);
         st[t].lo_key[s] = next;
-        st[t].expect[s] = ranked && !(d.flags & kDescWide) ? rank2 : 0u;
+        st[t].expect[s] = ranked ? rank2 : 0u;
     }
     // many times more candidates than needed: the next call should estimate its keys afresh
     if (full_cnt > loose_limit(d.k, d.n)) raise |= kErrLoose;
     if (wide) raise |= kErrWide;
+    if ((d.flags & kDescWide) && full_cnt > long_list(d.k)) raise |= kErrLong;
     if (raise) atomicOr(&result->err, raise);
     SBC_TS(1, 7);
 }

@@ -20,6 +20,8 @@ extern "C" long stub_live_blocks();
 extern "C" void stub_fail_allocation(long nth);
 extern "C" void stub_withhold_results(int on);
 extern "C" int stub_known_senders();
+extern "C" void stub_result_bits(uint32_t bits);
+extern "C" int stub_launched(const char* name, long from);
 
 #define CHECK(cond)                                                                     \
     do {                                                                                \
@@ -261,6 +263,43 @@ int main(int argc, char** argv) {
         const unsigned tiles = 19 + 31 * 2;
         CHECK(stub_grid(first + 1) == tiles && stub_grid(first + 2) == 4 * tiles);     // k_dec_tile_sums, k_dec_tile_place
         sbc_destroy(c); c = nullptr;
+    }
+
+    // ---- which calls have sweeps over their lists: by what the lists' length is going to be.  `first`: a call
+    // that samples, `later`: one on carried keys after a call that saw no long list; after a call that saw one
+    // (bit 512 of its error word) the sweeps come whatever the tensor ----
+    {
+        struct Case { int64_t n; double p; bool sampled; int first, later, after_long; };
+        const Case cases[] = {
+            {800000, 0.01, false, 0, 0, 0},            // 8000 kept entries: never
+            {1048576, 0.01, false, 0, 0, 1},           // 10485
+            {3276700, 0.01, false, 0, 0, 1},           // 32767
+            {3276800, 0.01, false, 1, 1, 1},           // 32768: always
+            {150000000, 1e-4, false, 0, 0, 1},         // 15000, keys from 10 sampled entries: 92,000
+            {200000000, 1e-4, false, 1, 0, 1},         // 20000: 122,000
+            {3000000, 0.01, true, 0, 0, 0},            // subsampled: about as many candidates as kept entries, 30000
+            {9000000, 0.01, true, 0, 0, 0},            // 90000
+            {9900000, 0.01, true, 1, 1, 1},            // 99000
+        };
+        for (const Case& k : cases) {
+            const Buffers s = fake_buffers({k.n, 1000});
+            const size_t nb = sbc_msg_bound_sampled(s.numel.data(), s.T(), k.p);
+            CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            CHECK(sbc_set_option(c, SBC_OPT_SAMPLED_THRESHOLD, k.sampled ? 1 : 0) == SBC_OK);
+            auto sweeps = [&](uint32_t bits) {
+                const long from = stub_launches();
+                stub_result_bits(bits);
+                CHECK(compress(c, s, k.p, nb, &nbytes) == SBC_OK);
+                stub_result_bits(0);
+                CHECK(stub_launched("k_threshold", from) == 1 && stub_launched("k_wide_count", from) == stub_launched("k_wide_collect", from));
+                return stub_launched("k_wide_count", from);
+            };
+            CHECK(sweeps(0) == k.first && sweeps(0) == k.later);
+            CHECK(sweeps(512) == k.later && sweeps(0) == k.after_long && sweeps(0) == k.later);
+            CHECK(sbc_set_option(c, SBC_OPT_WIDE_MIN_KEPT, 5000) == SBC_OK && sweeps(0) == 1 && sweeps(0) == 1);
+            CHECK(sbc_set_option(c, SBC_OPT_WIDE_MIN_KEPT, 1 << 30) == SBC_OK && sweeps(0) == 0 && sweeps(512) == 0 && sweeps(0) == 0);
+            sbc_destroy(c); c = nullptr;
+        }
     }
 
     // ---- a context with short candidate lists: the plan shares them out, large p does not fit ----

@@ -17,7 +17,10 @@ static const void* g_kernels[64];      // and their kernels
 static long g_live_blocks = 0;
 static long g_fail_alloc_at = -1;      // the n-th allocation from now fails (tests the clean-up path)
 static bool g_withhold = false;        // no results are sent
+static uint32_t g_result_bits = 0;     // the error word that results carry
 static hipError_t g_launch_error = hipSuccess;
+static struct { const void* host; const char* name; } g_names[128];      // every kernel with its mangled name
+static int g_n_names = 0;
 // The kernels that send results, by a part of their mangled name, and which of their arguments are the word
 // in pinned memory and the call's number.
 struct Sender { const char* name; int word, seq; const void* host[2]; };
@@ -30,6 +33,15 @@ extern "C" const void* stub_kernel(long launch) { return g_kernels[launch % 64];
 extern "C" long stub_live_blocks() { return g_live_blocks; }
 extern "C" void stub_fail_allocation(long nth) { g_fail_alloc_at = nth; }
 extern "C" void stub_withhold_results(int on) { g_withhold = on != 0; }
+extern "C" void stub_result_bits(uint32_t bits) { g_result_bits = bits; }
+// How many of the launches from number `from` on (of the latest 64) were of kernels with that name.
+extern "C" int stub_launched(const char* name, long from) {
+    int n = 0;
+    for (long i = from; i < g_launches; ++i)
+        for (int k = 0; k < g_n_names; ++k)
+            n += g_kernels[i % 64] == g_names[k].host && std::strstr(g_names[k].name, name);
+    return n;
+}
 extern "C" int stub_known_senders() {
     int n = 0;
     for (const Sender& s : g_senders) n += (s.host[0] != nullptr) + (s.host[1] != nullptr);
@@ -84,7 +96,8 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         return g_launch_error = hipErrorInvalidConfiguration;
     for (const Sender& s : g_senders)
         if ((f == s.host[0] || f == s.host[1]) && !g_withhold)       // (the number: bits 50 to 63 of the word)
-            **static_cast<uint64_t**>(args[s.word]) = (uint64_t)(*static_cast<uint32_t*>(args[s.seq]) & 0x3FFFu) << 50;
+            **static_cast<uint64_t**>(args[s.word]) = (uint64_t)(*static_cast<uint32_t*>(args[s.seq]) & 0x3FFFu) << 50 |
+                                                      (uint64_t)g_result_bits << 40;
     g_grids[g_launches % 64] = grid.x;
     g_kernels[g_launches++ % 64] = f;
     return hipSuccess;
@@ -100,6 +113,7 @@ hipError_t hipGetSymbolAddress(void** p, const void* symbol) { *p = const_cast<v
 void** __hipRegisterFatBinary(const void*) { static void* handle = nullptr; return &handle; }
 void __hipUnregisterFatBinary(void**) {}
 void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*, void*, void*, void*, int*) {
+    if (g_n_names < 128) g_names[g_n_names++] = {host, name};
     for (Sender& s : g_senders)
         if (std::strstr(name, s.name)) s.host[s.host[0] ? 1 : 0] = host;
 }
