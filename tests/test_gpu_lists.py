@@ -102,3 +102,18 @@ def test_compact_context_whose_segment_overflows():
         assert torch.equal(R, x - out)
     finally:
         sbc.sbc_destroy(ctx)
+
+
+def test_keys_left_by_a_sampled_call_on_data_of_two_scales():
+    """Three chunks of 256 hold entries fifty times as large as all others, fewer than are kept: a sampled
+    call's list ends near the k-th entry, far below the first of the large ones, and says nothing about what
+    follows it.  The key it leaves for the next call must not let half the tensor pass."""
+    n, p = CHUNK * 256, 0.01
+    with DeviceRun([n]) as run:
+        R = [np.zeros(n, np.float32)]
+        for r in range(8):
+            x = synth.gaussian_update(n, round_=r).reshape(-1, CHUNK)
+            x[40:43] *= 50.0
+            res = check_round(run, [x.reshape(-1)], R, p, check_decode=False)
+            assert max(sbc.sbc_last_candidates(run.ctx, 0)) < n // 8, (r, sbc.sbc_last_route(run.ctx))
+            R = [v.R_new for v in res]
