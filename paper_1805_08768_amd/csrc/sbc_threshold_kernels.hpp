@@ -165,11 +165,13 @@ __device__ __forceinline__ uint32_t window_bin(uint32_t key, uint32_t base) {
 // rank2 = 0 looks for none).  res[0] and res[2] must hold 0xFFFFFFFF when the first barrier is
 // reached.  The counts are zero again afterwards.  Two barriers.  (All 1024 threads, four bins each: one
 // 16-byte piece of LDS per thread, without bank conflicts; by 256 threads with sixteen bins 1.6 us instead of 0.7.)
-__device__ __forceinline__ void pick_bin(uint32_t* hist, uint32_t need, uint32_t rank2, uint32_t* scratch, uint32_t* res) {
+// Returns the thread's counts, of the bins from piece_bin() on.
+__device__ __forceinline__ uint32_t piece_bin() { return (uint32_t)(kThBins - 4) - 4u * threadIdx.x; }
+__device__ __forceinline__ uint4 pick_bin(uint32_t* hist, uint32_t need, uint32_t rank2, uint32_t* scratch, uint32_t* res) {
     static_assert(kThBins == 4 * kThThreads && kThThreads / 64 == 16, "16-byte pieces; one row of lanes holds the wavefronts' sums");
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     uint4* const h4 = reinterpret_cast<uint4*>(hist);
-    const int piece = kThBins / 4 - 1 - tid;
+    const uint32_t piece = piece_bin() / 4u;
     const uint4 v = h4[piece];
     h4[piece] = make_uint4(0u, 0u, 0u, 0u);
     const uint32_t sum = v.x + v.y + v.z + v.w;
@@ -187,13 +189,14 @@ __device__ __forceinline__ void pick_bin(uint32_t* hist, uint32_t need, uint32_t
         const uint32_t c[4] = {v.w, v.z, v.y, v.x};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t bin = (uint32_t)(4 * piece + 3 - j);
+            const uint32_t bin = 4u * piece + 3u - (uint32_t)j;
             if (cum < need && need <= cum + c[j]) { res[0] = bin; res[1] = cum; res[3] = c[j]; }
             if (cum < rank2 && rank2 <= cum + c[j]) res[2] = bin;
             cum += c[j];
         }
     }
     __syncthreads();
+    return v;
 }
 
 struct ThresholdShared {
@@ -335,10 +338,30 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
             }
         }
     };
-    auto stream = [&](auto f) {                        // f(entry), from memory (only where that is rare)
+    // The same from memory, entry by entry, for what is rare: f(key, index), of which the index is only there
+    // for keys that need(key) names.  (Both arrays have room for the last four's.)
+    auto again = [&](auto need_index, auto f) {
 #pragma nounroll
-        for (uint32_t i = first; i < mine_cnt; i += step_by) f(list.get(i));
+        for (uint32_t p0 = first; 4u * p0 < mine_cnt; p0 += 2u * step_by) {
+            u32x4_any k[2], x[2];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) { const uint32_t p = p0 + (uint32_t)j * step_by; k[j] = vecs[4u * p < mine_cnt ? p : p0]; }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t p = p0 + (uint32_t)j * step_by;
+                x[j] = 0u;
+                if (need_index(k[j].x) || need_index(k[j].y) || need_index(k[j].z) || need_index(k[j].w))
+                    x[j] = reinterpret_cast<const u32x4_any*>(list.key + list.to_idx)[4u * p < mine_cnt ? p : p0];
+            }
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint32_t i = 4u * (p0 + (uint32_t)j * step_by);
+#pragma unroll
+                for (uint32_t e = 0; e < 4u; ++e) if (i + e < mine_cnt) f(k[j][e], x[j][e]);
+            }
+        }
     };
+    auto no_index = [](uint32_t) { return false; };
 
     uint32_t tau = lo_key, itau = 0xFFFFFFFFu, keep = 0u, ties = 0u;
     // Filter key a following call may start from instead of sampling.  With the residual carried
@@ -437,13 +460,19 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
                 if (at_least < need) mine += (double)__uint_as_float(me & 0x7FFFFFFFu);
             }
         } else if (pick) {
-            pick_bin(sh.hist, need, 0u, sh.scratch, sh.res[1]);
+            const uint4 in_piece = pick_bin(sh.hist, need, 0u, sh.scratch, sh.res[1]);
             const uint32_t digit = uniform(sh.res[1][0]);
             ok = digit != 0xFFFFFFFFu;
             tau = from | (digit & (uint32_t)(kThBins - 1));
             ties = uniform(sh.res[1][3]);
             need -= uniform(sh.res[1][1]);
-            stream([&](const uint2& e) { add(e.x, e.x > tau && e.x <= beyond); });
+            // the bin's entries beyond tau, from their counts
+            const uint32_t counted[4] = {in_piece.x, in_piece.y, in_piece.z, in_piece.w};
+#pragma unroll
+            for (uint32_t j = 0; j < 4u; ++j) {
+                const uint32_t k = from + piece_bin() + j;
+                if (counted[j] != 0u && k > tau) mine += (double)counted[j] * (double)__uint_as_float(k & 0x7FFFFFFFu);
+            }
         }
         if (limit == 0u || most >= limit) sh.spread = 1u;
         mine = wave_sum_f64(mine);
@@ -467,10 +496,10 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
                     const int shift = level == 0 ? 20 : level == 1 ? 8 : 0, bits = level == 2 ? 8 : 12;
                     __syncthreads();                   // the results of the step before have been read
                     if (tid < 4) sh.res[0][tid] = 0xFFFFFFFFu;
-                    stream([&](const uint2& e) {
-                        const uint32_t v = mode ? ~e.y : e.x;
-                        if ((mode == 0 || e.x == tau) && (level == 0 || (v >> (shift + bits)) == found))
-                            atomicAdd(&sh.hist[(v >> shift) & ((1u << bits) - 1u)], 1u);
+                    again([&](uint32_t k) { return mode && k == tau; }, [&](uint32_t k, uint32_t idx) {
+                        if (mode && k != tau) return;
+                        const uint32_t v = mode ? ~idx : k;
+                        if (level == 0 || (v >> (shift + bits)) == found) atomicAdd(&sh.hist[(v >> shift) & ((1u << bits) - 1u)], 1u);
                     });
                     __syncthreads();
                     pick_bin(sh.hist, r, 0u, sh.scratch, sh.res[0]);
@@ -491,7 +520,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     }
     if (!placed) {                                     // uniform: added up here, with the threshold that was found at last
         limit = exact_limit(tau, kc);
-        stream([&](const uint2& e) { add(e.x, e.x > tau); });
+        again(no_index, [&](uint32_t k, uint32_t) { add(k, k > tau); });
         if (limit == 0u || most >= limit) sh.spread = 1u;
         mine = wave_sum_f64(mine);
         if ((tid & 63) == 63) sh.dsum[tid >> 6] = mine;
@@ -508,10 +537,10 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         if (tid < 256) sh.acc[tid] = 0ll;
         __syncthreads();
         long long scaled = 0ll;
-        stream([&](const uint2& e) {
-            if (!all && !cand_kept(e.x, e.y, tau, itau)) return;
+        again([&](uint32_t k) { return k == tau; }, [&](uint32_t k, uint32_t idx) {
+            if (!all && !cand_kept(k, idx, tau, itau)) return;
             uint32_t ex;
-            const long long m = signed_mantissa(e.x, s, ex);
+            const long long m = signed_mantissa(k, s, ex);
             if (common && ex - e_tau <= 24u) scaled += m << (ex - e_tau);
             else if (m != 0ll) atomicAdd(reinterpret_cast<unsigned long long*>(&sh.acc[ex]), (unsigned long long)m);
         });
