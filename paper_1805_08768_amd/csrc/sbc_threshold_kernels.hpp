@@ -76,15 +76,46 @@ struct ListCounts {
     uint32_t p, n;
     uint32_t segs;
     uint32_t over;        // some segment has more than it holds (nothing was stored beyond its end)
+    uint32_t crowded;     // some segment holds more than twice its part of the list
     uint32_t cnt[kSegs], before[kSegs];
     __device__ __forceinline__ uint32_t of(int side) const { return side ? n : p; }
     // as it was left in LDS, without the segments' figures
     __device__ __forceinline__ static ListCounts totals(const ListCounts& l) {
         ListCounts c;
-        c.p = uniform(l.p); c.n = uniform(l.n); c.segs = uniform(l.segs); c.over = uniform(l.over);
+        c.p = uniform(l.p); c.n = uniform(l.n); c.segs = uniform(l.segs); c.over = uniform(l.over); c.crowded = uniform(l.crowded);
         return c;
     }
+    // Entries [lo, hi) of the list as one piece that lie in segment g, counted from its start.
+    __device__ __forceinline__ uint2 part_of(uint32_t g, uint32_t lo, uint32_t hi) const {
+        const uint32_t b = uniform(before[g]), e = b + uniform(cnt[g]);
+        lo = max(lo, b); hi = min(hi, e);
+        return lo < hi ? make_uint2(lo - b, hi - b) : make_uint2(0u, 0u);
+    }
+    // Of `parts` wavefronts (more than there are segments) that share a crowded list of `all` entries, number me's:
+    // a segment, its place in it, and how many have that segment.  Every segment that holds anything has one, the
+    // others go by the entries, what is left over to the largest.
+    __device__ __forceinline__ uint3 share_of(uint32_t me, uint32_t parts, uint32_t all) const {
+        const uint32_t per = all / (parts - kSegs) + 1u;
+        uint32_t left = parts, largest = 0u, most = 0u;
+#pragma nounroll
+        for (uint32_t g = 0; g < kSegs; ++g) {
+            const uint32_t c = uniform(cnt[g]);
+            left -= c ? 1u + c / per : 0u;
+            if (c > most) { most = c; largest = g; }
+        }
+        uint3 share = make_uint3(largest, 0u, 1u);
+        uint32_t at = 0u;
+#pragma nounroll
+        for (uint32_t g = 0; g < kSegs; ++g) {
+            const uint32_t c = uniform(cnt[g]), has = (c ? 1u + c / per : 0u) + (g == largest ? left : 0u);
+            if (me - at < has) share = make_uint3(g, me - at, has);
+            at += has;
+        }
+        return share;
+    }
 };
+// Entries of a segment that are not worth cutting (k_threshold: what two wavefronts hold in registers).
+constexpr uint32_t kSegWhole = 2048;
 // Added up from the segments' counters by the first wavefront of a workgroup, for all of them: `to` lies in
 // LDS and holds once the next barrier has been passed.  (Every wavefront by itself: 0.6 us more.)
 __device__ __forceinline__ void count_list(ListCounts& to, const TensorDesc& d, const TensorState* __restrict__ st,
@@ -105,12 +136,16 @@ __device__ __forceinline__ void count_list(ListCounts& to, const TensorDesc& d, 
     upto += dpp_fetch<0x111, 0xf>(upto);
     upto += dpp_fetch<0x112, 0xf>(upto);
     upto += dpp_fetch<0x114, 0xf>(upto);
+    const int half = s ? 32 : 0;
+    const uint32_t mine = (uint32_t)(own >> half), all = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(upto >> half), (int)kSegs - 1);
+    const bool crowded = segs > 1u && __any(lane < kSegs && mine > kSegWhole && mine > all / (kSegs / 2u));
     if (lane < kSegs) {
-        const int half = s ? 32 : 0;
-        to.cnt[lane] = (uint32_t)(own >> half);
-        to.before[lane] = (uint32_t)(upto >> half) - (uint32_t)(own >> half);
+        to.cnt[lane] = mine;
+        to.before[lane] = (uint32_t)(upto >> half) - mine;
     }
-    if (lane == kSegs - 1u) { to.p = (uint32_t)upto; to.n = (uint32_t)(upto >> 32); to.segs = segs; to.over = over ? 1u : 0u; }
+    if (lane == kSegs - 1u) {
+        to.p = (uint32_t)upto; to.n = (uint32_t)(upto >> 32); to.segs = segs; to.over = over ? 1u : 0u; to.crowded = crowded ? 1u : 0u;
+    }
 }
 
 // What a tensor's candidate counts rule out before any selection: true if the tensor cannot be
@@ -291,16 +326,18 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     }
     const bool wide = wst.ok != 0u;
     // The list: this thread takes every step-th four of the `mine_cnt` entries from `list` on, starting with its own
-    // (a list in segments: two wavefronts each).
+    // (a list in segments: two wavefronts each, unless one of them is crowded: 21,000 kept entries all in one
+    // segment 37.6 us with two wavefronts, 14.5 so; spread evenly 15).
     const uint32_t segs = wide ? 1u : counts.segs;
     CandPtr list = wide ? wide_list(d, bitmap, s) : cand + d.cand_off + (s ? d.cand_cap : 0u);
     uint32_t mine_cnt = wide ? wst.count : full_cnt, step_by = kThThreads, first = (uint32_t)tid;
     if (segs > 1u) {                                   // uniform
-        const uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane(tid / (int)(kThThreads / kSegs));
-        mine_cnt = uniform(sh.counts.cnt[g]);
-        list = list + seg_before(d, segs, g);
-        step_by = kThThreads / kSegs;
-        first = (uint32_t)tid % (kThThreads / kSegs);
+        uint3 share = make_uint3(uniform((uint32_t)tid >> 6) / 2u, uniform((uint32_t)tid >> 6) % 2u, 2u);
+        if (__builtin_expect(counts.crowded != 0u, 0)) share = sh.counts.share_of(uniform((uint32_t)tid >> 6), kThThreads / 64u, full_cnt);
+        mine_cnt = uniform(sh.counts.cnt[share.x]);
+        list = list + seg_before(d, segs, share.x);
+        step_by = share.z * 64u;
+        first = share.y * 64u + (uint32_t)(tid & 63);
     }
     const uint32_t base = lo_key >> kThShift;
     // Sixteen keys of a thread at a time, in four loads that are in flight together; 0, which is the key of no
@@ -308,6 +345,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     // room for them.)
     constexpr int kVecs = 4;
     const u32x4_any* __restrict__ vecs = reinterpret_cast<const u32x4_any*>(list.key);
+    const uint32_t fours = mine_cnt / 4u + (mine_cnt % 4u ? 1u : 0u);          // (so that no place passes 2^32)
     const uint32_t wave_first = uniform(first);        // (the wavefront's first lane's)
     u32x4_any held[kVecs];
     auto load = [&](uint32_t p0) {
@@ -315,49 +353,57 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         for (int j = 0; j < kVecs; ++j) {
             const uint32_t p = p0 + (uint32_t)j * step_by;
             held[j] = 0u;
-            if (4u * p < mine_cnt) held[j] = vecs[p];
+            if (p < fours) held[j] = vecs[p];
         }
 #pragma unroll
         for (int j = 0; j < kVecs; ++j) {
-            const uint32_t i = 4u * (p0 + (uint32_t)j * step_by);
-            if (i < mine_cnt && i + 4u > mine_cnt) {   // (one lane of a list)
+            const uint32_t p = p0 + (uint32_t)j * step_by, left = mine_cnt - 4u * p;
+            if (p < fours && left < 4u) {            // (one lane of a list)
                 held[j].w = 0u;
-                if (i + 2u >= mine_cnt) held[j].z = 0u;
-                if (i + 1u >= mine_cnt) held[j].y = 0u;
+                if (left <= 2u) held[j].z = 0u;
+                if (left <= 1u) held[j].y = 0u;
             }
         }
     };
     const bool once = mine_cnt <= 4u * (uint32_t)kVecs * step_by;      // the keys stay in `held`
     auto for_fours = [&](bool again, auto f) {         // f(four keys, entries from the first lane's on) for the thread's share
-        for (uint32_t w0 = wave_first, p0 = first; 4u * w0 < mine_cnt; w0 += (uint32_t)kVecs * step_by, p0 += (uint32_t)kVecs * step_by) {
+        for (uint32_t w0 = wave_first, p0 = first; w0 < fours; w0 += (uint32_t)kVecs * step_by, p0 += (uint32_t)kVecs * step_by) {
             if (!again || !once) load(p0);
 #pragma unroll
             for (int j = 0; j < kVecs; ++j) {
-                const uint32_t i = 4u * (w0 + (uint32_t)j * step_by);
-                if (i < mine_cnt) f(held[j], mine_cnt - i);            // uniform
+                const uint32_t w = w0 + (uint32_t)j * step_by;
+                if (w < fours) f(held[j], mine_cnt - 4u * w);        // uniform
             }
         }
     };
     // The same from memory, entry by entry, for what is rare: f(key, index), of which the index is only there
-    // for keys that need(key) names.  (Both arrays have room for the last four's.)
+    // for keys that need_index(key) names.  (Both arrays have room for the last four's.)  Short lists take the short
+    // way: most are, and code that is fetched for the first time costs more than what it does (2.4 us on 64 entries).
     auto again = [&](auto need_index, auto f) {
+        if (__builtin_expect(mine_cnt <= step_by, 1)) {                // uniform
+            if (first < mine_cnt) {
+                const uint32_t k = list.key[first];
+                f(k, need_index(k) ? list.key[first + list.to_idx] : 0u);
+            }
+            return;
+        }
 #pragma nounroll
-        for (uint32_t p0 = first; 4u * p0 < mine_cnt; p0 += 2u * step_by) {
+        for (uint32_t p0 = first; p0 < fours; p0 += 2u * step_by) {
             u32x4_any k[2], x[2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) { const uint32_t p = p0 + (uint32_t)j * step_by; k[j] = vecs[4u * p < mine_cnt ? p : p0]; }
+            for (int j = 0; j < 2; ++j) { const uint32_t p = p0 + (uint32_t)j * step_by; k[j] = vecs[p < fours ? p : p0]; }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const uint32_t p = p0 + (uint32_t)j * step_by;
                 x[j] = 0u;
                 if (need_index(k[j].x) || need_index(k[j].y) || need_index(k[j].z) || need_index(k[j].w))
-                    x[j] = reinterpret_cast<const u32x4_any*>(list.key + list.to_idx)[4u * p < mine_cnt ? p : p0];
+                    x[j] = reinterpret_cast<const u32x4_any*>(list.key + list.to_idx)[p < fours ? p : p0];
             }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const uint32_t i = 4u * (p0 + (uint32_t)j * step_by);
+                const uint32_t p = p0 + (uint32_t)j * step_by, left = p < fours ? mine_cnt - 4u * p : 0u;
 #pragma unroll
-                for (uint32_t e = 0; e < 4u; ++e) if (i + e < mine_cnt) f(k[j][e], x[j][e]);
+                for (uint32_t e = 0; e < 4u; ++e) if (e < left) f(k[j][e], x[j][e]);
             }
         }
     };
@@ -612,15 +658,29 @@ __device__ __forceinline__ bool wide_applies(const TensorDesc& d, const ListCoun
     return (d.flags & kDescSampled) ? c.p >= 1u && c.n >= 1u : c.p >= d.k && c.n >= d.k;
 }
 
-// f(key, place in the list) for a thread's share of a side's list, which nb of the workgroups (of each segment,
-// nb / segs) take.
+// f(key, place in the list) for a thread's share of a side's list, which nb of the workgroups take: nb / segs of
+// each segment, or, where a segment is crowded, each its part of the list as a whole (42,000 kept entries all in
+// one segment: both sweeps 63 us the first way, 21 the second).
 template <int UNROLL, typename F>
 __device__ __forceinline__ void sweep_list(const TensorDesc& d, const ListCounts& c, uint32_t segs, int s, uint32_t nb, const CandPtr cand, F f) {
-    const uint32_t g = blockIdx.x % segs, cnt = uniform(c.cnt[g]);
-    const CandPtr list = cand + d.cand_off + (s ? d.cand_cap : 0u) + seg_before(d, segs, g);
-    const uint64_t stride = (uint64_t)(nb / segs) * kWideThreads;
+    const CandPtr whole = cand + d.cand_off + (s ? d.cand_cap : 0u);
+    const bool crowded = uniform(c.crowded) != 0u;
+    uint32_t g = crowded ? 0u : blockIdx.x % segs;
+    const uint32_t last = crowded ? segs : g + 1u;
+    const uint32_t per = uniform(c.of(s)) / nb + 1u;
+#pragma nounroll
+    for (; g < last; ++g) {
+        CandPtr list = whole + seg_before(d, segs, g);
+        uint64_t from = (uint64_t)(blockIdx.x / segs) * kWideThreads, stride = (uint64_t)(nb / segs) * kWideThreads;
+        uint32_t to = uniform(c.cnt[g]);
+        if (crowded) {                                 // this workgroup's part of the list as a whole, as far as it lies here
+            const uint64_t lo = (uint64_t)blockIdx.x * per, hi = lo + per;
+            const uint2 part = c.part_of(g, (uint32_t)min(lo, (uint64_t)0xFFFFFFFFu), (uint32_t)min(hi, (uint64_t)0xFFFFFFFFu));
+            from = part.x; to = part.y; stride = kWideThreads;
+        }
 #pragma unroll UNROLL
-    for (uint64_t i = (uint64_t)(blockIdx.x / segs) * kWideThreads + threadIdx.x; i < cnt; i += stride) f(list.key[i], list + i);
+        for (uint64_t i = from + threadIdx.x; i < to; i += stride) f(list.key[i], list + i);
+    }
 }
 
 // k_wide_count: window histogram of a side's list.  (Counting where the streaming kernel stores the

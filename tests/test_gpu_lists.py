@@ -117,3 +117,24 @@ def test_keys_left_by_a_sampled_call_on_data_of_two_scales():
             res = check_round(run, [x.reshape(-1)], R, p, check_decode=False)
             assert max(sbc.sbc_last_candidates(run.ctx, 0)) < n // 8, (r, sbc.sbc_last_route(run.ctx))
             R = [v.R_new for v in res]
+
+
+@pytest.mark.parametrize("sweeps", [False, True])
+@pytest.mark.parametrize("segments,ties", [((3,), False), ((3,), True), ((0, 7), False), ((0, 7), True)])
+def test_lists_crowded_into_few_segments(sweeps, segments, ties):
+    """All candidates of a list but a few in one or two of its eight segments: shares are cut from the list as
+    a whole, across the segments' borders."""
+    n, p = CHUNK * 91 - 77, 0.03
+    with DeviceRun([n, 700]) as run:
+        sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WIDE_MIN_KEPT, 9000 if sweeps else 1 << 30)
+        R = [np.zeros(n, np.float32), np.zeros(700, np.float32)]
+        for r in range(3):
+            x = synth.gaussian_update(CHUNK * 91, round_=r).reshape(-1, CHUNK)
+            for g in segments:
+                x[g::8] *= 40.0
+                if ties:                                  # a few values, most of them at the threshold
+                    x[g::8] = np.sign(x[g::8]) * np.float32(0.04) * np.float32(1 + r) * (1 + (np.abs(x[g::8]) > 0.09))
+            x[44, ::1000] = 3.0                           # (a segment with a few entries of its own)
+            dWs = [np.ascontiguousarray(x.reshape(-1)[:n]), synth.gaussian_update(700, round_=r, tensor=1)]
+            res = check_round(run, dWs, R, p, check_decode=False)
+            R = [v.R_new for v in res]
