@@ -639,10 +639,11 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
 // workgroup adds its counts to the shared histogram bin by bin, and those atomics cost more than
 // the reading when every workgroup has few entries per bin.
 // --------------------------------------------------------------------------
-// Entries that keep a workgroup of a sweep busy.  Eight workgroups take a list of up to 131072 entries, each
-// a segment: what a sweep over short lists costs is above all the workgroups' additions to the shared
-// histogram (20 lists by 32 workgroups with 1536 bins each: 8.5 us, by 8: 2.7 us).  3.9e6 entries a side
-// (1.5e9-entry tensor): 29 + 34 us; 69 + 62 with workgroups of 256 threads and 4096 entries.
+// Entries that keep a workgroup of a sweep busy.  Eight workgroups take a list of up to 147455 entries, each
+// a segment, sixteen one of up to 278527 and so on: what a sweep over short lists costs is above all the workgroups'
+// additions to the shared histogram (20 lists by 32 workgroups with 1536 bins each: 8.5 us, by 8: 2.7 us).  3.9e6
+// entries a side (1.5e9-entry tensor): 15 + 31 us (25 + 34 with a load of a thread in flight at a time instead of
+// eight or four; 69 + 62 with workgroups of 256 threads and 4096 entries).
 constexpr uint32_t kWidePerWorkgroup = 16384, kWideFew = 8;
 constexpr uint32_t kWideFound = 512;                   // entries of the k-th entry's bin that a workgroup collects in LDS
 
@@ -664,22 +665,30 @@ __device__ __forceinline__ bool wide_applies(const TensorDesc& d, const ListCoun
 template <int UNROLL, typename F>
 __device__ __forceinline__ void sweep_list(const TensorDesc& d, const ListCounts& c, uint32_t segs, int s, uint32_t nb, const CandPtr cand, F f) {
     const CandPtr whole = cand + d.cand_off + (s ? d.cand_cap : 0u);
+    uint32_t g = blockIdx.x % segs, last = g + 1u, lo = 0u, hi = 0u;
     const bool crowded = uniform(c.crowded) != 0u;
-    uint32_t g = crowded ? 0u : blockIdx.x % segs;
-    const uint32_t last = crowded ? segs : g + 1u;
-    const uint32_t per = uniform(c.of(s)) / nb + 1u;
+    if (crowded) {
+        const uint32_t all = uniform(c.of(s)), per = all / nb + 1u;
+        g = 0u; last = segs;
+        lo = (uint32_t)min((uint64_t)blockIdx.x * per, (uint64_t)all);
+        hi = (uint32_t)min((uint64_t)lo + per, (uint64_t)all);
+    }
 #pragma nounroll
     for (; g < last; ++g) {
-        CandPtr list = whole + seg_before(d, segs, g);
-        uint64_t from = (uint64_t)(blockIdx.x / segs) * kWideThreads, stride = (uint64_t)(nb / segs) * kWideThreads;
-        uint32_t to = uniform(c.cnt[g]);
-        if (crowded) {                                 // this workgroup's part of the list as a whole, as far as it lies here
-            const uint64_t lo = (uint64_t)blockIdx.x * per, hi = lo + per;
-            const uint2 part = c.part_of(g, (uint32_t)min(lo, (uint64_t)0xFFFFFFFFu), (uint32_t)min(hi, (uint64_t)0xFFFFFFFFu));
+        uint64_t from = (uint64_t)(blockIdx.x / segs) * kWideThreads, stride = (uint64_t)(nb / segs) * kWideThreads, to = uniform(c.cnt[g]);
+        if (crowded) {
+            const uint2 part = c.part_of(g, lo, hi);
             from = part.x; to = part.y; stride = kWideThreads;
         }
-#pragma unroll UNROLL
-        for (uint64_t i = from + threadIdx.x; i < to; i += stride) f(list.key[i], list + i);
+        const CandPtr list = whole + seg_before(d, segs, g);
+#pragma nounroll
+        for (uint64_t i0 = from + threadIdx.x; i0 < to; i0 += UNROLL * stride) {
+            uint32_t key[UNROLL];                      // (loads in flight together)
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) { const uint64_t i = i0 + u * stride; key[u] = list.key[i < to ? i : i0]; }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) { const uint64_t i = i0 + u * stride; if (i < to) f(key[u], list + i); }
+        }
     }
 }
 

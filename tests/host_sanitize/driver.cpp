@@ -22,6 +22,7 @@ extern "C" void stub_withhold_results(int on);
 extern "C" int stub_known_senders();
 extern "C" void stub_result_bits(uint32_t bits);
 extern "C" int stub_launched(const char* name, long from);
+extern "C" unsigned stub_grid_of(const char* name, long from);
 
 #define CHECK(cond)                                                                     \
     do {                                                                                \
@@ -298,6 +299,23 @@ int main(int argc, char** argv) {
             CHECK(sweeps(512) == k.later && sweeps(0) == k.after_long && sweeps(0) == k.later);
             CHECK(sbc_set_option(c, SBC_OPT_WIDE_MIN_KEPT, 5000) == SBC_OK && sweeps(0) == 1 && sweeps(0) == 1);
             CHECK(sbc_set_option(c, SBC_OPT_WIDE_MIN_KEPT, 1 << 30) == SBC_OK && sweeps(0) == 0 && sweeps(512) == 0 && sweeps(0) == 0);
+            sbc_destroy(c); c = nullptr;
+        }
+    }
+
+    // ---- workgroups per list of the sweeps: enough for the largest tensor's, eight at the least, a multiple of
+    // eight, fewer for each the more lists there are ----
+    {
+        struct Case { std::vector<int64_t> sizes; double p; unsigned blocks; };
+        const Case cases[] = {
+            {{1 << 20}, 0.5, 64}, {{1 << 20}, 0.1, 32}, {{1 << 20}, 0.05, 16}, {{1 << 22}, 0.01, 16}, {{200000}, 0.2, 16},
+            {{400000000}, 0.01, 256}, {std::vector<int64_t>(16, 1 << 20), 0.5, 16}, {std::vector<int64_t>(64, 1 << 20), 0.5, 8}};
+        for (const Case& k : cases) {
+            const Buffers s = fake_buffers(k.sizes);
+            CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            const long from = stub_launches();
+            CHECK(compress(c, s, k.p, sbc_msg_bound(s.numel.data(), s.T(), k.p), &nbytes) == SBC_OK);
+            CHECK(stub_grid_of("k_wide_count", from) == k.blocks && stub_grid_of("k_wide_collect", from) == k.blocks);
             sbc_destroy(c); c = nullptr;
         }
     }

@@ -34,6 +34,13 @@ extern "C" long stub_live_blocks() { return g_live_blocks; }
 extern "C" void stub_fail_allocation(long nth) { g_fail_alloc_at = nth; }
 extern "C" void stub_withhold_results(int on) { g_withhold = on != 0; }
 extern "C" void stub_result_bits(uint32_t bits) { g_result_bits = bits; }
+// Workgroups (x) of the first of the launches from number `from` on of a kernel with that name (0: none).
+extern "C" unsigned stub_grid_of(const char* name, long from) {
+    for (long i = from; i < g_launches; ++i)
+        for (int k = 0; k < g_n_names; ++k)
+            if (g_kernels[i % 64] == g_names[k].host && std::strstr(g_names[k].name, name)) return g_grids[i % 64];
+    return 0;
+}
 // How many of the launches from number `from` on (of the latest 64) were of kernels with that name.
 extern "C" int stub_launched(const char* name, long from) {
     int n = 0;
