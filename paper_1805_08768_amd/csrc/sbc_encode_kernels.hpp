@@ -112,24 +112,89 @@ __device__ __forceinline__ void put_bits(uint32_t* to, uint32_t w0, uint32_t n, 
     if ((uint32_t)v && w + 1u < n) atomicOr(&to[w + 1u], (uint32_t)v);
 }
 
-// The words [w0, w0 + n) of the chunk's bit string.
-__device__ __forceinline__ void write_codes(const ChunkCodes& c, int b, uint32_t* to, uint32_t w0, uint32_t n) {
+// One code, of gap `gap`, at bit pos, which moves on.
+__device__ __forceinline__ void put_code(uint32_t* to, uint32_t w0, uint32_t n, uint32_t& pos, uint32_t gap, int b) {
+    const uint32_t rem = gap & ((1u << b) - 1u);
+    uint32_t q = gap >> b;
+    while (q + (uint32_t)b + 1u > 32u) {               // a long unary run, 16 ones at a time
+        const uint32_t take = min(q, 16u);
+        put_bits(to, w0, n, pos, (1u << take) - 1u, take);
+        pos += take;
+        q -= take;
+    }
+    put_bits(to, w0, n, pos, (((1u << q) - 1u) << (b + 1)) | rem, q + (uint32_t)b + 1u);
+    pos += q + (uint32_t)b + 1u;
+}
+
+// The chunk's bit string, which fits kChunkWords words.
+__device__ __forceinline__ void write_codes(const ChunkCodes& c, int b, uint32_t* to) {
     uint32_t pe = c.pe, pos = c.start;
     for_bits(c.words, c.p0, [&](uint32_t x) {
-        if (pe) {
-            const uint32_t gap = x - pe, rem = gap & ((1u << b) - 1u);
-            uint32_t q = gap >> b;
-            while (q + (uint32_t)b + 1u > 32u) {       // a long unary run, 16 ones at a time
-                const uint32_t take = min(q, 16u);
-                put_bits(to, w0, n, pos, (1u << take) - 1u, take);
-                pos += take;
-                q -= take;
-            }
-            put_bits(to, w0, n, pos, (((1u << q) - 1u) << (b + 1)) | rem, q + (uint32_t)b + 1u);
-            pos += q + (uint32_t)b + 1u;
-        }
+        if (pe) put_code(to, 0u, (uint32_t)kChunkWords, pos, x - pe, b);
         pe = x + 1u;
     });
+}
+
+// A chunk so crowded that its bit string does not fit its words: its bitmap as a word per lane in four rounds,
+// so that no lane has more than 32 codes of a stretch (8192 kept entries at b = 6, 1800 words: k_emit_all 25 us;
+// 60 with 128 codes of a lane in each of seven stretches of 256 words).
+constexpr int kRawRounds = kChunkWords / 64;
+struct RawCodes {
+    uint32_t word[kRawRounds], pe[kRawRounds], start[kRawRounds];      // the lane's: bits, end of the entry before, first bit of the codes
+    uint32_t end[kRawRounds];                                          // the round's codes end there
+};
+__device__ __forceinline__ RawCodes raw_codes(const uint32_t* __restrict__ bitmap, int b) {
+    const uint32_t lane = threadIdx.x & 63u;
+    RawCodes c;
+    uint32_t ended = 0u, bits_before = 0u;
+#pragma unroll
+    for (int r = 0; r < kRawRounds; ++r) c.word[r] = bitmap[r * 64 + lane];
+#pragma unroll
+    for (int r = 0; r < kRawRounds; ++r) {
+        const uint32_t p0 = ((uint32_t)r * 64u + lane) * 32u;
+        uint32_t round_end, bits = 0u;
+        c.pe[r] = wave_excl_max(c.word[r] ? p0 + 32u - (uint32_t)__clz((int)c.word[r]) : 0u, &round_end);
+        if (c.pe[r] == 0u) c.pe[r] = ended;
+        uint32_t pe = c.pe[r];
+        for (uint32_t m = c.word[r]; m; m &= m - 1u) {
+            const uint32_t x = p0 + (uint32_t)__ffs((int)m) - 1u;
+            if (pe) bits += golomb_len(x - pe, b);
+            pe = x + 1u;
+        }
+        const uint32_t inc = wave_incl_sum(bits);
+        c.start[r] = bits_before + inc - bits;
+        bits_before += last_lane(inc);
+        c.end[r] = bits_before;
+        if (round_end) ended = round_end;
+    }
+    return c;
+}
+// The words [w0, w0 + n) of the bit string.
+__device__ __forceinline__ void write_raw(const RawCodes& c, int b, uint32_t* to, uint32_t w0, uint32_t n) {
+    const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+    for (int r = 0; r < kRawRounds; ++r) {
+        if (c.end[r] <= 32u * w0 || (r ? c.end[r - 1] : 0u) >= 32u * (w0 + n)) continue;     // uniform
+        uint32_t pe = c.pe[r], pos = c.start[r];
+        for (uint32_t m = c.word[r]; m && pos < 32u * (w0 + n); m &= m - 1u) {
+            const uint32_t x = ((uint32_t)r * 64u + lane) * 32u + (uint32_t)__ffs((int)m) - 1u;
+            if (pe) put_code(to, w0, n, pos, x - pe, b);
+            pe = x + 1u;
+        }
+    }
+}
+
+// The first 32 bits of the bit string of such a chunk: few of its codes, all of them the first lanes'.
+__device__ __forceinline__ void write_head(const ChunkCodes& c, int b, uint32_t* to) {
+    uint32_t pe = c.pe, pos = c.start;
+    if (pos >= 32u) return;
+    unsigned long long m = ((unsigned long long)c.words.y << 32) | c.words.x, rest = ((unsigned long long)c.words.w << 32) | c.words.z;
+    for (uint32_t p0 = c.p0; (m || rest) && pos < 32u; m &= m - 1ull) {
+        if (!m) { m = rest; rest = 0ull; p0 += 64u; }
+        const uint32_t x = p0 + (uint32_t)(__ffsll((long long)m) - 1);
+        if (pe) put_code(to, 0u, 1u, pos, x - pe, b);
+        pe = x + 1u;
+    }
 }
 
 // 32 bits from bit x on of a chunk's codes: the first entry's (gap >> b ones, a zero, b bits), then the
@@ -229,7 +294,8 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
     const ChunkCodes codes_of = chunk_codes(reinterpret_cast<const uint4*>(bm)[lane], b, inner_bits, first, last_end);
     // a chunk crowded with kept entries: the bitmap goes out instead, and of the codes only the first word
     const bool raw = inner_bits > 32u * (uint32_t)kChunkWords;
-    write_codes(codes_of, b, code_sh[wave], 0u, raw ? 1u : (uint32_t)kChunkWords);
+    if (__builtin_expect(raw, 0)) write_head(codes_of, b, code_sh[wave]);
+    else write_codes(codes_of, b, code_sh[wave]);
     wave_lds_fence();
     uint4* const out = reinterpret_cast<uint4*>(codes + (uint64_t)c * kChunkWords) + lane;
     if (raw) *out = codes_of.words;
@@ -380,34 +446,34 @@ struct ChunkStream {
     bool any, raw;
     unsigned long long at;
 };
-// Words of LDS per wavefront for a chunk's bit string (and zeros behind it).
-constexpr uint32_t kWindow = kChunkWords + 4;
+// Words of LDS per wavefront for W words of a chunk's bit string (and zeros behind them).
+template <uint32_t W>
+constexpr uint32_t kWindow = W + 4u;
 
 // The words of the stream that start in the chunk.  win: the bit string's words, zeros behind them (raw:
-// anything; bm then holds the lane's bitmap words).  gap_after(f, gap, any): chunk f of the same tensor,
-// or false if there is none.
-template <typename After>
-__device__ __forceinline__ void write_chunk(const ChunkStream& s, const uint4& bm, int b, uint32_t* win, const ChunkSummary* __restrict__ sum,
+// anything).  after(f, gap, any): chunk f of the same tensor, or false if there is none.
+template <uint32_t W, typename After>
+__device__ __forceinline__ void write_chunk(const ChunkStream& s, int b, uint32_t* win, const ChunkSummary* __restrict__ sum,
                                             const uint32_t* __restrict__ codes, const uint32_t* __restrict__ heads,
                                             uint32_t* __restrict__ to, After after) {
     const uint32_t lane = threadIdx.x & 63u;
     if (!s.any) return;
     const uint32_t lead = golomb_len(s.gap, b), bits = lead + s.inner;
     const unsigned long long first = (s.at + 31ull) >> 5, end = (s.at + bits + 31ull) >> 5;
-    ChunkCodes cc;
-    if (s.raw) { uint32_t x, y, z; cc = chunk_codes(bm, b, x, y, z); }
-    for (uint32_t i0 = 0u; ; i0 += (uint32_t)kChunkWords) {
-        // the words that need the bit string's words i0 .. i0 + kChunkWords (all, unless the chunk is raw)
+    RawCodes rc;
+    if (__builtin_expect(s.raw, 0)) rc = raw_codes(codes + (uint64_t)s.c * kChunkWords, b);
+    for (uint32_t i0 = 0u; ; i0 += W) {
+        // the words that need the bit string's words i0 .. i0 + W (all, unless the chunk is raw)
         unsigned long long lo = first, hi = end;
-        if (s.raw) {
+        if (__builtin_expect(s.raw, 0)) {
             wave_lds_fence();
-            for (uint32_t i = lane; i < kWindow; i += 64u) win[i] = 0u;
+            for (uint32_t i = lane; i < kWindow<W>; i += 64u) win[i] = 0u;
             wave_lds_fence();
-            write_codes(cc, b, win, i0, (uint32_t)kChunkWords + 1u);
+            write_raw(rc, b, win, i0, W + 1u);
             wave_lds_fence();
             const unsigned long long from = s.at + lead + 31ull;
             if (i0) lo = (from + 32ull * i0) >> 5;
-            hi = min(hi, (from + 32ull * (i0 + (uint32_t)kChunkWords)) >> 5);
+            hi = min(hi, (from + 32ull * (i0 + W)) >> 5);
         }
         for (unsigned long long w = lo + lane; w < hi; w += 64u) {
             const uint32_t x = (uint32_t)(32ull * w - s.at);
@@ -429,7 +495,7 @@ __device__ __forceinline__ void write_chunk(const ChunkStream& s, const uint4& b
             }
             to[w] = v;
         }
-        if (!s.raw || 32u * (i0 + (uint32_t)kChunkWords) >= s.inner) break;
+        if (!s.raw || 32u * (i0 + W) >= s.inner) break;
     }
 }
 
@@ -438,7 +504,7 @@ __device__ __forceinline__ void write_chunk(const ChunkStream& s, const uint4& b
 __device__ __forceinline__ uint4 load_codes(const uint32_t* __restrict__ codes, uint32_t c, const ChunkSummary& s) {
     const uint32_t lane = threadIdx.x & 63u;
     uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (sum_raw(s) || lane * 128u < sum_inner(s)) v = reinterpret_cast<const uint4*>(codes + (uint64_t)c * kChunkWords)[lane];
+    if (lane * 128u < sum_inner(s)) v = reinterpret_cast<const uint4*>(codes + (uint64_t)c * kChunkWords)[lane];
     return v;
 }
 __device__ __forceinline__ void stage_codes(uint32_t* win, const uint4& v) {
@@ -520,7 +586,8 @@ __global__ __launch_bounds__(NT) void k_emit_all(
         unsigned long long* __restrict__ host_word, uint32_t seq) {
     constexpr int NW = NT / 64, PER = kEmitAllPer;
     __shared__ uint32_t scratch[4][16];
-    __shared__ __attribute__((aligned(16))) uint32_t win_sh[NW][kWindow];
+    constexpr uint32_t W = NT <= 256 ? 1024u : 256u;   // (words of a crowded chunk put together at a time)
+    __shared__ __attribute__((aligned(16))) uint32_t win_sh[NW][kWindow<W>];
     extern __shared__ uint32_t offs[];                 // every chunk's bit offset in the payload, then the gaps
     uint32_t* const gaps = offs + n_chunks;
     constexpr uint32_t kNone = 0x80000000u, kStarts = 0x40000000u;     // (gaps are below 2^26 here)
@@ -616,7 +683,7 @@ __global__ __launch_bounds__(NT) void k_emit_all(
         const uint32_t tensor = offs[ct.y];
         finish_tensor(msg, st, counters, ct.x, mu_signed, nnz, (unsigned long long)(o - tensor) + (cs.any ? golomb_len(cs.gap, b) + cs.inner : 0u), tensor >> 5);
     }
-    write_chunk(cs, mine, b, win_sh[wave], sum, codes, heads, reinterpret_cast<uint32_t*>(msg + 32 + 24ull * (unsigned)T),
+    write_chunk<W>(cs, b, win_sh[wave], sum, codes, heads, reinterpret_cast<uint32_t*>(msg + 32 + 24ull * (unsigned)T),
                 [&](uint32_t f, uint32_t& gap_f, bool& any_f) {
                     if (f >= n_chunks) return false;
                     const uint32_t gf = gaps[f];
@@ -637,7 +704,8 @@ __global__ __launch_bounds__(kEncThreads) void k_emit(
         const uint64_t* __restrict__ chunk_bitoff, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, int T, int b, int pass, uint32_t n_chunks,
         uint32_t* __restrict__ stage, uint8_t* __restrict__ msg, uint64_t msg_capacity, ResultBlock* __restrict__ result,
         ResultBlock* __restrict__ next_result, unsigned long long* __restrict__ host_word, uint32_t seq) {
-    __shared__ __attribute__((aligned(16))) uint32_t win_sh[kEncWaves][kWindow];
+    constexpr uint32_t W = 512u;
+    __shared__ __attribute__((aligned(16))) uint32_t win_sh[kEncWaves][kWindow<W>];
     const uint32_t lane = threadIdx.x & 63u;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t c = blockIdx.x * (uint32_t)kEncWaves + (uint32_t)wave;
@@ -685,7 +753,7 @@ __global__ __launch_bounds__(kEncThreads) void k_emit(
     ChunkStream cs;
     cs.c = c; cs.gap = gap; cs.inner = sum_inner(own); cs.any = sum_any(own); cs.raw = sum_raw(own); cs.at = at;
     const uint32_t last = ct.y + nchunks;
-    write_chunk(cs, mine, b, win_sh[wave], sum, codes, heads, to, [&](uint32_t f, uint32_t& gap_f, bool& any_f) {
+    write_chunk<W>(cs, b, win_sh[wave], sum, codes, heads, to, [&](uint32_t f, uint32_t& gap_f, bool& any_f) {
         if (f >= last) return false;
         gap_f = chunk_gap[f];
         any_f = sum_any(sum[f]);

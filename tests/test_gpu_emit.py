@@ -3,7 +3,9 @@ runs over many words, words that several chunks share, streams of one word, and 
 of chunks at which the scan over them changes its form.  Every round against the oracle, bit for bit."""
 import numpy as np
 import pytest
+import torch
 
+from paper_1805_08768_amd import binding as sbc
 from parity_util import DeviceRun, check_round
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +68,37 @@ def test_calls_of_many_small_tensors(chunks):
         for r in range(2):
             dWs = [(g.standard_normal(s) * 1e-3).astype(np.float32) for s in sizes]
             R = [x.R_new for x in check_round(run, dWs, R, 0.03, check_decode=(chunks < 1000))]
+
+
+@pytest.mark.parametrize("p,chunks", [(1e-3, 1100), (2e-4, 4099)])
+@pytest.mark.parametrize("pattern", ["full", "ends", "two_thirds"])
+def test_full_chunks_in_calls_of_many_chunks(p, chunks, pattern):
+    """Chunks that are kept whole, at the chunk's ends or with gaps: their codes take several stretches of what a
+    wavefront puts together at a time, in the one launch for 1100 chunks and behind the scan for 4099."""
+    n = CHUNK * chunks - 77
+    k = max(1, int(np.floor(p * n)))
+    at = torch.arange(CHUNK * 5, CHUNK * 6)
+    if pattern == "ends":
+        at = torch.cat([at[:3000], at[-(k - 3000):]]) if k < CHUNK else at
+    elif pattern == "two_thirds":
+        at = at[at % 3 != 1]
+    rest = k - len(at)
+    assert rest >= 0 or k < CHUNK
+    at = at[:k] if rest < 0 else torch.cat([at, CHUNK * 6 + 40 + torch.arange(rest) * 5])      # the rest just behind it
+    assert len(at) == k
+    g = torch.Generator("cuda:0").manual_seed(chunks)
+    x = torch.randn(n, device="cuda:0", generator=g) * 1e-3
+    x[at.cuda()] = 1.0 + torch.rand(k, device="cuda:0", generator=g)
+    ctx = sbc.sbc_create(0, n, 1)
+    try:
+        R = torch.zeros_like(x)
+        msg = torch.zeros(sbc.sbc_msg_bound([n], p), dtype=torch.uint8, device="cuda:0")
+        nbytes = sbc.sbc_compress(ctx, [x], [R], p, msg)
+        out = torch.zeros_like(x)
+        sbc.sbc_decompress_accumulate(ctx, msg, nbytes, p, 1.0, [out])
+        assert torch.equal(torch.nonzero(out).flatten().cpu(), at)
+        assert torch.equal(R, x - out)
+        bits = np.unpackbits(sbc.sbc_last_mask(ctx, 0, n).numpy().view(np.uint8), bitorder="little")[:n]
+        assert np.array_equal(np.flatnonzero(bits), at.numpy())
+    finally:
+        sbc.sbc_destroy(ctx)
