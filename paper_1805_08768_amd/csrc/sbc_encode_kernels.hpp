@@ -221,6 +221,8 @@ __device__ __forceinline__ uint32_t chunk_bits(uint32_t x, uint32_t gap, int b, 
 // us on 25.6e6 entries at p = 0.001 (3243 chunks), 13.7 us at p = 0.01, 4.3 us on 512 chunks; 86 us on 1.5e9
 // entries (106 when it stored a bitmap of 1 KB per chunk, which the next kernel read, instead of the codes).
 // --------------------------------------------------------------------------
+// PAIRS: see k_threshold.
+template <bool PAIRS>
 __global__ __launch_bounds__(kEncThreads) void k_apply(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor, const ChunkRun* __restrict__ runs,
         const TensorState* __restrict__ st, TensorState* res, const CandPtr cand,
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
         e0[s] = make_uint2(0u, 0u);
-        if ((uint32_t)lane < run.cnt[s] && run.at[s] < cand_entries - 64u) e0[s] = cand.get(run.at[s] + (uint32_t)lane);
+        if (!PAIRS && (uint32_t)lane < run.cnt[s] && run.at[s] < cand_entries - 64u) e0[s] = cand.get(run.at[s] + (uint32_t)lane);
     }
     reinterpret_cast<uint4*>(bm)[lane] = make_uint4(0u, 0u, 0u, 0u);
     reinterpret_cast<uint4*>(code_sh[wave])[lane] = make_uint4(0u, 0u, 0u, 0u);
@@ -265,6 +267,9 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
     }
     const CandPtr list = cand + run.at[chosen];
     const uint32_t cnt = run.cnt[chosen];
+    const uint64_t off = desc[t].cand_off;
+    const uint2* const pair = pairs_of(cand, off, chosen) + (run.at[chosen] - off - (chosen ? desc[t].cand_cap : 0u));
+    const auto entry = [&](uint32_t i) { return PAIRS && (flags & kStDeferred) ? pair[i] : list.get(i); };
     wave_lds_fence();
     bool bad = false;
     auto keep = [&](const uint2& e) {
@@ -275,14 +280,14 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
         atomicOr(&bm[(e.y % (uint32_t)kChunk) >> 5], 1u << (e.y & 31u));
     };
     // (at the very end of the array the first entries were not read ahead)
-    const bool ahead = run.at[chosen] < cand_entries - 64u;
+    const bool ahead = !PAIRS && run.at[chosen] < cand_entries - 64u;
     if (ahead && (uint32_t)lane < cnt) keep(chosen ? e0[1] : e0[0]);
     for (uint32_t i0 = ahead ? 64u : 0u; i0 < cnt; i0 += 256u) {
         uint2 e[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const uint32_t i = i0 + 64u * u + (uint32_t)lane;
-            e[u] = list.get(i < cnt ? i : 0u);
+            e[u] = entry(i < cnt ? i : 0u);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)

@@ -77,7 +77,7 @@ struct sbc_ctx {
     TensorState* d_state = nullptr;
     unsigned long long* d_counters = nullptr;   // kSegs per tensor: candidates in each segment of its lists (zero between calls)
     uint32_t* d_cand = nullptr;           // the lists' keys, then their indexes
-    CandPtr cand() const { return {d_cand, cand_entries + 4u}; }      // (a few more: k_threshold reads four keys at a time)
+    CandPtr cand() const { return {d_cand, (cand_entries + 5u) & ~1ull}; }      // (a few more: k_threshold reads four at a time)
     ChunkRun* d_runs = nullptr;           // per chunk: where its candidates lie
     uint32_t* d_bitmap = nullptr;
     uint32_t* d_stage = nullptr;
@@ -340,11 +340,14 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
             }
         }
         // (c->d_order: see compress_begin)
-        SBC_LAUNCH(kStThreshold, profile, k_threshold, dim3(2u * (unsigned)T), dim3(kThThreads),
-                   P.d_desc, T > kComputeUnits / 2 ? c->d_order : nullptr, c->d_state, c->d_counters, c->cand(), c->d_bitmap, c->d_wide_state,
-                       c->d_wide_hist, c->d_wide_acc, pass, sweeps ? 1 : 0, P.carry, P.res_now);
+        const bool pairs = pass != 0 && c->fused_step;     // (of the tensors that are left, some may have lists in pairs)
+        const auto threshold = pairs ? k_threshold<true> : k_threshold<false>;
+        const auto apply = pairs ? k_apply<true> : k_apply<false>;
+        SBC_LAUNCH(kStThreshold, profile, threshold, dim3(2u * (unsigned)T), dim3(kThThreads), P.d_desc,
+                   T > kComputeUnits / 2 ? c->d_order : nullptr, c->d_state, c->d_counters, c->cand(), c->d_bitmap, c->d_wide_state,
+                   c->d_wide_hist, c->d_wide_acc, pass, sweeps ? 1 : 0, P.carry, P.res_now);
         const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
-        SBC_LAUNCH(kStApply, profile, k_apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
+        SBC_LAUNCH(kStApply, profile, apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
                    c->cand(), c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, pass, P.n_chunks, P.res_now);
         if (!c->fused_step && P.n_chunks <= kEmitAllChunks) {
             // the workgroups that write the codes scan the summaries of all chunks themselves, one launch less.  (Two
@@ -564,7 +567,7 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && hipMemset(c->d_state, 0, sizeof(TensorState) * T) == hipSuccess;
     ok = ok && dev_alloc(&c->d_counters, T * kSegs * kCounterStride) == hipSuccess;
     ok = ok && hipMemset(c->d_counters, 0, sizeof(unsigned long long) * T * kSegs * kCounterStride) == hipSuccess;
-    ok = ok && dev_alloc(&c->d_cand, 2u * (size_t)c->cand_entries + 8u) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_cand, 2u * (size_t)c->cand_entries + 8u) == hipSuccess;       // (see cand())
     ok = ok && dev_alloc(&c->d_runs, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_bitmap, (size_t)c->max_chunks * kChunkWords) == hipSuccess;
     ok = ok && dev_alloc(&c->d_stage, (size_t)c->stage_cap) == hipSuccess;

@@ -92,13 +92,16 @@ __device__ __forceinline__ void store_shared_u64(unsigned long long* p, unsigned
 __device__ __forceinline__ unsigned long long load_shared_u64(const unsigned long long* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ void store_cand(uint2* p, uint32_t key, uint32_t idx) {
+    store_shared_u64(reinterpret_cast<unsigned long long*>(p), (unsigned long long)key | ((unsigned long long)idx << 32));
+}
 __device__ __forceinline__ void store_cand(const CandPtr p, uint32_t key, uint32_t idx) {
     __hip_atomic_store(p.key, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(p.key + p.to_idx, idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint2 load_cand(const CandPtr p) {
-    return make_uint2(__hip_atomic_load(p.key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
-                      __hip_atomic_load(p.key + p.to_idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+__device__ __forceinline__ uint2 load_cand(const uint2* p) {
+    const unsigned long long v = load_shared_u64(reinterpret_cast<const unsigned long long*>(p));
+    return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
 }
 // every memory operation this wavefront has issued has completed
 __device__ __forceinline__ void wait_all_memory() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
@@ -161,11 +164,11 @@ struct LdsLists {
 
 // candidate lists too long for LDS: read from memory in every sweep
 struct MemLists {
-    CandPtr g[2];
+    const uint2* g[2];
     uint32_t cnt[2];
     template <int S, typename F>
     __device__ __forceinline__ void for_each(F f) const {
-        const CandPtr p = g[S];
+        const uint2* __restrict__ p = g[S];
         const uint32_t n = cnt[S];
         for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 8u * kStepThreads) {
             uint2 e[8];
@@ -826,7 +829,6 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         qp += x; qn += y;
         overflow = overflow || x > (uint32_t)kWaveQueue || y > (uint32_t)kWaveQueue;
     }
-    const CandPtr lp = cand + d.cand_off, ln = lp + d.cand_cap;
     unsigned long long* const counter = reinterpret_cast<unsigned long long*>(&st[t].cand_cnt[0]);
     const uint32_t grp = cc / (uint32_t)kGroupChunks;
     const uint32_t n_groups = (d.nchunks + kGroupChunks - 1u) / kGroupChunks;
@@ -857,8 +859,18 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
             if ((uint64_t)bp0 + qp > d.cand_cap || (uint64_t)bn0 + qn > d.cand_cap) {
                 // (beyond a list's capacity nothing is stored: the counters then show that the lists are not usable)
             } else {
-                for (uint32_t i = lane; i < wc_p; i += 64u) { const uint2 e = sh.wq(wave, 0)[i]; store_cand(lp + bp0 + before_p + i, e.x, e.y); }
-                for (uint32_t i = lane; i < wc_n; i += 64u) { const uint2 e = sh.wq(wave, 1)[i]; store_cand(ln + bn0 + before_n + i, e.x, e.y); }
+                // (in pairs only if this kernel reads the lists again)
+                for (int side = 0; side < 2; ++side) {
+                    const uint32_t n = side ? wc_n : wc_p, at = side ? bn0 + before_n : bp0 + before_p;
+                    const uint2* const q = sh.wq(wave, side);
+                    if (inline_t) {                       // uniform
+                        uint2* const list = pairs_of(cand, d.cand_off, side) + at;
+                        for (uint32_t i = lane; i < n; i += 64u) store_cand(list + i, q[i].x, q[i].y);
+                    } else {
+                        const CandPtr list = cand + (d.cand_off + (side ? d.cand_cap : 0u) + at);
+                        for (uint32_t i = lane; i < n; i += 64u) store_cand(list + i, q[i].x, q[i].y);
+                    }
+                }
             }
         }
         SBC_STEP_TS(2);
@@ -876,7 +888,7 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
     } else {
         // a queue overflowed (tie-heavy or constant data, or an all-pass key): A is stored now, and
         // the chunk's candidates (the wavefronts have counted all of them) are appended as one run
-        // from a second read of it, 2048 entries at a time with a block scan
+        // from a second read of it, 1024 entries at a time with a block scan
         store_A();
         wait_all_memory();
         if (tid == 0) {
@@ -888,25 +900,30 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         uint32_t at_p = sh.base[0], at_n = sh.base[1];
         // (nothing is stored beyond a list's capacity: the counters then show that the lists are not usable)
         const bool room = (uint64_t)at_p + qp <= d.cand_cap && (uint64_t)at_n + qn <= d.cand_cap;
-        for (uint32_t base0 = 0; room && base0 < cnt; base0 += 8u * kStepThreads) {      // uniform
-            uint32_t mp = 0u, mn = 0u, kk8[8];
+        for (uint32_t base0 = 0; room && base0 < cnt; base0 += 4u * kStepThreads) {      // uniform
+            uint32_t mp = 0u, mn = 0u, kk4[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
+            for (int j = 0; j < 4; ++j) {
                 const uint32_t pos = base0 + (uint32_t)j * kStepThreads + tid;
-                kk8[j] = key_of_bits(__float_as_uint(r[pos < cnt ? pos : 0u]));
-                if (pos < cnt && kk8[j] >= lo_p) mp |= 1u << j;
-                if (pos < cnt && ~kk8[j] >= lo_n) mn |= 1u << j;
+                kk4[j] = key_of_bits(__float_as_uint(r[pos < cnt ? pos : 0u]));
+                if (pos < cnt && kk4[j] >= lo_p) mp |= 1u << j;
+                if (pos < cnt && ~kk4[j] >= lo_n) mn |= 1u << j;
             }
             const uint32_t packed = __popc(mp) | (__popc(mn) << 16);
             uint32_t total;
             const uint32_t ex = block_excl_sum<uint32_t, kStepThreads>(packed, &total, sh.scratch32);
-            uint32_t op = at_p + (ex & 0xFFFFu), on = at_n + (ex >> 16);
+            const uint32_t op = at_p + (ex & 0xFFFFu), on = at_n + (ex >> 16);
             at_p += total & 0xFFFFu; at_n += total >> 16;
+            // (either form of the lists, key by key and index by index)
+            for (int side = 0; side < 2; ++side) {
+                const CandPtr list = inline_t ? CandPtr{reinterpret_cast<uint32_t*>(pairs_of(cand, d.cand_off, side)), 1u}
+                                              : cand + (d.cand_off + (side ? d.cand_cap : 0u));
+                const uint32_t m = side ? mn : mp;
+                uint32_t at = side ? on : op;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const uint32_t pos = base0 + (uint32_t)j * kStepThreads + tid;
-                if (mp & (1u << j)) store_cand(lp + op++, kk8[j], e0 + pos);
-                if (mn & (1u << j)) store_cand(ln + on++, ~kk8[j], e0 + pos);
+                for (int j = 0; j < 4; ++j)
+                    if (m & (1u << j))
+                        store_cand(list + ((uint64_t)at++ << (inline_t ? 1 : 0)), side ? ~kk4[j] : kk4[j], e0 + base0 + (uint32_t)j * kStepThreads + tid);
             }
         }
         note_run();
@@ -941,6 +958,8 @@ __global__ __launch_bounds__(kStepThreads, 4) void k_client_step(
         return;
     }
     bool defer = false;
+    const uint2* const lp = pairs_of(cand, d.cand_off, 0);
+    const uint2* const ln = pairs_of(cand, d.cand_off, 1);
     // Lists that fit region B beside the sort arrays of a tensor that keeps few entries (in region
     // A) are staged in LDS, every load in flight at once; longer ones are read from memory in
     // every sweep, and the sort arrays take both regions.

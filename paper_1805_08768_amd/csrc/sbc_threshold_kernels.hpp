@@ -274,7 +274,8 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // One workgroup of 1024 threads per (tensor, side); `order` lists the tensors by decreasing size
 // (null: as they come).  pass 0: every tensor no earlier kernel has finished or flagged; pass 1:
 // tensors handed over (histogram route, or left by the streaming kernel).  sweeps: k_wide_count and
-// k_wide_collect have run in this pass.
+// k_wide_collect have run in this pass.  PAIRS: in the second pass of a call with the fused step, where lists
+// that the streaming kernel has left are in pairs (pairs_of).
 // Every workgroup runs its code once, and for most it is a chain of short dependent steps: 1.2 us to the
 // counts, 1.3 to the list and its histogram, 0.8 to the bin, 0.5 for the second pass, 0.6 for the ranks, 0.7 to
 // the end, whatever the list.  Long lists are bound by the LDS histogram (14 cycles per 64 keys) and by the
@@ -283,6 +284,7 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // registers between the passes where a list has up to sixteen per thread; longer ones are read again.  (Tried:
 // 32 per thread, the next loads on their way during a batch, two copies of the histogram: no difference.)
 // --------------------------------------------------------------------------
+template <bool PAIRS>
 __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
         const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
@@ -345,6 +347,20 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     // room for them.)
     constexpr int kVecs = 4;
     const u32x4_any* __restrict__ vecs = reinterpret_cast<const u32x4_any*>(list.key);
+    const u32x4_any* __restrict__ index_vecs = reinterpret_cast<const u32x4_any*>(list.key + list.to_idx);
+    const bool pairs = PAIRS && (flags & kStDeferred);
+    const uint2* const pair = pairs_of(cand, d.cand_off, s);
+    const auto pair_at = [&](uint32_t i) { return pair[min(i, mine_cnt - 1u)]; };
+    auto keys_at = [&](uint32_t p) -> u32x4_any {
+        if constexpr (PAIRS)
+            if (pairs) return u32x4_any{pair_at(4u * p).x, pair_at(4u * p + 1u).x, pair_at(4u * p + 2u).x, pair_at(4u * p + 3u).x};
+        return vecs[p];
+    };
+    auto indexes_at = [&](uint32_t p) -> u32x4_any {
+        if constexpr (PAIRS)
+            if (pairs) return u32x4_any{pair_at(4u * p).y, pair_at(4u * p + 1u).y, pair_at(4u * p + 2u).y, pair_at(4u * p + 3u).y};
+        return index_vecs[p];
+    };
     const uint32_t fours = mine_cnt / 4u + (mine_cnt % 4u ? 1u : 0u);          // (so that no place passes 2^32)
     const uint32_t wave_first = uniform(first);        // (the wavefront's first lane's)
     u32x4_any held[kVecs];
@@ -353,7 +369,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         for (int j = 0; j < kVecs; ++j) {
             const uint32_t p = p0 + (uint32_t)j * step_by;
             held[j] = 0u;
-            if (p < fours) held[j] = vecs[p];
+            if (p < fours) held[j] = keys_at(p);
         }
 #pragma unroll
         for (int j = 0; j < kVecs; ++j) {
@@ -382,6 +398,8 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     auto again = [&](auto need_index, auto f) {
         if (__builtin_expect(mine_cnt <= step_by, 1)) {                // uniform
             if (first < mine_cnt) {
+                if constexpr (PAIRS)
+                    if (pairs) { const uint2 e = pair[first]; f(e.x, e.y); return; }
                 const uint32_t k = list.key[first];
                 f(k, need_index(k) ? list.key[first + list.to_idx] : 0u);
             }
@@ -391,13 +409,13 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         for (uint32_t p0 = first; p0 < fours; p0 += 2u * step_by) {
             u32x4_any k[2], x[2];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) { const uint32_t p = p0 + (uint32_t)j * step_by; k[j] = vecs[p < fours ? p : p0]; }
+            for (int j = 0; j < 2; ++j) { const uint32_t p = p0 + (uint32_t)j * step_by; k[j] = keys_at(p < fours ? p : p0); }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const uint32_t p = p0 + (uint32_t)j * step_by;
                 x[j] = 0u;
                 if (need_index(k[j].x) || need_index(k[j].y) || need_index(k[j].z) || need_index(k[j].w))
-                    x[j] = reinterpret_cast<const u32x4_any*>(list.key + list.to_idx)[p < fours ? p : p0];
+                    x[j] = indexes_at(p < fours ? p : p0);
             }
 #pragma unroll
             for (int j = 0; j < 2; ++j) {

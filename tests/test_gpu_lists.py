@@ -138,3 +138,23 @@ def test_lists_crowded_into_few_segments(sweeps, segments, ties):
             dWs = [np.ascontiguousarray(x.reshape(-1)[:n]), synth.gaussian_update(700, round_=r, tensor=1)]
             res = check_round(run, dWs, R, p, check_decode=False)
             R = [v.R_new for v in res]
+
+
+@pytest.mark.parametrize("carry", [0, 1])
+def test_lists_left_by_the_streaming_kernel(carry):
+    """With the fused step: tensors whose long lists are full of equal values are left to the kernels behind it,
+    which read their lists in pairs, at odd list capacities, beside tensors that it finishes and one that keeps
+    too many entries for it (its lists in two arrays)."""
+    sizes = [200001, 60007, 700001, 9001, 130000]
+    p, taken_over = 0.012, 0
+    with DeviceRun(sizes) as run:
+        sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_FUSED_STEP, 1)
+        sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_CARRY_FILTER_KEYS, carry)
+        R = [np.zeros(n, np.float32) for n in sizes]
+        for r in range(3):
+            dWs = [synth.gaussian_update(n, round_=r, tensor=i) if i in (2, 3) else synth.palette_update(n, round_=r, tensor=i)
+                   for i, n in enumerate(sizes)]
+            res = check_round(run, dWs, R, p, check_decode=(r == 0))
+            taken_over += bool(sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_TAKEN_OVER)
+            R = [x.R_new for x in res]
+    assert taken_over

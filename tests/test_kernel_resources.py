@@ -1,5 +1,7 @@
 """What the compiler reports about the built kernels: registers moved to scratch memory cost every
-workgroup a trip to memory, and nothing else shows them."""
+workgroup a trip to memory, and nothing else shows them.  In k_client_step the compiler has put those
+moves into a branch of one lane, so that the others read back what they had never stored: candidates of
+other tensors, then, in lists longer than LDS holds."""
 import os
 import re
 import shutil
@@ -37,10 +39,6 @@ def _spills(tmp_path):
 @pytest.mark.skipif(not os.path.exists(LIB) or not os.path.exists(READELF), reason="library not built here")
 def test_kernels_keep_their_registers(tmp_path):
     spills = _spills(tmp_path)
-    for kernel in ("k_accumulate_filter", "k_threshold", "k_apply", "k_emit", "k_finish_message", "k_decode", "k_average_apply"):
+    for kernel in ("k_accumulate_filter", "k_client_step", "k_threshold", "k_apply", "k_emit", "k_finish_message", "k_decode", "k_average_apply"):
         found = {s: n for s, n in spills.items() if kernel in s}
         assert found and not any(found.values()), found
-    # the streaming kernel that finishes tensors by itself keeps 32 entries per thread: a few registers
-    # go in the branch for chunks of many candidates (8; with 32 it spilled in the ordinary one, too)
-    found = {s: n for s, n in spills.items() if "k_client_step" in s}
-    assert len(found) == 2 and max(found.values()) <= 10, found
