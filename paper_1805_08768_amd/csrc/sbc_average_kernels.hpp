@@ -19,7 +19,8 @@ namespace sbc {
 constexpr int kAvgMaxMsgs = 64;               // messages per pass (a lane each)
 constexpr uint32_t kAvgBlock = 2048;          // entries per wavefront of k_average_apply
 constexpr uint32_t kAvgPerChunk = kChunk / kAvgBlock;
-constexpr uint32_t kAvgHalf = kAvgBlock / 2u; // ... of which it holds half at a time
+// ... of which it holds a part at a time: half for few messages, whole blocks for many (see k_average_apply)
+constexpr int kAvgWholeFrom = 48;
 constexpr uint32_t kAvgTags = 256;            // places of k_average_apply where entries of equal positions meet
 constexpr uint32_t kAvgNone = 0xFFFFFFFFu;    // no stream
 constexpr uint32_t kAvgWhole = 0xFFFFFFFEu;   // in a workgroup's second place: all wavefronts take the first stream
@@ -152,18 +153,20 @@ __global__ __launch_bounds__(256) void k_average_clear(const uint2* __restrict__
 
 // A workgroup per chunk of 8192 entries, a wavefront per block of 2048: enough entries of all messages
 // together (about 64 for 32 messages at p = 0.001) to give each lane one.  Bound by the store of the
-// result, which starts four round trips after the kernel: 102 MB in 22.4 us (a plain fill: 16 us); 23.3 with a
-// whole block per wavefront in LDS instead of half of it, which leaves room for four workgroups on a compute
-// unit instead of seven; 55.9 us with the messages one after another in each wavefront, two
-// lanes busy at a time (issue bound).  ADD: out already
-// holds the sum of the messages before these.
-template <bool ADD>
+// result, which starts four round trips after the kernel: 102 MB in 20.3 us (a plain fill: 16 us); 55.9 us with
+// the messages one after another in each wavefront, two lanes busy at a time (issue bound).
+// PART: entries of a block in LDS at a time.  Half a block leaves room for seven workgroups on a compute unit
+// instead of four, but goes through the entries twice, with a search among the messages for each: ResNet-50
+// shape, half / whole, 4 messages at p = 0.01 19.2 / 21.4 us, 8 24.2 / 25.8, 16 36.1 / 36.0, 32 59.1 / 56.3, 64
+// 105.0 / 97.6; at p = 0.001 32 messages 20.2 / 20.3 (with other data in the caches in between 22.4 / 24.1), 64 26.2 / 24.6.
+// ADD: out already holds the sum of the messages before these.
+template <bool ADD, uint32_t PART>
 __global__ __launch_bounds__(kEncThreads) void k_average_apply(
         const uint2* __restrict__ chunk_tensor, const AvgTensor* __restrict__ tensors, uint32_t M, uint32_t pos_stride,
         const uint32_t* __restrict__ positions, const uint32_t* __restrict__ marks, const float* __restrict__ addends,
         const ResultBlock* __restrict__ result) {
     static_assert(kAvgPerChunk == (uint32_t)kEncWaves, "a wavefront per block");
-    __shared__ __attribute__((aligned(16))) float acc_sh[kEncWaves][kAvgHalf];
+    __shared__ __attribute__((aligned(16))) float acc_sh[kEncWaves][PART];
     __shared__ __attribute__((aligned(16))) uint32_t tag_sh[kEncWaves][kAvgTags];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -202,9 +205,9 @@ __global__ __launch_bounds__(kEncThreads) void k_average_apply(
 #pragma unroll
     for (uint32_t i = 0; i < kAvgTags / 256u; ++i) reinterpret_cast<uint4*>(tag)[i * 64u + lane] = make_uint4(0u, 0u, 0u, 0u);
 #pragma nounroll
-    for (uint32_t h0 = 0u; h0 < cnt; h0 += kAvgHalf) {
+    for (uint32_t h0 = 0u; h0 < cnt; h0 += PART) {
 #pragma unroll
-        for (uint32_t i = 0; i < kAvgHalf / 256u; ++i) {
+        for (uint32_t i = 0; i < PART / 256u; ++i) {
             const uint32_t at = h0 + (i * 64u + lane) * 4u;
             f32x4 v = 0.f;
             if (ADD) {
@@ -223,7 +226,7 @@ __global__ __launch_bounds__(kEncThreads) void k_average_apply(
             const Entry now = next;
             if (base + 64u < total) next = entry(base + 64u + lane);
             const uint32_t at = now.at - h0;
-            bool todo = at < kAvgHalf;                 // (kAvgNone, or of the other half: not)
+            bool todo = at < PART;                 // (kAvgNone, or of the other half: not)
             const bool single = (uint32_t)__builtin_amdgcn_readfirstlane((int)now.m) ==
                                 (uint32_t)__builtin_amdgcn_readlane((int)now.m, (int)min(63u, total - base - 1u));
             if (single) {
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(kEncThreads) void k_average_apply(
             wave_lds_fence();
         }
 #pragma unroll
-        for (uint32_t i = 0; i < kAvgHalf / 256u; ++i) {
+        for (uint32_t i = 0; i < PART / 256u; ++i) {
             const uint32_t at = h0 + (i * 64u + lane) * 4u;
             const f32x4 v = reinterpret_cast<const f32x4*>(acc)[i * 64u + lane];
             if (at + 4u <= cnt) *(gf32x4_any_ptr)(out + at) = v;

@@ -1377,8 +1377,11 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         if (b <= 7) hipLaunchKernelGGL(k_average_decode<2>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         else if (b <= 11) hipLaunchKernelGGL(k_average_decode<3>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
-        if (m0 == 0) hipLaunchKernelGGL(k_average_apply<false>, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
-        else hipLaunchKernelGGL(k_average_apply<true>, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
+        constexpr uint32_t kHalf = kAvgBlock / 2u;
+        const auto apply = M < kAvgWholeFrom ? (m0 == 0 ? k_average_apply<false, kHalf> : k_average_apply<true, kHalf>)
+                                             : (m0 == 0 ? k_average_apply<false, kAvgBlock> : k_average_apply<true, kAvgBlock>);
+        hipLaunchKernelGGL(apply, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos,
+                           positions, marks, addends, res);
     }
     hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;

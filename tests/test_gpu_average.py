@@ -58,6 +58,7 @@ EDGES = [1, 2, 63, 2047, 2048, 2049, 6143, 8191, 8192, 8193, 40961]
     (0.2, EDGES + [300_007], (1, 5)),
     (0.12, EDGES + [170_003], (1, 3, 66)),
     (0.02, EDGES + [300_007, 1_200_001], (1, 63, 64, 65, 130)),
+    (0.03, EDGES + [90_001], (47, 48, 49)),           # half a block at a time, and whole ones
     (0.004, EDGES + [1_200_001], (3,)),
     (2e-4, EDGES + [2_500_003], (1, 9)),
     (1.2e-5, EDGES + [2_500_003], (9,)),
