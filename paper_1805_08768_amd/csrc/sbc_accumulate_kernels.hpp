@@ -361,8 +361,8 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
 }
 
 // --------------------------------------------------------------------------
-// Residual accumulation fused with the prefilter.  One workgroup per chunk of 8192 entries: 8 x 16-byte loads of each operand in flight
-// per thread, A stored over R and kept in LDS.  Every thread gathers two bit masks of its 32 entries, those at
+// Residual accumulation fused with the prefilter.  One workgroup per chunk of 8192 entries: 8 x 16-byte loads of
+// each operand in flight per thread, A stored over R and kept in LDS.  Every thread gathers two bit masks of its 32 entries, those at
 // or beyond each side's filter key (the keys' order is that of the values, so this is one comparison
 // of floats per side); one scan of the counts and one 64-bit atomic for both sides then give every
 // candidate its place, and each thread copies its few from LDS.  However many there are, the path is

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kDecThreads) void k_average_decode(
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t which = blockIdx.x / M, m = blockIdx.x - which * M;
     SBC_TS(2, 0);
-    if (which == 0u && m == 0u && tid == 0) { next_result->err = 0u; next_result->pad = 0u; next_result->msg_bytes = 0ull; }
+    if (which == 0u && m == 0u && tid == 0) next_result->err = 0u;
     const uint32_t second = ids[which * kDecWaves + 1];
     const bool whole = second == kAvgWhole;
     const uint32_t t = ids[which * kDecWaves + (whole ? 0 : wave)];
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kDecThreads) void k_average_decode(
 // Clears the tensors, a workgroup per chunk, and (if given) a result block.
 __global__ __launch_bounds__(256) void k_average_clear(const uint2* __restrict__ chunk_tensor, const AvgTensor* __restrict__ tensors,
                                                        ResultBlock* __restrict__ block) {
-    if (block && blockIdx.x == 0 && threadIdx.x == 0) { block->err = 0u; block->pad = 0u; block->msg_bytes = 0ull; }
+    if (block && blockIdx.x == 0 && threadIdx.x == 0) block->err = 0u;
     const uint2 ct = chunk_tensor[blockIdx.x];             // (tensor, its first chunk)
     const AvgTensor a = tensors[ct.x];
     const uint32_t e0 = (blockIdx.x - ct.y) * (uint32_t)kChunk, cnt = min((uint32_t)kChunk, a.n - e0);

@@ -420,7 +420,7 @@ struct MemBlocks {
     __device__ __forceinline__ ResultBlock* errors() const { return result; }
     __device__ __forceinline__ int32_t* status_word() const { return nullptr; }
     __device__ __forceinline__ void begin() const {
-        if (blockIdx.x == 0 && threadIdx.x == 0) { next_result->err = 0u; next_result->pad = 0u; next_result->msg_bytes = 0ull; }
+        if (blockIdx.x == 0 && threadIdx.x == 0) next_result->err = 0u;
     }
 };
 

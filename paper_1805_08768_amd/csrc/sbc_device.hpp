@@ -233,11 +233,10 @@ __device__ __forceinline__ uint32_t sum_end(const ChunkSummary& s) { return s.y 
 __host__ __device__ __forceinline__ bool sum_raw(const ChunkSummary& s) { return (s.y & 0x4000u) != 0u; }
 __device__ __forceinline__ bool sum_starts(const ChunkSummary& s) { return (s.y & 0x8000u) != 0u; }
 
-// Result block of a call.
+// Result block of a call: its error word (a block of 16 bytes, whose neighbours other calls use).
 struct ResultBlock {
     uint32_t err;
-    uint32_t pad;
-    uint64_t msg_bytes;
+    uint32_t pad[3];
 };
 
 // What the host learns of a call: one 8-byte word in pinned memory, stored at once: the message's size in

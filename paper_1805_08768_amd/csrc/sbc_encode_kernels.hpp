@@ -520,7 +520,8 @@ __device__ __forceinline__ void stage_codes(uint32_t* win, const uint4& v) {
 }
 
 // A tensor's table entry, and its state left clean for the next call.
-__device__ __forceinline__ void finish_tensor(uint8_t* __restrict__ msg, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, uint32_t t, float mu_signed, uint32_t nnz,
+__device__ __forceinline__ void finish_tensor(uint8_t* __restrict__ msg, TensorState* __restrict__ st,
+                                              unsigned long long* __restrict__ counters, uint32_t t, float mu_signed, uint32_t nnz,
                                               unsigned long long bit_len, unsigned long long word_off) {
     uint8_t* e = msg + 32 + 24ull * t;
     *reinterpret_cast<float*>(e) = mu_signed;
@@ -543,7 +544,7 @@ __device__ __forceinline__ void finish_call(uint8_t* __restrict__ msg, int T, in
     *reinterpret_cast<uint64_t*>(msg + 16) = payload_words;
     *reinterpret_cast<uint64_t*>(msg + 24) = 0ull;
     // the result block of the next call starts out clean
-    next_result->err = 0u; next_result->pad = 0u; next_result->msg_bytes = 0ull;
+    next_result->err = 0u;
 }
 
 // Most chunks of a call whose workgroups scan the summaries of all chunks themselves (8 bytes each), and
@@ -706,7 +707,8 @@ template <bool DIRECT>
 __global__ __launch_bounds__(kEncThreads) void k_emit(
         const TensorDesc* __restrict__ desc, const uint2* __restrict__ chunk_tensor, const ChunkSummary* __restrict__ sum,
         const uint32_t* __restrict__ codes, const uint32_t* __restrict__ heads, const uint32_t* __restrict__ chunk_gap,
-        const uint64_t* __restrict__ chunk_bitoff, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, int T, int b, int pass, uint32_t n_chunks,
+        const uint64_t* __restrict__ chunk_bitoff, TensorState* __restrict__ st, unsigned long long* __restrict__ counters,
+        int T, int b, int pass, uint32_t n_chunks,
         uint32_t* __restrict__ stage, uint8_t* __restrict__ msg, uint64_t msg_capacity, ResultBlock* __restrict__ result,
         ResultBlock* __restrict__ next_result, unsigned long long* __restrict__ host_word, uint32_t seq) {
     constexpr uint32_t W = 512u;

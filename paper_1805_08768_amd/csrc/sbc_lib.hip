@@ -138,7 +138,6 @@ struct sbc_ctx {
     std::vector<int64_t> cache_numel;
     uint64_t cache_total = 0, cache_chunks = 0, cache_stage_words = 0, cache_kept_total = 0, cache_max_bound = 0;
     uint32_t cache_scan_tiles = 1;        // most tiles of the chunk scan that a tensor has
-    uint32_t cache_chunks_max = 0;        // most chunks that a tensor has
     bool cache_all_inline = false;        // every tensor is finished inside the streaming kernel
     int cache_force_exact = 0;
     std::vector<TensorDesc> plan;         // without the pointers
@@ -205,7 +204,7 @@ struct sbc_ctx {
         uint8_t* msg8 = nullptr;
         size_t msg_capacity = 0, need = 0;
         uint32_t n_chunks = 0;
-        unsigned gather_y = 1, scan_tiles = 1, chunks_max = 0;
+        unsigned gather_y = 1, scan_tiles = 1;
     } pend;
 
     // last compress call, for the inspection entry points
@@ -732,7 +731,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     // that alternates between a few sets of buffers uploads nothing in the steady state.
     uint64_t total = 0, chunks = 0, stage_words = 0, kept_total = 0, max_bound = 0, groups = 0, cand_total = 0;
     bool all_inline = true;
-    uint32_t scan_tiles = 1, chunks_max = 0;
+    uint32_t scan_tiles = 1;
     // in the subsampled variant the keys must come from this call's sample
     const bool sampled = c->sampled != 0;
     const int force_exact = sampled ? 0 : c->force_exact;
@@ -753,7 +752,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     if (sizes_same) {
         total = c->cache_total; chunks = c->cache_chunks; stage_words = c->cache_stage_words;
         kept_total = c->cache_kept_total; max_bound = c->cache_max_bound;
-        scan_tiles = c->cache_scan_tiles; chunks_max = c->cache_chunks_max;
+        scan_tiles = c->cache_scan_tiles;
         all_inline = c->cache_all_inline;
         for (int i = 0; i < kDescSlots; ++i) {
             const DescSlot& sl = c->slot[i];
@@ -822,7 +821,6 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
             stage_words += bw;
             max_bound = std::max<uint64_t>(max_bound, bw);
             scan_tiles = std::max<uint32_t>(scan_tiles, (d.nchunks + kScanTile - 1u) / kScanTile);
-            chunks_max = std::max<uint32_t>(chunks_max, d.nchunks);
             if (total > (uint64_t)c->max_elems || cand_total > c->cand_entries || chunks > c->max_chunks || kept_total > c->kept_cap ||
                 stage_words > c->stage_cap || groups > c->max_groups)
                 return SBC_ECAPACITY;
@@ -888,7 +886,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         c->cache_T = T; c->cache_p = p;
         c->cache_total = total; c->cache_chunks = chunks; c->cache_stage_words = stage_words;
         c->cache_kept_total = kept_total; c->cache_max_bound = max_bound;
-        c->cache_scan_tiles = scan_tiles; c->cache_chunks_max = chunks_max;
+        c->cache_scan_tiles = scan_tiles;
         c->cache_all_inline = all_inline; c->cache_force_exact = force_exact;
         // (cache_valid is set once this call has completed: the uploads above must have happened)
     }
@@ -946,7 +944,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     P.sweeps = c->n_wide > 0 && (c->sweep_always || (use_history ? c->hist_long : c->sweep_sampled));
     for (int st = 0; st < kNumStages; ++st) P.timed[st] = false;
     P.res_now = res_now; P.res_next = res_next; P.d_desc = d_desc; P.msg8 = msg8;
-    P.msg_capacity = msg_capacity; P.need = need; P.n_chunks = n_chunks; P.gather_y = gather_y; P.scan_tiles = scan_tiles; P.chunks_max = chunks_max;
+    P.msg_capacity = msg_capacity; P.need = need; P.n_chunks = n_chunks; P.gather_y = gather_y; P.scan_tiles = scan_tiles;
     P.wait_on_event = wait_on_event;
     const int lvl = c->profile_level;
     bool* timed = P.timed;
