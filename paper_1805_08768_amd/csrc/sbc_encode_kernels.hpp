@@ -218,7 +218,7 @@ __device__ __forceinline__ uint32_t chunk_bits(uint32_t x, uint32_t gap, int b, 
 // --------------------------------------------------------------------------
 // Side, residual update and codes.  Bound by three dependent round trips to memory and, where a chunk
 // has hundreds of candidates, by the instructions for those and the scattered stores of the residual: 5.9
-// us on 25.6e6 entries at p = 0.001 (3243 chunks), 13.7 us at p = 0.01, 4.3 us on 512 chunks; 86 us on 1.5e9
+// us on 25.6e6 entries at p = 0.001 (3243 chunks), 12.3 us at p = 0.01, 4.3 us on 512 chunks; 88 us on 1.5e9
 // entries (106 when it stored a bitmap of 1 KB per chunk, which the next kernel read, instead of the codes).
 // --------------------------------------------------------------------------
 // PAIRS: see k_threshold.

@@ -279,7 +279,7 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // Every workgroup runs its code once, and for most it is a chain of short dependent steps: 1.2 us to the
 // counts, 1.3 to the list and its histogram, 0.8 to the bin, 0.5 for the second pass, 0.6 for the ranks, 0.7 to
 // the end, whatever the list.  Long lists are bound by the LDS histogram (14 cycles per 64 keys) and by the
-// fp64 sums: 10.2 us on 12,500 entries, 12.5 on 27,000, 25 on 61,000 (with the sweeps of k_wide_count and
+// fp64 sums: 10.2 us on 12,500 entries, 12.3 on 27,000, 18.6 on 60,000 (with the sweeps of k_wide_count and
 // k_wide_collect before a workgroup that staged keys in LDS: 19 us in all on 27,000, 37 on 61,000).  Keys stay in
 // registers between the passes where a list has up to sixteen per thread; longer ones are read again.  (Tried:
 // 32 per thread, the next loads on their way during a batch, two copies of the histogram: no difference.)

@@ -583,7 +583,7 @@ def test_calls_of_grid_wide_tensors_only_that_need_the_second_pass():
 
 def test_histogram_fallback_bitmap_and_grid_wide_tensors_in_one_call():
     """One call whose tensors take every route at once: tensor 0 keeps enough entries for the
-    sweeps; tensors 1 and 3 keep fewer, with lists beyond and around what k_threshold stages in LDS;
+    sweeps; tensors 1 and 3 keep fewer, with lists beyond and around what k_threshold holds in registers;
     tensor 2 has its large entries exactly where the sampler looks, so its filter keeps too few and the
     histogram route redoes it; tensor 4 has one chunk."""
     sizes = [250000, 170000, 50000, 100000, 300]
