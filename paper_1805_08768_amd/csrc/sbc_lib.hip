@@ -855,7 +855,8 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         // k_threshold's workgroups, two per tensor: largest tensors first if there are more of them than compute
         // units; if only some compute units get two (the first ones, from the 257th workgroup on), small tensors stand
         // at both of their places, and the large ones have a compute unit each (ResNet-50 shape, 322 workgroups, in
-        // the list's order, which ends with the largest: step 0.75 us more; largest first: 0.3 us more).
+        // the list's order, which ends with the largest: step 0.75 us more; largest first: 0.3 us more).  Only time
+        // depends on where a workgroup lands.
         const int twice = T > kComputeUnits / 2 && T <= kComputeUnits ? T - kComputeUnits / 2 : 0;
         for (int i = 0; i < T; ++i) c->h_order[i] = c->plan_order[i < twice ? T - 2 * twice + i : i < T - twice ? i - twice : i];
         for (int t = 0; t < T; ++t) {
