@@ -256,9 +256,13 @@ int sbc_decompress_accumulate_noalloc(int device, void* hip_stream,
  *       decode the messages of all clients back to back without waiting for each; validation
  *       failures of those calls are collected on the device and reported by sbc_decode_status().
  *       Every message buffer must stay unchanged until the stream has passed its call.  The
- *       option cannot be changed while a status is outstanding (SBC_EINVAL). */
+ *       option cannot be changed while a status is outstanding (SBC_EINVAL).
+ *   SBC_OPT_WAIT_LOOKS         (default 0 = 4096)  how often a workgroup of the kernel that completes a
+ *       step looks for results of workgroups that have not started (where other kernels fill the
+ *       GPU) before it leaves the step to kernels that wait for nobody, a microsecond each at the
+ *       most.  Tests lower it.  Same results. */
 enum { SBC_OPT_FORCE_EXACT_PATH = 1, SBC_OPT_CARRY_FILTER_KEYS = 2, SBC_OPT_WIDE_MIN_KEPT = 3,
-       SBC_OPT_SAMPLED_THRESHOLD = 4, SBC_OPT_DEFER_DECODE_STATUS = 5, SBC_OPT_FUSED_STEP = 6 };
+       SBC_OPT_SAMPLED_THRESHOLD = 4, SBC_OPT_DEFER_DECODE_STATUS = 5, SBC_OPT_FUSED_STEP = 6, SBC_OPT_WAIT_LOOKS = 7 };
 int sbc_set_option(sbc_ctx* ctx, int option, int value);
 
 /* With SBC_OPT_DEFER_DECODE_STATUS: waits until hip_stream (the stream the deferred
@@ -275,8 +279,9 @@ int sbc_decode_status(sbc_ctx* ctx, void* hip_stream);
  * without a successful call. */
 enum { SBC_ROUTE_CARRIED_KEYS = 1, SBC_ROUTE_HISTOGRAM = 2, SBC_ROUTE_WIDE = 4,
        SBC_ROUTE_LOOSE_KEYS = 8,    /* some filter key let so many entries pass that the next call samples afresh */
-       SBC_ROUTE_TAKEN_OVER = 16 }; /* a tensor the streaming kernel could not finish was completed by the
-                                       kernels that follow it in a second pass */
+       SBC_ROUTE_TAKEN_OVER = 16 }; /* a tensor the streaming kernel could not finish, or a step left as
+                                       SBC_OPT_WAIT_LOOKS says, was completed by the kernels that follow in a
+                                       second pass */
 int sbc_last_route(sbc_ctx* ctx);
 
 /* Inspection of the most recent sbc_compress() on this context, for tests and reports

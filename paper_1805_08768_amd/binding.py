@@ -29,6 +29,7 @@ SBC_OPT_WIDE_MIN_KEPT = 3
 SBC_OPT_SAMPLED_THRESHOLD = 4
 SBC_OPT_DEFER_DECODE_STATUS = 5
 SBC_OPT_FUSED_STEP = 6
+SBC_OPT_WAIT_LOOKS = 7
 SBC_ROUTE_CARRIED_KEYS = 1
 SBC_ROUTE_HISTOGRAM = 2
 SBC_ROUTE_WIDE = 4

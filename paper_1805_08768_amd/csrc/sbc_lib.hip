@@ -87,6 +87,20 @@ struct sbc_ctx {
     uint32_t* d_gap = nullptr;            // per chunk: gap before its first kept entry (calls of very many chunks)
     uint64_t* d_bitoff = nullptr;
     TileSummary* d_tile = nullptr;        // per tile of kScanTile chunks of a tensor
+    unsigned long long* d_flow = nullptr; // what the workgroups of k_emit_all leave for one another (see flow())
+    uint32_t flow_tag = 0;                // number of its latest launch, 1 to 0xFFFF
+    uint32_t flow_sides = 0, flow_taken = 0;      // workgroups of its launches that select sides / take chunks
+    size_t flow_words() const { return kGroupWords * (size_t)kEmitGroups + 2u * kSideWords * (size_t)std::min<int64_t>(max_tensors, kEmitAllChunks) + 1u; }
+    StepFlow flow() const {
+        const size_t T = (size_t)std::min<int64_t>(max_tensors, kEmitAllChunks);
+        StepFlow f;
+        f.groups = d_flow;
+        f.sides = f.groups + kGroupWords * (size_t)kEmitGroups;
+        f.started = reinterpret_cast<uint32_t*>(f.sides + 2u * kSideWords * T);
+        f.sides_before = flow_sides; f.taken = flow_taken;
+        f.tag = flow_tag;
+        return f;
+    }
     ResultBlock* d_result = nullptr;      // two for compress, two for decode, used in turn; [4] collects the
                                           // errors of decode calls whose status is deferred, [5] is a spare
     // sweeps over long lists
@@ -161,6 +175,7 @@ struct sbc_ctx {
     int carry_keys = 1;
     int carry_stale_run = 0;                 // sampled calls in a row that found the previous call's keys stale
     int carry_backoff = 0, carry_hold = 0;   // sampled calls after a call whose carried keys let a flood pass
+    uint32_t flow_looks = kFlowLooks;     // (tests lower it)
     int fused_step = 0;                   // the streaming kernel finishes the tensors it can by itself
     int sampled = 0;                      // subsampled variant: the sampled threshold decides what is kept
     int defer_decode = 0;                 // decode calls return once enqueued; sbc_decode_status reports
@@ -196,6 +211,7 @@ struct sbc_ctx {
         int T = 0, b = 0, slot = 0, force_exact = 0, carry = 0;
         double p = 0.0;
         bool slot_is_new = false, use_history = false, sampled = false, all_inline = false, sweeps = false;
+        bool left = false;            // k_emit_all has not applied every tensor that it has selected
         bool wait_on_event = false;   // begin/end form: the wait ends with this step, not with the stream
         bool timed[kNumStages] = {};
         ResultBlock* res_now = nullptr;
@@ -266,7 +282,7 @@ void free_all(sbc_ctx* c) {
     (void)hipFree(c->d_desc); (void)hipFree(c->d_chunk_tensor); (void)hipFree(c->d_sched); (void)hipFree(c->d_group); (void)hipFree(c->d_order); (void)hipFree(c->d_hist);
     (void)hipFree(c->d_state); (void)hipFree(c->d_counters); (void)hipFree(c->d_cand); (void)hipFree(c->d_bitmap); (void)hipFree(c->d_stage);
     (void)hipFree(c->d_kept); (void)hipFree(c->d_sum); (void)hipFree(c->d_head); (void)hipFree(c->d_gap); (void)hipFree(c->d_bitoff); (void)hipFree(c->d_tile);
-    (void)hipFree(c->d_result); (void)hipFree(c->d_dec_blocks);
+    (void)hipFree(c->d_flow); (void)hipFree(c->d_result); (void)hipFree(c->d_dec_blocks);
     if (c->h_dec_blocks) (void)hipHostFree(c->h_dec_blocks);
     (void)hipFree(c->d_seg_pack); (void)hipFree(c->d_tile_fn); (void)hipFree(c->d_tile_sum);
     (void)hipFree(c->d_wide_state); (void)hipFree(c->d_wide_hist); (void)hipFree(c->d_wide_acc); (void)hipFree(c->d_runs);
@@ -298,15 +314,14 @@ int status_of_err(uint32_t err) {
 // stop event that take the dispatch's own begin and end time stamps (event 2s and 2s+1 for
 // stage s), so the figure is the kernel's duration without the gaps between dispatches.
 // Expects c (context), lvl (profile level), stream and timed[] in scope.
-#define SBC_LAUNCH(stage, on, kernel, grid, block, ...) SBC_LAUNCH_LDS(stage, on, kernel, grid, block, 0, __VA_ARGS__)
-#define SBC_LAUNCH_LDS(stage, on, kernel, grid, block, lds, ...)                                           \
+#define SBC_LAUNCH(stage, on, kernel, grid, block, ...)                                                    \
     do {                                                                                                   \
         if ((on) && (lvl >= 2 || (lvl == 1 && ((stage) == kStAccumulate || (stage) == kStSample)))) {      \
-            hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, c->ev[2 * (stage)], c->ev[2 * (stage) + 1], 0, \
+            hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, c->ev[2 * (stage)], c->ev[2 * (stage) + 1], 0, \
                                   __VA_ARGS__);                                                            \
             timed[stage] = true;                                                                           \
         } else {                                                                                           \
-            hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                             \
+            hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);                               \
         }                                                                                                  \
     } while (0)
 
@@ -339,34 +354,44 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
             }
         }
         // (c->d_order: see compress_begin)
+        const uint32_t* const order = T > kComputeUnits / 2 ? c->d_order : nullptr;
+        const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
+        const bool in_one = !c->fused_step && P.n_chunks <= kEmitAllChunks;
+        if (in_one && pass == 0) {
+            // the rest of the step in one launch
+            if (++c->flow_tag > kTagMask) {
+                // the numbers start over: none of the words that launches have left may carry one of them
+                c->flow_tag = 1u;
+                hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_flow), 2ull * c->flow_words());
+                c->flow_sides = c->flow_taken = 0u;
+            }
+            const StepSweeps swept = {c->d_wide_state, c->d_wide_hist, c->d_wide_acc, sweeps ? 1 : 0};
+            const StepChunks chunks = {c->d_chunk_tensor, c->d_runs, c->d_bitmap, c->d_sum, c->d_head, c->cand_entries};
+            const StepSizes sizes = {T, b, P.n_chunks, P.carry, c->flow_looks};
+            const auto launch = [&](auto kernel, uint32_t per) {
+                const uint32_t takers = (P.n_chunks + per - 1u) / per;
+                SBC_LAUNCH(kStEmit, profile, kernel, dim3(2u * (unsigned)T + takers), dim3(kEmitThreads), P.d_desc, order,
+                           c->d_state, c->d_counters, c->cand(), swept, chunks, c->flow(), sizes, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
+                           P.res_next, c->h_result_dev, ++c->result_seq);
+                c->flow_sides += 2u * (unsigned)T; c->flow_taken += takers;
+            };
+            if (P.n_chunks <= kEmitFew) launch(k_emit_all<8u, k_threshold_side<false>>, 8u);
+            else launch(k_emit_all<16u, k_threshold_side<false>>, 16u);
+            return;
+        }
         const bool pairs = pass != 0 && c->fused_step;     // (of the tensors that are left, some may have lists in pairs)
         const auto threshold = pairs ? k_threshold<true> : k_threshold<false>;
         const auto apply = pairs ? k_apply<true> : k_apply<false>;
-        SBC_LAUNCH(kStThreshold, profile, threshold, dim3(2u * (unsigned)T), dim3(kThThreads), P.d_desc,
-                   T > kComputeUnits / 2 ? c->d_order : nullptr, c->d_state, c->d_counters, c->cand(), c->d_bitmap, c->d_wide_state,
-                   c->d_wide_hist, c->d_wide_acc, pass, sweeps ? 1 : 0, P.carry, P.res_now);
-        const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
+        SBC_LAUNCH(kStThreshold, profile, threshold, dim3(2u * (unsigned)T), dim3(kThThreads), P.d_desc, order, c->d_state, c->d_counters,
+                   c->cand(), c->d_bitmap, c->d_wide_state, c->d_wide_hist, c->d_wide_acc, pass, sweeps ? 1 : 0, P.carry, P.res_now);
         SBC_LAUNCH(kStApply, profile, apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
-                   c->cand(), c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, pass, P.n_chunks, P.res_now);
-        if (!c->fused_step && P.n_chunks <= kEmitAllChunks) {
-            // the workgroups that write the codes scan the summaries of all chunks themselves, one launch less.  (Two
-            // sizes: few chunks want many small workgroups, the scan over many wants large ones.)
-            const size_t lds = 2u * sizeof(uint32_t) * P.n_chunks;
-            if (P.n_chunks <= kEmitFew)
-                SBC_LAUNCH_LDS(kStEmit, profile, k_emit_all<256>, dim3((P.n_chunks + 3u) / 4u), dim3(256), lds, c->d_chunk_tensor,
-                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, c->d_counters, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
-                               P.res_next, c->h_result_dev, ++c->result_seq);
-            else
-                SBC_LAUNCH_LDS(kStEmit, profile, k_emit_all<1024>, dim3((P.n_chunks + 15u) / 16u), dim3(1024), lds, c->d_chunk_tensor,
-                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, c->d_counters, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
-                               P.res_next, c->h_result_dev, ++c->result_seq);
-            return;
-        }
+                   c->cand(), c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, P.left ? kPassAll : pass, P.n_chunks, P.res_now);
+        const int scan_pass = in_one ? kPassAll : pass;
         if (P.scan_tiles > 1)
             hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_state,
-                               c->d_sum, c->d_tile, b, pass);
+                               c->d_sum, c->d_tile, b, scan_pass);
         SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
-                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, pass, P.res_now);
+                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, scan_pass, P.res_now);
         if (!c->fused_step) {
             SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
                        c->d_gap, c->d_bitoff, c->d_state, c->d_counters, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
@@ -576,6 +601,8 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
     ok = ok && dev_alloc(&c->d_gap, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_bitoff, (size_t)c->max_chunks) == hipSuccess;
     ok = ok && dev_alloc(&c->d_tile, (size_t)(c->max_chunks / kScanTile) + T + 1) == hipSuccess;
+    ok = ok && dev_alloc(&c->d_flow, c->flow_words()) == hipSuccess;
+    ok = ok && hipMemset(c->d_flow, 0, sizeof(unsigned long long) * c->flow_words()) == hipSuccess;
     ok = ok && dev_alloc(&c->d_result, 6) == hipSuccess;
     ok = ok && dev_alloc(&c->d_dec_blocks, T + kMaxDecExtra) == hipSuccess;
     const size_t avg_room = T + (sizeof(uint32_t) * kDecWaves * (T + kMaxDecExtra) + sizeof(AvgTensor) - 1) / sizeof(AvgTensor);
@@ -679,6 +706,10 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
             c->sweep_all = value != 0;
             c->cache_valid = false;                    // which tensors are wide is part of both plans
             c->dev_dec_valid = false;
+            return SBC_OK;
+        case SBC_OPT_WAIT_LOOKS:
+            if (value < 0) return SBC_EINVAL;
+            c->flow_looks = value ? (uint32_t)value : kFlowLooks;
             return SBC_OK;
         default: return SBC_EINVAL;
     }
@@ -927,7 +958,9 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
                            (uint64_t)c->max_groups * (sizeof(GroupState) / 4));
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_counters),
                            (uint64_t)c->max_tensors * kSegs * kCounterStride * 2u);
-        // (the sweeps' histograms are left clean only if all of the call's kernels have run)
+        // (what follows is left as it should be only if all of the call's kernels have run)
+        hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_flow), 2ull * c->flow_words());
+        c->flow_sides = c->flow_taken = 0u;
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, c->d_wide_hist, (uint64_t)c->max_wide * 2 * kThBins);
     }
     c->result_dirty = true;                           // until this call has completed normally
@@ -941,7 +974,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     sbc_ctx::Pending& P = c->pend;
     P.stream = stream; P.T = T; P.b = b; P.p = p; P.slot = slot; P.slot_is_new = slot_is_new;
     P.force_exact = force_exact; P.use_history = use_history; P.sampled = sampled;
-    P.all_inline = all_inline;
+    P.all_inline = all_inline; P.left = false;
     P.sweeps = c->n_wide > 0 && (c->sweep_always || (use_history ? c->hist_long : c->sweep_sampled));
     for (int st = 0; st < kNumStages; ++st) P.timed[st] = false;
     P.res_now = res_now; P.res_next = res_next; P.d_desc = d_desc; P.msg8 = msg8;
@@ -1030,6 +1063,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
     c->last_deferred = (err & kErrDeferred) != 0u;
     if ((err & (kErrPrefilter | kErrDeferred)) && !(err & (kErrInternal | kErrNonFinite | kErrOverflow))) {
         c->last_used_exact_path = (err & kErrPrefilter) != 0u;
+        P.left = !c->fused_step && (err & kErrDeferred) != 0u;
         hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(res_now),
                            (uint64_t)(sizeof(ResultBlock) / 4));
         if (err & kErrPrefilter) {

@@ -284,15 +284,25 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // registers between the passes where a list has up to sixteen per thread; longer ones are read again.  (Tried:
 // 32 per thread, the next loads on their way during a batch, two copies of the histogram: no difference.)
 // --------------------------------------------------------------------------
+// For k_emit_all: one thread calls running() on the way (behind the list's loads, which would wait for what it
+// does) and done() when the state has been written.
+// --------------------------------------------------------------------------
+struct SideResult {
+    bool ok;                                           // false: the lists cannot be used, or an invariant is violated
+    uint32_t tau, itau, kc, raise;
+    double mean;
+};
 template <bool PAIRS>
-__global__ __launch_bounds__(kThThreads, 8) void k_threshold(
+struct k_threshold_side {
+template <typename Running, typename Done>
+static __device__ __forceinline__ void select(ThresholdShared& sh, const uint32_t item,
         const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
         const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
-        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int sweeps, int carry, ResultBlock* __restrict__ result) {
-    __shared__ __attribute__((aligned(16))) ThresholdShared sh;
+        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int sweeps, int carry, ResultBlock* __restrict__ result,
+        Running running, Done done) {
     SBC_TS(1, 0);
-    const int s = (int)(blockIdx.x & 1u), tid = threadIdx.x;
-    const int t = order ? (int)order[blockIdx.x >> 1] : (int)(blockIdx.x >> 1);
+    const int s = (int)(item & 1u), tid = threadIdx.x;
+    const int t = order ? (int)order[item >> 1] : (int)(item >> 1);
     const TensorDesc d = desc[t];
     const uint32_t flags = st[t].flags;
     const uint32_t lo_key = st[t].lo_key[s], expect = st[t].expect[s];
@@ -306,12 +316,18 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         if (tid == 8) sh.spread = 0u;
         if (tid == 9) sh.n_found = 0u;
     }
-    if (pass == 0 ? (flags & (kStInlineDone | kStDeferred | kStFailed)) != 0u : (flags & (kStExact | kStDeferred)) == 0u) return;
+    if (pass == 0 ? (flags & (kStInlineDone | kStDeferred | kStFailed)) != 0u : (flags & (kStExact | kStDeferred)) == 0u) {
+        if (tid == 0) { running(); done(t, s, SideResult{false, 0u, 0u, 0u, 0u, 0.0}); }       // (not in k_emit_all)
+        return;
+    }
     count_list(sh.counts, d, st, counters, t, s, flags);
     __syncthreads();                                   // (and the histogram's counts are zero)
     SBC_TS(1, 1);
     const ListCounts counts = ListCounts::totals(sh.counts);
-    if (lists_unusable(d, st, t, counts, pass, s == 0 && tid == 0, result)) return;
+    if (lists_unusable(d, st, t, counts, pass, s == 0 && tid == 0, result)) {
+        if (tid == 0) { running(); done(t, s, SideResult{false, 0u, 0u, 0u, 0u, 0.0}); }
+        return;
+    }
     const uint32_t full_cnt = counts.of(s);
     const uint32_t kc = kept_of_side(d, full_cnt);
     const bool pick = kc < full_cnt || !(d.flags & kDescSampled);      // else every candidate is kept
@@ -473,6 +489,7 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         if (placed) need -= uniform(sh.res[0][1]);
         SBC_TS(1, 3);
     }
+    if (tid == 0) running();
     if (placed) {
         // the entries beyond the bin (if all are kept: every one, and there is no bin), and those in it
         const uint32_t from = pick ? prefix << kThShift : 0xFFFFF000u, beyond = pick ? from + (uint32_t)(kThBins - 1) : 0u;
@@ -578,7 +595,10 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
             }
         }
         if (!ok) {                                     // uniform; cannot happen
-            if (tid == 0) atomicOr(&result->err, kErrInternal);
+            if (tid == 0) {
+                atomicOr(&result->err, kErrInternal);
+                done(t, s, SideResult{false, 0u, 0u, 0u, 0u, 0.0});
+            }
             return;
         }
     }
@@ -621,12 +641,13 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     }
     SBC_TS(1, 6);                                      // sum done
     if (tid != 0) return;
+    const double mean = S / (double)kc;
     st[t].cand_seen[s] = full_cnt;                     // (inspection only)
     st[t].tau[s] = tau;
     st[t].itau[s] = itau;
     st[t].kc[s] = kc;
     st[t].S[s] = S;
-    st[t].mean[s] = S / (double)kc;
+    st[t].mean[s] = mean;
     uint32_t raise = 0u;
     if (carry && pick) {
         const bool ranked = next_bin != 0xFFFFFFFFu;
@@ -648,7 +669,19 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
     if (wide) raise |= kErrWide;
     if ((d.flags & kDescWide) && full_cnt > long_list(d.k)) raise |= kErrLong;
     if (raise) atomicOr(&result->err, raise);
+    done(t, s, SideResult{true, tau, itau, kc, raise, mean});
     SBC_TS(1, 7);
+}
+};
+
+template <bool PAIRS>
+__global__ __launch_bounds__(kThThreads, 8) void k_threshold(
+        const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
+        const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
+        uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int sweeps, int carry, ResultBlock* __restrict__ result) {
+    __shared__ __attribute__((aligned(16))) ThresholdShared sh;
+    k_threshold_side<PAIRS>::select(sh, blockIdx.x, desc, order, st, counters, cand, bitmap, ws, whist, wacc, pass, sweeps, carry, result,
+                                    []() {}, [](int, int, const SideResult&) {});
 }
 
 // --------------------------------------------------------------------------

@@ -1,0 +1,84 @@
+"""The launch that completes a step (selection, side, residual, codes and message in workgroups that wait for one
+another's results) where it changes its form: numbers of chunks per workgroup and of workgroups, streams whose last words go
+back over many workgroups, steps left to the second pass, and the number of a launch starting over.  Against
+the oracle, bit for bit."""
+import numpy as np
+import pytest
+
+from paper_1805_08768_amd import binding as sbc, synth
+from parity_util import DeviceRun, check_round
+
+pytestmark = pytest.mark.gpu
+
+CHUNK = 8192
+
+
+def _rounds(run, sizes, p, rounds, check_decode=True):
+    """The routes that the rounds took, together."""
+    R = [np.zeros(n, np.float32) for n in sizes]
+    routes = 0
+    for r in range(rounds):
+        dWs = [synth.gaussian_update(n, round_=r, tensor=i) for i, n in enumerate(sizes)]
+        R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=check_decode and r == 0)]
+        routes |= sbc.sbc_last_route(run.ctx)
+    return routes
+
+
+@pytest.mark.parametrize("chunks", [1, 7, 8, 9, 255, 256, 257, 1023, 1024, 1025, 1041])
+def test_workgroups_of_eight_and_sixteen_chunks(chunks):
+    """One long tensor between short ones: 256 chunks are the most that go eight to a workgroup, 1024 fill 64 workgroups."""
+    sizes = [700, CHUNK * chunks - 3, 1, 9000] if chunks > 9 else [CHUNK * chunks - 3]
+    if chunks > 9:
+        sizes[1] -= CHUNK * 4                             # (the short ones have four chunks)
+    with DeviceRun(sizes) as run:
+        _rounds(run, sizes, 0.002, 2)
+
+
+@pytest.mark.parametrize("p", [1.5e-6, 4e-6, 2e-5])
+@pytest.mark.parametrize("where", ["spread", "ends"])
+def test_words_that_many_workgroups_share(p, where):
+    """A few kept entries in 1100 chunks: most workgroups have none, and a word of the stream begins far before the
+    chunk that it ends in.  Between two tensors that end in the middle of a workgroup's chunks."""
+    n = CHUNK * 1100 - 5
+    k = max(1, int(np.floor(p * n)))
+    g = np.random.default_rng(k)
+    sizes = [CHUNK * 3 + 1, n, CHUNK + 2]
+    with DeviceRun(sizes) as run:
+        R = [np.zeros(s, np.float32) for s in sizes]
+        for r in range(2):
+            dWs = [(g.standard_normal(s) * 1e-3).astype(np.float32) for s in sizes]
+            at = g.choice(n, k, replace=False) if where == "spread" else np.concatenate([np.arange(k // 2), n - 1 - np.arange(k - k // 2)])
+            dWs[1][at] = 1.0 + g.random(k, dtype=np.float32)
+            R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=(r == 0))]
+
+
+@pytest.mark.parametrize("sizes,p", [([2000003], 0.01), ([60000] * 30 + [400000], 0.02), ([CHUNK * 300 + 77, 5, 900000], 0.001), ([100] * 700, 0.1)])
+def test_steps_left_to_the_second_pass(sizes, p):
+    """After a single look for sides that nobody has started to select: whatever part of the step has been done by then is
+    done again."""
+    with DeviceRun(sizes) as run:
+        sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WAIT_LOOKS, 1)
+        left = bool(_rounds(run, sizes, p, 4, check_decode=False) & sbc.SBC_ROUTE_TAKEN_OVER)
+        sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WAIT_LOOKS, 0)
+        R = [x.cpu().numpy() for x in run.R]
+        for r in range(2):
+            dWs = [synth.gaussian_update(n, round_=9 + r, tensor=i) for i, n in enumerate(sizes)]
+            R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=False)]
+        assert not sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_TAKEN_OVER
+        assert left or len(sizes) < 30                    # (few sides may all have been started by the first look)
+
+
+def test_launch_numbers_start_over():
+    """More steps on one context than the numbers that a launch's words carry (16 bits), then one of another size, which
+    meets words of old launches."""
+    import torch
+    big, small = [300000, 64, 8193], [5000]
+    with DeviceRun(big) as run:
+        _rounds(run, big, 0.01, 2, check_decode=False)
+        x = torch.from_numpy(synth.gaussian_update(small[0])).cuda()
+        dW, R = sbc.TensorList([x]), sbc.TensorList([torch.zeros_like(x)])
+        msg = sbc.MessageBuffer(torch.zeros(sbc.sbc_msg_bound(small, 0.01), dtype=torch.uint8, device="cuda:0"))
+        for _ in range(0xFFFF - 3):
+            sbc.sbc_compress(run.ctx, dW, R, 0.01, msg)
+        run.R = [torch.zeros(n, dtype=torch.float32, device="cuda:0") for n in big]
+        _rounds(run, big, 0.01, 5, check_decode=False)
