@@ -186,7 +186,8 @@ int sbc_decompress_accumulate(sbc_ctx* ctx, void* hip_stream,
  * sbc_decompress_accumulate per message, in order, would leave there, bit for bit.  The messages are
  * decoded at the same time and the dense result is written once.
  * msgs, msg_bytes   host arrays of n_msgs device pointers (8-byte aligned) and sizes
- * other arguments, errors and completion as for sbc_decompress_accumulate; the status is final when the
+ * other arguments, errors and completion as for sbc_decompress_accumulate (the kernel that stores out may
+ * still be running when the call returns; the messages have been read by then); the status is final when the
  * call returns, whatever SBC_OPT_DEFER_DECODE_STATUS says.  After SBC_ECORRUPT out may hold anything. */
 int sbc_decompress_average(sbc_ctx* ctx, void* hip_stream, const void* const* msgs, const size_t* msg_bytes, int n_msgs,
                            const int64_t* numel, int n_tensors, double p, float scale, float* const* out);

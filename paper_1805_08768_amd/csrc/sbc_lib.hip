@@ -126,6 +126,8 @@ struct sbc_ctx {
     std::vector<int64_t> avg_numel;
     uint32_t avg_blocks = 0, avg_chunks = 0, avg_pos = 0;
     uint64_t avg_marks = 0;
+    hipStream_t avg_stream = nullptr;     // stream of the last such call, whose last kernel may still be running
+    bool avg_running = false;
     bool avg_clears = false;              // the chunk table holds the call's tensors
     bool avg_fits = false;                // and no stream is too long for one workgroup
 
@@ -405,6 +407,17 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
     SBC_LAUNCH(kStGather, profile, k_finish_message, dim3(T, P.gather_y), dim3(256), P.d_desc, c->d_state, T, b,
                c->d_stage, c->d_kept, c->d_group, P.msg8, (uint64_t)P.msg_capacity, P.res_now, P.res_next,
                c->h_result_dev, ++c->result_seq);
+}
+
+// The last average returned when its status was known, before its last kernel had ended: what works on the context's
+// scratch on another stream comes after that.
+int settle_average(sbc_ctx* c, hipStream_t stream) {
+    if (c->avg_running && c->avg_stream != stream && hipStreamSynchronize(c->avg_stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return SBC_EHIP;
+    }
+    c->avg_running = c->avg_running && c->avg_stream == stream;
+    return SBC_OK;
 }
 
 // The pending step's result block on its way to the host / waited for.
@@ -877,6 +890,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
         (void)hipGetLastError();
         return SBC_EHIP;
     }
+    if (const int rc = settle_average(c, stream)) return rc;
     if (!sizes_same) {
         // tables that depend on the sizes only: tensors by decreasing size, chunk -> tensor
         c->plan_order.resize(T);
@@ -1158,6 +1172,7 @@ int sbc_decompress_accumulate(sbc_ctx* c, void* hip_stream, const void* msg, siz
     DeviceGuard guard(c->device);
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
     const bool deferred = c->defer_decode != 0;
+    if (const int rc = settle_average(c, stream)) return rc;
     if (!same && c->deferred_pending) {
         // the pinned table below may still be read by an upload of an earlier deferred call
         if (hipStreamSynchronize(stream) != hipSuccess) { (void)hipGetLastError(); return SBC_EHIP; }
@@ -1323,9 +1338,11 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
                       std::memcmp(c->avg_out.data(), out, sizeof(float*) * T) == 0;
     DeviceGuard guard(c->device);
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    if (!same) {
+    if (!same)
         for (int t = 0; t < T; ++t)
             if (numel[t] < 1 || numel[t] >= (int64_t)1 << 32 || !out[t] || ((uintptr_t)out[t] & 3u)) return SBC_EINVAL;
+    if (const int rc = settle_average(c, stream)) return rc;
+    if (!same) {
         // (every earlier call has waited for its uploads from the pinned tables)
         c->avg_valid = false;
         uint64_t pos = 0, marks = 0, chunks = 0;
@@ -1410,17 +1427,27 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         if (b <= 7) hipLaunchKernelGGL(k_average_decode<2>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         else if (b <= 11) hipLaunchKernelGGL(k_average_decode<3>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
+        // The status is what the decoding kernels find: it goes out between the last of them and the kernel that adds
+        // the positions up and stores the result, so that the caller gets on with what it enqueues next while that one
+        // runs (32 messages of the ResNet-50 shape, a call among others: 59.0 us with the status behind it, 47.1 so).
+        if (m0 + M == n_msgs)
+            hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
         constexpr uint32_t kHalf = kAvgBlock / 2u;
         const auto apply = M < kAvgWholeFrom ? (m0 == 0 ? k_average_apply<false, kHalf> : k_average_apply<true, kHalf>)
                                              : (m0 == 0 ? k_average_apply<false, kAvgBlock> : k_average_apply<true, kAvgBlock>);
         hipLaunchKernelGGL(apply, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos,
                            positions, marks, addends, res);
     }
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
     if (hipGetLastError() != hipSuccess) return SBC_EHIP;
+    c->avg_running = true;
+    c->avg_stream = stream;
     if (const int rc = wait_result(c->h_result_dec, c->dec_seq, true, stream)) return rc;
     const uint32_t err = result_err_of(*c->h_result_dec);
     if (err == 0u) c->dec_result_dirty = false;
+    else if (hipStreamSynchronize(stream) != hipSuccess) {             // (the last kernel looks at that word: nobody clears it before)
+        (void)hipGetLastError();
+        return SBC_EHIP;
+    }
     if ((err & kErrDeferred) && !(err & kErrCorrupt))     // a stream of more positions than there is room for
         return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);
     return status_of_err(err & ~kErrDeferred);

@@ -1,0 +1,88 @@
+"""The server average returns when its status is known, before its last kernel has ended: what follows at once, on the same
+stream or another, with the same context, must not meet it half way."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1805_08768_amd import binding as sbc, synth
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _messages(sizes, p, count, seed):
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        out = []
+        for c in range(count):
+            dW = [torch.from_numpy(synth.gaussian_update(n, client=c, round_=seed, tensor=t)).to(DEV) for t, n in enumerate(sizes)]
+            msg = torch.zeros(sbc.sbc_msg_bound(sizes, p), dtype=torch.uint8, device=DEV)
+            n = sbc.sbc_compress(ctx, dW, [torch.zeros_like(x) for x in dW], p, msg)
+            torch.cuda.synchronize()
+            out.append((msg, n))
+        return out
+    finally:
+        sbc.sbc_destroy(ctx)
+
+
+def _reference(messages, sizes, p):
+    """One message after another, waited for."""
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        out = [torch.zeros(n, device=DEV) for n in sizes]
+        for m, n in messages:
+            sbc.sbc_decompress_accumulate(ctx, m, n, p, 1.0 / len(messages), out)
+            torch.cuda.synchronize()
+        return out
+    finally:
+        sbc.sbc_destroy(ctx)
+
+
+@pytest.mark.parametrize("then", ["average", "compress", "corrupt", "decode"])
+@pytest.mark.parametrize("same_stream", [True, False])
+def test_what_follows_an_average(then, same_stream):
+    sizes, p = [9000000, 300, 70001], 0.004               # (an average whose last kernel stores 36 MB)
+    small = [400000, 5]
+    a, b = _messages(sizes, p, 3, 1), _messages(small, p, 2, 2)
+    want_a, want_b = _reference(a, sizes, p), _reference(b, small, p)
+    dW = [torch.from_numpy(synth.gaussian_update(n, round_=7, tensor=t)).to(DEV) for t, n in enumerate(sizes)]
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    other = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        msg2 = torch.zeros(sbc.sbc_msg_bound(sizes, p), dtype=torch.uint8, device=DEV)
+        n2 = sbc.sbc_compress(other, dW, [torch.zeros_like(x) for x in dW], p, msg2)
+        first = torch.cuda.Stream()
+        second = first if same_stream else torch.cuda.Stream()
+        bad = b[0][0].clone()
+        bad[32 + 24 * len(small):] = 255
+        torch.cuda.synchronize()
+        for _ in range(4):
+            out_a, out_b = [torch.full((n,), 7.0, device=DEV) for n in sizes], [torch.full((n,), 7.0, device=DEV) for n in small]
+            R = [torch.zeros_like(x) for x in dW]
+            msg = torch.zeros_like(msg2)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(first):
+                sbc.sbc_decompress_average(ctx, a, p, 1.0 / len(a), out_a)
+            with torch.cuda.stream(second):
+                if then == "average":
+                    sbc.sbc_decompress_average(ctx, b, p, 1.0 / len(b), out_b)
+                elif then == "corrupt":
+                    with pytest.raises(sbc.SbcError):
+                        sbc.sbc_decompress_average(ctx, [(bad, b[0][1]), b[1]], p, 0.5, out_b)
+                    sbc.sbc_decompress_average(ctx, b, p, 1.0 / len(b), out_b)
+                elif then == "compress":
+                    n = sbc.sbc_compress(ctx, dW, R, p, msg)
+                else:
+                    out_b = [torch.zeros(n, device=DEV) for n in small]
+                    for m, nb in b:
+                        sbc.sbc_decompress_accumulate(ctx, m, nb, p, 1.0 / len(b), out_b)
+            torch.cuda.synchronize()
+            assert all(torch.equal(x, y) for x, y in zip(out_a, want_a))
+            if then == "compress":
+                assert n == n2 and torch.equal(msg[:n], msg2[:n])
+            else:
+                assert all(torch.equal(x, y) for x, y in zip(out_b, want_b))
+    finally:
+        sbc.sbc_destroy(ctx)
+        sbc.sbc_destroy(other)
