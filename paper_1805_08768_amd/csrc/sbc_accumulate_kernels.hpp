@@ -373,6 +373,23 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
 // 5.6.  Operands that are only 4-byte aligned take the same loads (24 ragged tensors of 12e6 entries in
 // one buffer: 27.4 us, 35 with scalar ones).
 // --------------------------------------------------------------------------
+// Which workgroup takes which chunk, and how many run at a time, is what memory rate hangs on beyond the last-level
+// cache.  Workgroups go to the eight compute-unit groups in turn; each takes runs of kRun consecutive chunks, so
+// that it has whole pieces of 128 KB of each array.  In large calls two of them share a compute unit instead of the four that
+// its registers hold (the launch asks for LDS that nobody uses, kStreamRoom, see kPairsFrom): 32 streams of
+// 4 KB requests from every one of 256 compute units keep more of memory's pages open than it has.  Whole steps in us, one
+// tensor: 1.5e9 entries 3505, two at a time 3255, with runs of four as well 3050 (6.4 TB/s in this kernel; runs of two
+// 3214, of eight 3093, of sixteen 3140, a contiguous eighth per compute-unit group 3112, one at a time 3758; four
+// at a time with runs of eight 3320), 400e6 941 / 848, 100e6 258 / 246, 45e6 150.8 / 149.3, 30e6 109.5 / 109.4, 23e6
+// 89.8 / 90.8; LSTM shape 162 / 156, ResNet-50 shape at p = 0.01 97.7 / 95.9.
+constexpr uint32_t kRun = 4, kComputeUnitGroups = 8;
+constexpr size_t kStreamRoom = 23552;                     // 55 KB in all: two to a compute unit, and room for another kernel's
+__device__ __forceinline__ uint32_t chunk_of_workgroup() {
+    constexpr uint32_t G = kRun * kComputeUnitGroups;
+    const uint32_t i = blockIdx.x % G, g0 = blockIdx.x - i;
+    return g0 + G <= gridDim.x ? g0 + i % kComputeUnitGroups * kRun + i / kComputeUnitGroups : blockIdx.x;
+}
+
 struct FilterShared {
     f32x4 a[kChunk / 4];
     uint32_t base[2];
@@ -398,7 +415,7 @@ __global__ __launch_bounds__(kStreamThreads, 4) void k_accumulate_filter(
         ChunkRun* __restrict__ runs, ResultBlock* __restrict__ result) {
     __shared__ FilterShared sh;
     const int tid = threadIdx.x;
-    const uint32_t c = blockIdx.x;
+    const uint32_t c = chunk_of_workgroup();
     const uint2 ct = chunk_tensor[c];                     // (tensor, its first chunk)
     const int t = (int)ct.x;
     const TensorDesc d = desc[t];

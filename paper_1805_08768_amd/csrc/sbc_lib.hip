@@ -316,14 +316,15 @@ int status_of_err(uint32_t err) {
 // stop event that take the dispatch's own begin and end time stamps (event 2s and 2s+1 for
 // stage s), so the figure is the kernel's duration without the gaps between dispatches.
 // Expects c (context), lvl (profile level), stream and timed[] in scope.
-#define SBC_LAUNCH(stage, on, kernel, grid, block, ...)                                                    \
+#define SBC_LAUNCH(stage, on, kernel, grid, block, ...) SBC_LAUNCH_LDS(stage, on, kernel, grid, block, 0, __VA_ARGS__)
+#define SBC_LAUNCH_LDS(stage, on, kernel, grid, block, lds, ...)                                           \
     do {                                                                                                   \
         if ((on) && (lvl >= 2 || (lvl == 1 && ((stage) == kStAccumulate || (stage) == kStSample)))) {      \
-            hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, c->ev[2 * (stage)], c->ev[2 * (stage) + 1], 0, \
+            hipExtLaunchKernelGGL(kernel, grid, block, lds, stream, c->ev[2 * (stage)], c->ev[2 * (stage) + 1], 0, \
                                   __VA_ARGS__);                                                            \
             timed[stage] = true;                                                                           \
         } else {                                                                                           \
-            hipLaunchKernelGGL(kernel, grid, block, 0, stream, __VA_ARGS__);                               \
+            hipLaunchKernelGGL(kernel, grid, block, lds, stream, __VA_ARGS__);                             \
         }                                                                                                  \
     } while (0)
 
@@ -728,30 +729,33 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
     }
 }
 
-// What a step's streaming pass sends past the last-level cache (no result depends on it).  Up to the
-// cache's size (12 bytes per entry pass through): nothing; 24 ragged tensors of 12e6 entries 27.4 us, 30
-// past it.  Beyond it: update and residual, for whatever ran in between, another client's step or a training
-// step, has displaced the residual by the time of the next step, and where that has written, the cache's
-// dirty lines leave it in the middle of this pass.  Only where the residual is read again before that can
-// happen is it kept: by the histogram route of this very call, or by the next step if that follows
+// What a step's streaming pass sends past the last-level cache (no result depends on it): update and residual,
+// for whatever runs until the next step, another client's step or a training step, displaces the residual, and
+// where that has written, the cache's dirty lines leave it in the middle of this pass.  Only where the residual is read
+// again before that can happen is it kept: by the histogram route of this very call, or by the next step if that follows
 // at once, that is, if since the step before this one no more than this step's bytes and one and a half
 // times the cache's can have moved at 6 TB/s (ResNet-50 shape: 118 us, of which such a step itself
-// takes 88 to 100).  A residual larger than the cache always goes past it, and so does the update, which
-// nobody reads again (66e6 entries, one client back to back: 170 us with it in the cache, 128 without).
-// Kernel times in us, residual kept / sent past:
+// takes 88 to 100).  A residual larger than the cache always goes past it, and so does the update of such a step, which
+// nobody reads again (66e6 entries, one client back to back: 170 us with it in the cache, 128 without), unless
+// both fit it.  Kernel times in us, residual kept / sent past:
 //     entries   one client, back to back   three clients in turn   after 0.6 GiB read   ... read and written
 //     25.6e6           56 / 58                   60 / 59               60 / 59               65 / 61
 //     45e6             90 / 98                  110 / 98               98 / 98              111 / 100
 //     66e6            128 / 139                 168 / 139             136 / 141             163 / 142
 //     100e6           249 / 213                 266 / 211             201 / 214             249 / 220
-constexpr uint64_t kCacheBytes = 256ull << 20;
+// Steps of up to 160 MiB (12 bytes per entry pass through) leave it all in the cache, where a few clients in turn still
+// find part of it.  Whole steps in us, kept / sent past: 12e6 entries, three clients in turn 62.2 / 64.4, eight 70.0 / 64.0;
+// 14e6, seven 69.9 / 63.5; 16e6, six 75.6 / 68.4; 20e6, three 98.6 / 88.0, five 89.5 / 79.9; 22e6, four 98.5 / 87.2.
+constexpr uint64_t kCacheBytes = 256ull << 20, kKeptBytes = 160ull << 20;
+constexpr uint64_t kPairsFrom = 24000000;  // entries from which the streaming pass has two workgroups to a compute unit (see kRun)
 static int accumulate_past_cache(sbc_ctx* c, uint64_t total, bool force_exact) {
     const auto now = std::chrono::steady_clock::now();
     const std::chrono::duration<double> since = now - c->last_begin;
     c->last_begin = now;
-    if (total * 12ull <= kCacheBytes) return kPastNothing;
-    const bool at_once = c->last_T > 0 && since.count() * 6e12 <= (double)(total * 12ull + kCacheBytes + kCacheBytes / 2);
-    return total * 4ull <= kCacheBytes && (force_exact || at_once) ? kPastUpdate : kPastAll;
+    if (total * 12ull <= kKeptBytes) return kPastNothing;
+    const bool again = force_exact || (c->last_T > 0 && since.count() * 6e12 <= (double)(total * 12ull + kCacheBytes + kCacheBytes / 2));
+    if (again && total * 12ull <= kCacheBytes) return kPastNothing;
+    return again && total * 4ull <= kCacheBytes ? kPastUpdate : kPastAll;
 }
 
 static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, float* const* residual,
@@ -1009,11 +1013,12 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     P.carry = carry;
     if (!c->fused_step) {
         const int past = accumulate_past_cache(c, total, force_exact != 0);
+        const size_t room = total >= kPairsFrom ? kStreamRoom : 0;
         if (past == kPastAll) {
-            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+            SBC_LAUNCH_LDS(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), room, d_desc,
                        c->d_chunk_tensor, c->d_state, c->d_counters, c->cand(), c->d_runs, res_now);
         } else if (past == kPastUpdate) {
-            SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastUpdate>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
+            SBC_LAUNCH_LDS(kStAccumulate, true, k_accumulate_filter<kPastUpdate>, dim3(n_chunks), dim3(kStreamThreads), room, d_desc,
                        c->d_chunk_tensor, c->d_state, c->d_counters, c->cand(), c->d_runs, res_now);
         } else {
             SBC_LAUNCH(kStAccumulate, true, k_accumulate_filter<kPastNothing>, dim3(n_chunks), dim3(kStreamThreads), d_desc,
