@@ -622,7 +622,7 @@ __device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint
 // one tensor of 2^20 35.2 / 31.8, 24 ragged tensors of 12e6 65.8 / 61.5, ResNet-50 shape (3243 chunks) at p = 0.001 83.3
 // / 82.6, at p = 0.01, where the chunks of other tensors are done while the longest list is selected, 103.0 / 96.1.
 // Beyond 4096 chunks the workgroups do not all find room at once and wait for each other's instructions: 8060 chunks
-// 162 / 165.
+// 162 / 171.
 // --------------------------------------------------------------------------
 constexpr uint32_t kEmitAllChunks = 4096;
 constexpr int kEmitThreads = kThThreads;
