@@ -46,10 +46,10 @@ __device__ __forceinline__ uint32_t wave_excl_max(uint32_t v, uint32_t* total) {
     return (threadIdx.x & 63) ? prev : 0u;
 }
 // Does a pass of k_apply / k_emit work on a tensor with these state flags?  (kPassAll: behind k_emit_all, which
-// leaves the scan over the chunks to the second pass, of every tensor.)
+// leaves the scan over the chunks to the second pass, of every tensor that has been selected.)
 constexpr int kPassAll = 2;
 __device__ __forceinline__ bool encoded_in_pass(uint32_t flags, int pass) {
-    if (pass == kPassAll) return true;
+    if (pass == kPassAll) return (flags & kStFailed) == 0u;
     return pass == 0 ? (flags & (kStInlineDone | kStDeferred | kStFailed)) == 0u : (flags & (kStExact | kStDeferred)) != 0u;
 }
 
@@ -300,7 +300,12 @@ __global__ __launch_bounds__(kEncThreads) void k_apply(
     const uint32_t flags = st[t].flags;
     const double mean_p = st[t].mean[0], mean_n = st[t].mean[1];
     const uint32_t tau_p = st[t].tau[0], tau_n = st[t].tau[1], itau_p = st[t].itau[0], itau_n = st[t].itau[1];
-    if (!encoded_in_pass(flags, pass)) return;
+    if (!encoded_in_pass(flags, pass)) {
+        // (its error bit stops the call; cannot be missing: what is encoded below would be another call's)
+        if (pass == kPassAll && lane == 0 && !(__hip_atomic_load(&result->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrStops))
+            atomicOr(&result->err, kErrInternal);
+        return;
+    }
     // Alg. 2 compares the means (sums that differ may still give equal means: the positive side then)
     const int chosen = mean_p >= mean_n ? 0 : 1;
     const float mu32 = (float)(chosen ? mean_n : mean_p);

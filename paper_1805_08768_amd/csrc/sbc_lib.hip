@@ -1073,12 +1073,22 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
         }
     }
     uint32_t err = result_err_of(*c->h_result);
+    if (!c->fused_step && (err & kErrDeferred)) {
+        // k_emit_all has left the step because sides were not being selected yet when its word went out.  They are once
+        // it has ended, and what they raise (a filter that fell short, a list that overflowed) stands in the error word
+        // only: that word again, behind the kernel.
+        hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dev, res_now, ++c->result_seq);
+        rc = enqueue_result_copy(c);
+        if (rc == SBC_OK) rc = wait_result(c);
+        if (rc != SBC_OK) return rc;
+        err |= result_err_of(*c->h_result);
+    }
     c->last_used_exact_path = false;
     c->last_used_wide = (err & kErrWide) != 0u;
 
     // ---- second pass: the histogram route for the tensors whose filter kept fewer than k candidates,
     // and the selection for the tensors the streaming kernel left to it ----
-    const uint32_t loose = err & (kErrLoose | kErrStaleKeys);
+    const uint32_t loose = err & (kErrLoose | kErrStaleKeys | kErrLong);
     c->last_deferred = (err & kErrDeferred) != 0u;
     if ((err & (kErrPrefilter | kErrDeferred)) && !(err & (kErrInternal | kErrNonFinite | kErrOverflow))) {
         c->last_used_exact_path = (err & kErrPrefilter) != 0u;

@@ -21,6 +21,7 @@ extern "C" void stub_fail_allocation(long nth);
 extern "C" void stub_withhold_results(int on);
 extern "C" int stub_known_senders();
 extern "C" void stub_result_bits(uint32_t bits);
+extern "C" void stub_next_result_bits(const char* kernel, uint32_t bits);
 extern "C" int stub_launched(const char* name, long from);
 extern "C" unsigned stub_grid_of(const char* name, long from);
 
@@ -362,6 +363,52 @@ int main(int argc, char** argv) {
             sbc_destroy(c); c = nullptr;
             CHECK(stub_live_blocks() == 0);
         }
+
+    // ---- a step that k_emit_all leaves to the second pass (bit 64), in which sides that start after its word has gone
+    // out raise more: what they raise counts as if it had been in that word ----
+    {
+        const Buffers s = fake_buffers({3000000, 1000});
+        const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), 0.01);
+        struct Case { uint32_t early, late; int status, histogram; };
+        const Case cases[] = {{64, 0, SBC_OK, 0}, {64, 8, SBC_OK, 1}, {64 | 8, 0, SBC_OK, 1}, {64, 8 | 16, SBC_OK, 1},
+                              {64, 128, SBC_ECAPACITY, 0}, {64, 2, SBC_EINTERNAL, 0}, {64, 8 | 128, SBC_ECAPACITY, 0},
+                              {64 | 1, 0, SBC_ENONFINITE, 0}};
+        CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+        for (int begin_end = 0; begin_end < 2; ++begin_end)
+            for (const Case& k : cases) {
+                CHECK(compress(c, s, 0.01, nb, &nbytes) == SBC_OK);
+                const long from = stub_launches();
+                stub_next_result_bits("k_emit_all", k.early);
+                stub_next_result_bits("k_publish", (k.early & ~64u) | k.late);
+                int status;
+                if (begin_end) {
+                    CHECK(sbc_compress_begin(c, nullptr, s.dW.data(), s.R.data(), s.numel.data(), s.T(), 0.01, kMsg, nb) == SBC_OK);
+                    status = sbc_compress_end(c, &nbytes);
+                } else {
+                    status = compress(c, s, 0.01, nb, &nbytes);
+                }
+                CHECK(status == k.status);
+                CHECK(stub_launched("k_publish", from) == 1);
+                CHECK(stub_launched("k_hist_flagged", from) == k.histogram && stub_launched("k_extract", from) == k.histogram);
+                CHECK(stub_launched("7k_apply", from) == (k.status == SBC_OK ? 1 : 0));
+                const int route = sbc_last_route(c);
+                if (k.status == SBC_OK)
+                    CHECK((route & (SBC_ROUTE_TAKEN_OVER | SBC_ROUTE_HISTOGRAM)) == (SBC_ROUTE_TAKEN_OVER | (k.histogram ? SBC_ROUTE_HISTOGRAM : 0)) &&
+                          !(route & SBC_ROUTE_LOOSE_KEYS) == !(k.late & 16));
+            }
+        // a long list (bit 512) that such a side has found: the next call sweeps, as ever
+        for (int late = 0; late < 2; ++late) {
+            CHECK(compress(c, s, 0.01, nb, &nbytes) == SBC_OK);
+            stub_next_result_bits("k_emit_all", late ? 64u : 64u | 512u);
+            stub_next_result_bits("k_publish", 512u);
+            CHECK(compress(c, s, 0.01, nb, &nbytes) == SBC_OK);
+            const long from = stub_launches();
+            CHECK(compress(c, s, 0.01, nb, &nbytes) == SBC_OK);
+            CHECK(stub_launched("k_wide_count", from) == 1);
+        }
+        sbc_destroy(c); c = nullptr;
+        CHECK(stub_live_blocks() == 0);
+    }
 
     // ---- the average over a round's messages: argument errors, and its two tables at their limits ----
     {

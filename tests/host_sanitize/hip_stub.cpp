@@ -18,6 +18,7 @@ static long g_live_blocks = 0;
 static long g_fail_alloc_at = -1;      // the n-th allocation from now fails (tests the clean-up path)
 static bool g_withhold = false;        // no results are sent
 static uint32_t g_result_bits = 0;     // the error word that results carry
+static struct { const char* kernel; uint32_t bits; } g_next[4];          // ... and the next result of kernels with that name
 static hipError_t g_launch_error = hipSuccess;
 static struct { const void* host; const char* name; } g_names[128];      // every kernel with its mangled name
 static int g_n_names = 0;
@@ -34,6 +35,10 @@ extern "C" long stub_live_blocks() { return g_live_blocks; }
 extern "C" void stub_fail_allocation(long nth) { g_fail_alloc_at = nth; }
 extern "C" void stub_withhold_results(int on) { g_withhold = on != 0; }
 extern "C" void stub_result_bits(uint32_t bits) { g_result_bits = bits; }
+extern "C" void stub_next_result_bits(const char* kernel, uint32_t bits) {
+    for (auto& n : g_next)
+        if (!n.kernel) { n = {kernel, bits}; return; }
+}
 // Workgroups (x) of the first of the launches from number `from` on of a kernel with that name (0: none).
 extern "C" unsigned stub_grid_of(const char* name, long from) {
     for (long i = from; i < g_launches; ++i)
@@ -102,9 +107,13 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
         (uint64_t)grid.x * block.x > 0xFFFFFFFFull || grid.y > 65535u || grid.z > 65535u)
         return g_launch_error = hipErrorInvalidConfiguration;
     for (const Sender& s : g_senders)
-        if ((f == s.host[0] || f == s.host[1]) && !g_withhold)       // (the number: bits 50 to 63 of the word)
+        if ((f == s.host[0] || f == s.host[1]) && !g_withhold) {     // (the number: bits 50 to 63 of the word)
+            uint32_t bits = g_result_bits;
+            for (auto& n : g_next)
+                if (n.kernel && std::strstr(s.name, n.kernel)) { bits = n.bits; n.kernel = nullptr; break; }
             **static_cast<uint64_t**>(args[s.word]) = (uint64_t)(*static_cast<uint32_t*>(args[s.seq]) & 0x3FFFu) << 50 |
-                                                      (uint64_t)g_result_bits << 40;
+                                                      (uint64_t)bits << 40;
+        }
     g_grids[g_launches % 64] = grid.x;
     g_kernels[g_launches++ % 64] = f;
     return hipSuccess;

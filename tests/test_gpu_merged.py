@@ -52,11 +52,12 @@ def test_words_that_many_workgroups_share(p, where):
             R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=(r == 0))]
 
 
-@pytest.mark.parametrize("sizes,p", [([2000003], 0.01), ([60000] * 30 + [400000], 0.02), ([CHUNK * 300 + 77, 5, 900000], 0.001), ([100] * 700, 0.1)])
-def test_steps_left_to_the_second_pass(sizes, p):
+@pytest.mark.parametrize("sizes,p,sampled", [([2000003], 0.01, False), ([60000] * 30 + [400000], 0.02, False), ([CHUNK * 300 + 77, 5, 900000], 0.001, False),
+                                             ([100] * 700, 0.1, False), ([2000003, 900000], 0.01, True)])
+def test_steps_left_to_the_second_pass(sizes, p, sampled):
     """After a single look for sides that nobody has started to select: whatever part of the step has been done by then is
     done again."""
-    with DeviceRun(sizes) as run:
+    with DeviceRun(sizes, sampled=sampled) as run:
         sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WAIT_LOOKS, 1)
         left = bool(_rounds(run, sizes, p, 4, check_decode=False) & sbc.SBC_ROUTE_TAKEN_OVER)
         sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WAIT_LOOKS, 0)
@@ -65,7 +66,36 @@ def test_steps_left_to_the_second_pass(sizes, p):
             dWs = [synth.gaussian_update(n, round_=9 + r, tensor=i) for i, n in enumerate(sizes)]
             R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=False)]
         assert not sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_TAKEN_OVER
-        assert left or len(sizes) < 30                    # (few sides may all have been started by the first look)
+        print("left" if left else "not left", flush=True)
+        if not left and len(sizes) < 30:
+            pytest.skip("the steps were right, but the few sides had all been started by the first look")
+        assert left
+
+
+@pytest.mark.parametrize("compact", [False, True])
+def test_steps_left_whose_lists_cannot_be_used(compact):
+    """600 sides on 512 places, so that some start after others have looked for them.  Data that shrinks by a thousand with
+    the residual cleared (carried keys let nothing pass, or too little) and that grows by a thousand (everything
+    passes: more than a compact context's lists hold), in steps left after a single look."""
+    sizes, p = [12000] * 299 + [500000], 0.02
+    scales = [1.0, 1.0, 1e-3, 1e-3, 1e-3, 1.0, 1.0, 1.0, 1e-3]
+    routes = []
+    with DeviceRun(sizes, compact=compact) as run:
+        sbc.sbc_set_option(run.ctx, sbc.SBC_OPT_WAIT_LOOKS, 1)
+        R = [np.zeros(n, np.float32) for n in sizes]
+        for r, scale in enumerate(scales):
+            if r and scale < scales[r - 1]:
+                R = [np.zeros(n, np.float32) for n in sizes]
+                for x in run.R:
+                    x.zero_()
+            dWs = [synth.gaussian_update(n, round_=r, tensor=i) * np.float32(scale) for i, n in enumerate(sizes)]
+            R = [x.R_new for x in check_round(run, dWs, R, p, check_decode=False)]
+            routes.append(sbc.sbc_last_route(run.ctx))
+    print("routes", routes, flush=True)
+    left = [bool(x & sbc.SBC_ROUTE_TAKEN_OVER) for x in routes]
+    histogram = [bool(x & sbc.SBC_ROUTE_HISTOGRAM) for x in routes]
+    assert any(left) and histogram[2] and histogram[8]
+    assert not compact or histogram[5]
 
 
 def test_launch_numbers_start_over():
