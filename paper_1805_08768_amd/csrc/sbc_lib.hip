@@ -126,8 +126,8 @@ struct sbc_ctx {
     std::vector<int64_t> avg_numel;
     uint32_t avg_blocks = 0, avg_chunks = 0, avg_pos = 0;
     uint64_t avg_marks = 0;
-    hipStream_t avg_stream = nullptr;     // stream of the last such call, whose last kernel may still be running
-    bool avg_running = false;
+    hipEvent_t ev_average = nullptr;      // the end of the last such call's last kernel,
+    bool avg_running = false;             // which may not have come when the call returns
     bool avg_clears = false;              // the chunk table holds the call's tensors
     bool avg_fits = false;                // and no stream is too long for one workgroup
 
@@ -300,7 +300,8 @@ void free_all(sbc_ctx* c) {
     if (c->h_state) (void)hipHostFree(c->h_state);
     if (c->ev_ok) for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
     if (c->ev_result) (void)hipEventDestroy(c->ev_result);
-    c->ev_result = nullptr;
+    if (c->ev_average) (void)hipEventDestroy(c->ev_average);
+    c->ev_result = c->ev_average = nullptr;
     c->ev_ok = false;
 }
 
@@ -411,14 +412,32 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
 }
 
 // The last average returned when its status was known, before its last kernel had ended: what works on the context's
-// scratch on another stream comes after that.
+// scratch comes after that.  An event of the context's own stands for that kernel, for its stream may be gone
+// by now.  (Where the caller records a graph on this stream, which must not wait for anything outside, the host waits;
+// in that thread only the relaxed mode admits to look at events.)
 int settle_average(sbc_ctx* c, hipStream_t stream) {
-    if (c->avg_running && c->avg_stream != stream && hipStreamSynchronize(c->avg_stream) != hipSuccess) {
+    if (!c->avg_running) return SBC_OK;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    hipError_t e = hipEventQuery(c->ev_average);
+    if (e == hipErrorNotReady) {
         (void)hipGetLastError();
-        return SBC_EHIP;
+        hipStreamCaptureStatus recording = hipStreamCaptureStatusNone;
+        e = hipStreamIsCapturing(stream, &recording);
+        if (e == hipSuccess && recording == hipStreamCaptureStatusNone) {
+            e = hipStreamWaitEvent(stream, c->ev_average, 0);          // (still running for calls on further streams)
+        } else if (e == hipSuccess) {
+            e = hipEventSynchronize(c->ev_average);
+            c->avg_running = false;
+        }
+    } else {
+        c->avg_running = false;
     }
-    c->avg_running = c->avg_running && c->avg_stream == stream;
-    return SBC_OK;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) return SBC_OK;
+    (void)hipGetLastError();
+    c->avg_running = false;                               // (no call fails for it twice)
+    return SBC_EHIP;
 }
 
 // The pending step's result block on its way to the host / waited for.
@@ -658,10 +677,11 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
         } else {
             c->ev_ok = true;
         }
-        if (ok && hipEventCreateWithFlags(&c->ev_result, hipEventDisableTiming) != hipSuccess) {
-            c->ev_result = nullptr;
-            ok = false;
-        }
+        for (hipEvent_t* ev : {&c->ev_result, &c->ev_average})
+            if (ok && hipEventCreateWithFlags(ev, hipEventDisableTiming) != hipSuccess) {
+                *ev = nullptr;
+                ok = false;
+            }
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -1444,24 +1464,32 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         // The status is what the decoding kernels find: it goes out between the last of them and the kernel that adds
         // the positions up and stores the result, so that the caller gets on with what it enqueues next while that one
-        // runs (32 messages of the ResNet-50 shape, a call among others: 59.0 us with the status behind it, 47.1 so).
+        // runs (32 messages of the ResNet-50 shape, a call among others: 59.0 us with the status behind it, 48.6 so; 1.6
+        // of them for the event, as the launch's own; recorded behind the launch it takes 3.1).
         if (m0 + M == n_msgs)
             hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
         constexpr uint32_t kHalf = kAvgBlock / 2u;
         const auto apply = M < kAvgWholeFrom ? (m0 == 0 ? k_average_apply<false, kHalf> : k_average_apply<true, kHalf>)
                                              : (m0 == 0 ? k_average_apply<false, kAvgBlock> : k_average_apply<true, kAvgBlock>);
-        hipLaunchKernelGGL(apply, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos,
-                           positions, marks, addends, res);
+        hipExtLaunchKernelGGL(apply, dim3(c->avg_chunks), dim3(kEncThreads), 0, stream, nullptr, m0 + M == n_msgs ? c->ev_average : nullptr, 0,
+                              c->d_avg_chunk, c->d_avg_tensor, (uint32_t)M, c->avg_pos, positions, marks, addends, res);
     }
-    if (hipGetLastError() != hipSuccess) return SBC_EHIP;
-    c->avg_running = true;
-    c->avg_stream = stream;
-    if (const int rc = wait_result(c->h_result_dec, c->dec_seq, true, stream)) return rc;
-    const uint32_t err = result_err_of(*c->h_result_dec);
-    if (err == 0u) c->dec_result_dirty = false;
-    else if (hipStreamSynchronize(stream) != hipSuccess) {             // (the last kernel looks at that word: nobody clears it before)
+    if (hipGetLastError() != hipSuccess) {
+        (void)hipStreamSynchronize(stream);               // (of what was launched nobody else knows)
         (void)hipGetLastError();
         return SBC_EHIP;
+    }
+    c->avg_running = true;
+    if (const int rc = wait_result(c->h_result_dec, c->dec_seq, true, stream)) return rc;
+    const uint32_t err = result_err_of(*c->h_result_dec);
+    if (err == 0u) {
+        c->dec_result_dirty = false;
+    } else {                                              // (the last kernel looks at that word: nobody clears it before)
+        c->avg_running = false;
+        if (hipStreamSynchronize(stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return SBC_EHIP;
+        }
     }
     if ((err & kErrDeferred) && !(err & kErrCorrupt))     // a stream of more positions than there is room for
         return average_in_turn(c, stream, msgs, msg_bytes, n_msgs, numel, T, p, scale, out);

@@ -22,6 +22,11 @@ extern "C" void stub_withhold_results(int on);
 extern "C" int stub_known_senders();
 extern "C" void stub_result_bits(uint32_t bits);
 extern "C" void stub_next_result_bits(const char* kernel, uint32_t bits);
+extern "C" void stub_stream_gone(void* stream);
+extern "C" void stub_stream_records(void* stream);
+extern "C" void stub_events_pending(int on);
+extern "C" int stub_stream_waits();
+extern "C" int stub_event_waits();
 extern "C" int stub_launched(const char* name, long from);
 extern "C" unsigned stub_grid_of(const char* name, long from);
 
@@ -478,6 +483,48 @@ int main(int argc, char** argv) {
                 CHECK(stub_live_blocks() == 0);
             }
         }
+    }
+
+    // ---- what follows an average whose last kernel is still running: waits for that kernel on its own stream, whatever has
+    // become of the average's (a destroyed one); a stream that records a graph has the host wait.  Nothing to wait
+    // for once the kernel has ended, or the average failed ----
+    {
+        const Buffers s = fake_buffers({3000000, 1000});
+        const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), p);
+        const void* const msgs[2] = {kMsg, kMsg};
+        const size_t lens[2] = {nb, nb};
+        void* const first = reinterpret_cast<void*>(0x1000);
+        void* const second = reinterpret_cast<void*>(0x2000);
+        const auto average = [&](void* stream) { return sbc_decompress_average(c, stream, msgs, lens, 2, s.numel.data(), s.T(), p, 0.5f, s.out.data()); };
+        const auto decode = [&](void* stream) { return sbc_decompress_accumulate(c, stream, kMsg, nb, s.numel.data(), s.T(), p, 1.f, s.out.data()); };
+        const auto step = [&](void* stream) {
+            return sbc_compress(c, stream, s.dW.data(), s.R.data(), s.numel.data(), s.T(), p, kMsg, nb, &nbytes);
+        };
+        for (int pending = 0; pending < 2; ++pending) {
+            CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            CHECK(average(first) == SBC_OK);
+            stub_stream_gone(first);
+            stub_events_pending(pending);
+            int waits = stub_stream_waits();
+            CHECK(step(second) == SBC_OK && step(second) == SBC_OK && decode(second) == SBC_OK && average(second) == SBC_OK);
+            CHECK(stub_stream_waits() - waits == (pending ? 4 : 0));
+            stub_stream_gone(nullptr);
+            CHECK(sbc_set_option(c, SBC_OPT_DEFER_DECODE_STATUS, 1) == SBC_OK && decode(second) == SBC_OK && average(first) == SBC_OK);
+            stub_stream_records(second);
+            waits = stub_event_waits();
+            CHECK(decode(second) == SBC_OK && decode(second) == SBC_OK);
+            CHECK(stub_event_waits() - waits == pending);
+            stub_stream_records(nullptr);
+            CHECK(sbc_decode_status(c, second) == SBC_OK && sbc_set_option(c, SBC_OPT_DEFER_DECODE_STATUS, 0) == SBC_OK);
+            CHECK(average(second) == SBC_OK);
+            stub_next_result_bits("k_publish", 4);         // (a corrupt message: the call drains its stream)
+            CHECK(average(second) == SBC_ECORRUPT);
+            waits = stub_stream_waits();
+            CHECK(decode(first) == SBC_OK && stub_stream_waits() == waits);
+            stub_events_pending(0);
+            sbc_destroy(c); c = nullptr;
+        }
+        CHECK(stub_live_blocks() == 0);
     }
 
     // ---- the average over 64 messages of more tensors than one launch can decode for all of them: fewer

@@ -4,7 +4,8 @@
 // checked against the size it allocated; copies and fills happen at once; kernel launches do
 // nothing, but that those which send a call's result to pinned host memory send "no error, empty
 // message" with the call's number (or, if the test says so, end without it, as a kernel does that
-// finds an invariant violated); events and streams are inert.  One device.
+// finds an invariant violated); streams and events are inert, but that one stream can be made one that has been
+// destroyed, one that records a graph, and events ones that have not happened.  One device.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdint>
@@ -20,6 +21,9 @@ static bool g_withhold = false;        // no results are sent
 static uint32_t g_result_bits = 0;     // the error word that results carry
 static struct { const char* kernel; uint32_t bits; } g_next[4];          // ... and the next result of kernels with that name
 static hipError_t g_launch_error = hipSuccess;
+static hipStream_t g_gone = nullptr, g_recording = nullptr;
+static bool g_events_pending = false;
+static int g_stream_waits = 0, g_event_waits = 0, g_relaxed = 0;
 static struct { const void* host; const char* name; } g_names[128];      // every kernel with its mangled name
 static int g_n_names = 0;
 // The kernels that send results, by a part of their mangled name, and which of their arguments are the word
@@ -54,6 +58,11 @@ extern "C" int stub_launched(const char* name, long from) {
             n += g_kernels[i % 64] == g_names[k].host && std::strstr(g_names[k].name, name);
     return n;
 }
+extern "C" void stub_stream_gone(void* s) { g_gone = (hipStream_t)s; }
+extern "C" void stub_stream_records(void* s) { g_recording = (hipStream_t)s; }
+extern "C" void stub_events_pending(int on) { g_events_pending = on != 0; }
+extern "C" int stub_stream_waits() { return g_stream_waits; }
+extern "C" int stub_event_waits() { return g_event_waits; }
 extern "C" int stub_known_senders() {
     int n = 0;
     for (const Sender& s : g_senders) n += (s.host[0] != nullptr) + (s.host[1] != nullptr);
@@ -87,18 +96,36 @@ hipError_t hipHostFree(void* p) { return stub_free(p); }
 hipError_t hipHostGetDevicePointer(void** dev, void* host, unsigned int) { *dev = host; return hipSuccess; }
 
 hipError_t hipMemcpy(void* dst, const void* src, size_t bytes, hipMemcpyKind) { if (bytes) std::memcpy(dst, src, bytes); return hipSuccess; }
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t) {
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t s) {
+    if (s && s == g_gone) return hipErrorContextIsDestroyed;
     if (bytes) std::memcpy(dst, src, bytes);
     return hipSuccess;
 }
 hipError_t hipMemset(void* dst, int value, size_t bytes) { if (bytes) std::memset(dst, value, bytes); return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) { return s && s == g_gone ? hipErrorContextIsDestroyed : hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* status) {
+    *status = s && s == g_recording ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* mode) {
+    g_relaxed += *mode == hipStreamCaptureModeRelaxed ? 1 : -1;
+    *mode = g_relaxed ? hipStreamCaptureModeGlobal : hipStreamCaptureModeRelaxed;
+    return hipSuccess;
+}
 
 hipError_t hipEventCreate(hipEvent_t* e) { return stub_alloc(reinterpret_cast<void**>(e), 8); }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return stub_alloc(reinterpret_cast<void**>(e), 8); }
 hipError_t hipEventDestroy(hipEvent_t e) { return stub_free(e); }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
-hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { ++g_event_waits; return g_recording && !g_relaxed ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) {
+    if (g_recording && !g_relaxed) return hipErrorStreamCaptureUnsupported;
+    return g_events_pending ? hipErrorNotReady : hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
+    ++g_stream_waits;
+    return s && s == g_recording ? hipErrorStreamCaptureIsolation : hipSuccess;
+}
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {

@@ -41,8 +41,11 @@ def _reference(messages, sizes, p):
 
 @pytest.mark.parametrize("then", ["average", "compress", "corrupt", "decode"])
 @pytest.mark.parametrize("same_stream", [True, False])
-def test_what_follows_an_average(then, same_stream):
-    sizes, p = [9000000, 300, 70001], 0.004               # (an average whose last kernel stores 36 MB)
+@pytest.mark.parametrize("p", [0.002, 0.004])
+def test_what_follows_an_average(then, same_stream, p):
+    # (at 0.002 an average whose last kernel stores 36 MB; at 0.004 the longest stream has more tiles than the averaging
+    # kernels take, and the messages are decoded in turn)
+    sizes = [9000000, 300, 70001]
     small = [400000, 5]
     a, b = _messages(sizes, p, 3, 1), _messages(small, p, 2, 2)
     want_a, want_b = _reference(a, sizes, p), _reference(b, small, p)
@@ -86,3 +89,79 @@ def test_what_follows_an_average(then, same_stream):
     finally:
         sbc.sbc_destroy(ctx)
         sbc.sbc_destroy(other)
+
+
+def test_stream_of_an_average_that_is_destroyed():
+    """A context whose last average ran on a stream that its caller has destroyed goes on working on others."""
+    import ctypes
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL([line.split()[-1] for line in f if "libamdhip64" in line][0])
+    sizes, p = [3000000, 70001], 0.004
+    a = _messages(sizes, p, 3, 1)
+    want = _reference(a, sizes, p)
+    dW = [torch.from_numpy(synth.gaussian_update(n, round_=7, tensor=t)).to(DEV) for t, n in enumerate(sizes)]
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        msg = torch.zeros(sbc.sbc_msg_bound(sizes, p), dtype=torch.uint8, device=DEV)
+        for synchronized in (True, False):
+            out, again = [[torch.full((n,), 7.0, device=DEV) for n in sizes] for _ in range(2)]
+            torch.cuda.synchronize()
+            handle = ctypes.c_void_p()
+            assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0          # (non-blocking)
+            with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+                sbc.sbc_decompress_average(ctx, a, p, 1.0 / len(a), out)
+            if synchronized:
+                assert hip.hipStreamSynchronize(handle) == 0
+            assert hip.hipStreamDestroy(handle) == 0
+            with torch.cuda.stream(torch.cuda.Stream()):
+                sbc.sbc_decompress_average(ctx, a, p, 1.0 / len(a), again)
+                n = sbc.sbc_compress(ctx, dW, [torch.zeros_like(x) for x in dW], p, msg)
+                torch.cuda.current_stream().synchronize()
+                one = [torch.zeros(n, device=DEV) for n in sizes]
+                sbc.sbc_decompress_accumulate(ctx, msg, n, p, 1.0, one)
+            torch.cuda.synchronize()
+            assert all(torch.equal(x, y) for x, y in zip(out, want)) and all(torch.equal(x, y) for x, y in zip(again, want))
+            assert all(int((x != 0).sum()) == max(1, int(p * n)) for x, n in zip(one, sizes))
+    finally:
+        sbc.sbc_destroy(ctx)
+
+
+def test_decode_recorded_while_an_average_runs():
+    """A deferred decode in a graph whose recording begins before the average's last kernel on another stream has ended."""
+    sizes, p = [9000000, 70001], 0.002
+    a = _messages(sizes, p, 3, 1)
+    want = _reference(a, sizes, p)
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        sbc.sbc_set_option(ctx, sbc.SBC_OPT_DEFER_DECODE_STATUS, 1)
+        out, one = [[torch.zeros(n, device=DEV) for n in sizes] for _ in range(2)]
+        first, second = torch.cuda.Stream(), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(second):
+            sbc.sbc_decompress_accumulate(ctx, a[0][0], a[0][1], p, 0.5, one)           # (the tables are there)
+        sbc.sbc_decode_status(ctx, second)
+        with torch.cuda.stream(second):
+            sbc.sbc_decompress_accumulate(ctx, a[0][0], a[0][1], p, 0.5, one)           # (and the status word is clean)
+        torch.cuda.synchronize()
+        want_one = [x * 0.5 for x in one]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(first):
+            sbc.sbc_decompress_average(ctx, a, p, 1.0 / len(a), out)
+        with torch.cuda.stream(second):
+            graph.capture_begin()
+            try:
+                sbc.sbc_decompress_accumulate(ctx, a[0][0], a[0][1], p, 0.5, one)
+            finally:
+                graph.capture_end()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(out, want))
+        for _ in range(3):
+            with torch.cuda.stream(second):
+                for x in one:
+                    x.zero_()
+                graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(x, y) for x, y in zip(one, want_one))
+        sbc.sbc_decode_status(ctx, second)
+    finally:
+        sbc.sbc_destroy(ctx)
