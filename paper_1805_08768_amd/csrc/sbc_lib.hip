@@ -996,8 +996,10 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
                            (uint64_t)c->max_groups * (sizeof(GroupState) / 4));
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_counters),
                            (uint64_t)c->max_tensors * kSegs * kCounterStride * 2u);
-        // (what follows is left as it should be only if all of the call's kernels have run)
-        hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_flow), 2ull * c->flow_words());
+        // (what follows is left as it should be only if all of the call's kernels have run; k_emit_all's words are
+        // clean until its first launch, whatever the number of that one)
+        if (c->flow_sides | c->flow_taken)
+            hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(c->d_flow), 2ull * c->flow_words());
         c->flow_sides = c->flow_taken = 0u;
         hipLaunchKernelGGL(k_zero_words, dim3(64), dim3(256), 0, stream, c->d_wide_hist, (uint64_t)c->max_wide * 2 * kThBins);
     }

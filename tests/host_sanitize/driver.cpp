@@ -415,6 +415,23 @@ int main(int argc, char** argv) {
         CHECK(stub_live_blocks() == 0);
     }
 
+    // ---- scratch memory that a context's creation leaves clean: a first call clears no words that only earlier launches
+    // can have left, a call after one that failed does ----
+    {
+        const Buffers s = fake_buffers({3000000, 1000});
+        const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), p);
+        CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+        const int cleared[] = {4, 0, 0, 5, 0};
+        for (int call = 0; call < 5; ++call) {
+            const long from = stub_launches();
+            stub_withhold_results(call == 2);
+            CHECK(compress(c, s, p, nb, &nbytes) == (call == 2 ? SBC_EINTERNAL : SBC_OK));
+            stub_withhold_results(0);
+            CHECK(stub_launched("k_zero_words", from) == cleared[call]);
+        }
+        sbc_destroy(c); c = nullptr;
+    }
+
     // ---- the average over a round's messages: argument errors, and its two tables at their limits ----
     {
         std::vector<const void*> msgs(130, kMsg);
