@@ -1,11 +1,14 @@
 // The rest of the client step once the thresholds are known, a wavefront per chunk of 8192 entries:
-//   k_emit_all : calls of up to 4096 chunks, everything behind the streaming pass in one launch: the sides'
+//   k_emit_all : calls of few tensors and up to 3584 chunks, everything behind the streaming pass in one launch: the sides'
 //                selection (k_threshold_side), Alg. 2's side decision, Alg. 1's residual line and Alg. 3, the message
-//   k_apply    : the same steps as launches of their own, for calls of very many chunks, for the second pass and behind
+//   k_apply    : the same steps as launches of their own, for calls of more chunks or tensors, for the second pass and behind
 //                the streaming kernel that finishes tensors: side decision, residual line and Alg. 3 within the
 //                chunk, from the chunk's run of candidates: the codes of all its kept entries but the first, whose
 //                predecessor lies in another chunk, as a bit string of its own, and a summary
-//   k_tile_summary, k_tensor_scan, k_emit : the scan over a tensor's chunks in tiles of 4096 (predecessors, bit
+//   k_emit_scan : up to 4096 chunks: every workgroup scans the summaries of the call's chunks (predecessors, bit
+//                offsets, the tensors' places in the payload), then every wavefront puts its chunk's first code and bit
+//                string together, shifted to their place
+//   k_tile_summary, k_tensor_scan, k_emit : more chunks: the scan over a tensor's chunks in tiles of 4096 (predecessors, bit
 //                offsets), then every wavefront puts its chunk's first code and bit string together, shifted to their
 //                place (into the message, or, behind the streaming kernel that finishes tensors, into the
 //                tensors' staging words, from which k_finish_message assembles the message)
@@ -617,8 +620,8 @@ __device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint
 }
 
 // --------------------------------------------------------------------------
-// From the candidate lists to the message in one launch (k_emit_all), for calls of up to kEmitAllChunks chunks.
-// The first 2 T workgroups each select one side of a tensor; the others take up to sixteen chunks
+// From the candidate lists to the message in one launch (k_emit_all), for calls of up to kEmitAllChunks chunks
+// in up to kEmitAllTensors tensors.  The first 2 T workgroups each select one side of a tensor; the others take up to sixteen chunks
 // each, a wavefront per chunk, and go through k_apply's work and the message's words.  They do not end between these steps but wait
 // for what they need of one another's results, which go through memory as words that carry the call's number
 // (StepFlow): every wait is for such a word to carry it.  A launch costs 2 us from the last workgroup of the one before
@@ -626,10 +629,14 @@ __device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint
 // Whole steps in us, threshold, apply and emit as three launches / in one: 328,000 entries in four tensors 40.9 / 36.6,
 // one tensor of 2^20 35.2 / 31.8, 24 ragged tensors of 12e6 65.8 / 61.5, ResNet-50 shape (3243 chunks) at p = 0.001 83.3
 // / 82.6, at p = 0.01, where the chunks of other tensors are done while the longest list is selected, 103.0 / 96.1.
-// Beyond 4096 chunks the workgroups do not all find room at once and wait for each other's instructions: 8060 chunks
-// 162 / 171.
+// Beyond that the workgroups that wait get into the others' way: one tensor of 3500 chunks at p = 1e-4 86 / 86, of 3750
+// 90 / 93, eight tensors of 3500 chunks 85 / 84, of 4000 93 / 96, 8060 chunks 162 / 171.  The chip holds 512 workgroups of
+// this size; where sides take nearly all of these places, those with chunks start late: 200 tensors of 1000 chunks 42 / 42, 240
+// 43 / 44, 512 47 / 49, 255 tensors of 300 chunks 30 / 32, 4000 of 4000 entries 157 / 168.  Nor does it pay where a chunk keeps
+// more than kFewKept entries, for the workgroups that wait have only their first 256 candidates of either side at
+// hand, and the residual's stores come last: one tensor of 4.2e6 entries at p = 0.05 57 / 57, 0.07 60 / 63, 0.2 78 / 93.
 // --------------------------------------------------------------------------
-constexpr uint32_t kEmitAllChunks = 4096;
+constexpr uint32_t kEmitAllChunks = 3584, kEmitAllTensors = 200;
 constexpr int kEmitThreads = kThThreads;
 // Calls of up to so many chunks have eight per workgroup, else sixteen: what a workgroup looks at of all lower ones grows
 // with their number (one tensor of 512 chunks, step: four each 39.1 us, eight 38.0, sixteen 37.6; 128 chunks 32.2, 31.8, 32.2).
@@ -1122,6 +1129,134 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
         for_kept([&](const uint2& x) { R[x.y] = __uint_as_float(bits_of_key(chosen ? ~x.x : x.x)) - mu_signed; });
     }
     SBC_TS(0, 8);
+}
+
+// --------------------------------------------------------------------------
+// The message behind k_apply, for calls of up to kScanAllChunks chunks that k_emit_all does not take or has left to
+// the second pass: a wavefront per chunk.  NT threads, at most kScanAllPer chunks each in the scan, which every workgroup
+// repeats: that is cheaper than a launch for it (1.6 us and its own round trips), up to 4096 chunks: 6.4 us
+// on the 3243 chunks of the ResNet-50 shape, 4.9 on 512, 4.3 on 41 (11, 9 and 9 us for codes into staging
+// words and a copy from there into the message); with 8060 chunks, eight per thread, 22 us, where
+// k_tensor_scan and k_emit take 4.8 and 5.9.  Workgroups of 256 threads for few chunks, for the scans over
+// sixteen wavefronts cost more than what they scan there.
+// --------------------------------------------------------------------------
+constexpr int kScanAllPer = 4;
+constexpr uint32_t kScanAllChunks = 1024 * kScanAllPer;
+static_assert(kEmitAllChunks <= kScanAllChunks, "whatever k_emit_all leaves");
+constexpr uint32_t kScanFew = 256 * kScanAllPer;       // calls of up to so many chunks take workgroups of 256 threads
+template <int NT>
+__global__ __launch_bounds__(NT) void k_emit_scan(
+        const uint2* __restrict__ chunk_tensor, const ChunkSummary* __restrict__ sum, const uint32_t* __restrict__ codes,
+        const uint32_t* __restrict__ heads, TensorState* __restrict__ st, unsigned long long* __restrict__ counters, int T, int b, uint32_t n_chunks,
+        uint8_t* __restrict__ msg, uint64_t msg_capacity, ResultBlock* __restrict__ result, ResultBlock* __restrict__ next_result,
+        unsigned long long* __restrict__ host_word, uint32_t seq) {
+    constexpr int NW = NT / 64, PER = kScanAllPer;
+    __shared__ uint32_t scratch[4][16];
+    constexpr uint32_t W = NT <= 256 ? 1024u : 256u;   // (words of a crowded chunk put together at a time)
+    __shared__ __attribute__((aligned(16))) uint32_t win_sh[NW][kWindow<W>];
+    extern __shared__ uint32_t offs[];                 // every chunk's bit offset in the payload, then the gaps
+    uint32_t* const gaps = offs + n_chunks;
+    constexpr uint32_t kNone = 0x80000000u, kStarts = 0x40000000u;     // (gaps are below 2^26 here)
+    static_assert((uint64_t)kScanAllChunks * kChunk <= 1u << 26, "positions and offsets in 32 bits");
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t c = blockIdx.x * (uint32_t)NW + (uint32_t)wave;
+    const uint32_t per = (n_chunks + NT - 1u) / NT, c0 = (uint32_t)tid * per;
+    const uint32_t err_in = result->err;
+    ChunkSummary s[PER], own = make_uint2(0u, 0u);
+    uint2 ct = make_uint2(0u, 0u);
+    if (c < n_chunks) { own = sum[c]; ct = chunk_tensor[c]; }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        s[j] = make_uint2(0u, 0u);
+        if ((uint32_t)j < per && c0 + (uint32_t)j < n_chunks) s[j] = sum[c0 + (uint32_t)j];
+    }
+    if (err_in & kErrStops) {                          // uniform: tensors have to be redone, or the call fails
+        if (blockIdx.x == 0 && tid == 0) publish(host_word, seq, err_in, 0ull);
+        return;
+    }
+    const uint4 mine = load_codes(codes, c, own);
+    const float mu_signed = st[ct.x].mu_signed;
+    const uint32_t nnz = st[ct.x].nnz;
+    // what precedes the thread's chunks: the end of the last kept entry, or the start of the tensor (positions in
+    // the call-wide numbering of chunks)
+    uint32_t end = 0u, all;                            // (all: first the scan's unused total, then the bits of all chunks)
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t base = (c0 + (uint32_t)j) * (uint32_t)kChunk;
+        if (sum_starts(s[j])) end = base;
+        if (sum_any(s[j])) end = base + sum_end(s[j]);
+    }
+    end = scan_block<NW, true>(end, all, scratch[0]);
+    uint32_t gap[PER], len[PER], bits = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t base = (c0 + (uint32_t)j) * (uint32_t)kChunk;
+        if (sum_starts(s[j])) end = base;
+        gap[j] = base + sum_first(s[j]) - end;
+        len[j] = sum_any(s[j]) ? golomb_len(gap[j], b) + sum_inner(s[j]) : 0u;
+        bits += len[j];
+        if (sum_any(s[j])) end = base + sum_end(s[j]);
+    }
+    uint32_t at = scan_block<NW, false>(bits, all, scratch[1]);
+    uint32_t payload_words = (all + 31u) >> 5, shift = 0u;     // shift: of the tensor the thread's first chunk belongs to,
+                                                               // from the bits of all chunks one after another
+    if (T > 1) {                                       // uniform: every tensor starts on a word
+        // where, among those bits, the tensor that a chunk belongs to starts
+        uint32_t origin = 0u, last_origin, x = at;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (sum_starts(s[j])) origin = x;
+            x += len[j];
+        }
+        origin = scan_block<NW, true>(origin, last_origin, scratch[2]);
+        // words of the tensors before that one (a tensor's are counted where the next one starts)
+        uint32_t words = 0u, from = origin;
+        x = at;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (sum_starts(s[j])) { words += (x - from + 31u) >> 5; from = x; }
+            x += len[j];
+        }
+        const uint32_t before = scan_block<NW, false>(words, payload_words, scratch[3]);
+        payload_words += (all - last_origin + 31u) >> 5;
+        shift = 32u * before - origin;
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t cj = c0 + (uint32_t)j;
+        if ((uint32_t)j < per && cj < n_chunks) {
+            if (sum_starts(s[j])) shift = ((at + shift + 31u) & ~31u) - at;    // (a word boundary behind the tensor before)
+            offs[cj] = at + shift;
+            gaps[cj] = (sum_any(s[j]) ? gap[j] : kNone) | (sum_starts(s[j]) ? kStarts : 0u);
+            at += len[j];
+        }
+    }
+    uint32_t err = err_in;
+    if (32ull + 24ull * (unsigned)T + 4ull * payload_words > msg_capacity) err |= kErrInternal;      // (cannot happen)
+    if (blockIdx.x == 0 && tid == 0) {
+        if (err & kErrInternal) publish(host_word, seq, err, 0ull);
+        else finish_call(msg, T, b, payload_words, err, next_result, host_word, seq);
+    }
+    if (err & kErrInternal) return;                    // uniform
+    stage_codes(win_sh[wave], mine);
+    __syncthreads();
+    if (c >= n_chunks) return;
+    const uint32_t g = (uint32_t)__builtin_amdgcn_readfirstlane((int)gaps[c]), o = (uint32_t)__builtin_amdgcn_readfirstlane((int)offs[c]);
+    ChunkStream cs;
+    cs.c = c; cs.gap = g & (kStarts - 1u); cs.inner = sum_inner(own); cs.any = !(g & kNone); cs.raw = sum_raw(own); cs.at = o;
+    if ((tid & 63) == 0 && (c + 1u == n_chunks || (gaps[c + 1u] & kStarts))) {
+        const uint32_t tensor = offs[ct.y];
+        finish_tensor(msg, st, counters, ct.x, mu_signed, nnz, (unsigned long long)(o - tensor) + (cs.any ? golomb_len(cs.gap, b) + cs.inner : 0u), tensor >> 5);
+    }
+    write_chunk<W>(cs, b, win_sh[wave], sum, codes, heads, reinterpret_cast<uint32_t*>(msg + 32 + 24ull * (unsigned)T),
+                [&](uint32_t f, uint32_t& gap_f, bool& any_f) {
+                    if (f >= n_chunks) return false;
+                    const uint32_t gf = gaps[f];
+                    gap_f = gf & (kStarts - 1u);
+                    any_f = !(gf & kNone);
+                    return !(gf & kStarts);
+                });
 }
 
 // --------------------------------------------------------------------------

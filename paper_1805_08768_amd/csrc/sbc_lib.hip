@@ -90,9 +90,9 @@ struct sbc_ctx {
     unsigned long long* d_flow = nullptr; // what the workgroups of k_emit_all leave for one another (see flow())
     uint32_t flow_tag = 0;                // number of its latest launch, 1 to 0xFFFF
     uint32_t flow_sides = 0, flow_taken = 0;      // workgroups of its launches that select sides / take chunks
-    size_t flow_words() const { return kGroupWords * (size_t)kEmitGroups + 2u * kSideWords * (size_t)std::min<int64_t>(max_tensors, kEmitAllChunks) + 1u; }
+    size_t flow_words() const { return kGroupWords * (size_t)kEmitGroups + 2u * kSideWords * (size_t)std::min<int64_t>(max_tensors, kEmitAllTensors) + 1u; }
     StepFlow flow() const {
-        const size_t T = (size_t)std::min<int64_t>(max_tensors, kEmitAllChunks);
+        const size_t T = (size_t)std::min<int64_t>(max_tensors, kEmitAllTensors);
         StepFlow f;
         f.groups = d_flow;
         f.sides = f.groups + kGroupWords * (size_t)kEmitGroups;
@@ -213,7 +213,8 @@ struct sbc_ctx {
         int T = 0, b = 0, slot = 0, force_exact = 0, carry = 0;
         double p = 0.0;
         bool slot_is_new = false, use_history = false, sampled = false, all_inline = false, sweeps = false;
-        bool left = false;            // k_emit_all has not applied every tensor that it has selected
+        bool in_one = false;          // k_emit_all completes the step
+        bool left = false;            // ... and has not applied every tensor that it has selected
         bool wait_on_event = false;   // begin/end form: the wait ends with this step, not with the stream
         bool timed[kNumStages] = {};
         ResultBlock* res_now = nullptr;
@@ -360,8 +361,7 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
         // (c->d_order: see compress_begin)
         const uint32_t* const order = T > kComputeUnits / 2 ? c->d_order : nullptr;
         const dim3 per_chunk((P.n_chunks + kEncWaves - 1u) / kEncWaves), block(kEncThreads);
-        const bool in_one = !c->fused_step && P.n_chunks <= kEmitAllChunks;
-        if (in_one && pass == 0) {
+        if (P.in_one && pass == 0) {
             // the rest of the step in one launch
             if (++c->flow_tag > kTagMask) {
                 // the numbers start over: none of the words that launches have left may carry one of them
@@ -390,12 +390,24 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
                    c->cand(), c->d_bitmap, c->d_wide_state, c->d_wide_hist, c->d_wide_acc, pass, sweeps ? 1 : 0, P.carry, P.res_now);
         SBC_LAUNCH(kStApply, profile, apply, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_runs, c->d_state, c->d_state,
                    c->cand(), c->cand_entries, c->d_bitmap, c->d_sum, c->d_head, b, P.left ? kPassAll : pass, P.n_chunks, P.res_now);
-        const int scan_pass = in_one ? kPassAll : pass;
+        if (!c->fused_step && P.n_chunks <= kScanAllChunks) {
+            // (the workgroups that write the codes scan the summaries of all chunks themselves.  Two sizes: few chunks want
+            // many small workgroups, the scan over many wants large ones.)
+            const size_t lds = 2u * sizeof(uint32_t) * P.n_chunks;
+            const auto launch = [&](auto kernel, unsigned threads) {
+                SBC_LAUNCH_LDS(kStEmit, profile, kernel, dim3((P.n_chunks + threads / 64u - 1u) / (threads / 64u)), dim3(threads), lds, c->d_chunk_tensor,
+                               c->d_sum, c->d_bitmap, c->d_head, c->d_state, c->d_counters, T, b, P.n_chunks, P.msg8, (uint64_t)P.msg_capacity,
+                               P.res_now, P.res_next, c->h_result_dev, ++c->result_seq);
+            };
+            if (P.n_chunks <= kScanFew) launch(k_emit_scan<256>, 256u);
+            else launch(k_emit_scan<1024>, 1024u);
+            return;
+        }
         if (P.scan_tiles > 1)
             hipLaunchKernelGGL(k_tile_summary, dim3(T, P.scan_tiles), dim3(kScanThreads), 0, stream, P.d_desc, c->d_state,
-                               c->d_sum, c->d_tile, b, scan_pass);
+                               c->d_sum, c->d_tile, b, pass);
         SBC_LAUNCH(kStTensorScan, profile, k_tensor_scan, dim3(T, P.scan_tiles), dim3(kScanThreads), P.d_desc, c->d_sum,
-                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, scan_pass, P.res_now);
+                   c->d_tile, c->d_gap, c->d_bitoff, c->d_state, b, pass, P.res_now);
         if (!c->fused_step) {
             SBC_LAUNCH(kStEmit, profile, k_emit<true>, per_chunk, block, P.d_desc, c->d_chunk_tensor, c->d_sum, c->d_bitmap, c->d_head,
                        c->d_gap, c->d_bitoff, c->d_state, c->d_counters, T, b, pass, P.n_chunks, c->d_stage, P.msg8, (uint64_t)P.msg_capacity, P.res_now,
@@ -1015,6 +1027,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     P.stream = stream; P.T = T; P.b = b; P.p = p; P.slot = slot; P.slot_is_new = slot_is_new;
     P.force_exact = force_exact; P.use_history = use_history; P.sampled = sampled;
     P.all_inline = all_inline; P.left = false;
+    P.in_one = !c->fused_step && n_chunks <= kEmitAllChunks && T <= (int)kEmitAllTensors && p * (double)kChunk <= (double)kFewKept;
     P.sweeps = c->n_wide > 0 && (c->sweep_always || (use_history ? c->hist_long : c->sweep_sampled));
     for (int st = 0; st < kNumStages; ++st) P.timed[st] = false;
     P.res_now = res_now; P.res_next = res_next; P.d_desc = d_desc; P.msg8 = msg8;
@@ -1095,7 +1108,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
         }
     }
     uint32_t err = result_err_of(*c->h_result);
-    if (!c->fused_step && (err & kErrDeferred)) {
+    if (P.in_one && (err & kErrDeferred)) {
         // k_emit_all has left the step because sides were not being selected yet when its word went out.  They are once
         // it has ended, and what they raise (a filter that fell short, a list that overflowed) stands in the error word
         // only: that word again, behind the kernel.
@@ -1114,7 +1127,7 @@ int sbc_compress_end(sbc_ctx* c, size_t* msg_bytes) {
     c->last_deferred = (err & kErrDeferred) != 0u;
     if ((err & (kErrPrefilter | kErrDeferred)) && !(err & (kErrInternal | kErrNonFinite | kErrOverflow))) {
         c->last_used_exact_path = (err & kErrPrefilter) != 0u;
-        P.left = !c->fused_step && (err & kErrDeferred) != 0u;
+        P.left = P.in_one && (err & kErrDeferred) != 0u;
         hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(res_now),
                            (uint64_t)(sizeof(ResultBlock) / 4));
         if (err & kErrPrefilter) {

@@ -75,7 +75,7 @@ int main(int argc, char** argv) {
         std::fclose(f);
     }
     CHECK(model.size() >= 100);
-    CHECK(stub_known_senders() == 5);                  // k_emit_all for few and for many chunks, k_emit, k_finish_message, k_publish
+    CHECK(stub_known_senders() == 7);                  // k_emit_all and k_emit_scan for few and for many chunks, k_emit, k_finish_message, k_publish
 
     // ---- scalar helpers ----
     const double bad_p[] = {0.0, 1.0, -1.0, 2.0, 0.0 / 1.0 - 0.0, 1e-12};
@@ -413,6 +413,31 @@ int main(int argc, char** argv) {
         }
         sbc_destroy(c); c = nullptr;
         CHECK(stub_live_blocks() == 0);
+    }
+
+    // ---- which kernels complete a step: one launch for few tensors, chunks and kept entries per chunk, three up to 4096
+    // chunks, four beyond; a second pass never waits ----
+    {
+        struct Case { std::vector<int64_t> sizes; double p; int all, scan, emit; };
+        const Case cases[] = {
+            {{3584 * 8192}, 0.001, 1, 0, 0}, {{3584 * 8192 + 1}, 0.001, 0, 1, 0}, {{4096 * 8192}, 0.001, 0, 1, 0}, {{4096 * 8192 + 1}, 0.001, 0, 0, 1},
+            {std::vector<int64_t>(200, 100), 0.01, 1, 0, 0}, {std::vector<int64_t>(201, 100), 0.01, 0, 1, 0}, {std::vector<int64_t>(4097, 1), 0.01, 0, 0, 1},
+            {{1000000}, 0.0625, 1, 0, 0}, {{1000000}, 0.0626, 0, 1, 0}, {{1000000}, 0.9, 0, 1, 0}, {{1}, 1e-6, 1, 0, 0}};
+        for (const Case& k : cases) {
+            const Buffers s = fake_buffers(k.sizes);
+            const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), k.p);
+            CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            for (int second : {0, 1}) {
+                const long from = stub_launches();
+                const char* const sender = k.all ? "k_emit_all" : k.scan ? "k_emit_scan" : "6k_emit";
+                if (second) stub_next_result_bits(sender, 8);
+                CHECK(compress(c, s, k.p, nb, &nbytes) == SBC_OK);
+                CHECK(stub_launched("10k_emit_all", from) == k.all && stub_launched("6k_emit", from) == k.emit * (1 + second));
+                CHECK(stub_launched("11k_emit_scan", from) == k.scan + second * (1 - k.emit));
+                CHECK(stub_launched("11k_threshold", from) == (k.all ? 0 : 1) + second && stub_launched("7k_apply", from) == (k.all ? 0 : 1) + second);
+            }
+            sbc_destroy(c); c = nullptr;
+        }
     }
 
     // ---- scratch memory that a context's creation leaves clean: a first call clears no words that only earlier launches

@@ -30,7 +30,7 @@ static int g_n_names = 0;
 // in pinned memory and the call's number.
 struct Sender { const char* name; int word, seq; const void* host[2]; };
 static Sender g_senders[] = {
-    {"10k_emit_all", 13, 14, {}}, {"6k_emitILb1E", 18, 19, {}}, {"16k_finish_message", 11, 12, {}}, {"9k_publish", 0, 2, {}}};
+    {"10k_emit_all", 13, 14, {}}, {"11k_emit_scan", 13, 14, {}}, {"6k_emitILb1E", 18, 19, {}}, {"16k_finish_message", 11, 12, {}}, {"9k_publish", 0, 2, {}}};
 
 extern "C" long stub_launches() { return g_launches; }
 extern "C" unsigned stub_grid(long launch) { return g_grids[launch % 64]; }

@@ -53,7 +53,7 @@ def test_words_that_many_workgroups_share(p, where):
 
 
 @pytest.mark.parametrize("sizes,p,sampled", [([2000003], 0.01, False), ([60000] * 30 + [400000], 0.02, False), ([CHUNK * 300 + 77, 5, 900000], 0.001, False),
-                                             ([100] * 700, 0.1, False), ([2000003, 900000], 0.01, True)])
+                                             ([100] * 200, 0.05, False), ([2000003, 900000], 0.01, True)])
 def test_steps_left_to_the_second_pass(sizes, p, sampled):
     """After a single look for sides that nobody has started to select: whatever part of the step has been done by then is
     done again."""
@@ -74,10 +74,10 @@ def test_steps_left_to_the_second_pass(sizes, p, sampled):
 
 @pytest.mark.parametrize("compact", [False, True])
 def test_steps_left_whose_lists_cannot_be_used(compact):
-    """600 sides on 512 places, so that some start after others have looked for them.  Data that shrinks by a thousand with
+    """400 sides, of which some are being selected only after others have looked for them.  Data that shrinks by a thousand with
     the residual cleared (carried keys let nothing pass, or too little) and that grows by a thousand (everything
     passes: more than a compact context's lists hold), in steps left after a single look."""
-    sizes, p = [12000] * 299 + [500000], 0.02
+    sizes, p = [12000] * 199 + [500000], 0.02
     scales = [1.0, 1.0, 1e-3, 1e-3, 1e-3, 1.0, 1.0, 1.0, 1e-3]
     routes = []
     with DeviceRun(sizes, compact=compact) as run:
@@ -96,6 +96,21 @@ def test_steps_left_whose_lists_cannot_be_used(compact):
     histogram = [bool(x & sbc.SBC_ROUTE_HISTOGRAM) for x in routes]
     assert any(left) and histogram[2] and histogram[8]
     assert not compact or histogram[5]
+
+
+@pytest.mark.parametrize("sizes,p", [([64] * 201, 0.05), ([CHUNK * 820 - 5] + [3, 9000] * 101, 0.002), ([CHUNK * 1100 + 1] + [5] * 200, 1.5e-6), ([CHUNK * 2 - 1] * 201, 0.3),
+                                     ([700, CHUNK * 40, 5], 0.0625), ([700, CHUNK * 40, 5], 0.0627), ([CHUNK * 1030 + 9, 3], 0.07)])
+def test_calls_beyond_one_launch(sizes, p):
+    """More tensors or more kept entries per chunk than the launch that completes a step takes (and the most it takes): selection,
+    residual and message in launches of their own, up to 1024 chunks and beyond, with words that many chunks share and with
+    chunks whose codes do not fit their words; then data that the carried keys let nothing of through."""
+    with DeviceRun(sizes) as run:
+        _rounds(run, sizes, p, 3)
+        for x in run.R:
+            x.zero_()
+        check_round(run, [synth.gaussian_update(n, tensor=i) * np.float32(1e-3) for i, n in enumerate(sizes)],
+                    [np.zeros(n, np.float32) for n in sizes], p, check_decode=False)
+        assert p in (1.5e-6, 0.3) or sbc.sbc_last_route(run.ctx) & sbc.SBC_ROUTE_HISTOGRAM
 
 
 def test_launch_numbers_start_over():
