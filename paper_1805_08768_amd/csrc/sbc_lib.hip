@@ -762,30 +762,34 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
 }
 
 // What a step's streaming pass sends past the last-level cache (no result depends on it): update and residual,
-// for whatever runs until the next step, another client's step or a training step, displaces the residual, and
+// for whatever runs until the next step, other clients' steps or a training step, displaces the residual, and
 // where that has written, the cache's dirty lines leave it in the middle of this pass.  Only where the residual is read
 // again before that can happen is it kept: by the histogram route of this very call, or by the next step if that follows
-// at once, that is, if since the step before this one no more than this step's bytes and one and a half
-// times the cache's can have moved at 6 TB/s (ResNet-50 shape: 118 us, of which such a step itself
-// takes 88 to 100).  A residual larger than the cache always goes past it, and so does the update of such a step, which
-// nobody reads again (66e6 entries, one client back to back: 170 us with it in the cache, 128 without), unless
-// both fit it.  Kernel times in us, residual kept / sent past:
-//     entries   one client, back to back   three clients in turn   after 0.6 GiB read   ... read and written
-//     25.6e6           56 / 58                   60 / 59               60 / 59               65 / 61
-//     45e6             90 / 98                  110 / 98               98 / 98              111 / 100
-//     66e6            128 / 139                 168 / 139             136 / 141             163 / 142
-//     100e6           249 / 213                 266 / 211             201 / 214             249 / 220
-// Steps of up to 160 MiB (12 bytes per entry pass through) leave it all in the cache, where a few clients in turn still
-// find part of it.  Whole steps in us, kept / sent past: 12e6 entries, three clients in turn 62.2 / 64.4, eight 70.0 / 64.0;
-// 14e6, seven 69.9 / 63.5; 16e6, six 75.6 / 68.4; 20e6, three 98.6 / 88.0, five 89.5 / 79.9; 22e6, four 98.5 / 87.2.
+// at once.  That is taken from the time since the step before this one: what such a step takes by itself (12 bytes per
+// entry at 6 TB/s, 40 us, 35 us per million kept entries) and 100 us, about the time of one other client's step
+// and less than two of them take.  A residual larger than the cache always goes past it, and so does the update of
+// a step that does not fit it as a whole, for nobody reads that again.
+// Steps of 14e6 to 66e6 entries at p = 0.001, whole ones of one client back to back and of several in turn, and the pass alone
+// (us) behind other traffic, residual kept / sent past (25.6e6: the ResNet-50 shape, else one tensor; up to 22e6 the
+// update kept as well):
+//     entries   one client    two in turn    three         five         0.6 GiB read   0.3 GiB read and written
+//     14e6       66.7 / 74.5   64.8 / 71.8   70.4 / 71.6   76.6 / 70.6    31.4 / 35.0    45.4 / 34.8
+//     20e6       86.5 / 90.4   85.3 / 90.9   96.2 / 92.3   95.3 / 91.9    44.2 / 47.8    62.1 / 46.6
+//     25.6e6     82.5 / 84.3   81.9 / 85.0   90.3 / 85.0   97.2 / 85.2    51.6 / 55.6    65.5 / 55.3
+//     45e6      152   / 154   170   / 153   174   / 153                   87.7 / 90.4   108.0 / 91.0
+//     66e6      203   / 205   222   / 200   217   / 200                  123.2 / 126.5  146.8 / 128.7
+//     100e6     320   / 276   319   / 273   313   / 273                  180.3 / 186.7  218.0 / 188.8
+// Steps of up to 160 MiB leave it all in the cache, where a few clients in turn still find part of it (12e6 entries: one
+// client 61.7 / 63.5, three 62.5 / 65.0, eight 68.6 / 63.7).
 constexpr uint64_t kCacheBytes = 256ull << 20, kKeptBytes = 160ull << 20;
 constexpr uint64_t kPairsFrom = 24000000;  // entries from which the streaming pass has two workgroups to a compute unit (see kRun)
-static int accumulate_past_cache(sbc_ctx* c, uint64_t total, bool force_exact) {
+static int accumulate_past_cache(sbc_ctx* c, uint64_t total, double p, bool force_exact) {
     const auto now = std::chrono::steady_clock::now();
     const std::chrono::duration<double> since = now - c->last_begin;
     c->last_begin = now;
     if (total * 12ull <= kKeptBytes) return kPastNothing;
-    const bool again = force_exact || (c->last_T > 0 && since.count() * 6e12 <= (double)(total * 12ull + kCacheBytes + kCacheBytes / 2));
+    const double alone = (double)total * 12.0 / 6e12 + 40e-6 + p * (double)total * 35e-12;
+    const bool again = force_exact || (c->last_T > 0 && since.count() <= alone + 100e-6);
     if (again && total * 12ull <= kCacheBytes) return kPastNothing;
     return again && total * 4ull <= kCacheBytes ? kPastUpdate : kPastAll;
 }
@@ -1047,7 +1051,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     const int carry = c->carry_keys && !sampled && !force_exact ? 1 : 0;
     P.carry = carry;
     if (!c->fused_step) {
-        const int past = accumulate_past_cache(c, total, force_exact != 0);
+        const int past = accumulate_past_cache(c, total, p, force_exact != 0);
         const size_t room = total >= kPairsFrom ? kStreamRoom : 0;
         if (past == kPastAll) {
             SBC_LAUNCH_LDS(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), room, d_desc,
