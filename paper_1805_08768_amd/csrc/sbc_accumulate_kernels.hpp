@@ -380,8 +380,7 @@ __device__ __forceinline__ void append_candidates(const uint32_t (&key)[PER], ui
 // 4 KB requests from every one of 256 compute units keep more of memory's pages open than it has.  Whole steps in us, one
 // tensor: 1.5e9 entries 3505, two at a time 3255, with runs of four as well 3050 (6.4 TB/s in this kernel; runs of two
 // 3214, of eight 3093, of sixteen 3140, a contiguous eighth per compute-unit group 3112, one at a time 3758; four
-// at a time with runs of eight 3320), 400e6 941 / 848, 100e6 258 / 246, 45e6 150.8 / 149.3, 30e6 109.5 / 109.4, 23e6
-// 89.8 / 90.8; LSTM shape 162 / 156, ResNet-50 shape at p = 0.01 97.7 / 95.9.
+// at a time with runs of eight 3320), 400e6 941 / 848, 100e6 258 / 246, LSTM shape 162 / 156; smaller ones beside kPairsFrom.
 constexpr uint32_t kRun = 4, kComputeUnitGroups = 8;
 constexpr size_t kStreamRoom = 23552;                     // 55 KB in all: two to a compute unit, and room for another kernel's
 __device__ __forceinline__ uint32_t chunk_of_workgroup() {

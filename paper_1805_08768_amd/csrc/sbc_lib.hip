@@ -782,7 +782,12 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
 // Steps of up to 160 MiB leave it all in the cache, where a few clients in turn still find part of it (12e6 entries: one
 // client 61.7 / 63.5, three 62.5 / 65.0, eight 68.6 / 63.7).
 constexpr uint64_t kCacheBytes = 256ull << 20, kKeptBytes = 160ull << 20;
-constexpr uint64_t kPairsFrom = 24000000;  // entries from which the streaming pass has two workgroups to a compute unit (see kRun)
+// Entries from which the streaming pass has two workgroups to a compute unit instead of four (see kRun): where the residual
+// goes past the cache, and where it is kept, for loads that hit the cache want more of them in flight.  Whole steps at p =
+// 0.001 in us, four / two: sent past 24e6 106.2 / 104.9, 30e6 124.9 / 124.4, 45e6 152.1 / 149.0, 66e6 196 / 192; kept
+// ResNet-50 shape 82.7 / 84.3, 30e6 120.6 / 125.4 (in twenty tensors 90.1 / 92.2), 45e6 151.3 / 150.3 (117.7 / 120.1), 55e6
+// 169.9 / 168.5, 66e6 201 / 198.
+constexpr uint64_t kPairsFrom = 24000000, kPairsKeptFrom = 55000000;
 static int accumulate_past_cache(sbc_ctx* c, uint64_t total, double p, bool force_exact) {
     const auto now = std::chrono::steady_clock::now();
     const std::chrono::duration<double> since = now - c->last_begin;
@@ -1052,7 +1057,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     P.carry = carry;
     if (!c->fused_step) {
         const int past = accumulate_past_cache(c, total, p, force_exact != 0);
-        const size_t room = total >= kPairsFrom ? kStreamRoom : 0;
+        const size_t room = total >= (past == kPastAll ? kPairsFrom : kPairsKeptFrom) ? kStreamRoom : 0;
         if (past == kPastAll) {
             SBC_LAUNCH_LDS(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), room, d_desc,
                        c->d_chunk_tensor, c->d_state, c->d_counters, c->cand(), c->d_runs, res_now);

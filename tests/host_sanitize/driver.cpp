@@ -30,6 +30,7 @@ extern "C" int stub_stream_waits();
 extern "C" int stub_event_waits();
 extern "C" int stub_launched(const char* name, long from);
 extern "C" unsigned stub_grid_of(const char* name, long from);
+extern "C" size_t stub_lds_of(const char* name, long from);
 
 #define CHECK(cond)                                                                     \
     do {                                                                                \
@@ -282,6 +283,31 @@ int main(int argc, char** argv) {
         CHECK(kept > 0);
         for (int call = 0; call < 20; ++call) CHECK(past(600));
         sbc_destroy(c); c = nullptr;
+    }
+
+    // ---- how many workgroups of the streaming pass share a compute unit (LDS that it asks for and does not use) ----
+    {
+        struct Case { int64_t n; bool kept, sent; };
+        const Case cases[] = {{23000000, false, false}, {24000000, false, true}, {54000000, false, true}, {55000000, true, true}, {100000000, true, true}};
+        for (const Case& k : cases) {
+            const Buffers s = fake_buffers({k.n});
+            const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), p);
+            CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            const auto pairs = [&]() {
+                const long from = stub_launches();
+                CHECK(compress(c, s, p, nb, &nbytes) == SBC_OK);
+                const size_t lds = stub_lds_of("k_accumulate_filter", from);
+                CHECK(lds == 0 || lds == 23552);
+                return lds != 0;
+            };
+            pairs();
+            int differ = 0;                            // (a busy machine may come late for some of them)
+            for (int call = 0; call < 100; ++call) differ += pairs() != k.kept;
+            CHECK(differ < 100);
+            usleep(50000);
+            CHECK(pairs() == k.sent);
+            sbc_destroy(c); c = nullptr;
+        }
     }
 
     // ---- more streams of two tiles than the tiled decoder has places, and one of 19 tiles: that one has a

@@ -14,6 +14,7 @@
 
 static long g_launches = 0;
 static unsigned g_grids[64];           // workgroups (x) of the latest launches
+static size_t g_lds[64];               // their dynamic LDS
 static const void* g_kernels[64];      // and their kernels
 static long g_live_blocks = 0;
 static long g_fail_alloc_at = -1;      // the n-th allocation from now fails (tests the clean-up path)
@@ -48,6 +49,13 @@ extern "C" unsigned stub_grid_of(const char* name, long from) {
     for (long i = from; i < g_launches; ++i)
         for (int k = 0; k < g_n_names; ++k)
             if (g_kernels[i % 64] == g_names[k].host && std::strstr(g_names[k].name, name)) return g_grids[i % 64];
+    return 0;
+}
+// ... and its dynamic LDS.
+extern "C" size_t stub_lds_of(const char* name, long from) {
+    for (long i = from; i < g_launches; ++i)
+        for (int k = 0; k < g_n_names; ++k)
+            if (g_kernels[i % 64] == g_names[k].host && std::strstr(g_names[k].name, name)) return g_lds[i % 64];
     return 0;
 }
 // How many of the launches from number `from` on (of the latest 64) were of kernels with that name.
@@ -128,7 +136,7 @@ hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t, unsigned) {
 }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
 
-hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t shmem, hipStream_t) {
     // (as the runtime does: at most 2^32 - 1 work items in a dimension)
     if (grid.x == 0 || grid.y == 0 || grid.z == 0 || block.x == 0 || block.x * block.y * block.z > 1024 ||
         (uint64_t)grid.x * block.x > 0xFFFFFFFFull || grid.y > 65535u || grid.z > 65535u)
@@ -142,6 +150,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, si
                                                       (uint64_t)bits << 40;
         }
     g_grids[g_launches % 64] = grid.x;
+    g_lds[g_launches % 64] = shmem;
     g_kernels[g_launches++ % 64] = f;
     return hipSuccess;
 }
