@@ -815,7 +815,8 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
     const uint32_t wave = uniform((uint32_t)tid >> 6);
     const int T = sizes.T, b = sizes.b;
     const uint32_t n_chunks = sizes.n_chunks, tag = flow.tag, n_sides = 2u * (uint32_t)T;
-    const uint32_t err_in = result->err;               // (of the kernels before this one)
+    // (of the kernels before this one; sides of this one may have raised theirs there already)
+    const uint32_t err_in = __hip_atomic_load(&result->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     SBC_TS(0, 0);
     if (blockIdx.x < n_sides) {                        // uniform
         Select::select(sh.select, blockIdx.x, desc, order, st, counters, cand, chunks.codes, sweeps.ws, sweeps.hist, sweeps.acc, 0, sweeps.on,
