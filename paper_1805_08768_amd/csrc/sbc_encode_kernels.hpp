@@ -1074,6 +1074,7 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
         if (lane < (int)NW) lower = wave_sh[lane];
     }
     if (wave == 0u) {
+        wave_lds_fence();                              // (flags_sh, which lanes of this wavefront have raised)
         const Stretch all = a > 64u ? stretch_of_lane(join_lanes<true>(lower), NW - 1u) : stretch_of_lane(lower, 63u);
         // (positions + 1 here and there)
         const uint32_t open_gap = open_first + a * CPW * (uint32_t)kChunk - end_in;
