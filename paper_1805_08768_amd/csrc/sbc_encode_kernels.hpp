@@ -1,6 +1,6 @@
 // The rest of the client step once the thresholds are known, a wavefront per chunk of 8192 entries:
 //   k_emit_all : calls of few tensors and up to 3584 chunks, everything behind the streaming pass in one launch: the sides'
-//                selection (k_threshold_side), Alg. 2's side decision, Alg. 1's residual line and Alg. 3, the message
+//                selection (select_side), Alg. 2's side decision, Alg. 1's residual line and Alg. 3, the message
 //   k_apply    : the same steps as launches of their own, for calls of more chunks or tensors, for the second pass and behind
 //                the streaming kernel that finishes tensors: side decision, residual line and Alg. 3 within the
 //                chunk, from the chunk's run of candidates: the codes of all its kept entries but the first, whose
@@ -793,7 +793,7 @@ constexpr uint32_t kFlowLooks = 4096, kFlowMostLooks = 1u << 22;
 // other launches of this kernel among them, some may not have started: a workgroup waits for those a while
 // and then leaves the call to the kernels of the second pass (kErrDeferred).
 // --------------------------------------------------------------------------
-template <uint32_t CPW, typename Select>
+template <uint32_t CPW>
 __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
         const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
         unsigned long long* __restrict__ counters, const CandPtr cand, const StepSweeps sweeps, const StepChunks chunks, const StepFlow flow,
@@ -819,8 +819,8 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
     const uint32_t err_in = __hip_atomic_load(&result->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     SBC_TS(0, 0);
     if (blockIdx.x < n_sides) {                        // uniform
-        Select::select(sh.select, blockIdx.x, desc, order, st, counters, cand, chunks.codes, sweeps.ws, sweeps.hist, sweeps.acc, 0, sweeps.on,
-                       sizes.carry, result, [&]() { atomicAdd(flow.started, 1u); }, [&](int t, int s, const SideResult& r) {
+        select_side<false>(sh.select, blockIdx.x, desc, order, st, counters, cand, chunks.codes, sweeps.ws, sweeps.hist, sweeps.acc, 0, sweeps.on,
+                           sizes.carry, result, [&]() { atomicAdd(flow.started, 1u); }, [&](int t, int s, const SideResult& r) {
             unsigned long long* const to = flow.sides + ((size_t)t * 2u + (uint32_t)s) * kSideWords;
             const unsigned long long mean = (unsigned long long)__double_as_longlong(r.mean);
             if (r.raise || !r.ok) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // (the error word has them before anybody can see this)

@@ -379,8 +379,8 @@ void launch_selection_and_encode(sbc_ctx* c, int pass) {
                            P.res_next, c->h_result_dev, ++c->result_seq);
                 c->flow_sides += 2u * (unsigned)T; c->flow_taken += takers;
             };
-            if (P.n_chunks <= kEmitFew) launch(k_emit_all<8u, k_threshold_side<false>>, 8u);
-            else launch(k_emit_all<16u, k_threshold_side<false>>, 16u);
+            if (P.n_chunks <= kEmitFew) launch(k_emit_all<8u>, 8u);
+            else launch(k_emit_all<16u>, 16u);
             return;
         }
         const bool pairs = pass != 0 && c->fused_step;     // (of the tensors that are left, some may have lists in pairs)

@@ -292,10 +292,8 @@ struct SideResult {
     uint32_t tau, itau, kc, raise;
     double mean;
 };
-template <bool PAIRS>
-struct k_threshold_side {
-template <typename Running, typename Done>
-static __device__ __forceinline__ void select(ThresholdShared& sh, const uint32_t item,
+template <bool PAIRS, typename Running, typename Done>
+__device__ __forceinline__ void select_side(ThresholdShared& sh, const uint32_t item,
         const TensorDesc* __restrict__ desc, const uint32_t* __restrict__ order, TensorState* __restrict__ st,
         const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
         uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int sweeps, int carry, ResultBlock* __restrict__ result,
@@ -672,7 +670,6 @@ static __device__ __forceinline__ void select(ThresholdShared& sh, const uint32_
     done(t, s, SideResult{true, tau, itau, kc, raise, mean});
     SBC_TS(1, 7);
 }
-};
 
 template <bool PAIRS>
 __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
@@ -680,8 +677,8 @@ __global__ __launch_bounds__(kThThreads, 8) void k_threshold(
         const unsigned long long* __restrict__ counters, const CandPtr cand, uint32_t* __restrict__ bitmap, const WideState* __restrict__ ws,
         uint32_t* __restrict__ whist, const long long* __restrict__ wacc, int pass, int sweeps, int carry, ResultBlock* __restrict__ result) {
     __shared__ __attribute__((aligned(16))) ThresholdShared sh;
-    k_threshold_side<PAIRS>::select(sh, blockIdx.x, desc, order, st, counters, cand, bitmap, ws, whist, wacc, pass, sweeps, carry, result,
-                                    []() {}, [](int, int, const SideResult&) {});
+    select_side<PAIRS>(sh, blockIdx.x, desc, order, st, counters, cand, bitmap, ws, whist, wacc, pass, sweeps, carry, result,
+                       []() {}, [](int, int, const SideResult&) {});
 }
 
 // --------------------------------------------------------------------------
