@@ -321,8 +321,9 @@ int sbc_profile_enable(sbc_ctx* ctx, int level);
 int sbc_profile_level(sbc_ctx* ctx, int level);
 
 /* Accumulated time of stage `stage` (0 .. n-1 in launch order; SBC_EINVAL past the end):
- * *name gets a static string (the kernel's name), *total_ms the summed duration over
- * *calls bracketed launches.  Out pointers are host memory and may be NULL. */
+ * *name gets a static string (the kernel's name, that of the latest step where it depends on the
+ * call: k_emit_all also does the work of k_threshold and k_apply, which then have no launches),
+ * *total_ms the summed duration over *calls bracketed launches.  Out pointers are host memory and may be NULL. */
 int sbc_profile_read(sbc_ctx* ctx, int stage, const char** name, double* total_ms, int64_t* calls);
 
 /* Measurement support: enqueues a plain device-to-device streaming copy kernel of `bytes`

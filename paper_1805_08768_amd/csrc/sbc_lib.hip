@@ -203,6 +203,7 @@ struct sbc_ctx {
     hipEvent_t ev[2 * kNumStages] = {};
     bool ev_ok = false;
     hipEvent_t ev_result = nullptr;       // recorded behind the copy of a client step's result block
+    const char* emit_name = "k_emit";     // the kernel that completed the latest step's message
     double stage_ms[kNumStages] = {};
     int64_t stage_calls[kNumStages] = {};
 
@@ -1037,6 +1038,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     P.force_exact = force_exact; P.use_history = use_history; P.sampled = sampled;
     P.all_inline = all_inline; P.left = false;
     P.in_one = !c->fused_step && n_chunks <= kEmitAllChunks && T <= (int)kEmitAllTensors && p * (double)kChunk <= (double)kFewKept;
+    c->emit_name = P.in_one ? "k_emit_all" : !c->fused_step && n_chunks <= kScanAllChunks ? "k_emit_scan" : "k_emit";
     P.sweeps = c->n_wide > 0 && (c->sweep_always || (use_history ? c->hist_long : c->sweep_sampled));
     for (int st = 0; st < kNumStages; ++st) P.timed[st] = false;
     P.res_now = res_now; P.res_next = res_next; P.d_desc = d_desc; P.msg8 = msg8;
@@ -1560,7 +1562,7 @@ int sbc_profile_level(sbc_ctx* c, int level) {
 int sbc_profile_read(sbc_ctx* c, int stage, const char** name, double* total_ms, int64_t* calls) {
     if (!c || stage < 0 || stage >= kNumStages) return SBC_EINVAL;
     // (the streaming pass is one of two kernels, by SBC_OPT_FUSED_STEP)
-    if (name) *name = (stage == kStAccumulate && !c->fused_step) ? "k_accumulate_filter" : kStageNames[stage];
+    if (name) *name = (stage == kStAccumulate && !c->fused_step) ? "k_accumulate_filter" : stage == kStEmit ? c->emit_name : kStageNames[stage];
     if (total_ms) *total_ms = c->stage_ms[stage];
     if (calls) *calls = c->stage_calls[stage];
     return SBC_OK;

@@ -9,6 +9,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <ctime>
 #include <vector>
 
@@ -482,6 +483,13 @@ int main(int argc, char** argv) {
             const Buffers s = fake_buffers(k.sizes);
             const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), k.p);
             CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
+            const auto reported = [&](const char* kernel) {
+                for (int stage = 0; ; ++stage) {
+                    const char* name = nullptr;
+                    if (sbc_profile_read(c, stage, &name, nullptr, nullptr) != SBC_OK) return false;
+                    if (std::strcmp(name, kernel) == 0) return true;
+                }
+            };
             for (int second : {0, 1}) {
                 const long from = stub_launches();
                 const char* const sender = k.all ? "k_emit_all" : k.scan ? "k_emit_scan" : "6k_emit";
@@ -489,6 +497,7 @@ int main(int argc, char** argv) {
                 CHECK(compress(c, s, k.p, nb, &nbytes) == SBC_OK);
                 CHECK(stub_launched("10k_emit_all", from) == k.all && stub_launched("6k_emit", from) == k.emit * (1 + second));
                 CHECK(stub_launched("11k_emit_scan", from) == k.scan + second * (1 - k.emit));
+                CHECK(reported(k.all ? "k_emit_all" : k.scan ? "k_emit_scan" : "k_emit"));
                 CHECK(stub_launched("11k_threshold", from) == (k.all ? 0 : 1) + second && stub_launched("7k_apply", from) == (k.all ? 0 : 1) + second);
             }
             sbc_destroy(c); c = nullptr;
