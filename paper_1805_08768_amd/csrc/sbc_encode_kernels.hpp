@@ -815,8 +815,6 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
     const uint32_t wave = uniform((uint32_t)tid >> 6);
     const int T = sizes.T, b = sizes.b;
     const uint32_t n_chunks = sizes.n_chunks, tag = flow.tag, n_sides = 2u * (uint32_t)T;
-    // (of the kernels before this one; sides of this one may have raised theirs there already)
-    const uint32_t err_in = __hip_atomic_load(&result->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     SBC_TS(0, 0);
     if (blockIdx.x < n_sides) {                        // uniform
         select_side<false>(sh.select, blockIdx.x, desc, order, st, counters, cand, chunks.codes, sweeps.ws, sweeps.hist, sweeps.acc, 0, sweeps.on,
@@ -832,6 +830,9 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
     }
     // (1 us that there is to wait anyway: the sides' workgroups have the memory to themselves for their first loads.  With
     // 500 workgroups that take chunks those took 5.4 us, 1.3 so.)
+    // (of the kernels before this one; sides of this one may have raised theirs there already.  A round trip to memory,
+    // which the sides' workgroups would wait for: 1 us.)
+    const uint32_t err_in = __hip_atomic_load(&result->err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __builtin_amdgcn_s_sleep(32);
     if (tid == 0) { next_item = atomicAdd(flow.started + 1, 1u) - flow.taken; flags_sh = 0u; }
     __syncthreads();
