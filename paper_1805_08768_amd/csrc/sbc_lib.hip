@@ -768,7 +768,8 @@ int sbc_set_option(sbc_ctx* c, int option, int value) {
 // again before that can happen is it kept: by the histogram route of this very call, or by the next step if that follows
 // at once.  That is taken from the time since the step before this one: what such a step takes by itself (12 bytes per
 // entry at 6 TB/s, 40 us, 35 us per million kept entries) and 100 us, about the time of one other client's step
-// and less than two of them take.  A residual larger than the cache always goes past it, and so does the update of
+// and less than two of them take; in the begin/end form, where other clients' steps overlap this one's, 25 us
+// (ResNet-50 shape, three clients in flight 57 us a step, with the residual kept 64).  A residual larger than the cache always goes past it, and so does the update of
 // a step that does not fit it as a whole, for nobody reads that again.
 // Steps of 14e6 to 66e6 entries at p = 0.001, whole ones of one client back to back and of several in turn, and the pass alone
 // (us) behind other traffic, residual kept / sent past (25.6e6: the ResNet-50 shape, else one tensor; up to 22e6 the
@@ -789,13 +790,13 @@ constexpr uint64_t kCacheBytes = 256ull << 20, kKeptBytes = 160ull << 20;
 // ResNet-50 shape 82.7 / 84.3, 30e6 120.6 / 125.4 (in twenty tensors 90.1 / 92.2), 45e6 151.3 / 150.3 (117.7 / 120.1), 55e6
 // 169.9 / 168.5, 66e6 201 / 198.
 constexpr uint64_t kPairsFrom = 24000000, kPairsKeptFrom = 55000000;
-static int accumulate_past_cache(sbc_ctx* c, uint64_t total, double p, bool force_exact) {
+static int accumulate_past_cache(sbc_ctx* c, uint64_t total, double p, bool force_exact, bool overlapped) {
     const auto now = std::chrono::steady_clock::now();
     const std::chrono::duration<double> since = now - c->last_begin;
     c->last_begin = now;
     if (total * 12ull <= kKeptBytes) return kPastNothing;
     const double alone = (double)total * 12.0 / 6e12 + 40e-6 + p * (double)total * 35e-12;
-    const bool again = force_exact || (c->last_T > 0 && since.count() <= alone + 100e-6);
+    const bool again = force_exact || (c->last_T > 0 && since.count() <= alone + (overlapped ? 25e-6 : 100e-6));
     if (again && total * 12ull <= kCacheBytes) return kPastNothing;
     return again && total * 4ull <= kCacheBytes ? kPastUpdate : kPastAll;
 }
@@ -1058,7 +1059,7 @@ static int compress_begin(sbc_ctx* c, void* hip_stream, const float* const* dW, 
     const int carry = c->carry_keys && !sampled && !force_exact ? 1 : 0;
     P.carry = carry;
     if (!c->fused_step) {
-        const int past = accumulate_past_cache(c, total, p, force_exact != 0);
+        const int past = accumulate_past_cache(c, total, p, force_exact != 0, wait_on_event);
         const size_t room = total >= (past == kPastAll ? kPairsFrom : kPairsKeptFrom) ? kStreamRoom : 0;
         if (past == kPastAll) {
             SBC_LAUNCH_LDS(kStAccumulate, true, k_accumulate_filter<kPastAll>, dim3(n_chunks), dim3(kStreamThreads), room, d_desc,

@@ -262,27 +262,35 @@ int main(int argc, char** argv) {
     }
 
     // ---- ... where "at once" is what the step takes by itself and that of one other client: 20e6 entries at p = 0.001
-    // after 150 us, at p = 0.2 after 300, but neither after 600 ----
+    // after 150 us (in the begin/end form, in which several clients' steps overlap, after 90), at p = 0.2 after 300 (220), but
+    // neither after 600 ----
     for (double q : {0.001, 0.2}) {
         const Buffers s = fake_buffers({20000000, 1000});
         const size_t nb = sbc_msg_bound(s.numel.data(), s.T(), q);
         CHECK(sbc_create(&c, 0, s.total(), s.T()) == SBC_OK);
         timespec last = {};
-        const auto past = [&](long after_us) {
+        const auto past = [&](long after_us, bool overlapped) {
             timespec now;
             do clock_gettime(CLOCK_MONOTONIC, &now);
             while ((now.tv_sec - last.tv_sec) * 1000000000l + now.tv_nsec - last.tv_nsec < after_us * 1000l);
             last = now;
             const long from = stub_launches();
-            CHECK(compress(c, s, q, nb, &nbytes) == SBC_OK);
+            if (overlapped)
+                CHECK(sbc_compress_begin(c, nullptr, s.dW.data(), s.R.data(), s.numel.data(), s.T(), q, kMsg, nb) == SBC_OK &&
+                      sbc_compress_end(c, &nbytes) == SBC_OK);
+            else
+                CHECK(compress(c, s, q, nb, &nbytes) == SBC_OK);
             CHECK(stub_launched("k_accumulate_filterILi0E", from) + stub_launched("k_accumulate_filterILi2E", from) == 1);
             return stub_launched("k_accumulate_filterILi2E", from);
         };
-        past(0);
-        int kept = 0;                                  // (a busy machine may come late for some of them)
-        for (int call = 0; call < 100; ++call) kept += !past(q < 0.1 ? 150 : 300);
-        CHECK(kept > 0);
-        for (int call = 0; call < 20; ++call) CHECK(past(600));
+        past(0, false);
+        for (bool overlapped : {false, true}) {
+            int kept = 0;                              // (a busy machine may come late for some of them)
+            for (int call = 0; call < 100; ++call) kept += !past(overlapped ? (q < 0.1 ? 90 : 220) : (q < 0.1 ? 150 : 300), overlapped);
+            CHECK(kept > 0);
+            for (int call = 0; call < 20; ++call) CHECK(past(600, overlapped));
+        }
+        for (int call = 0; call < 20; ++call) CHECK(past(q < 0.1 ? 150 : 300, true));
         sbc_destroy(c); c = nullptr;
     }
 
