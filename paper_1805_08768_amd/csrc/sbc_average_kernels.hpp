@@ -8,7 +8,7 @@
 // The dense result is written once, in full lines, and never cleared or read beforehand.
 // ResNet-50 shape (25.6e6 entries): 32 messages at p = 0.001 took 303 us one after another (a clear and
 // 32 launches of 8.4 us that leave most of the chip idle), now 50 us for the two kernels and the status
-// (49 us per call among others, for the call returns when the status is known); four at p = 0.01 took 109 us, now 72 us.
+// (47 us per call among others, for the call returns when the status is known); four at p = 0.01 took 109 us, now 72 us.
 #pragma once
 
 #include "sbc_decode_kernels.hpp"

@@ -691,7 +691,9 @@ static int create_context(sbc_ctx** out, int device, int64_t max_total_elems, in
             c->ev_ok = true;
         }
         for (hipEvent_t* ev : {&c->ev_result, &c->ev_average})
-            if (ok && hipEventCreateWithFlags(ev, hipEventDisableTiming) != hipSuccess) {
+            // (ev_average orders work of this device alone: the fence for the host and other devices is the caller's
+            // synchronisation, as without an event; with it 32 messages of the ResNet-50 shape take 48.6 us, without 47.0)
+            if (ok && hipEventCreateWithFlags(ev, ev == &c->ev_average ? hipEventDisableTiming | hipEventDisableSystemFence : hipEventDisableTiming) != hipSuccess) {
                 *ev = nullptr;
                 ok = false;
             }
@@ -1491,8 +1493,8 @@ int sbc_decompress_average(sbc_ctx* c, void* hip_stream, const void* const* msgs
         else hipLaunchKernelGGL(k_average_decode<4>, grid, block, 0, stream, list, (uint32_t)M, ids, c->d_avg_tensor, T, b, scale, c->avg_pos, positions, marks, addends, res, res_next);
         // The status is what the decoding kernels find: it goes out between the last of them and the kernel that adds
         // the positions up and stores the result, so that the caller gets on with what it enqueues next while that one
-        // runs (32 messages of the ResNet-50 shape, a call among others: 59.0 us with the status behind it, 48.6 so; 1.6
-        // of them for the event, as the launch's own; recorded behind the launch it takes 3.1).
+        // runs (32 messages of the ResNet-50 shape, a call among others: 59.0 us with the status behind it, 47.0 so; the
+        // event as the launch's own takes nothing, recorded behind the launch 1.3).
         if (m0 + M == n_msgs)
             hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, stream, c->h_result_dec_dev, res, ++c->dec_seq);
         constexpr uint32_t kHalf = kAvgBlock / 2u;

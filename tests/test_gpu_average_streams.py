@@ -165,3 +165,61 @@ def test_decode_recorded_while_an_average_runs():
         sbc.sbc_decode_status(ctx, second)
     finally:
         sbc.sbc_destroy(ctx)
+
+
+def test_what_an_average_has_stored_is_there_for_the_host_and_other_streams():
+    """Right after the stream has been waited for: in pinned host memory, in a copy to the host, and for another stream behind an
+    event of the caller's.  Averages of different messages in turn, so that whatever is missing shows as the one before's."""
+    sizes, p = [9000000, 300, 70001], 0.002               # (36 MB: more than the caches closest to the compute units hold)
+    rounds = [_messages(sizes, p, 3, r) for r in range(2)]
+    want = [[x.cpu() for x in _reference(m, sizes, p)] for m in rounds]
+    want_dev = [[x.to(DEV) for x in w] for w in want]
+    ctx = sbc.sbc_create(0, sum(sizes), len(sizes))
+    try:
+        stream, other = torch.cuda.Stream(), torch.cuda.Stream()
+        flat = torch.zeros(sum(sizes) + 64, pin_memory=True)
+        out = [torch.zeros(n, device=DEV) for n in sizes]
+        host = [torch.zeros(n, pin_memory=True) for n in sizes]
+        class Pinned:                                     # (the binding takes device tensors; the library any device-visible memory)
+            ptrs = (sbc.ctypes.c_void_p * len(sizes))()
+            numel_arr = (sbc.ctypes.c_int64 * len(sizes))(*sizes)
+            tensors = sizes
+        at = 0
+        for t, n in enumerate(sizes):
+            Pinned.ptrs[t] = flat.data_ptr() + 4 * at
+            at += (n + 15) // 16 * 16
+        torch.cuda.synchronize()
+        for r in range(24):
+            messages, w, w_dev = rounds[r % 2], want[r % 2], want_dev[r % 2]
+            with torch.cuda.stream(stream):
+                arr = (sbc.ctypes.c_void_p * len(messages))(*[m.data_ptr() for m, _ in messages])
+                lens = (sbc.ctypes.c_size_t * len(messages))(*[n for _, n in messages])
+                rc = sbc.load().sbc_decompress_average(ctx, stream.cuda_stream, arr, lens, len(messages), Pinned.numel_arr, len(sizes), p,
+                                                       1.0 / len(messages), Pinned.ptrs)
+                assert rc == sbc.SBC_OK
+            stream.synchronize()
+            at = 0
+            for n, x in zip(sizes, w):
+                assert torch.equal(flat[at:at + n], x), "pinned, round %d" % r
+                at += (n + 15) // 16 * 16
+            with torch.cuda.stream(stream):
+                sbc.sbc_decompress_average(ctx, messages, p, 1.0 / len(messages), out)
+            stream.synchronize()
+            for h, x in zip(host, out):
+                h.copy_(x, non_blocking=True)
+            torch.cuda.current_stream().synchronize()
+            assert all(torch.equal(h, x) for h, x in zip(host, w)), "copied, round %d" % r
+            messages, w, w_dev = rounds[(r + 1) % 2], want[(r + 1) % 2], want_dev[(r + 1) % 2]
+            with torch.cuda.stream(stream):
+                sbc.sbc_decompress_average(ctx, messages, p, 1.0 / len(messages), out)
+                behind = torch.cuda.Event()
+                behind.record(stream)
+            with torch.cuda.stream(other):
+                other.wait_event(behind)
+                same = torch.stack([(x == y).all() for x, y in zip(out, w_dev)])
+                for h, x in zip(host, out):
+                    h.copy_(x, non_blocking=True)
+            other.synchronize()
+            assert bool(same.all()) and all(torch.equal(h, x) for h, x in zip(host, w)), "other stream, round %d" % r
+    finally:
+        sbc.sbc_destroy(ctx)
