@@ -142,8 +142,9 @@ __device__ __forceinline__ void write_codes(const ChunkCodes& c, int b, uint32_t
 }
 
 // A chunk so crowded that its bit string does not fit its words: its bitmap as a word per lane in four rounds,
-// so that no lane has more than 32 codes of a stretch (8192 kept entries at b = 6, 1800 words: k_emit_all 25 us;
-// 60 with 128 codes of a lane in each of seven stretches of 256 words).
+// so that no lane has more than 32 codes of a stretch (8192 kept entries at b = 6, 1800 words: k_emit_scan 25 us;
+// 60 with 128 codes of a lane in each of seven stretches of 256 words.  k_emit_all has stretches of 256 words, for with 512
+// or 1024 it takes as long: 2000 kept entries in one of 25 chunks 55 us, threshold, apply and emit by themselves 45).
 constexpr int kRawRounds = kChunkWords / 64;
 struct RawCodes {
     uint32_t word[kRawRounds], pe[kRawRounds], start[kRawRounds];      // the lane's: bits, end of the entry before, first bit of the codes
@@ -596,29 +597,6 @@ __device__ __forceinline__ void finish_call(uint8_t* __restrict__ msg, int T, in
     next_result->err = 0u;
 }
 
-// Exclusive prefix sum / maximum over a workgroup with one barrier; scratch: 16 words used by this scan alone.
-// (the wavefronts' values lie in the first lanes: two or four steps scan them)
-template <int NW, bool MAX>
-__device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint32_t* scratch) {
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t inc = MAX ? wave_incl_max(v) : wave_incl_sum(v);
-    if (lane == 63) scratch[w] = inc;
-    __syncthreads();
-    uint32_t waves = lane < NW ? scratch[lane] : 0u;
-    auto step = [&](uint32_t o) { waves = MAX ? max(waves, o) : waves + o; };
-    step(dpp_fetch<0x111, 0xf>(waves));
-    step(dpp_fetch<0x112, 0xf>(waves));
-    if constexpr (NW > 4) {
-        step(dpp_fetch<0x114, 0xf>(waves));
-        step(dpp_fetch<0x118, 0xf>(waves));
-    }
-    static_assert(NW <= 16, "a row of lanes");
-    total = (uint32_t)__builtin_amdgcn_readlane((int)waves, NW - 1);
-    const uint32_t before = w ? (uint32_t)__builtin_amdgcn_readlane((int)waves, w - 1) : 0u;
-    if constexpr (MAX) return max(before, dpp_fetch<0x138, 0xf>(inc));         // (the lane before; 0 for lane 0)
-    else return before + inc - v;
-}
-
 // --------------------------------------------------------------------------
 // From the candidate lists to the message in one launch (k_emit_all), for calls of up to kEmitAllChunks chunks
 // in up to kEmitAllTensors tensors.  The first 2 T workgroups each select one side of a tensor; the others take up to sixteen chunks
@@ -630,11 +608,11 @@ __device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint
 // one tensor of 2^20 35.2 / 31.8, 24 ragged tensors of 12e6 65.8 / 61.5, ResNet-50 shape (3243 chunks) at p = 0.001 83.3
 // / 82.6, at p = 0.01, where the chunks of other tensors are done while the longest list is selected, 103.0 / 96.1.
 // Beyond that the workgroups that wait get into the others' way: one tensor of 3500 chunks at p = 1e-4 86 / 86, of 3750
-// 90 / 93, eight tensors of 3500 chunks 85 / 84, of 4000 93 / 96, 8060 chunks 162 / 171.  The chip holds 512 workgroups of
+// 90 / 93, eight tensors of 3500 chunks 85 / 85, of 4000 93 / 96, 8060 chunks 162 / 171.  The chip holds 512 workgroups of
 // this size; where sides take nearly all of these places, those with chunks start late: 200 tensors of 1000 chunks 42 / 42, 240
 // 43 / 44, 512 47 / 49, 255 tensors of 300 chunks 30 / 32, 4000 of 4000 entries 157 / 168.  Nor does it pay where a chunk keeps
 // more than kFewKept entries, for the workgroups that wait have only their first 256 candidates of either side at
-// hand, and the residual's stores come last: one tensor of 4.2e6 entries at p = 0.05 57 / 57, 0.07 60 / 63, 0.2 78 / 93.
+// hand, and the residual's stores come last: one tensor of 4.2e6 entries at p = 0.05 57 / 57, 0.07 63 / 66, 0.2 93 / 110.
 // --------------------------------------------------------------------------
 constexpr uint32_t kEmitAllChunks = 3584, kEmitAllTensors = 200;
 constexpr int kEmitThreads = kThThreads;
@@ -1132,6 +1110,29 @@ __global__ __launch_bounds__(kEmitThreads, 8) void k_emit_all(
         for_kept([&](const uint2& x) { R[x.y] = __uint_as_float(bits_of_key(chosen ? ~x.x : x.x)) - mu_signed; });
     }
     SBC_TS(0, 8);
+}
+
+// Exclusive prefix sum / maximum over a workgroup with one barrier; scratch: 16 words used by this scan alone.
+// (the wavefronts' values lie in the first lanes: two or four steps scan them)
+template <int NW, bool MAX>
+__device__ __forceinline__ uint32_t scan_block(uint32_t v, uint32_t& total, uint32_t* scratch) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t inc = MAX ? wave_incl_max(v) : wave_incl_sum(v);
+    if (lane == 63) scratch[w] = inc;
+    __syncthreads();
+    uint32_t waves = lane < NW ? scratch[lane] : 0u;
+    auto step = [&](uint32_t o) { waves = MAX ? max(waves, o) : waves + o; };
+    step(dpp_fetch<0x111, 0xf>(waves));
+    step(dpp_fetch<0x112, 0xf>(waves));
+    if constexpr (NW > 4) {
+        step(dpp_fetch<0x114, 0xf>(waves));
+        step(dpp_fetch<0x118, 0xf>(waves));
+    }
+    static_assert(NW <= 16, "a row of lanes");
+    total = (uint32_t)__builtin_amdgcn_readlane((int)waves, NW - 1);
+    const uint32_t before = w ? (uint32_t)__builtin_amdgcn_readlane((int)waves, w - 1) : 0u;
+    if constexpr (MAX) return max(before, dpp_fetch<0x138, 0xf>(inc));         // (the lane before; 0 for lane 0)
+    else return before + inc - v;
 }
 
 // --------------------------------------------------------------------------

@@ -283,7 +283,6 @@ __device__ __forceinline__ double sum_of_exponents(F at) {
 // k_wide_collect before a workgroup that staged keys in LDS: 19 us in all on 27,000, 37 on 61,000).  Keys stay in
 // registers between the passes where a list has up to sixteen per thread; longer ones are read again.  (Tried:
 // 32 per thread, the next loads on their way during a batch, two copies of the histogram: no difference.)
-// --------------------------------------------------------------------------
 // For k_emit_all: one thread calls running() on the way (behind the list's loads, which would wait for what it
 // does) and done() when the state has been written.
 // --------------------------------------------------------------------------
